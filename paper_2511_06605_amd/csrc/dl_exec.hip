@@ -467,6 +467,7 @@ template <> struct list_cap<dl_fused_item> { static constexpr int big = 32; };
 
 constexpr uint32_t DL_UROWS_MAX_ITEMS = 65535;    // a grid's second dimension goes no further
 constexpr uint64_t TABLE_ENTRIES_TARGET = 8192;  // table kernels: aim for at most this many one-tile entries
+constexpr uint64_t PLAIN_WAVE_MIN_BYTES = 48ull << 20;  // bytes moved (read + written) from which a list of plain copies takes one-wavefront workgroups
 constexpr uint64_t UNIFORM_ROWS_MIN_BYTES = 4ull << 20;  // source bytes from which a uniform long list takes the row kernel
 constexpr uint64_t UNIFORM_ROWS_STAGE_BYTES = 768ull << 20;  // bytes moved (read + written) from which its table is staged even where it could be pushed
 constexpr size_t TABLE_STAGE_MIN = 512;          // tables at least this long are staged in device memory first
@@ -509,6 +510,7 @@ inline void with_policy(int policy, F f)
     switch (policy) {
     case DL_POL_STREAM: f(std::integral_constant<int, DL_POL_STREAM>{}); break;
     case DL_POL_WT: f(std::integral_constant<int, DL_POL_WT>{}); break;
+    case DL_POL_STREAM_IN: f(std::integral_constant<int, DL_POL_STREAM_IN>{}); break;
     default: f(std::integral_constant<int, DL_POL_PLAIN>{}); break;
     }
 }
@@ -1093,15 +1095,22 @@ dl_launch_shape dl_choose_shape(uint64_t src_bytes, uint64_t max_item_bytes, uin
     uint32_t split = c.fan_split;
     if (split == 0) split = max_k > 4 ? 4u : max_k > 2 ? 2u : 1u;
     if (max_k == 1) split = 1;
+    const uint64_t moved = src_bytes * (1ull + max_k);  // upper bound on bytes read + written
     uint32_t tile = c.tile_bytes;
-    if (tile == 0) tile = 4096u / split;
+    uint32_t most = 256u;  // threads of a workgroup
+    // Plain copies beyond the launch-bound sizes: a workgroup is one wavefront that moves one row, so consecutive
+    // rows of the address stream go to different XCDs.  All-to-all between eight ranks with 512 KiB / 1 MiB / 4 MiB chunks,
+    // 256 threads against 64: 10.8 / 26.6 / 83.4 us against 10.6 / 24.0 / 79.7; at 256 KiB chunks (32 MiB moved)
+    // the larger workgroup is 1-3 % ahead when the buffers are in the caches and 8 % behind when they are not.
+    if (max_k == 1 && tile == 0 && c.block_threads == 0 && moved >= PLAIN_WAVE_MIN_BYTES) most = 64u;
+    if (tile == 0) tile = 16u * most / split;
     sh.tile_bytes = tile;
     uint32_t bt = c.block_threads;
     if (bt == 0) {
         // threads of one sub-group: enough for the tile (or the largest item if that is smaller)
         const uint64_t span = max_item_bytes < tile ? max_item_bytes : tile;
         uint32_t sub = floor_pow2(span / 16 ? span / 16 : 1);
-        if (sub > 256u / split) sub = 256u / split;
+        if (sub > most / split) sub = most / split;
         if (sub < 64) sub = 64;
         bt = sub * split;
     }
@@ -1109,12 +1118,14 @@ dl_launch_shape dl_choose_shape(uint64_t src_bytes, uint64_t max_item_bytes, uin
     sh.block_threads = bt;
     sh.split = split;
     sh.max_blocks = c.max_blocks;
-    const uint64_t moved = src_bytes * (1ull + max_k);  // upper bound on bytes read + written
-    // Streaming hints: where the caller asks for them; and for lists of plain copies too large for anything of
-    // them to stay in the on-die caches (cold and warm alike 3-6 % faster at 512 MiB moved; copies with several
-    // destinations were 10 % slower with them, smaller plain lists slower when their buffers are reused).
-    const bool stream = moved >= c.nontemporal_min_bytes || (max_k == 1 && moved >= c.stream_plain_min_bytes);
-    sh.policy = stream ? DL_POL_STREAM : moved <= c.write_through_max_bytes ? DL_POL_WT : DL_POL_PLAIN;
+    // Streaming hints on both sides where the caller asks for them.  Streaming loads with write-through stores for
+    // lists of plain copies from 96 MiB moved (a third of the Infinity Cache read, see DL_POL_STREAM_IN): with
+    // 64 MiB moved the call and a kernel that reads its output take 27.2 us against 26.3 without, with 128 MiB 40.7
+    // against 42.3.  Copies with several destinations load a row from several wavefronts and lose 10 % with them.
+    const bool plain_stream = max_k == 1 && moved >= c.stream_plain_min_bytes;
+    sh.policy = moved >= c.nontemporal_min_bytes ? DL_POL_STREAM
+                : plain_stream                   ? DL_POL_STREAM_IN
+                : moved <= c.write_through_max_bytes ? DL_POL_WT : DL_POL_PLAIN;
     return sh;
 }
 

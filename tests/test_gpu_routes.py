@@ -1,0 +1,44 @@
+"""Sizes at which a request changes kernels: both sides of every line of the launch shape's rules, byte for byte
+against the CPU checker (copies: the bar is bit-exact, there is no tolerance)."""
+
+import numpy as np
+import pytest
+
+import paper_2511_06605_amd as dl
+from paper_2511_06605_amd import inputs
+
+from gpu_util import DevBuf, stream, sync
+
+pytestmark = pytest.mark.gpu
+
+KiB, MiB = 1024, 1024 * 1024
+
+
+@pytest.fixture(scope="module", autouse=True)
+def library():
+    import torch
+    assert torch.cuda.is_available()
+    torch.cuda.set_device(0)
+    dl.dl_init(0)
+    yield
+    dl.dl_shutdown()
+
+
+# 48 MiB and 96 MiB: 64 chunks of 384 and 768 KiB read and written, 28 swaps of 877.7 and 1755.4 KiB
+@pytest.mark.parametrize("op,c", [("alltoall", c) for c in (384 * KiB - 16, 384 * KiB, 384 * KiB + 17, 768 * KiB - 1, 768 * KiB)] +
+                         [("inplace", c) for c in (877 * KiB, 878 * KiB + 5, 1755 * KiB + 16, 1756 * KiB)])
+def test_plain_lists_around_their_size_rules(ref, op, c):
+    W = 8
+    C = inputs.uniform_chunks(W, c)
+    ins = inputs.alltoall_inputs(C, seed=c, kind="u8")
+    d_in = [DevBuf(a.size, fill=a, shift=(0 if c % 16 == 0 else 3)) for a in ins]
+    if op == "alltoall":
+        want = ref.alltoall(ins, C)
+        d_out = [DevBuf(w.size) for w in want]
+        dl.dl_alltoall([b.ptr() for b in d_in], [b.ptr() for b in d_out], C, stream())
+    else:
+        want, d_out = ref.alltoall_inplace(ins, c), d_in
+        dl.dl_alltoall_inplace([b.ptr() for b in d_in], c, stream())
+    sync()
+    for got, w in zip(d_out, want):
+        assert np.array_equal(got.host(), w) and got.guards_intact()
