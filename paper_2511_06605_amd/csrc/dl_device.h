@@ -31,7 +31,8 @@ __device__ __forceinline__ DL_GLOBAL V *dl_global(const void *p)
 constexpr int DL_UNROLL = 4;
 
 // Cache policy of the copy loop's loads and stores.
-//  PLAIN    ordinary loads and stores (write-back L2): best for the largest requests.
+//  STREAM_OUT  ordinary loads, non-temporal write-through stores: copies with several destinations whose output
+//           outgrows the on-die caches.  What is written does not push out the sources, which are read several times.
 //  STREAM   non-temporal hint on both: kept as a tunable.
 //  STREAM_IN  non-temporal loads, write-through stores: lists of plain copies too large for the on-die caches to
 //           hold both sides.  The loads pass the Infinity Cache by, so the sources do not push out what is being
@@ -49,7 +50,7 @@ constexpr int DL_UNROLL = 4;
 //           write-back before the completion word.  A wavefront that used this policy
 //           must execute dl_drain_stores() before it signals anything: the compiler
 //           does not count the stores issued from inline assembly.
-enum : int { DL_POL_PLAIN = 0, DL_POL_STREAM = 1, DL_POL_WT = 2, DL_POL_COHERENT = 3, DL_POL_STREAM_IN = 4 };
+enum : int { DL_POL_STREAM_OUT = 0, DL_POL_STREAM = 1, DL_POL_WT = 2, DL_POL_COHERENT = 3, DL_POL_STREAM_IN = 4 };
 
 template <int POL, typename V>
 __device__ __forceinline__ V dl_ld(const DL_GLOBAL V *p)
@@ -76,6 +77,8 @@ __device__ __forceinline__ void dl_st(DL_GLOBAL V *p, V v)
     // vector ALU write to its data registers (the hardware reads them a cycle late).  The compiler
     // pads its own stores for this, but it cannot see that the assembly below is one, and it is free
     // to reuse v's registers in the very next instruction.
+    else if constexpr (POL == DL_POL_STREAM_OUT && sizeof(V) == 16)
+        asm volatile("global_store_dwordx4 %0, %1, off sc1 nt\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
     else if constexpr ((POL == DL_POL_WT || POL == DL_POL_STREAM_IN) && sizeof(V) == 16)
         asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
     else if constexpr (POL == DL_POL_COHERENT && sizeof(V) == 16)
@@ -119,7 +122,9 @@ __device__ __forceinline__ void dl_st16(char *p, dl_u32x4 v)
     DL_GLOBAL dl_u32x4u *q = (DL_GLOBAL dl_u32x4u *)(uint64_t)p;
     if constexpr (POL == DL_POL_STREAM)
         __builtin_nontemporal_store(v, q);
-    else if constexpr (POL == DL_POL_WT || POL == DL_POL_STREAM_IN)  // (the s_nop: see dl_st)
+    else if constexpr (POL == DL_POL_STREAM_OUT)  // (the s_nop: see dl_st)
+        asm volatile("global_store_dwordx4 %0, %1, off sc1 nt\n\ts_nop 1" : : "v"(q), "v"(v) : "memory");
+    else if constexpr (POL == DL_POL_WT || POL == DL_POL_STREAM_IN)
         asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(q), "v"(v) : "memory");
     else if constexpr (POL == DL_POL_COHERENT)
         asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" : : "v"(q), "v"(v) : "memory");
@@ -653,6 +658,47 @@ __device__ __forceinline__ void dl_rows_body(const Item &it, uint32_t tile, uint
             dl_st16<POL>(dq + byte, v);
         }
     }
+}
+
+// Large read-once/write-k items, two destinations at a time.  The rows of an item are taken in chunks of
+// DL_PAIR_ROWS; a chunk's rows are written to the first two destinations, then to the next two, and so on, one
+// wavefront (= one workgroup) per row and pair.  What bounds a large fan-out is the memory side, and it does better
+// the fewer streams are written at once: with all eight destinations of an all-gather in flight together 64 MiB per
+// rank took 781 us, and 810 to 965 when the buffers lay badly against each other; in pairs 740, however they lie.
+// The row is loaded once per pair, and all but the first of these loads hit the L2: workgroups are dealt round-robin
+// to the eight XCDs and a chunk's pairs are a multiple of eight workgroups apart, so a row always goes to the same
+// XCD, whose share of a 4 MiB chunk is 512 KiB (1, 4 and 16 MiB chunks were within 1 % of each other).
+// `local`: the workgroup's index within the item.  Destinations in their own order, the unused ones null.
+template <int POL, bool ON_GRID>
+__device__ __forceinline__ void dl_pair_body(const dl_fused_item &it, uint32_t local)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    const char *src = it.src;
+    const uint64_t bytes = it.bytes;
+    const uint32_t shift = ON_GRID ? 0u : dl_item_shift(it);
+    uint32_t row, pair;
+    if (!dl_pair_locate(local, dl_pair_rows(bytes, shift), (it.k + 1u) >> 1, &row, &pair)) return;
+    char *const d0 = it.dst[2u * pair];
+    char *const d1 = it.dst[2u * pair + 1u];
+    const bool ragged = ON_GRID ? false : dl_item_ragged(it);
+    const uint32_t kind = ON_GRID ? (uint32_t)DL_ROW_PLAIN : dl_row_kind(ragged, shift, bytes, row);
+    const uint64_t byte = (((uint64_t)row << 10) - shift) + (lane << 4);
+    uint32_t odd = 0;
+    if constexpr (!ON_GRID) odd = __builtin_amdgcn_readfirstlane(((uint32_t)(uint64_t)src - shift) & 3u);
+    if (kind == DL_ROW_EDGE)
+        dl_row_edges(shift, bytes, row, lane, [&](uint64_t i) {
+            const uint8_t v = dl_ld<POL>(dl_global<uint8_t>(src) + i);
+            dl_st<POL>(dl_global<uint8_t>(d0) + i, v);
+            if (d1) dl_st<POL>(dl_global<uint8_t>(d1) + i, v);
+        });
+    if (!dl_lane_whole(byte, bytes, kind)) return;
+    dl_u32x4 v;
+    if (odd)
+        v = dl_ld16_shifted_row<POL>(src + byte, odd, lane == 63u || !dl_lane_whole(byte + 16u, bytes, kind));
+    else
+        v = dl_ld16<POL>(src + byte);
+    dl_st16<POL>(d0 + byte, v);
+    if (d1) dl_st16<POL>(d1 + byte, v);
 }
 
 // Row path over a list in the kernel arguments: global tile b -> (item, tile).

@@ -68,7 +68,7 @@ __global__ void __launch_bounds__(BUILD_THREADS) dl_dispatch_build_kernel(const 
                                                                           dl_fused_item *__restrict__ items,
                                                                           const dl_pushed ps)
 {
-    constexpr int POL = PUSHED ? DL_POL_COHERENT : DL_POL_PLAIN;
+    constexpr int POL = PUSHED ? DL_POL_COHERENT : DL_POL_WT;
     __shared__ uint32_t before_block[DISPATCH_W];          // rows taken by the tokens of earlier blocks
     __shared__ uint32_t in_wave[BUILD_WAVES][DISPATCH_W];  // per wavefront: destinations of its own 64 tokens
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;

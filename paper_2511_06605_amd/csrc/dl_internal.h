@@ -58,6 +58,7 @@ struct dl_launch_shape {
     int policy;           // cache policy of the copy loop (DL_POL_*)
     bool rows = false;    // the list qualifies for the row path of the list kernels
     bool chain = false;   // prelaunch mode, a large request: a one-workgroup gate kernel waits, the copy kernel follows it on the stream
+    bool pairs = false;   // read-once/write-k items written two destinations at a time (see dl_pair_body)
     uint32_t rows2d_width = 0;  // row path on a two-dimensional grid (item by item), this many tiles wide; 0: one-dimensional
 };
 

@@ -76,6 +76,30 @@ DL_HD uint64_t dl_item_tiles(const Item &it, uint32_t tile_bytes)
     return span / tile_bytes + (span % tile_bytes ? 1u : 0u);
 }
 
+// Rows of 1 KiB that an item takes on that grid, and workgroups of the kernel that writes its destinations in pairs.
+DL_HD uint32_t dl_pair_rows(uint64_t bytes, uint32_t shift) { return (uint32_t)((bytes + shift + 1023u) >> 10); }
+DL_HD uint64_t dl_pair_blocks(const dl_fused_item &it)
+{
+    return it.bytes ? (uint64_t)dl_pair_rows(it.bytes, dl_item_shift(it)) * ((it.k + 1u) >> 1) : 0u;
+}
+
+// Row and pair of destinations of that kernel's workgroup `local` of an item of `rows` rows and `pairs` (1..4) pairs:
+// the rows in chunks of DL_PAIR_ROWS, a chunk's rows for the first pair, then for the second, ...  False: past the item.
+constexpr uint32_t DL_PAIR_ROWS = 4096;
+
+DL_HD bool dl_pair_locate(uint32_t local, uint32_t rows, uint32_t pairs, uint32_t *row, uint32_t *pair)
+{
+    const uint32_t whole = local / DL_PAIR_ROWS;
+    const uint32_t chunk = pairs == 3u ? whole / 3u : whole >> (pairs >> 1);  // (one, two or four pairs: a shift)
+    const uint32_t row0 = chunk * DL_PAIR_ROWS;
+    if (row0 >= rows) return false;
+    const uint32_t n = rows - row0 < DL_PAIR_ROWS ? rows - row0 : DL_PAIR_ROWS;  // rows of this chunk
+    const uint32_t in_chunk = local - row0 * pairs;
+    *pair = (in_chunk >= n ? 1u : 0u) + (in_chunk >= 2u * n ? 1u : 0u) + (in_chunk >= 3u * n ? 1u : 0u);
+    *row = row0 + (in_chunk - *pair * n);
+    return *pair < pairs;
+}
+
 // Bytes [*lo, *hi) of an item that tile `tile` covers (*lo >= *hi: none).
 DL_HD void dl_tile_range(uint32_t shift, uint64_t bytes, uint64_t tile, uint32_t tile_bytes, uint64_t *lo, uint64_t *hi)
 {

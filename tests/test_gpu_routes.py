@@ -42,3 +42,35 @@ def test_plain_lists_around_their_size_rules(ref, op, c):
     sync()
     for got, w in zip(d_out, want):
         assert np.array_equal(got.host(), w) and got.guards_intact()
+
+
+def _fanout(sizes, shifts, seed):
+    """Read-once/write-k items, item i of sizes[i] = (bytes, k) bytes, with its buffers moved by the given shifts."""
+    rng = np.random.default_rng(seed)
+    src = [DevBuf(n, fill=rng.integers(0, 256, n, dtype=np.uint8), shift=shifts[i % len(shifts)]) for i, (n, _) in enumerate(sizes)]
+    dst = [[DevBuf(n, shift=shifts[(i + j + 1) % len(shifts)]) for j in range(k)] for i, (n, k) in enumerate(sizes)]
+    return src, dst, [dict(src=s.ptr(), bytes=n, dst=[d.ptr() for d in ds]) for (n, _), s, ds in zip(sizes, src, dst)]
+
+
+# output that is streamed: destinations in pairs, rows in chunks of 4096 of 1 KiB
+@pytest.mark.parametrize("shifts", [[0], [16, 0, 1, 127]])
+@pytest.mark.parametrize("sizes", [
+    [(1, 1), (15, 2), (16, 3), (17, 4), (1023, 5), (1024, 6), (1025, 7), (2047, 8)],       # an item of a row or two
+    [(4 * MiB, 7)], [(4 * MiB - 1, 6)], [(4 * MiB + 1, 5), (3, 2)], [(4 * MiB - 127, 8), (4 * MiB + 1024, 3)],
+    [(8 * MiB + 5, 6), (8 * MiB, 2)],
+    [(5000 + 100 * i, 1 + i % 8) for i in range(20)],                                      # more than eight items
+])
+def test_destinations_in_pairs(ref, sizes, shifts):
+    before = dl.dl_get_config().write_through_max_bytes
+    src, dst, items = _fanout(sizes, shifts, seed=len(sizes))
+    dl.dl_set_config(write_through_max_bytes=0)
+    try:
+        dl.dl_batch_fanout(items, stream())
+    finally:
+        dl.dl_set_config(write_through_max_bytes=before)
+    sync()
+    for s, ds in zip(src, dst):
+        want = ref.broadcast(s.host(), len(ds))
+        assert s.guards_intact()
+        for d, w in zip(ds, want):
+            assert np.array_equal(d.host(), w) and d.guards_intact()
