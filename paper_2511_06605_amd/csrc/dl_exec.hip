@@ -477,6 +477,8 @@ template <> struct list_cap<dl_fused_item> { static constexpr int big = 32; };
 constexpr uint32_t DL_UROWS_MAX_ITEMS = 65535;    // a grid's second dimension goes no further
 constexpr uint64_t TABLE_ENTRIES_TARGET = 8192;  // table kernels: aim for at most this many one-tile entries
 constexpr uint64_t PLAIN_WAVE_MIN_BYTES = 48ull << 20;  // bytes moved (read + written) from which a list of plain copies takes one-wavefront workgroups
+constexpr uint64_t FAN_WAVE_MIN_BYTES = 3ull << 20;         // bytes moved above which a copy with several destinations takes one wavefront per row
+constexpr uint64_t FAN_STREAM_IN_MIN_BYTES = 88ull << 20;   // ... with streaming loads from this many
 constexpr uint64_t UNIFORM_ROWS_MIN_BYTES = 4ull << 20;  // source bytes from which a uniform long list takes the row kernel
 constexpr uint64_t UNIFORM_ROWS_STAGE_BYTES = 768ull << 20;  // bytes moved (read + written) from which its table is staged even where it could be pushed
 constexpr size_t TABLE_STAGE_MIN = 512;          // tables at least this long are staged in device memory first
@@ -1058,9 +1060,11 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
     if (n <= (size_t)NBIG) {
         uint64_t tile_end[NBIG];
         if constexpr (std::is_same<Item, dl_fused_item>::value) {
-            // one-shot requests whose output outgrows the caches, where the caller has not fixed the shape
+            // one-shot requests, where the caller has not fixed the shape
             const dl_config &c = g_dl.cfg;
-            if (!arm && sh.policy == DL_POL_STREAM_OUT && !c.tile_bytes && !c.block_threads && !c.fan_split && !sh.max_blocks) {
+            const bool free_shape = !arm && !c.tile_bytes && !c.block_threads && !c.fan_split && !sh.max_blocks;
+            const uint64_t moved = total * (1ull + kmax);
+            if (free_shape && sh.policy == DL_POL_STREAM_OUT) {  // the output outgrows the caches
                 uint64_t acc = 0;
                 for (size_t i = 0; i < n; ++i) tile_end[i] = acc += dl_pair_blocks(items[i]);
                 if (acc < (1ull << 26)) {  // a grid has fewer than 2^32 threads
@@ -1069,6 +1073,23 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
                     if (n <= (size_t)NMAX_SMALL) return launch_klist<Item, NMAX_SMALL>(items, n, tile_end, sh, stream, arm);
                     return launch_klist<Item, NBIG>(items, n, tile_end, sh, stream, arm);
                 }
+            } else if (free_shape && sh.policy == DL_POL_WT && moved > FAN_WAVE_MIN_BYTES) {
+                // Between the launch-bound requests and those: one wavefront per row, which stores it to all
+                // destinations, instead of several that each load it.  Buffers warm / cold, several wavefronts
+                // against one, in a graph of 30: all-gather over eight ranks of 32 KiB 1.98 / 1.86 against 2.08 / 1.96 us,
+                // 64 KiB 2.42 / 3.36 : 2.19 / 3.12, 256 KiB 4.11 / 5.94 : 3.77 / 4.71, 1 MiB 10.8 / 16.5 : 10.6 / 15.0;
+                // 2 MiB to seven others 3.86 / 5.38 : 3.51 / 4.52; of 1 MiB and 5 bytes over five ranks 5.95 / 9.15 : 5.36 / 8.11.
+                // A workgroup is that one wavefront, or eight where loads are shifted (1 MiB + 5 over eight
+                // ranks: 11.6 us with one, 11.4 with eight, 13.0 with four; 1 MiB: 10.7, 10.6, 11.3).
+                bool on_grid = true;
+                for (size_t i = 0; i < n; ++i) on_grid = on_grid && item_on_grid(items[i]);
+                sh.split = 1;
+                sh.block_threads = on_grid ? 64u : 512u;
+                sh.tile_bytes = 16u * sh.block_threads;
+                // With one load per row the loads can be streaming ones (see DL_POL_STREAM_IN), from the size at which
+                // output and sources no longer share the caches: 72 MiB moved 10.70 us either way, 84 MiB 14.7 -> 15.1,
+                // 90 MiB (3 MiB per rank over five) 18.3 -> 15.6, 108 MiB 21.3 -> 19.0.
+                if (moved >= FAN_STREAM_IN_MIN_BYTES) sh.policy = DL_POL_STREAM_IN;
             }
         }
         for (;;) {

@@ -74,3 +74,16 @@ def test_destinations_in_pairs(ref, sizes, shifts):
         assert s.guards_intact()
         for d, w in zip(ds, want):
             assert np.array_equal(d.host(), w) and d.guards_intact()
+
+
+# an all-gather over five ranks reads and writes 30 B; 3, 88 and 144 MiB are B = 104857, 3075822 and 5033164
+@pytest.mark.parametrize("W,B,shift", [(5, b, s) for b, s in ((104857, 0), (104858, 1), (104960, 0), (3075712, 0), (3075823, 2), (3075840, 0),
+                                                             (5033088, 0), (5033165, 1), (5033216, 0))] + [(2, 600000, 0), (12, 70000, 5)])
+def test_fanouts_around_their_size_rules(ref, W, B, shift):
+    ins = inputs.allgather_inputs(W, B, seed=B)
+    d_in = [DevBuf(B, fill=a, shift=shift) for a in ins]
+    d_out = [DevBuf(W * B, shift=2 * shift) for _ in range(W)]
+    dl.dl_allgather([b.ptr() for b in d_in], [b.ptr() for b in d_out], B, stream())
+    sync()
+    for got, w in zip(d_out, ref.allgather(ins)):
+        assert np.array_equal(got.host(), w) and got.guards_intact()
