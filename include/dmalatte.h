@@ -112,8 +112,8 @@ int dl_last_hip_error(void);
 
 /*
  * Failures that only the device can notice.  The table of a long list (more
- * copies than fit the kernel arguments), and the mask of a token dispatch
- * lowered on the device, are written by the host straight into device memory
+ * copies than fit the kernel arguments), and the mask of a token dispatch of
+ * more than 2048 tokens, are written by the host straight into device memory
  * and sealed with a stamp; the kernel looks for the stamp before it reads
  * (the two cross the host link in order, and the launch follows them; paper
  * Sec. III-B2: the engine fetches its commands after the doorbell).  Every
@@ -432,7 +432,7 @@ typedef struct dl_config {
     uint32_t max_blocks;         /* cap on the one-shot grid; workgroups then stride over the tiles; 0 = one workgroup per tile */
     uint32_t fan_split;          /* sub-groups of a workgroup that share out the destinations of a fused copy: 1, 2 or 4; 0 = choose */
     uint32_t infer_broadcast;    /* 1: dl_batch_copy merges copies that share source and size into read-once/write-k copies; default 1 */
-    uint32_t device_lowering;    /* 1: dl_token_dispatch with 512 tokens or more (W = 8, one-shot mode, validation off) sends only the mask to the device, which derives the copies itself; default 1 */
+    uint32_t device_lowering;    /* 1: dl_token_dispatch (W = 8, one-shot mode, validation off; DL_MODE_AUTO: 512 tokens or more) sends only the mask to the device, which places the rows itself; default 1 */
     uint32_t table_push;         /* 1: the table of a long list (more copies than fit the kernel arguments) is written by the host straight into device memory, through the BAR, when the device exposes one that covers its memory and the table is short enough; 0: always through pinned host memory; default 1 */
     uint64_t write_through_max_bytes; /* requests moving at most this many bytes (read + written) use write-through stores, larger ones streaming stores; default 144 MiB */
     uint64_t stream_plain_min_bytes;  /* lists of plain 1:1 copies and swaps (all-to-all, batches) moving at least this many bytes (a swap's two ranges counted once each) use streaming loads, so that what is read does not push what is written out of the on-die caches; default 96 MiB; UINT64_MAX = never */
@@ -481,8 +481,10 @@ int dl_batch_fanout(const dl_plan_item *items, size_t n, void *stream);
  * hold row_bytes times the number of non-zero entries in column j of dest.
  * Lowered to one read-once/write-k copy per token; a token with no destination
  * moves nothing.  tokens: host array of W counts.  1 <= W <= DL_MAX_FANOUT.
- * The lowering runs on the host, or (dl_config.device_lowering, many tokens) on
- * the device from the mask alone; the result is the same.
+ * The lowering runs on the host, or (8 ranks, one-shot, dl_config.device_lowering)
+ * on the device from the mask alone; the result is the same.  On the device a
+ * request of up to 2048 tokens is one launch and nothing else, so it may be
+ * captured into a HIP graph (with the mask it was issued with).
  */
 int dl_token_dispatch(const void *const *in, void *const *out, int W, const uint32_t *tokens, size_t row_bytes,
                       const uint8_t *dest, void *stream);
@@ -491,15 +493,15 @@ int dl_token_dispatch(const void *const *in, void *const *out, int W, const uint
  * dl_token_dispatch with the routing mask in DEVICE memory, where the router
  * kernel of a mixture-of-experts layer leaves it: same layout (one byte per
  * (token, rank), non-zero = send), same result, but dest_device is a device
- * pointer (8-byte aligned) and nothing of the mask crosses the host link: the
- * device counts, builds the copy list and executes it, three launches on
- * `stream`, ordered behind whatever produced the mask there.  Always executed
- * as in DL_MODE_ONESHOT.  The host does not learn how many rows each rank
+ * pointer (8-byte aligned) and nothing of the mask crosses the host link: one
+ * launch on `stream`, ordered behind whatever produced the mask there, counts
+ * and copies.  Always executed as in DL_MODE_ONESHOT; it uses no memory of the
+ * library's and may be captured into a HIP graph (a replay reads the mask anew).  The host does not learn how many rows each rank
  * receives: out[j] must have room for what the mask sends it (at most all
  * tokens).  Rows and buffers may have any length and alignment.  Limits:
  * exactly 8 ranks (DL_ERR_INVALID otherwise); at most
- * DL_DISPATCH_DEVICE_MAX_TOKENS tokens in all (one slot of the library's table
- * memory holds their copy list; more: DL_ERR_CAPACITY, nothing is enqueued).
+ * DL_DISPATCH_DEVICE_MAX_TOKENS tokens in all (every workgroup counts the tokens
+ * in front of its own; more: DL_ERR_CAPACITY, nothing is enqueued).
  */
 #define DL_DISPATCH_DEVICE_MAX_TOKENS 10240
 int dl_token_dispatch_device(const void *const *in, void *const *out, int W, const uint32_t *tokens, size_t row_bytes,

@@ -685,10 +685,11 @@ int dl_token_dispatch(const void *const *in, void *const *out, int W, const uint
     if (g_dl.inited && dl_device_error_pending()) return DL_ERR_LOST;
     if (g_dl.inited && (g_dl.mode == DL_MODE_ONESHOT || g_dl.mode == DL_MODE_AUTO) && !g_dl.validate &&
         g_dl.cfg.device_lowering) {
-        // many tokens: only the destination mask goes to the device, which works out the rest itself (one-shot
-        // execution; in DL_MODE_AUTO that is what the table gives such a request)
+        // only the destination mask goes to the device, which works out the rest itself (one-shot execution; in
+        // DL_MODE_AUTO that is what the table gives a request of many tokens)
         bool taken = false;
-        const int rc = dl_dispatch_on_device(in, out, W, tokens, row_bytes, dest, (hipStream_t)stream, &taken);
+        const uint64_t least = g_dl.mode == DL_MODE_AUTO ? MODE_LIMITS.dispatch_device_tokens : 1u;
+        const int rc = dl_dispatch_on_device(in, out, W, tokens, row_bytes, dest, least, (hipStream_t)stream, &taken);
         if (taken) t_dl_last.mode = DL_MODE_ONESHOT;
         if (taken || rc != DL_OK) return rc;
     }

@@ -572,6 +572,32 @@ __device__ __forceinline__ bool dl_lane_whole(uint64_t byte, uint64_t bytes, uin
     return kind == DL_ROW_EDGE && byte < bytes && bytes - byte >= 16u;
 }
 
+// Row `row` of a plain copy by one wavefront (see dl_rows_body).
+template <int POL, bool ON_GRID>
+__device__ __forceinline__ void dl_plain_row(const dl_plain_item &it, uint64_t row)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    const char *src = it.src;
+    char *dst = it.dst;
+    const uint64_t bytes = it.bytes;
+    const bool ragged = ON_GRID ? false : dl_item_ragged(it);
+    const uint32_t shift = ON_GRID ? 0u : dl_item_shift(it);
+    const uint32_t kind = ON_GRID ? (uint32_t)DL_ROW_PLAIN : dl_row_kind(ragged, shift, bytes, row);
+    const uint64_t byte = ((row << 10) - shift) + (lane << 4);
+    uint32_t odd = 0;
+    if constexpr (POL != DL_POL_COHERENT && !ON_GRID)
+        odd = __builtin_amdgcn_readfirstlane(((uint32_t)(uint64_t)src - shift) & 3u);
+    if (kind == DL_ROW_EDGE)
+        dl_row_edges(shift, bytes, row, lane, [&](uint64_t i) {
+            dl_st<POL>(dl_global<uint8_t>(dst) + i, dl_ld<POL>(dl_global<uint8_t>(src) + i));
+        });
+    if (!dl_lane_whole(byte, bytes, kind)) return;
+    if (odd)
+        dl_st16<POL>(dst + byte, dl_ld16_shifted_row<POL>(src + byte, odd, lane == 63u || !dl_lane_whole(byte + 16u, bytes, kind)));
+    else
+        dl_st16<POL>(dst + byte, dl_ld16<POL>(src + byte));
+}
+
 // Row path: the hot loop of large requests, kept to a few dozen instructions and two scalar round trips per
 // wavefront.  Rows are the 1 KiB rows of the grid of the item's first destination (see dl_tile_range; a tile
 // is (1 << wpg_log2) rows), and lane l of a row moves the 16 bytes at row * 1024 + 16 l - shift of the item:
@@ -615,17 +641,6 @@ __device__ __forceinline__ void dl_rows_body(const Item &it, uint32_t tile, uint
         dl_ld_many<POL, 2>(xy, from);
         dl_st16<POL>(pa + byte, xy[1]);
         dl_st16<POL>(pb + byte, xy[0]);
-    } else if constexpr (std::is_same<Item, dl_plain_item>::value) {
-        char *dst = it.dst;
-        if (kind == DL_ROW_EDGE)
-            dl_row_edges(shift, bytes, row, lane, [&](uint64_t i) {
-                dl_st<POL>(dl_global<uint8_t>(dst) + i, dl_ld<POL>(dl_global<uint8_t>(src) + i));
-            });
-        if (!dl_lane_whole(byte, bytes, kind)) return;
-        if (odd)
-            dl_st16<POL>(dst + byte, dl_ld16_shifted_row<POL>(src + byte, odd, lane == 63u || !dl_lane_whole(byte + 16u, bytes, kind)));
-        else
-            dl_st16<POL>(dst + byte, dl_ld16<POL>(src + byte));
     } else {
         const uint32_t slots = (uint32_t)DL_FAN >> sl;
         const uint32_t base = (wave >> wl) * slots;
@@ -699,6 +714,13 @@ __device__ __forceinline__ void dl_pair_body(const dl_fused_item &it, uint32_t l
         v = dl_ld16<POL>(src + byte);
     dl_st16<POL>(d0 + byte, v);
     if (d1) dl_st16<POL>(d1 + byte, v);
+}
+
+template <int POL, bool ON_GRID = false>
+__device__ __forceinline__ void dl_rows_body(const dl_plain_item &it, uint32_t tile, uint32_t wl, uint32_t)
+{
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    dl_plain_row<POL, ON_GRID>(it, ((uint64_t)tile << wl) + (wave & ((1u << wl) - 1u)));
 }
 
 // Row path over a list in the kernel arguments: global tile b -> (item, tile).
@@ -793,4 +815,30 @@ __device__ __forceinline__ void dl_run_tile(const dl_klist<Item, NMAX> &p, uint3
     const uint32_t d = dl_find_item(p, b, &first);
     if (d >= p.n) return;
     dl_run_item<POL>(p.item[d], (uint64_t)(b - first), p.tile_bytes, p.split);
+}
+
+// ----------------------------------------------------------- launch-time choices
+
+// Calls f with the cache policy as a compile-time constant.
+template <class F>
+inline void dl_with_policy(int policy, F f)
+{
+    switch (policy) {
+    case DL_POL_STREAM: f(std::integral_constant<int, DL_POL_STREAM>{}); break;
+    case DL_POL_WT: f(std::integral_constant<int, DL_POL_WT>{}); break;
+    case DL_POL_STREAM_IN: f(std::integral_constant<int, DL_POL_STREAM_IN>{}); break;
+    default: f(std::integral_constant<int, DL_POL_STREAM_OUT>{}); break;
+    }
+}
+
+// ... and with whether every item lies on the grid (see dl_rows_body) as one too.
+template <class F>
+inline void dl_with_policy_and_grid(int policy, bool on_grid, F f)
+{
+    dl_with_policy(policy, [&](auto pol) {
+        if (on_grid)
+            f(pol, std::true_type{});
+        else
+            f(pol, std::false_type{});
+    });
 }

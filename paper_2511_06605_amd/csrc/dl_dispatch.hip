@@ -1,14 +1,18 @@
-// Token dispatch lowered on the device (Sec. IV-B: a token that goes to several experts is one
-// source with several destinations).  The host-side lowering writes one 88-byte item per token and
-// ships that table over the host link; for thousands of tokens that "control" work (Sec. III-B2) is
-// as long as the copy.  Here only the destination mask (W bytes per token) crosses the link:
-//   1. the mask goes to device memory (written there by the host through the BAR where that is possible, else
-//      through the pinned ring and a copy),
-//   2. a small kernel builds the item table there, one token per thread: its source row and, for
-//      every rank it goes to, the row it lands on (receive buffers are packed in token order, so
-//      that is an exclusive prefix count per column of the mask; the host, which touches every mask
-//      word anyway, sends along the counts at every 256th token, the kernel counts inside its 256),
-//   3. the row kernel for long lists of equal items executes the table.
+// Token dispatch placed on the device (Sec. IV-B: a token that goes to several experts is one source with several
+// destinations).  Receive buffers are packed in token order, so where a token's row lands is a count: of the tokens
+// before it that go to the same rank.  No copy list exists anywhere; every workgroup works out the places of its own
+// tokens and copies their rows, in one launch:
+//   - the mask on the host: the host packs it to a byte per token and counts the rows taken before every group of 64
+//     tokens (control work, Sec. III-B2, done where the mask is); both travel in the kernel arguments (up to 2048
+//     tokens), or through the BAR, or, where that way is not open, in the arguments of several launches;
+//   - the mask in device memory: every workgroup counts the tokens in front of its own group itself (at most 80 KiB
+//     of mask, which the L2 holds).
+// Inside a group of 64 the places come from one ballot per rank.
+//
+// Before, a kernel built a table of 88-byte items from the mask (and another counted for it) and the row kernel for
+// long lists read the table back, one workgroup of two wavefronts per 1 KiB row.  Rows of 14 336 bytes, call to call:
+// 128 tokens per rank (93 MB moved) with the mask on the host 25.1 us in two launches, now 15.2 in one, with the mask
+// on the device 28.4 (three launches) and 16.4; 512 per rank (370 MB) 72.6 : 57.9 and 75.7 : 58.9.
 #include "dl_device.h"
 #include "dl_internal.h"
 
@@ -16,156 +20,228 @@
 
 namespace {
 
-constexpr int DISPATCH_W = 8;            // ranks this path handles: exactly 8 (one 64-bit mask word per token)
-constexpr uint32_t BUILD_THREADS = 256;  // tokens per workgroup of the build kernel
-constexpr uint32_t BUILD_WAVES = BUILD_THREADS / 64;
+constexpr int DISPATCH_W = 8;              // ranks this path handles: exactly 8 (one 64-bit mask word per token)
+constexpr uint32_t GROUP = 64;             // tokens whose places one wavefront's ballots tell apart
+constexpr uint32_t DISPATCH_GROUPS = 32;   // groups per launch with the mask in the kernel arguments (3.2 KiB of the 4 KiB they may take)
+constexpr uint32_t MAX_WAVES = 8;          // wavefronts of a workgroup
+constexpr int ROWS_PER_WAVE = 2;           // 1 KiB rows in flight per wavefront
 
-struct build_args {
+struct dispatch_args {
     const char *in[DISPATCH_W];
     char *out[DISPATCH_W];
-    uint32_t first_token[DISPATCH_W + 1];  // tokens before rank i; entries past W hold the total
-    uint32_t W;
-    uint32_t tokens;  // over all ranks
+    uint32_t first_token[DISPATCH_W];  // tokens before rank i
+    uint32_t tokens;                   // over all ranks
+    uint32_t token0;                   // of them, where this launch begins (a multiple of GROUP)
     uint64_t row_bytes;
+    uint32_t token_waves;              // wavefronts that share a token's rows
+    uint32_t wg_tokens;                // tokens of a workgroup (a power of two, at most GROUP)
 };
 
-// Workgroup b builds the items of tokens 256 b .. 256 b + 255, one token per thread.  No workgroup
-// waits for another: the rows that earlier blocks' tokens took in each receive buffer come with the
-// mask (block_rows: W counts per block, written by the host), the rows taken inside the block come
-// from wavefront ballots.
-//
-// PUSHED: the host wrote the mask into device memory just before the launch; it is read past the caches, where
-// a line of whatever used that memory before may linger.
-// Per block of 256 tokens and per rank: how many of the block's tokens go to that rank (any non-zero mask byte
-// counts).  For a mask that is already in device memory: what the host otherwise counts while it folds the mask.
-__global__ void __launch_bounds__(BUILD_THREADS) dl_dispatch_count_kernel(const uint8_t *__restrict__ mask, uint32_t tokens,
-                                                                          uint32_t *__restrict__ counts)
+struct dispatch_group {
+    uint32_t taken[DISPATCH_W];  // rows that earlier groups' tokens take in each receive buffer
+    uint8_t ranks[GROUP];        // bit j: the token goes to rank j
+};
+
+struct dispatch_list {
+    dispatch_args a;
+    dispatch_group group[DISPATCH_GROUPS];
+};
+static_assert(sizeof(dispatch_list) <= 4096, "kernel arguments");
+static_assert(sizeof(dispatch_group) % 16 == 0, "whole words");
+
+// What one wavefront copies of a token's row: 1 KiB rows `row0`, row0 + stride, ..., ROWS_PER_WAVE of them.
+// On the grid (see dl_rows_body) every row is loaded once, into registers, as soon as the token is known; the loads are
+// in flight while the wavefront finds out where the row goes (128 tokens per rank, mask on the device: 18.1 -> 16.4 us).
+// Off the grid the destinations lie differently against each other, and stores across 16-byte boundaries go to
+// memory in pieces; there each destination is a plain copy cut on its own grid, whose loads after the first one hit
+// the caches (rows of 14 338 bytes, 512 tokens per rank: 103 us with one load and unaligned stores, 76 this way).
+template <int POL, bool ON_GRID>
+struct dispatch_row {
+    const char *src;
+    uint64_t bytes;
+    uint32_t row0, stride;
+    dl_u32x4 v[ON_GRID ? ROWS_PER_WAVE : 1];
+
+    __device__ __forceinline__ uint64_t byte(int i) const
+    {
+        return ((uint64_t)(row0 + (uint32_t)i * stride) << 10) + ((threadIdx.x & 63u) << 4);
+    }
+    // token < a.tokens
+    __device__ __forceinline__ void load(const dispatch_args &a, uint32_t token, uint32_t first_row)
+    {
+        // the token's rank is the last one that starts at or before it
+        src = a.in[0];
+        uint32_t first = 0;
+#pragma unroll
+        for (int r = 1; r < DISPATCH_W; ++r)
+            if (a.first_token[r] <= token) {
+                src = a.in[r];
+                first = a.first_token[r];
+            }
+        src += (uint64_t)(token - first) * a.row_bytes;
+        bytes = a.row_bytes;
+        row0 = first_row;
+        stride = a.token_waves;
+        if constexpr (ON_GRID) {
+#pragma unroll
+            for (int i = 0; i < ROWS_PER_WAVE; ++i)
+                if (byte(i) < bytes) v[i] = dl_ld16<POL>(src + byte(i));
+        }
+    }
+    // The token is number `in_group` of the 64 whose ranks the lanes hold in `mine`; `taken(j)` rows were placed in
+    // receive buffer j before the group.
+    template <class Taken>
+    __device__ __forceinline__ void store(const dispatch_args &a, uint32_t in_group, uint32_t mine, Taken taken) const
+    {
+        const uint64_t before = (1ull << in_group) - 1ull;
+#pragma unroll
+        for (int j = 0; j < DISPATCH_W; ++j) {
+            const uint64_t votes = __ballot((mine >> j) & 1u);
+            if (!((votes >> in_group) & 1u)) continue;
+            char *const d = a.out[j] + (uint64_t)(taken(j) + (uint32_t)__popcll(votes & before)) * bytes;
+            if constexpr (ON_GRID) {
+#pragma unroll
+                for (int i = 0; i < ROWS_PER_WAVE; ++i)
+                    if (byte(i) < bytes) dl_st16<POL>(d + byte(i), v[i]);
+            } else {
+                const dl_plain_item it{src, d, bytes};
+                for (int i = 0; i < ROWS_PER_WAVE; ++i) dl_plain_row<POL, false>(it, row0 + (uint32_t)i * stride);
+            }
+        }
+    }
+};
+
+// Wavefront -> its token of the workgroup, and its first row.
+__device__ __forceinline__ void dl_dispatch_place(const dispatch_args &a, uint32_t *token_in_wg, uint32_t *row0)
 {
-    __shared__ uint32_t in_wave[BUILD_WAVES][DISPATCH_W];
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    const uint32_t token = blockIdx.x * BUILD_THREADS + tid;
-    const uint64_t mine = token < tokens ? dl_global<uint64_t>(mask)[token] : 0ull;
-#pragma unroll
-    for (int j = 0; j < DISPATCH_W; ++j) {
-        const uint64_t votes = __ballot(((mine >> (8 * j)) & 0xFFu) != 0);
-        if (lane == 0) in_wave[wave][j] = (uint32_t)__popcll(votes);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t t = 0, w = wave;
+    while (w >= a.token_waves) {  // (at most MAX_WAVES rounds)
+        w -= a.token_waves;
+        ++t;
     }
-    __syncthreads();
-    if (tid < DISPATCH_W) {
-        uint32_t c = 0;
-#pragma unroll
-        for (uint32_t w = 0; w < BUILD_WAVES; ++w) c += in_wave[w][tid];
-        counts[blockIdx.x * DISPATCH_W + tid] = c;
-    }
+    *token_in_wg = t;
+    *row0 = blockIdx.x * a.token_waves * ROWS_PER_WAVE + w;
 }
 
-// COUNTS: block_rows holds every block's own counts (dl_dispatch_count_kernel), and the rows taken by earlier
-// blocks are summed up here; else it holds those sums already (the host's).
-template <bool PUSHED, bool COUNTS = false>
-__global__ void __launch_bounds__(BUILD_THREADS) dl_dispatch_build_kernel(const uint8_t *__restrict__ mask,
-                                                                          const uint32_t *__restrict__ block_rows,
-                                                                          const build_args a,
-                                                                          dl_fused_item *__restrict__ items,
-                                                                          const dl_pushed ps)
+template <int POL, bool ON_GRID>
+__global__ void __launch_bounds__(64 * MAX_WAVES) dl_dispatch_list_kernel(const dispatch_list p)
 {
-    constexpr int POL = PUSHED ? DL_POL_COHERENT : DL_POL_WT;
-    __shared__ uint32_t before_block[DISPATCH_W];          // rows taken by the tokens of earlier blocks
-    __shared__ uint32_t in_wave[BUILD_WAVES][DISPATCH_W];  // per wavefront: destinations of its own 64 tokens
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    constexpr uint32_t W = DISPATCH_W;
-    const uint32_t block0 = blockIdx.x * BUILD_THREADS;
-    const uint32_t token = block0 + tid;
-    const bool valid = token < a.tokens;
-    uint64_t mine = 0;
-    if constexpr (PUSHED) {
-        // one lane sees the slot's stamp first: only what is read after that is known to be this request's
-        __shared__ uint32_t sealed;
-        if (tid == 0) sealed = dl_pushed_sealed(mask, ps) ? 1u : 0u;
-        __syncthreads();
-        if (!sealed) {
-            // The mask never became complete (the writes were on their way before the launch, so: never).  The row
-            // kernel behind this one executes whatever the table holds: give it an entry that moves nothing for
-            // every token of this block, and let the host hear of the loss.
-            if (valid) {
-                dl_fused_item none;
-                none.src = nullptr;
-                none.bytes = 0;
-                none.k = 0;
-                none.pad = 0;
-#pragma unroll
-                for (int q = 0; q < DL_FAN; ++q) none.dst[q] = nullptr;
-                items[token] = none;
-            }
-            if (tid == 0) dl_pushed_report_lost(ps);
-            return;
-        }
-        if (tid < DISPATCH_W)
-            before_block[tid] = dl_ld<POL>(dl_global<uint32_t>(block_rows) + blockIdx.x * DISPATCH_W + tid);
-        mine = valid ? dl_ld<POL>(dl_global<uint64_t>(mask) + token) : 0ull;
-    } else if constexpr (COUNTS) {
-        if (tid < DISPATCH_W) {
-            uint32_t before = 0;
-            for (uint32_t b = 0; b < blockIdx.x; ++b) before += block_rows[b * DISPATCH_W + tid];
-            before_block[tid] = before;
-        }
-        mine = valid ? dl_ld<POL>(dl_global<uint64_t>(mask) + token) : 0ull;
-    } else {
-        if (tid < DISPATCH_W) before_block[tid] = dl_ld<POL>(dl_global<uint32_t>(block_rows) + blockIdx.x * DISPATCH_W + tid);
-        mine = valid ? dl_ld<POL>(dl_global<uint64_t>(mask) + token) : 0ull;
+    uint32_t t, row0;
+    dl_dispatch_place(p.a, &t, &row0);
+    const uint32_t first = blockIdx.y * p.a.wg_tokens;  // within this launch
+    const dispatch_group &g = p.group[first / GROUP];
+    const uint32_t token = p.a.token0 + first + t;
+    if (token >= p.a.tokens) return;
+    const uint32_t mine = g.ranks[threadIdx.x & 63u];
+    dispatch_row<POL, ON_GRID> row;
+    row.load(p.a, token, row0);
+    row.store(p.a, (first + t) % GROUP, mine, [&](int j) { return g.taken[j]; });
+}
+
+// The groups in device memory, written there by the host through the BAR just before the launch: read past the caches,
+// once the slot's stamp has been seen (see dl_pushed_entry in the row kernels), and handed on through LDS.
+template <int POL, bool ON_GRID>
+__global__ void __launch_bounds__(64 * MAX_WAVES) dl_dispatch_pushed_kernel(const dispatch_args a, const dispatch_group *groups,
+                                                                            const dl_pushed ps)
+{
+    constexpr uint32_t WORDS = sizeof(dispatch_group) / 8;
+    __shared__ uint64_t raw[WORDS];
+    __shared__ uint32_t sealed;
+    uint32_t t, row0;
+    dl_dispatch_place(a, &t, &row0);
+    const uint32_t first = blockIdx.y * a.wg_tokens;
+    const bool valid = first + t < a.tokens;  // uniform over the wavefront
+    if (threadIdx.x == 0) sealed = dl_pushed_sealed(groups, ps) ? 1u : 0u;
+    __syncthreads();
+    if (!sealed) {
+        if (threadIdx.x == 0) dl_pushed_report_lost(ps);  // nothing copied by this workgroup; the host hears of it
+        return;
     }
-    bool m[DISPATCH_W];
-    uint32_t pos[DISPATCH_W], k = 0;
-#pragma unroll
-    for (int j = 0; j < DISPATCH_W; ++j) {
-        m[j] = ((mine >> (8 * j)) & 0xFFu) != 0;
-        const uint64_t votes = __ballot(m[j]);
-        pos[j] = (uint32_t)__popcll(votes & ((1ull << lane) - 1ull));  // earlier tokens of this wavefront
-        if (lane == 0) in_wave[wave][j] = (uint32_t)__popcll(votes);
-        k += m[j] ? 1u : 0u;
-    }
+    if (threadIdx.x < WORDS) raw[threadIdx.x] = dl_ld<DL_POL_COHERENT>(dl_global<uint64_t>(groups + first / GROUP) + threadIdx.x);
+    dispatch_row<POL, ON_GRID> row;
+    if (valid) row.load(a, first + t, row0);
     __syncthreads();
     if (!valid) return;
-#pragma unroll
-    for (int j = 0; j < DISPATCH_W; ++j) {
-        pos[j] += before_block[j];
-#pragma unroll
-        for (uint32_t w = 0; w < BUILD_WAVES; ++w) pos[j] += w < wave ? in_wave[w][j] : 0u;
-    }
+    const dispatch_group &g = *reinterpret_cast<const dispatch_group *>(raw);
+    const uint32_t mine = g.ranks[threadIdx.x & 63u];
+    row.store(a, (first + t) % GROUP, mine, [&](int j) { return (uint32_t)__builtin_amdgcn_readfirstlane(g.taken[j]); });
+}
 
-    // the token's rank is the last one that starts at or before it; its send buffer and first token are
-    // picked by compares against kernel arguments (no load depends on the token)
-    const char *base = a.in[0];
-    uint32_t first = 0;
+// Every byte of a mask word to 0 or 1.
+__device__ __forceinline__ uint64_t dl_mask_fold(uint64_t w)
+{
+    w |= w >> 4;
+    w |= w >> 2;
+    w |= w >> 1;
+    return w & 0x0101010101010101ull;
+}
+
+template <int POL, bool ON_GRID>
+__global__ void __launch_bounds__(64 * MAX_WAVES) dl_dispatch_mask_kernel(const dispatch_args a, const uint8_t *__restrict__ mask)
+{
+    __shared__ uint32_t part[MAX_WAVES][4];
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t waves = blockDim.x >> 6;
+    uint32_t t, row0;
+    dl_dispatch_place(a, &t, &row0);
+    const uint32_t first = blockIdx.y * a.wg_tokens;
+    const uint32_t group0 = first & ~(GROUP - 1u);  // the same for the whole workgroup: wg_tokens divides GROUP
+    const bool valid = first + t < a.tokens;  // uniform over the wavefront
+    const DL_GLOBAL uint64_t *words = dl_global<uint64_t>(mask);
+    const uint64_t own = group0 + lane < a.tokens ? words[group0 + lane] : 0ull;
+    // the tokens before the group, two per 16-byte load, BATCH loads in flight; a thread sums at most
+    // DL_DISPATCH_DEVICE_MAX_TOKENS / 64 words, so a byte of the sum does not overflow
+    static_assert(DL_DISPATCH_DEVICE_MAX_TOKENS / 64 <= 255, "bytewise sums");
+    constexpr uint32_t BATCH = 4;
+    const uint32_t step = 2u * blockDim.x;
+    dl_u32x4 w[BATCH];
+    const auto fetch = [&](uint32_t i) {
 #pragma unroll
-    for (int r = 1; r < DISPATCH_W; ++r)
-        if ((uint32_t)r < W && a.first_token[r] <= token) {
-            base = a.in[r];
-            first = a.first_token[r];
+        for (uint32_t u = 0; u < BATCH; ++u) {
+            w[u] = dl_u32x4{0, 0, 0, 0};
+            if (i + u * step < group0) w[u] = dl_ld16<DL_POL_WT>((const char *)mask + 8ull * (i + u * step));
         }
-    dl_fused_item it;
-    it.src = base + (uint64_t)(token - first) * a.row_bytes;
-    it.bytes = a.row_bytes;
-    it.k = k;
-    it.pad = 0;
+    };
+    uint64_t sum = 0;
+    const auto add = [&] {
 #pragma unroll
-    for (int s = 0; s < DL_FAN; ++s) it.dst[s] = nullptr;
-    // destination number d (in rank order) goes to sub-group d / per (0 or 1), slot 4 (d / per) + d % per,
-    // per = ceil(k / 2): the layout of slots_by_subgroup for DL_TABLE_ROWS_SPLIT sub-groups
-    static_assert(DL_TABLE_ROWS_SPLIT == 2 && DL_FAN == 8, "slot layout below is written for two sub-groups of four");
-    const uint32_t per = (k + 1u) >> 1;
-    uint32_t d = 0;
-#pragma unroll
-    for (int j = 0; j < DISPATCH_W; ++j) {
-        if (m[j]) {
-            char *p = a.out[j] + (uint64_t)pos[j] * a.row_bytes;
-            const uint32_t slot = d >= per ? 4u + d - per : d;
-#pragma unroll
-            for (int s = 0; s < DL_FAN; ++s)
-                if ((uint32_t)s == slot) it.dst[s] = p;
-            ++d;
-        }
+        for (uint32_t u = 0; u < BATCH; ++u)
+            sum += dl_mask_fold(w[u].x | ((uint64_t)w[u].y << 32)) + dl_mask_fold(w[u].z | ((uint64_t)w[u].w << 32));
+    };
+    fetch(2u * threadIdx.x);
+    dispatch_row<POL, ON_GRID> row;
+    if (valid) row.load(a, first + t, row0);  // behind the mask's first loads: those come back first
+    add();
+    for (uint32_t i = 2u * threadIdx.x + BATCH * step; i < group0; i += BATCH * step) {
+        fetch(i);
+        add();
     }
-    items[token] = it;
+    // to 16 bits a column, two columns a word: columns 0|2, 1|3, 4|6, 5|7
+    const uint32_t lo = (uint32_t)sum, hi = (uint32_t)(sum >> 32);
+    uint32_t c[4] = {lo & 0x00FF00FFu, (lo >> 8) & 0x00FF00FFu, hi & 0x00FF00FFu, (hi >> 8) & 0x00FF00FFu};
+    static_assert(DL_DISPATCH_DEVICE_MAX_TOKENS < 65536, "16-bit counts");
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        for (int o = 32; o; o >>= 1) c[q] += __shfl_xor(c[q], o);
+        if (lane == 0) part[wave][q] = c[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        uint32_t s = 0;
+        for (uint32_t w = 0; w < waves; ++w) s += part[w][q];
+        c[q] = __builtin_amdgcn_readfirstlane(s);
+    }
+    const uint64_t bits = dl_mask_fold(own);
+    uint32_t mine = 0;
+#pragma unroll
+    for (int j = 0; j < DISPATCH_W; ++j) mine |= ((uint32_t)(bits >> (8 * j)) & 1u) << j;
+    if (!valid) return;
+    row.store(a, first + t - group0, mine, [&](int j) {
+        const uint32_t both = c[(j >> 2) * 2 + (j & 1)];
+        return (j & 2) ? both >> 16 : both & 0xFFFFu;
+    });
 }
 
 // How far behind a DL_CUT boundary the first destination of a row can lie: rows stand whole multiples of
@@ -187,10 +263,71 @@ bool rows_on_grid(const void *const *in, void *const *out, int W, size_t row_byt
     return m == 0 && (row_bytes & 15u) == 0 && worst_shift(out, W, row_bytes) == 0;
 }
 
+// What both kernels are told, and their grid: a token's rows are shared out over up to MAX_WAVES wavefronts (a longer
+// row takes several workgroups, blockIdx.x); short rows put several tokens into a workgroup.
+struct dispatch_shape {
+    uint32_t grid_x;
+    uint32_t threads;
+    int policy;
+    bool on_grid;
+};
+
+int dispatch_setup(const void *const *in, void *const *out, const uint32_t *tokens, uint64_t total, size_t row_bytes,
+                   dispatch_args *a, dispatch_shape *sh)
+{
+    uint32_t first = 0;
+    for (int i = 0; i < DISPATCH_W; ++i) {
+        a->in[i] = (const char *)in[i];
+        a->out[i] = (char *)out[i];
+        a->first_token[i] = first;
+        first += tokens[i];
+    }
+    a->tokens = (uint32_t)total;
+    a->token0 = 0;
+    a->row_bytes = row_bytes;
+    const uint64_t rows = (row_bytes + worst_shift(out, DISPATCH_W, row_bytes) + 1023u) >> 10;
+    if (rows * total >= (1ull << 30)) return DL_ERR_INVALID;  // beyond a grid
+    const uint32_t per_wg = MAX_WAVES * ROWS_PER_WAVE;
+    sh->grid_x = (uint32_t)((rows + per_wg - 1) / per_wg);
+    a->token_waves = (uint32_t)((rows + sh->grid_x * ROWS_PER_WAVE - 1) / (sh->grid_x * ROWS_PER_WAVE));
+    a->wg_tokens = 1;
+    while (2u * a->wg_tokens * a->token_waves <= MAX_WAVES) a->wg_tokens *= 2;
+    sh->threads = 64u * a->wg_tokens * a->token_waves;
+    sh->on_grid = rows_on_grid(in, out, DISPATCH_W, row_bytes);
+    // Cache policy by an upper bound of what is moved (every token to every rank; top-8 of 256 experts: two thirds of
+    // that), at the lines of the fan-outs of a list: write-through stores, with streaming loads, streamed output.
+    // 128 tokens of 14 336 bytes per rank (126 MiB by this measure) 15.8 / 15.3 / 17.1 us, 512 (504 MiB) 70.6 / 71.8 / 58.6.
+    const uint64_t bound = total * row_bytes * (1u + DISPATCH_W);
+    const dl_config &c = g_dl.cfg;
+    sh->policy = bound >= c.nontemporal_min_bytes ? DL_POL_STREAM
+                 : bound > c.write_through_max_bytes ? DL_POL_STREAM_OUT : bound >= DL_FAN_STREAM_IN_MIN_BYTES ? DL_POL_STREAM_IN : DL_POL_WT;
+    return DL_OK;
+}
+
+// `m` tokens (at most GROUP) of the mask to their group's record; `placed` is carried from group to group.
+void pack_group(dispatch_group *g, const uint8_t *mask, uint32_t m, uint32_t (&placed)[DISPATCH_W])
+{
+    memcpy(g->taken, placed, sizeof placed);
+    uint64_t acc = 0;  // bytewise sums of at most 64 words of zeros and ones
+    for (uint32_t t = 0; t < m; ++t) {
+        uint64_t w;
+        memcpy(&w, mask + t * (size_t)DISPATCH_W, sizeof w);
+        w |= w >> 4;
+        w |= w >> 2;
+        w |= w >> 1;
+        w &= 0x0101010101010101ull;
+        acc += w;
+        // the eight low bits into one byte: the multiplication moves bit 8 j to bit 56 + j
+        g->ranks[t] = (uint8_t)((w * 0x0102040810204080ull) >> 56);
+    }
+    memset(g->ranks + m, 0, GROUP - m);
+    for (int j = 0; j < DISPATCH_W; ++j) placed[j] += (uint32_t)(acc >> (8 * j)) & 0xFFu;
+}
+
 }  // namespace
 
 int dl_dispatch_on_device(const void *const *in, void *const *out, int W, const uint32_t *tokens, size_t row_bytes,
-                          const uint8_t *dest, hipStream_t stream, bool *taken)
+                          const uint8_t *dest, uint64_t min_tokens, hipStream_t stream, bool *taken)
 {
     *taken = false;
     const dl_config &c = g_dl.cfg;
@@ -202,89 +339,58 @@ int dl_dispatch_on_device(const void *const *in, void *const *out, int W, const 
         total += tokens[i];
         if ((tokens[i] && !in[i]) || !out[i]) return DL_OK;  // the host lowering reports what is wrong
     }
-    // worth two small launches only for many tokens; mask, block counts and item table share one ring slot
-    const uint64_t blocks = (total + BUILD_THREADS - 1) / BUILD_THREADS;
-    const uint64_t mask_bytes = (total * (uint64_t)W + 255u) & ~(uint64_t)255u;               // then the block counts:
-    const uint64_t head_bytes = (mask_bytes + blocks * DISPATCH_W * sizeof(uint32_t) + 255u) & ~(uint64_t)255u;
-    if (total < 512 || head_bytes + total * sizeof(dl_fused_item) > DL_RING_SLOT_BYTES)
-        return DL_OK;
+    if (total == 0 || total < min_tokens || total >= (1ull << 21)) return DL_OK;  // (a grid has at most 65535 rows of workgroups)
+    if (dl_debug_lose_armed() && total <= DISPATCH_GROUPS * GROUP) return DL_OK;  // the hook loses tables; the host lowering makes one
 
-    size_t slot;
-    char *host, *dev;
-    int rc = dl_ring_acquire(&slot, &host, &dev);  // the item table's place (and the mask's, if it is staged)
+    dispatch_list p;
+    dispatch_shape sh;
+    int rc = dispatch_setup(in, out, tokens, total, row_bytes, &p.a, &sh);
     if (rc != DL_OK) return rc;
-    char *pushed = dl_push_acquire(head_bytes, stream, &rc);
-    if (rc != DL_OK) return rc;
+    const uint64_t groups = (total + GROUP - 1) / GROUP;
+    char *pushed = nullptr;
+    if (groups > DISPATCH_GROUPS) {
+        // too long for the kernel arguments of one launch: all groups through the BAR, if that way is open
+        pushed = dl_push_acquire(groups * sizeof(dispatch_group), stream, &rc);
+        if (rc != DL_OK) return rc;
+    }
     *taken = true;
-    // One 64-bit word per token, every byte 0 or 1.  Adding words adds the eight columns bytewise: the running
-    // sums are unpacked every 128 tokens (a byte holds 255), and before every 256th token they go out as that
-    // block's counts of rows already taken.
-    static_assert(DISPATCH_W == 8 && BUILD_THREADS == 256, "a token's mask is one 64-bit word; blocks of 256 tokens");
-    uint64_t *words = (uint64_t *)(pushed ? pushed : host);
-    uint32_t *block_rows = (uint32_t *)((char *)words + mask_bytes);
-    uint32_t taken_rows[DISPATCH_W] = {0};
-    for (size_t t0 = 0; t0 < total; t0 += 128) {
-        if ((t0 & 255u) == 0)
-            for (int j = 0; j < DISPATCH_W; ++j) block_rows[(t0 >> 8) * DISPATCH_W + j] = taken_rows[j];
-        const size_t t1 = t0 + 128 < total ? t0 + 128 : total;
-        uint64_t acc = 0;
-        for (size_t t = t0; t < t1; ++t) {  // a plain loop over words: the compiler vectorises it
-            uint64_t w;
-            memcpy(&w, dest + t * (size_t)DISPATCH_W, sizeof w);
-            // a non-zero byte becomes 1: fold its bits into bit 0, keep bit 0 of every byte
-            w |= w >> 4;
-            w |= w >> 2;
-            w |= w >> 1;
-            w &= 0x0101010101010101ull;
-            words[t] = w;  // write only: the slot may be device memory behind the BAR
-            acc += w;
+    uint32_t placed[DISPATCH_W] = {0};
+    if (pushed) {
+        dispatch_group *slot = (dispatch_group *)pushed;
+        for (uint64_t g = 0; g < groups; ++g) {
+            dispatch_group one;  // packed here, then written in one go: the slot is write only
+            const uint64_t t0 = g * GROUP;
+            pack_group(&one, dest + t0 * DISPATCH_W, (uint32_t)(total - t0 < GROUP ? total - t0 : GROUP), placed);
+            memcpy(slot + g, &one, sizeof one);
         }
-        for (int j = 0; j < DISPATCH_W; ++j) taken_rows[j] += (uint32_t)(acc >> (8 * j)) & 0xFFu;
+        const dl_pushed ps = dl_push_kernel_args(dl_push_seal(pushed));
+        const dim3 grid(sh.grid_x, (uint32_t)((total + p.a.wg_tokens - 1) / p.a.wg_tokens));
+        dl_with_policy_and_grid(sh.policy, sh.on_grid, [&](auto pol, auto og) {
+            hipLaunchKernelGGL((dl_dispatch_pushed_kernel<decltype(pol)::value, decltype(og)::value>), grid, dim3(sh.threads), 0,
+                               stream, p.a, (const dispatch_group *)pushed, ps);
+        });
+        DL_HIP(hipGetLastError());
+        return dl_push_commit(stream);
     }
-    uint64_t stamp = 0;
-    if (pushed) {
-        stamp = dl_push_seal(pushed);
-    } else {
-        rc = dl_ring_stage(slot, head_bytes, stream);
-        if (rc != DL_OK) return rc;
+    for (uint64_t g0 = 0; g0 < groups; g0 += DISPATCH_GROUPS) {
+        const uint64_t g1 = groups - g0 < DISPATCH_GROUPS ? groups : g0 + DISPATCH_GROUPS;
+        for (uint64_t g = g0; g < g1; ++g) {
+            const uint64_t t0 = g * GROUP;
+            pack_group(&p.group[g - g0], dest + t0 * DISPATCH_W, (uint32_t)(total - t0 < GROUP ? total - t0 : GROUP), placed);
+        }
+        p.a.token0 = (uint32_t)(g0 * GROUP);
+        const uint64_t n = (g1 * GROUP < total ? g1 * GROUP : total) - g0 * GROUP;
+        const dim3 grid(sh.grid_x, (uint32_t)((n + p.a.wg_tokens - 1) / p.a.wg_tokens));
+        dl_with_policy_and_grid(sh.policy, sh.on_grid, [&](auto pol, auto og) {
+            hipLaunchKernelGGL((dl_dispatch_list_kernel<decltype(pol)::value, decltype(og)::value>), grid, dim3(sh.threads), 0, stream, p);
+        });
+        DL_HIP(hipGetLastError());
     }
-    const char *head = pushed ? pushed : dev;
-
-    build_args a;
-    uint32_t first = 0;
-    for (int i = 0; i < DISPATCH_W; ++i) {
-        a.in[i] = i < W ? (const char *)in[i] : nullptr;
-        a.out[i] = i < W ? (char *)out[i] : nullptr;
-        a.first_token[i] = first;
-        if (i < W) first += tokens[i];
-    }
-    a.first_token[DISPATCH_W] = first;
-    a.W = (uint32_t)W;
-    a.tokens = (uint32_t)total;
-    a.row_bytes = row_bytes;
-    dl_fused_item *items = (dl_fused_item *)(dev + head_bytes);
-    const dim3 grid((uint32_t)blocks);
-    const uint8_t *mask = (const uint8_t *)head;
-    const uint32_t *rows_before = (const uint32_t *)(head + mask_bytes);
-    const dl_pushed ps = dl_push_kernel_args(stamp);
-    if (pushed)
-        hipLaunchKernelGGL(dl_dispatch_build_kernel<true>, grid, dim3(BUILD_THREADS), 0, stream, mask, rows_before, a, items, ps);
-    else
-        hipLaunchKernelGGL(dl_dispatch_build_kernel<false>, grid, dim3(BUILD_THREADS), 0, stream, mask, rows_before, a, items, ps);
-    DL_HIP(hipGetLastError());
-    if (pushed) {
-        rc = dl_push_commit(stream);
-        if (rc != DL_OK) return rc;
-    }
-    rc = dl_launch_fused_rows_table(items, (uint32_t)total, row_bytes, worst_shift(out, W, row_bytes),
-                                    rows_on_grid(in, out, W, row_bytes), stream);
-    if (rc != DL_OK) return rc;
-    return dl_ring_release(slot, stream);
+    return DL_OK;
 }
 
-// Token dispatch with the routing mask in device memory (dl_token_dispatch_device): nothing of the request but
-// the kernel arguments comes from the host.  Three launches on the caller's stream: count per block, build the
-// item table (in a slot of the library's table memory), execute it.
+// Token dispatch with the routing mask in device memory (dl_token_dispatch_device): one launch on the caller's
+// stream, nothing of the request but the kernel arguments comes from the host, and no memory of the library's is used.
 extern "C" int dl_token_dispatch_device(const void *const *in, void *const *out, int W, const uint32_t *tokens,
                                         size_t row_bytes, const uint8_t *dest_device, void *stream)
 {
@@ -300,40 +406,16 @@ extern "C" int dl_token_dispatch_device(const void *const *in, void *const *out,
         if ((tokens[i] && !in[i]) || !out[i]) return DL_ERR_INVALID;
     }
     if (total > DL_DISPATCH_DEVICE_MAX_TOKENS) return DL_ERR_CAPACITY;
-    const uint64_t blocks = (total + BUILD_THREADS - 1) / BUILD_THREADS;
-    const uint64_t head_bytes = (blocks * DISPATCH_W * sizeof(uint32_t) + 255u) & ~(uint64_t)255u;
-    static_assert((((DL_DISPATCH_DEVICE_MAX_TOKENS + BUILD_THREADS - 1) / BUILD_THREADS * DISPATCH_W * sizeof(uint32_t) + 255u) & ~(size_t)255u) +
-                          DL_DISPATCH_DEVICE_MAX_TOKENS * sizeof(dl_fused_item) <= DL_RING_SLOT_BYTES,
-                  "counts and table of the largest request fit one slot of the table memory");
-    hipStream_t hs = (hipStream_t)stream;
-
-    size_t slot;
-    char *host, *dev;
-    int rc = dl_ring_acquire(&slot, &host, &dev);
+    dispatch_args a;
+    dispatch_shape sh;
+    const int rc = dispatch_setup(in, out, tokens, total, row_bytes, &a, &sh);
     if (rc != DL_OK) return rc;
-    uint32_t *counts = (uint32_t *)dev;
-    dl_fused_item *items = (dl_fused_item *)(dev + head_bytes);
-    hipLaunchKernelGGL(dl_dispatch_count_kernel, dim3((uint32_t)blocks), dim3(BUILD_THREADS), 0, hs, dest_device,
-                       (uint32_t)total, counts);
+    const dim3 grid(sh.grid_x, (uint32_t)((total + a.wg_tokens - 1) / a.wg_tokens));
+    dl_with_policy_and_grid(sh.policy, sh.on_grid, [&](auto pol, auto og) {
+        hipLaunchKernelGGL((dl_dispatch_mask_kernel<decltype(pol)::value, decltype(og)::value>), grid, dim3(sh.threads), 0,
+                           (hipStream_t)stream, a, dest_device);
+    });
     DL_HIP(hipGetLastError());
-    build_args a;
-    uint32_t first = 0;
-    for (int i = 0; i < DISPATCH_W; ++i) {
-        a.in[i] = (const char *)in[i];
-        a.out[i] = (char *)out[i];
-        a.first_token[i] = first;
-        first += tokens[i];
-    }
-    a.first_token[DISPATCH_W] = first;
-    a.W = (uint32_t)W;
-    a.tokens = (uint32_t)total;
-    a.row_bytes = row_bytes;
-    hipLaunchKernelGGL((dl_dispatch_build_kernel<false, true>), dim3((uint32_t)blocks), dim3(BUILD_THREADS), 0, hs,
-                       dest_device, (const uint32_t *)counts, a, items, dl_push_kernel_args(0));
-    DL_HIP(hipGetLastError());
-    rc = dl_launch_fused_rows_table(items, (uint32_t)total, row_bytes, worst_shift(out, W, row_bytes),
-                                    rows_on_grid(in, out, W, row_bytes), hs);
-    if (rc != DL_OK) return rc;
     t_dl_last.mode = DL_MODE_ONESHOT;
-    return dl_ring_release(slot, hs);
+    return DL_OK;
 }

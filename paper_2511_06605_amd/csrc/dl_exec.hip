@@ -478,7 +478,6 @@ constexpr uint32_t DL_UROWS_MAX_ITEMS = 65535;    // a grid's second dimension g
 constexpr uint64_t TABLE_ENTRIES_TARGET = 8192;  // table kernels: aim for at most this many one-tile entries
 constexpr uint64_t PLAIN_WAVE_MIN_BYTES = 48ull << 20;  // bytes moved (read + written) from which a list of plain copies takes one-wavefront workgroups
 constexpr uint64_t FAN_WAVE_MIN_BYTES = 3ull << 20;         // bytes moved above which a copy with several destinations takes one wavefront per row
-constexpr uint64_t FAN_STREAM_IN_MIN_BYTES = 88ull << 20;   // ... with streaming loads from this many
 constexpr uint64_t UNIFORM_ROWS_MIN_BYTES = 4ull << 20;  // source bytes from which a uniform long list takes the row kernel
 constexpr uint64_t UNIFORM_ROWS_STAGE_BYTES = 768ull << 20;  // bytes moved (read + written) from which its table is staged even where it could be pushed
 constexpr size_t TABLE_STAGE_MIN = 512;          // tables at least this long are staged in device memory first
@@ -513,30 +512,6 @@ struct ring_t {
     uint64_t armed[RING_SLOTS]{};         // ticket of the armed (prelaunch mode) request whose table is in the slot, or 0
     size_t next = 0;
 } g_ring;
-
-// Calls f with the cache policy as a compile-time constant.
-template <class F>
-inline void with_policy(int policy, F f)
-{
-    switch (policy) {
-    case DL_POL_STREAM: f(std::integral_constant<int, DL_POL_STREAM>{}); break;
-    case DL_POL_WT: f(std::integral_constant<int, DL_POL_WT>{}); break;
-    case DL_POL_STREAM_IN: f(std::integral_constant<int, DL_POL_STREAM_IN>{}); break;
-    default: f(std::integral_constant<int, DL_POL_STREAM_OUT>{}); break;
-    }
-}
-
-// ... and with whether every item lies on the grid (see dl_rows_body) as one too.
-template <class F>
-inline void with_policy_and_grid(int policy, bool on_grid, F f)
-{
-    with_policy(policy, [&](auto pol) {
-        if (on_grid)
-            f(pol, std::true_type{});
-        else
-            f(pol, std::false_type{});
-    });
-}
 
 // The item's first destination stands on a DL_CUT boundary, its length is a multiple of 16 and its source one of 4.
 template <class Item>
@@ -621,7 +596,7 @@ int launch_klist(const Item *items, size_t n, const uint64_t *tile_end, const dl
     if constexpr (std::is_same<Item, dl_fused_item>::value) {
         if (sh.pairs) {  // (tile_end counts workgroups: one per row and pair of destinations)
             const uint32_t blocks = (uint32_t)tile_end[n - 1];
-            with_policy_and_grid(sh.policy, on_grid, [&](auto pol, auto og) {
+            dl_with_policy_and_grid(sh.policy, on_grid, [&](auto pol, auto og) {
                 hipLaunchKernelGGL((dl_exec_pairs_kernel<NMAX, decltype(pol)::value, decltype(og)::value>), dim3(blocks),
                                    dim3(64), 0, stream, p);
             });
@@ -647,22 +622,22 @@ int launch_klist(const Item *items, size_t n, const uint64_t *tile_end, const dl
         else
             hipLaunchKernelGGL((dl_armed_list_kernel<Item, NMAX, false>), dim3(g), dim3(sh.block_threads), 0, stream, p, a);
     } else if (sh.rows && sh.rows2d_width) {
-        with_policy_and_grid(sh.policy, on_grid, [&](auto pol, auto og) {
+        dl_with_policy_and_grid(sh.policy, on_grid, [&](auto pol, auto og) {
             hipLaunchKernelGGL((dl_exec_rows2d_kernel<Item, NMAX, decltype(pol)::value, decltype(og)::value>),
                                dim3(sh.rows2d_width, (uint32_t)n), dim3(sh.block_threads), 0, stream, p);
         });
     } else if (sh.rows) {
-        with_policy_and_grid(sh.policy, on_grid, [&](auto pol, auto og) {
+        dl_with_policy_and_grid(sh.policy, on_grid, [&](auto pol, auto og) {
             hipLaunchKernelGGL((dl_exec_rows_kernel<Item, NMAX, decltype(pol)::value, decltype(og)::value>), dim3(grid),
                                dim3(sh.block_threads), 0, stream, p);
         });
     } else if (sh.max_blocks && grid > sh.max_blocks) {
-        with_policy(sh.policy, [&](auto pol) {
+        dl_with_policy(sh.policy, [&](auto pol) {
             hipLaunchKernelGGL((dl_exec_list_strided_kernel<Item, NMAX, decltype(pol)::value>), dim3(sh.max_blocks),
                                dim3(sh.block_threads), 0, stream, p);
         });
     } else {
-        with_policy(sh.policy, [&](auto pol) {
+        dl_with_policy(sh.policy, [&](auto pol) {
             hipLaunchKernelGGL((dl_exec_list_kernel<Item, NMAX, decltype(pol)::value>), dim3(grid),
                                dim3(sh.block_threads), 0, stream, p);
         });
@@ -852,7 +827,7 @@ bool launch_uniform_rows(const Item *items, size_t n, const dl_launch_shape &sh,
         dslot = (const Item *)(g_ring.dev + s * RING_SLOT_BYTES);
     }
     const dl_pushed ps = dl_push_kernel_args(stamp);
-    with_policy_and_grid(sh.policy, on_grid, [&](auto pol, auto og) {
+    dl_with_policy_and_grid(sh.policy, on_grid, [&](auto pol, auto og) {
         if (pushed)
             hipLaunchKernelGGL((dl_exec_urows_kernel<Item, decltype(pol)::value, true, decltype(og)::value>),
                                dim3((uint32_t)tpi, (uint32_t)n), dim3(threads), 0, stream, dslot,
@@ -992,7 +967,7 @@ int launch_table(const Item *items, size_t n, dl_launch_shape sh, hipStream_t st
                     g_ring.armed[s] = a.ticket;
             }
         } else {
-            with_policy(sh.policy, [&](auto pol) {
+            dl_with_policy(sh.policy, [&](auto pol) {
                 if (pushed)
                     hipLaunchKernelGGL((dl_exec_table_kernel<Item, decltype(pol)::value, true>), dim3((uint32_t)m),
                                        dim3(sh.block_threads), 0, stream, slot, (uint32_t)m, sh.split, ps);
@@ -1089,7 +1064,7 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
                 // With one load per row the loads can be streaming ones (see DL_POL_STREAM_IN), from the size at which
                 // output and sources no longer share the caches: 72 MiB moved 10.70 us either way, 84 MiB 14.7 -> 15.1,
                 // 90 MiB (3 MiB per rank over five) 18.3 -> 15.6, 108 MiB 21.3 -> 19.0.
-                if (moved >= FAN_STREAM_IN_MIN_BYTES) sh.policy = DL_POL_STREAM_IN;
+                if (moved >= DL_FAN_STREAM_IN_MIN_BYTES) sh.policy = DL_POL_STREAM_IN;
             }
         }
         for (;;) {
@@ -1267,54 +1242,17 @@ int dl_standby_launch(void *rec_mem, const dl_arm *a, hipStream_t stream)
     return DL_OK;
 }
 
-int dl_launch_fused_rows_table(const dl_fused_item *dev_items, uint32_t n, uint64_t item_bytes, uint32_t max_shift,
-                               bool on_grid, hipStream_t stream)
-{
-    // the table's destinations are laid out for DL_TABLE_ROWS_SPLIT sub-groups (see slots_by_subgroup)
-    const uint32_t split = DL_TABLE_ROWS_SPLIT, threads = DL_TABLE_ROWS_THREADS, tile = 16u * threads / split;
-    const uint64_t tpi = (item_bytes + max_shift + tile - 1) / tile;
-    if (n == 0 || n > DL_UROWS_MAX_ITEMS || max_shift >= DL_CUT || tpi * n >= (1ull << 30)) return DL_ERR_INVALID;
-    const dl_launch_shape sh = dl_choose_shape((uint64_t)n * item_bytes, item_bytes, 8);
-    with_policy_and_grid(sh.policy, on_grid && max_shift == 0, [&](auto pol, auto og) {
-        hipLaunchKernelGGL((dl_exec_urows_kernel<dl_fused_item, decltype(pol)::value, false, decltype(og)::value>),
-                           dim3((uint32_t)tpi, n), dim3(threads), 0, stream, dev_items, log2u(threads / 64u / split),
-                           log2u(split), dl_push_kernel_args(0));
-    });
-    DL_HIP(hipGetLastError());
-    return DL_OK;
-}
-
 int dl_launch_plain_table(const dl_plain_item *dev_items, uint32_t m, uint32_t entry_bytes, uint64_t moved, hipStream_t stream)
 {
     if (m == 0) return DL_OK;
     const dl_launch_shape sh = dl_choose_shape(moved / 2, entry_bytes, 1);  // for the cache policy
-    with_policy(sh.policy, [&](auto pol) {
+    dl_with_policy(sh.policy, [&](auto pol) {
         hipLaunchKernelGGL((dl_exec_table_kernel<dl_plain_item, decltype(pol)::value, false>), dim3(m), dim3(256), 0,
                            stream, dev_items, m, 1u, dl_push_kernel_args(0));
     });
     DL_HIP(hipGetLastError());
     return DL_OK;
 }
-
-int dl_ring_acquire(size_t *slot, char **host, char **dev)
-{
-    if (!g_ring.base) return DL_ERR_STATE;
-    const size_t s = g_ring.next++ % RING_SLOTS;
-    if (g_ring.used[s]) {
-        const int rc = wait_for_readers(g_ring.ev[s], g_ring.armed[s]);
-        if (rc != DL_OK) {
-            --g_ring.next;
-            return rc;
-        }
-    }
-    g_ring.armed[s] = 0;
-    *slot = s;
-    *host = g_ring.base + s * RING_SLOT_BYTES;
-    *dev = g_ring.dev + s * RING_SLOT_BYTES;
-    return DL_OK;
-}
-
-int dl_ring_stage(size_t slot, uint64_t bytes, hipStream_t stream) { return stage_slot(slot, bytes, stream); }
 
 void dl_ring_forget_armed()
 {
@@ -1346,6 +1284,11 @@ dl_pushed dl_push_kernel_args(uint64_t stamp)
     return ps;
 }
 
+char *dl_push_acquire(size_t bytes, hipStream_t stream, int *rc) { return push_acquire(bytes, stream, rc); }
+uint64_t dl_push_seal(char *slot) { return push_seal(slot); }
+int dl_push_commit(hipStream_t stream) { return push_commit(stream, 0); }
+bool dl_debug_lose_armed() { return g_debug_lose_tries != 0; }
+
 bool dl_device_error_pending() { return g_lost && __atomic_load_n(g_lost, __ATOMIC_ACQUIRE) != 0; }
 
 extern "C" int dl_last_device_error(void)
@@ -1360,17 +1303,6 @@ extern "C" int dl_debug_lose_next_table(uint32_t tries)
     if (!g_ring.push || !g_dl.cfg.table_push) return DL_ERR_STATE;  // no table goes through the BAR here
     if (tries > 1024) return DL_ERR_INVALID;  // 0 disarms the hook
     g_debug_lose_tries = tries;
-    return DL_OK;
-}
-
-char *dl_push_acquire(size_t bytes, hipStream_t stream, int *rc) { return push_acquire(bytes, stream, rc); }
-uint64_t dl_push_seal(char *slot) { return push_seal(slot); }
-int dl_push_commit(hipStream_t stream) { return push_commit(stream, 0); }
-
-int dl_ring_release(size_t slot, hipStream_t stream)
-{
-    DL_HIP(hipEventRecord(g_ring.ev[slot], stream));
-    g_ring.used[slot] = true;
     return DL_OK;
 }
 

@@ -109,6 +109,8 @@ int dl_exec_fused(const dl_fused_item *items, size_t n, hipStream_t stream, cons
 int dl_exec_swap(const dl_swap_item *items, size_t n, hipStream_t stream, const dl_arm *arm, bool *launched);
 int dl_exec_init();
 int dl_exec_shutdown();
+// Bytes moved from which a copy with several destinations that loads every row once uses streaming loads.
+constexpr uint64_t DL_FAN_STREAM_IN_MIN_BYTES = 88ull << 20;
 dl_launch_shape dl_choose_shape(uint64_t src_bytes, uint64_t max_item_bytes, uint32_t max_k);
 
 // Shape of the row kernel over a table of read-once/write-k items in device memory: sub-groups per
@@ -116,14 +118,8 @@ dl_launch_shape dl_choose_shape(uint64_t src_bytes, uint64_t max_item_bytes, uin
 constexpr uint32_t DL_TABLE_ROWS_SPLIT = 2;
 constexpr uint32_t DL_TABLE_ROWS_THREADS = 128;
 
-// dl_exec.hip: the staging ring (pinned host slots of DL_RING_SLOT_BYTES, each with a device mirror).
-//   dl_ring_acquire  waits until the next slot's previous user has finished on the device
-//   dl_ring_stage    enqueues a copy of the first `bytes` (a multiple of 16) of the host slot to its mirror
-//   dl_ring_release  marks the slot as in use until everything enqueued on `stream` so far has finished
+// dl_exec.hip: the staging ring: pinned host slots of this size, each with a device mirror.
 constexpr size_t DL_RING_SLOT_BYTES = 1u << 20;
-int dl_ring_acquire(size_t *slot, char **host, char **dev);
-int dl_ring_stage(size_t slot, uint64_t bytes, hipStream_t stream);
-int dl_ring_release(size_t slot, hipStream_t stream);
 // dl_exec.hip: short tables written by the host straight into device memory (through the BAR).
 //   dl_push_acquire  a slot for `bytes` (at most DL_PUSH_PAYLOAD_BYTES) that a kernel launched on `stream` next
 //                    will read, or null if that way is not open (no such BAR, switched off, too long);
@@ -138,22 +134,16 @@ int dl_ring_release(size_t slot, hipStream_t stream);
 //                    the one stream besides the default stream that cannot go away between two calls
 //   dl_push_kernel_args  what the kernel that reads the slot gets: the stamp, how often to look for it, where to
 //                    report that it never came (stamp 0: a kernel whose table did not go this way)
+//   dl_debug_lose_armed  the test hook waits for a table (dl_debug_lose_next_table)
 //   dl_device_error_pending  a kernel has reported such a loss and dl_last_device_error() has not been called since
+char *dl_push_acquire(size_t bytes, hipStream_t stream, int *rc);
 uint64_t dl_push_seal(char *slot);
+int dl_push_commit(hipStream_t stream);
 dl_pushed dl_push_kernel_args(uint64_t stamp);
 bool dl_device_error_pending();
 void dl_ring_forget_armed();
 void dl_ring_own_stream(hipStream_t stream);
-char *dl_push_acquire(size_t bytes, hipStream_t stream, int *rc);
-int dl_push_commit(hipStream_t stream);
-
-// dl_exec.hip: the row kernel over a table of n equally sized read-once/write-k items that is already in
-// device memory, destinations laid out for DL_TABLE_ROWS_SPLIT sub-groups (see slots_by_subgroup).  max_shift: no
-// item's first destination lies further than this behind a DL_CUT boundary (0: they all stand on one); every item
-// gets the workgroups that the worst position allowed by it needs.  on_grid: every item lies as the on-grid
-// instance of the row kernel wants it (see dl_rows_body).
-int dl_launch_fused_rows_table(const dl_fused_item *dev_items, uint32_t n, uint64_t item_bytes, uint32_t max_shift,
-                               bool on_grid, hipStream_t stream);
+bool dl_debug_lose_armed();
 
 // dl_exec.hip: the table kernel over m plain copies of at most entry_bytes (< 2^32) each that are already in device
 // memory (entry b is workgroup b's), with the cache policy that suits `moved` bytes read + written.
@@ -162,11 +152,10 @@ int dl_launch_plain_table(const dl_plain_item *dev_items, uint32_t m, uint32_t e
 // dl_static.hip: the address of this device's copy of the static table (dl_batch_copy_static).
 int dl_static_init(int device);
 
-// dl_dispatch.hip: token dispatch lowered on the device (the destination mask is scanned into a table of
-// read-once/write-k items in device memory, which the row kernel then executes).  *taken says whether the request qualified; if not,
-// nothing was enqueued and the caller lowers on the host.
+// dl_dispatch.hip: token dispatch whose rows are placed on the device.  *taken says whether the request qualified (at
+// least min_tokens tokens among other things); if not, nothing was enqueued and the caller lowers on the host.
 int dl_dispatch_on_device(const void *const *in, void *const *out, int W, const uint32_t *tokens, size_t row_bytes,
-                          const uint8_t *dest, hipStream_t stream, bool *taken);
+                          const uint8_t *dest, uint64_t min_tokens, hipStream_t stream, bool *taken);
 
 // Standby executors (DL_MODE_STANDBY): armed kernels that wait, not for a request that is known already, but for
 // any small request.  The host writes the request's copy list into a record (in device memory, through the BAR,

@@ -87,3 +87,65 @@ def test_fanouts_around_their_size_rules(ref, W, B, shift):
     sync()
     for got, w in zip(d_out, ref.allgather(ins)):
         assert np.array_equal(got.host(), w) and got.guards_intact()
+
+
+W = 8
+
+
+def _dispatch(ref, counts, row, seed, entry, shift=0, top_k=4):
+    import torch
+    ins = inputs.token_rows(W, counts, row, seed=seed)
+    dest = inputs.moe_token_destinations(W, counts, seed=seed + 1, n_experts=64, top_k=top_k)
+    want = ref.token_dispatch(ins, row, dest)
+    d_in = [DevBuf(a.size, fill=a, shift=shift) for a in ins]
+    d_out = [DevBuf(w.size, shift=2 * shift) for w in want]
+    args = [b.ptr() for b in d_in], [b.ptr() for b in d_out], counts, row
+    if entry == "host":
+        dl.dl_token_dispatch(*args, dest, stream())
+    else:
+        dl.dl_token_dispatch_device(*args, torch.from_numpy(dest).cuda(), stream())
+    sync()
+    for j in range(W):
+        assert np.array_equal(d_out[j].host(), want[j]) and d_out[j].guards_intact(), f"receiver {j}"
+
+
+# rows of 1 .. 8 wavefronts and of several workgroups; tokens around a group of 64, around what the kernel arguments
+# hold (2048), and beyond it through the BAR or in several launches
+@pytest.mark.parametrize("entry,push", [("host", 1), ("host", 0), ("device", 1)])
+@pytest.mark.parametrize("counts,row,shift", [
+    ([8] * 8, 2048, 0), ([8] * 7 + [7], 4096, 0), ([9, 8, 8, 8, 8, 8, 8, 8], 6144, 0), ([3, 0, 0, 70, 1, 0, 0, 9], 10240, 0),
+    ([20] * 8, 14336, 0), ([20] * 8, 16384, 0), ([6] * 8, 16384 + 128, 0), ([5] * 8, 50000, 3), ([256] * 8, 256, 0),
+    ([255] * 7 + [264], 1024, 1), ([257, 256, 256, 256, 256, 256, 256, 256], 1040, 0), ([900, 0, 1, 800, 64, 63, 65, 700], 384, 5)])
+def test_token_dispatch_shapes(ref, counts, row, shift, entry, push):
+    dl.dl_set_config(table_push=push)
+    try:
+        _dispatch(ref, counts, row, seed=row + sum(counts), entry=entry, shift=shift)
+    finally:
+        dl.dl_set_config(table_push=1)
+
+
+def test_token_dispatch_in_a_graph(ref):
+    """The mask on the device: one launch, captured once; every replay follows the mask of the moment."""
+    import torch
+    counts, row = [40] * W, 3072
+    ins = inputs.token_rows(W, counts, row, seed=1)
+    d_in = [DevBuf(a.size, fill=a) for a in ins]
+    d_out = [DevBuf(sum(counts) * row) for _ in range(W)]
+    mask = torch.zeros((sum(counts), W), dtype=torch.uint8, device="cuda")
+    args = [b.ptr() for b in d_in], [b.ptr() for b in d_out], counts, row, mask
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        dl.dl_token_dispatch_device(*args, torch.cuda.current_stream())
+    for replay in range(4):
+        dest = inputs.moe_token_destinations(W, counts, seed=50 + replay, n_experts=64, top_k=3)
+        mask.copy_(torch.from_numpy(dest))
+        for b in d_out:
+            b.view().zero_()
+        sync()
+        g.replay()
+        torch.cuda.synchronize()
+        for j, w in enumerate(ref.token_dispatch(ins, row, dest)):
+            got = d_out[j].host()
+            assert np.array_equal(got[:w.size], w) and not got[w.size:].any() and d_out[j].guards_intact(), (replay, j)
