@@ -106,11 +106,12 @@ class PlanItem(ctypes.Structure):
 
 
 _lib = None
+_marshal = None
 
 
 def lib() -> ctypes.CDLL:
     """The loaded library; raises if it has not been built."""
-    global _lib
+    global _lib, _marshal
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -186,8 +187,17 @@ def lib() -> ctypes.CDLL:
         fn = getattr(L, name)
         fn.restype = res
         fn.argtypes = args
-    _lib = L
+    from . import _marshal as m  # built next to the library (build.py)
+    m.bind(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in m.NAMES)
+    _lib, _marshal = L, m
     return L
+
+
+def _native():
+    """The marshalling module, bound to the loaded library."""
+    if _marshal is None:
+        lib()
+    return _marshal
 
 
 # ------------------------------------------------------------------ marshalling
@@ -266,7 +276,7 @@ def dl_shutdown() -> None:
 
 
 def dl_set_mode(mode: int) -> None:
-    _check(lib().dl_set_mode(mode), "dl_set_mode")
+    _check(_native().set_mode(mode), "dl_set_mode")
 
 
 def dl_get_mode() -> int:
@@ -319,48 +329,33 @@ def dl_set_config(cfg: Config | None = None, **fields) -> None:
 
 def dl_batch_copy(descs, stream=None) -> None:
     """descs: sequence of (src, dst, bytes)."""
-    descs = list(descs)
-    _check(lib().dl_batch_copy(_desc_array(descs), len(descs), _stream(stream)), "dl_batch_copy")
+    _check(_native().batch_copy(descs, stream), "dl_batch_copy")
 
 
 def dl_batch_copy_static(descs, stream=None) -> None:
     """descs: sequence of (src, dst, bytes); the variant that allocates nothing."""
-    descs = list(descs)
-    _check(lib().dl_batch_copy_static(_desc_array(descs), len(descs), _stream(stream)), "dl_batch_copy_static")
+    _check(_native().batch_copy_static(descs, stream), "dl_batch_copy_static")
 
 
 def dl_broadcast(src, dsts, nbytes: int, stream=None) -> None:
-    dsts = list(dsts)
-    _check(lib().dl_broadcast(_addr(src), _ptr_array(dsts), len(dsts), int(nbytes), _stream(stream)), "dl_broadcast")
+    _check(_native().broadcast(src, dsts, nbytes, stream), "dl_broadcast")
 
 
 def dl_allgather(ins, outs, bytes_per_rank: int, stream=None) -> None:
-    ins, outs = list(ins), list(outs)
-    if len(ins) != len(outs):
-        raise ValueError("need as many receive buffers as send buffers")
-    _check(lib().dl_allgather(_ptr_array(ins), _ptr_array(outs), len(ins), int(bytes_per_rank), _stream(stream)),
-           "dl_allgather")
+    _check(_native().allgather(ins, outs, bytes_per_rank, stream), "dl_allgather")
 
 
 def dl_alltoall(ins, outs, chunk_bytes, stream=None) -> None:
-    ins, outs = list(ins), list(outs)
-    W = len(ins)
-    if len(outs) != W:
-        raise ValueError("need as many receive buffers as send buffers")
-    _check(lib().dl_alltoall(_ptr_array(ins), _ptr_array(outs), W, _chunk_array(chunk_bytes, W), _stream(stream)),
-           "dl_alltoall")
+    _check(_native().alltoall(ins, outs, chunk_bytes, stream), "dl_alltoall")
 
 
 def dl_batch_swap(descs, stream=None) -> None:
     """descs: sequence of (a, b, bytes)."""
-    descs = list(descs)
-    _check(lib().dl_batch_swap(_swap_array(descs), len(descs), _stream(stream)), "dl_batch_swap")
+    _check(_native().batch_swap(descs, stream), "dl_batch_swap")
 
 
 def dl_alltoall_inplace(bufs, chunk_bytes: int, stream=None) -> None:
-    bufs = list(bufs)
-    _check(lib().dl_alltoall_inplace(_ptr_array(bufs), len(bufs), int(chunk_bytes), _stream(stream)),
-           "dl_alltoall_inplace")
+    _check(_native().alltoall_inplace(bufs, chunk_bytes, stream), "dl_alltoall_inplace")
 
 
 def _dispatch_args(ins, outs, tokens, dest):
@@ -385,19 +380,16 @@ def dl_batch_fanout(items, stream=None) -> None:
 
 
 def dl_token_dispatch(ins, outs, tokens, row_bytes: int, dest, stream=None) -> None:
-    a, b, W, tok, d = _dispatch_args(ins, outs, tokens, dest)
-    _check(lib().dl_token_dispatch(a, b, W, tok, int(row_bytes), d, _stream(stream)), "dl_token_dispatch")
+    status = _native().token_dispatch(ins, outs, tokens, row_bytes, dest, stream)
+    if status is NotImplemented:  # dest is no contiguous buffer of bytes: make one
+        a, b, W, tok, d = _dispatch_args(ins, outs, tokens, dest)
+        status = lib().dl_token_dispatch(a, b, W, tok, int(row_bytes), d, _stream(stream))
+    _check(status, "dl_token_dispatch")
 
 
 def dl_token_dispatch_device(ins, outs, tokens, row_bytes: int, dest_device, stream=None) -> None:
     """dest_device: device buffer of (total tokens) x W bytes, non-zero where a token goes to a rank."""
-    ins, outs = list(ins), list(outs)
-    W = len(ins)
-    if len(outs) != W or len(tokens) != W:
-        raise ValueError("need W send buffers, W receive buffers and W token counts")
-    tok = (ctypes.c_uint32 * W)(*[int(t) for t in tokens])
-    _check(lib().dl_token_dispatch_device(_ptr_array(ins), _ptr_array(outs), W, tok, int(row_bytes), _addr(dest_device),
-                                          _stream(stream)), "dl_token_dispatch_device")
+    _check(_native().token_dispatch_device(ins, outs, tokens, row_bytes, dest_device, stream), "dl_token_dispatch_device")
 
 
 # -------------------------------------------------------------------- prelaunch
@@ -411,17 +403,17 @@ def dl_prelaunch_stop() -> None:
 
 
 def dl_last_ticket() -> int:
-    return int(lib().dl_last_ticket())
+    return _native().last_ticket()
 
 
 def dl_trigger(ticket: int | None = None) -> None:
     t = dl_last_ticket() if ticket is None else ticket
-    _check(lib().dl_trigger(t), "dl_trigger")
+    _check(_native().trigger(t), "dl_trigger")
 
 
 def dl_wait(ticket: int | None = None, timeout_ns: int = 5_000_000_000) -> None:
     t = dl_last_ticket() if ticket is None else ticket
-    _check(lib().dl_wait(t, timeout_ns), "dl_wait")
+    _check(_native().wait(t, timeout_ns), "dl_wait")
 
 
 def dl_wait_armed(ticket: int | None = None, timeout_ns: int = 5_000_000_000) -> None:

@@ -5,10 +5,12 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdmalatte.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 SOURCES = ["dl_api.hip", "dl_exec.hip", "dl_prelaunch.hip", "dl_dispatch.hip", "dl_static.hip"]
 
 HIPCC_FLAGS = [
@@ -33,7 +35,10 @@ def _run(cmd, verbose):
 
 
 def build(verbose: bool = False) -> str:
-    """The library."""
+    """The library, and the extension module that marshals Python arguments for it."""
+    _run([os.environ.get("CC", "gcc"), "-O2", "-std=c11", "-fPIC", "-shared", "-Wall", "-Wextra", "-Wno-unused-parameter",
+          "-Wno-missing-field-initializers", "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "dl_marshal.c"), "-o", MARSHAL],
+         verbose)
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     _run([hipcc, *HIPCC_FLAGS, *[os.path.join(CSRC, s) for s in SOURCES], "-o", LIB], verbose)
     return LIB

@@ -1,0 +1,168 @@
+"""The marshalling module against the ctypes helpers: what the library's entry points are handed, recorded by stubs
+in their place (no GPU, no library call)."""
+
+import ctypes
+
+import numpy as np
+import pytest
+
+from paper_2511_06605_amd import binding
+
+vp, sz, u64, u32 = ctypes.c_void_p, ctypes.c_size_t, ctypes.c_uint64, ctypes.c_uint32
+PP = ctypes.POINTER(vp)
+
+
+class Tensor:
+    def __init__(self, p):
+        self.p = p
+
+    def data_ptr(self):
+        return self.p
+
+    def __index__(self):     # a one-element tensor has a value as well: not what is wanted
+        return 7
+
+
+class Stream:
+    cuda_stream = 0xABC0
+
+
+@pytest.fixture()
+def calls():
+    """Binds the module to stubs that note their arguments as Python values; the real entry points afterwards."""
+    L, m = binding.lib(), binding._native()
+    seen = []
+
+    def words(p, n):
+        return [p[i] or 0 for i in range(n)]
+
+    def triples(p, n):
+        q = ctypes.cast(p, ctypes.POINTER(u64)) if n else None
+        return [tuple(q[3 * i:3 * i + 3]) for i in range(n)]
+
+    def note(name, f):
+        def g(*a):
+            seen.append((name,) + f(*a))
+            return -5
+        return g
+
+    def dispatch(i, o, W, t, row, d, s):
+        n = sum(t[:W])
+        return words(i, W), words(o, W), list(t[:W]), row, d or 0, s or 0, (bytes((ctypes.c_uint8 * (n * W)).from_address(d)) if d and d < 1 << 60 else None)
+
+    kinds = {
+        "dl_allgather": ([PP, PP, ctypes.c_int, sz, vp], lambda i, o, W, b, s: (words(i, W), words(o, W), b, s or 0)),
+        "dl_alltoall": ([PP, PP, ctypes.c_int, ctypes.POINTER(sz), vp], lambda i, o, W, c, s: (words(i, W), words(o, W), list(c[:W * W]), s or 0)),
+        "dl_alltoall_inplace": ([PP, ctypes.c_int, sz, vp], lambda b, W, c, s: (words(b, W), c, s or 0)),
+        "dl_broadcast": ([vp, PP, ctypes.c_int, sz, vp], lambda a, d, k, b, s: (a or 0, words(d, k), b, s or 0)),
+        "dl_batch_copy": ([vp, sz, vp], lambda p, n, s: (triples(p, n), s or 0)),
+        "dl_batch_copy_static": ([vp, sz, vp], lambda p, n, s: (triples(p, n), s or 0)),
+        "dl_batch_swap": ([vp, sz, vp], lambda p, n, s: (triples(p, n), s or 0)),
+        "dl_token_dispatch": ([PP, PP, ctypes.c_int, ctypes.POINTER(u32), sz, vp, vp], dispatch),
+        "dl_token_dispatch_device": ([PP, PP, ctypes.c_int, ctypes.POINTER(u32), sz, vp, vp], dispatch),
+        "dl_set_mode": ([ctypes.c_int], lambda v: (v,)),
+        "dl_trigger": ([u64], lambda v: (v,)),
+        "dl_wait": ([u64, u64], lambda t, ns: (t, ns)),
+    }
+    keep = []
+    for name in m.NAMES:
+        if name == "dl_last_ticket":
+            keep.append(ctypes.CFUNCTYPE(u64)(lambda: 2 ** 63 + 1))
+        else:
+            keep.append(ctypes.CFUNCTYPE(ctypes.c_int, *kinds[name][0])(note(name, kinds[name][1])))
+    m.bind([ctypes.cast(f, vp).value for f in keep])
+    yield m, seen
+    m.bind([ctypes.cast(getattr(L, n), vp).value for n in m.NAMES])
+
+
+A = [0x10, Tensor(0x2000000000), None, np.uint64(0x7FFFFFFFFFFF)]
+A_WORDS = [0x10, 0x2000000000, 0, 0x7FFFFFFFFFFF]
+
+
+@pytest.mark.parametrize("stream,handle", [(None, 0), (0, 0), (0x77, 0x77), (Stream(), 0xABC0)])
+def test_pointer_lists_and_streams(calls, stream, handle):
+    m, seen = calls
+    B = [Tensor(2 ** 63), 1, 2, 3]
+    assert m.allgather(A, tuple(B), np.int64(4096), stream) == -5
+    assert m.allgather((x for x in A), iter(B), 5.0, stream) == -5
+    assert m.alltoall_inplace(A, 2 ** 33, stream) == -5
+    assert m.broadcast(Tensor(0x99), A, 1, stream) == -5
+    assert m.allgather(range(1, 70), range(1, 70), 1, stream) == -5            # more than fits the stack
+    assert m.allgather([], [], 1, stream) == -5
+    assert seen == [("dl_allgather", A_WORDS, [2 ** 63, 1, 2, 3], 4096, handle), ("dl_allgather", A_WORDS, [2 ** 63, 1, 2, 3], 5, handle),
+                    ("dl_alltoall_inplace", A_WORDS, 2 ** 33, handle), ("dl_broadcast", 0x99, A_WORDS, 1, handle),
+                    ("dl_allgather", list(range(1, 70)), list(range(1, 70)), 1, handle), ("dl_allgather", [], [], 1, handle)]
+    assert words_of(binding._ptr_array(A)) == A_WORDS
+
+
+def words_of(arr):
+    return [v or 0 for v in arr]
+
+
+@pytest.mark.parametrize("chunks", [[[1, 2], [3, 2 ** 40]], np.array([[1, 2], [3, 2 ** 40]], dtype=np.uint64), [1, 2, 3, 2 ** 40],
+                                    np.array([1, 2, 3, 2 ** 40]), [[1, 2], 3, 2 ** 40], [(1.0, 2), np.array([3, 2 ** 40])]])
+def test_chunk_matrices(calls, chunks):
+    m, seen = calls
+    assert m.alltoall([8, 9], [10, 11], chunks, 3) == -5
+    assert seen == [("dl_alltoall", [8, 9], [10, 11], [1, 2, 3, 2 ** 40], 3)]
+    assert list(binding._chunk_array(chunks, 2)) == [1, 2, 3, 2 ** 40]
+
+
+@pytest.mark.parametrize("call,name", [("batch_copy", "dl_batch_copy"), ("batch_copy_static", "dl_batch_copy_static"), ("batch_swap", "dl_batch_swap")])
+def test_triples(calls, call, name):
+    m, seen = calls
+    f = getattr(m, call)
+    descs = [(0x10, Tensor(0x20), 3), [Tensor(5), None, np.int32(9)], np.array([1, 2, 3], dtype=np.uint64)]
+    assert f(descs, None) == -5 and f(iter(descs), Stream()) == -5 and f([], 1) == -5
+    got = [(0x10, 0x20, 3), (5, 0, 9), (1, 2, 3)]
+    assert seen == [(name, got, 0), (name, got, 0xABC0), (name, [], 1)]
+    for bad in ([(1, 2)], [(1, 2, 3, 4)], [()]):
+        with pytest.raises(ValueError):
+            f(bad, None)
+    for bad in ([(1, 2, "x")], [("x", 2, 3)], [(1, 2, None)], [5], 5):
+        with pytest.raises((TypeError, ValueError)):
+            f(bad, None)
+    assert len(seen) == 3
+
+
+def test_dispatch_masks(calls):
+    m, seen = calls
+    mask = np.arange(6, dtype=np.uint8).reshape(3, 2)
+    assert m.token_dispatch([1, 2], [3, 4], [2, np.int32(1)], 16, mask, 9) == -5
+    assert m.token_dispatch([1, 2], [3, 4], [2, 1], 16, mask != 0, None) == -5
+    assert m.token_dispatch([1, 2], [3, 4], [2, 1], 16, bytes(6), None) == -5
+    assert [c[1:5] for c in seen] == [([1, 2], [3, 4], [2, 1], 16)] * 3
+    assert [c[7] for c in seen] == [bytes(range(6)), b"\0" + b"\1" * 5, bytes(6)]
+    for other in (mask.astype(np.int32), mask.T, mask.tolist(), np.asfortranarray(mask), mask[::-1]):
+        assert m.token_dispatch([1, 2], [3, 4], [2, 1], 16, other, None) is NotImplemented
+    with pytest.raises(ValueError):
+        m.token_dispatch([1, 2], [3, 4], [2, 2], 16, mask, None)
+    with pytest.raises(ValueError):
+        m.token_dispatch([1, 2], [3, 4], [3], 16, mask, None)
+    assert m.token_dispatch_device([1, 2], [3, 4], [2, 1], 16, Tensor(2 ** 62), None) == -5
+    assert seen[-1][:6] == ("dl_token_dispatch_device", [1, 2], [3, 4], [2, 1], 16, 2 ** 62)
+    assert len(seen) == 4
+
+
+def test_small_calls_and_errors(calls):
+    m, seen = calls
+    assert m.set_mode(-1) == -5 and m.trigger(2 ** 64 - 1) == -5 and m.wait(np.uint64(3), 5_000_000_000) == -5
+    assert m.last_ticket() == 2 ** 63 + 1
+    assert seen == [("dl_set_mode", -1), ("dl_trigger", 2 ** 64 - 1), ("dl_wait", 3, 5_000_000_000)]
+
+    class Broken:
+        def data_ptr(self):
+            raise RuntimeError("no storage")
+
+    with pytest.raises(RuntimeError):
+        m.allgather([Broken()], [1], 1, None)
+    with pytest.raises(ValueError):
+        m.allgather([1], [1, 2], 1, None)
+    with pytest.raises(ValueError):
+        m.alltoall([1, 2], [1, 2], [[1, 2], [3]], None)
+    with pytest.raises(ValueError):
+        m.alltoall([1, 2], [1, 2], [[1, 2], [3, 4, 5]], None)
+    for args in ((), (1,), ([1], [1], 1), ([1], [1], 1, None, None), ([1], [1], "x", None), ([1], [1], 1, "x"), (3, [1], 1, None)):
+        with pytest.raises((TypeError, ValueError)):
+            m.allgather(*args)
+    assert len(seen) == 3
