@@ -22,8 +22,10 @@
  *    dl_wait() on the ticket of the call.
  *  - Stream capture: in one-shot mode a request whose lowered list fits the
  *    kernel arguments (at most 64 plain copies, or 32 read-once/write-k copies;
- *    all-gather up to 16 ranks, every broadcast, all-to-all up to 8 ranks)
- *    is exactly one kernel launch and nothing else, so it may be
+ *    all-gather up to 16 ranks, every broadcast, all-to-all up to 8 ranks; and
+ *    up to 480 plain copies or swaps of one length, each side's addresses within
+ *    4 GiB, or 64 GiB where they agree modulo 16) is exactly one kernel launch
+ *    and nothing else, so it may be
  *    issued on a stream that is being captured into a HIP graph.  Longer
  *    lists go through table memory that the library reuses (host writes at
  *    call time, events) and must not be captured; neither may prelaunch,

@@ -489,6 +489,22 @@ struct dl_klist {
     Item item[NMAX];
 };
 
+// A list of equally long copies (or swaps) too long for dl_klist, in the kernel arguments all the same: every address
+// as an offset from the lowest one of its side, in units of 1 << unit_log2 bytes.
+struct dl_offset_head {
+    const char *src;
+    char *dst;
+    uint64_t bytes;
+    uint32_t unit_log2;
+    uint32_t wpg_log2;
+};
+template <int NMAX>
+struct dl_offset_list : dl_offset_head {
+    struct {
+        uint32_t src, dst;
+    } at[NMAX];
+};
+
 // Item of global tile b: the number of items whose last tile lies before b,
 // and (in *first) the number of tiles before that item.  A short list is
 // compared entry by entry on the scalar unit (b is uniform, the list sits in

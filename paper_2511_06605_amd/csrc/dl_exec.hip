@@ -89,6 +89,22 @@ __global__ void __launch_bounds__(512) dl_exec_urows_kernel(const Item *__restri
         dl_rows_body<POL, ON_GRID>(items[d], blockIdx.x, wpg_log2, split_log2);
 }
 
+// Row path over equally long copies given by offsets in the kernel arguments (cache blocks moved between two pools):
+// blockIdx.y the item, blockIdx.x the tile within it.  Nothing is fetched through memory that the host has just
+// written, so the two round trips in front of every row of a pushed table (stamp, entry) are gone: 256 copies of 64 KiB
+// 7.4 us of kernel, now 6.2 (10.4 -> 9.8 us a call); of 256 KiB 28.5 -> 21.6 us, of 1 MiB 97.3 -> 85.7 us, where one-wavefront
+// workgroups count as well.
+template <class Item, int NMAX, int POL, bool ON_GRID>
+__global__ void __launch_bounds__(512) dl_exec_offsets_kernel(const dl_offset_list<NMAX> p)
+{
+    const uint32_t d = blockIdx.y;
+    Item it;
+    it.src = p.src + ((uint64_t)p.at[d].src << p.unit_log2);
+    it.dst = p.dst + ((uint64_t)p.at[d].dst << p.unit_log2);
+    it.bytes = p.bytes;
+    dl_rows_body<POL, ON_GRID>(it, blockIdx.x, p.wpg_log2, 0u);
+}
+
 // General path: any tile size, one workgroup per tile.
 template <class Item, int NMAX, int POL>
 __global__ void __launch_bounds__(512) dl_exec_list_kernel(const dl_klist<Item, NMAX> p)
@@ -480,6 +496,7 @@ constexpr uint64_t PLAIN_WAVE_MIN_BYTES = 48ull << 20;  // bytes moved (read + w
 constexpr uint64_t FAN_WAVE_MIN_BYTES = 3ull << 20;         // bytes moved above which a copy with several destinations takes one wavefront per row
 constexpr uint64_t UNIFORM_ROWS_MIN_BYTES = 4ull << 20;  // source bytes from which a uniform long list takes the row kernel
 constexpr uint64_t UNIFORM_ROWS_STAGE_BYTES = 768ull << 20;  // bytes moved (read + written) from which its table is staged even where it could be pushed
+constexpr uint64_t OFFSETS_MIN_BYTES = 64ull << 20;  // bytes moved per launch where a long uniform list takes several instead of a table
 constexpr size_t TABLE_STAGE_MIN = 512;          // tables at least this long are staged in device memory first
 constexpr size_t RING_SLOTS = 4;
 constexpr size_t RING_SLOT_BYTES = DL_RING_SLOT_BYTES;
@@ -753,6 +770,76 @@ int stage_slot(size_t s, uint64_t bytes, hipStream_t stream)
     return launch_klist<dl_plain_item, NMAX_SMALL>(&stage, 1, &stage_tiles, ssh, stream, nullptr);
 }
 
+// Equally long plain copies or swaps that do not fit a dl_klist but whose offsets do fit the kernel arguments (up to
+// 480): one launch and nothing else.  Returns false if the list does not qualify (and nothing was enqueued).
+template <class Item, int NMAX>
+int launch_offsets_sized(const Item *items, size_t n, const dl_offset_head &head, uint32_t width, uint32_t threads, int policy,
+                         bool on_grid, hipStream_t stream)
+{
+    dl_offset_list<NMAX> p;
+    static_cast<dl_offset_head &>(p) = head;
+    for (size_t i = 0; i < n; ++i) {
+        p.at[i].src = (uint32_t)((uint64_t)(items[i].src - head.src) >> head.unit_log2);
+        p.at[i].dst = (uint32_t)((uint64_t)(items[i].dst - head.dst) >> head.unit_log2);
+    }
+    dl_with_policy_and_grid(policy, on_grid, [&](auto pol, auto og) {
+        hipLaunchKernelGGL((dl_exec_offsets_kernel<Item, NMAX, decltype(pol)::value, decltype(og)::value>), dim3(width, (uint32_t)n),
+                           dim3(threads), 0, stream, p);
+    });
+    DL_HIP(hipGetLastError());
+    return DL_OK;
+}
+
+template <class Item>
+bool launch_offsets(const Item *items, size_t n, const dl_launch_shape &sh, hipStream_t stream, int *rc)
+{
+    const dl_config &c = g_dl.cfg;
+    constexpr int SMALL = 256, BIG = 480;
+    static_assert(sizeof(dl_offset_list<BIG>) <= 4096, "kernel arguments");
+    if (c.tile_bytes || c.block_threads || sh.max_blocks) return false;
+    // A longer list takes several launches if each of them has enough to do to hide the kernel start in between
+    // (512 blocks of 512 KiB: 98.5 us from a table, 87.6 in two launches).
+    const size_t launches = (n + BIG - 1) / BIG, per = (n + launches - 1) / launches;
+    if (launches > 1 && 2u * items[0].bytes * per < OFFSETS_MIN_BYTES) return false;
+    // the addresses relative to the lowest one of each side: 16-byte units if all of them agree modulo 16, else bytes
+    const char *src = items[0].src, *src_hi = src, *dst = items[0].dst, *dst_hi = dst;
+    uint64_t apart = 0, any_src = 0, any_dst = 0;
+    uint32_t worst = 0;  // how far behind its grid the worst first destination lies
+    const uint64_t bytes = items[0].bytes;
+    for (size_t i = 0; i < n; ++i) {
+        const Item &it = items[i];
+        if (it.bytes != bytes) return false;
+        src = it.src < src ? it.src : src;
+        src_hi = it.src > src_hi ? it.src : src_hi;
+        dst = it.dst < dst ? it.dst : dst;
+        dst_hi = it.dst > dst_hi ? it.dst : dst_hi;
+        any_src |= (uint64_t)it.src;
+        any_dst |= (uint64_t)it.dst;
+        apart |= ((uint64_t)it.src ^ (uint64_t)items[0].src) | ((uint64_t)it.dst ^ (uint64_t)items[0].dst);
+        const uint32_t shift = dl_item_shift(it);
+        worst = shift > worst ? shift : worst;
+    }
+    const bool on_grid = (any_dst & (DL_CUT - 1u)) == 0 && (any_src & 3u) == 0 && (bytes & 15u) == 0;  // (item_on_grid for all)
+    dl_offset_head head;
+    head.unit_log2 = (apart & 15u) ? 0u : 4u;
+    if (((uint64_t)(src_hi - src) >> head.unit_log2) >> 32 || ((uint64_t)(dst_hi - dst) >> head.unit_log2) >> 32) return false;
+    const uint32_t threads = sh.block_threads, tile = 16u * threads;
+    const uint64_t width = (bytes + worst + tile - 1u) / tile;  // of that item; the others may leave a workgroup without work
+    if (width * n >= (1ull << 30) || width * threads >= (1ull << 32)) return false;
+    head.src = src;
+    head.dst = (char *)dst;
+    head.bytes = bytes;
+    head.wpg_log2 = log2u(threads / 64u);
+    *rc = DL_OK;
+    for (size_t i = 0; i < n && *rc == DL_OK; i += per) {
+        const size_t m = n - i < per ? n - i : per;
+        *rc = m <= (size_t)SMALL
+                  ? launch_offsets_sized<Item, SMALL>(items + i, m, head, (uint32_t)width, threads, sh.policy, on_grid, stream)
+                  : launch_offsets_sized<Item, BIG>(items + i, m, head, (uint32_t)width, threads, sh.policy, on_grid, stream);
+    }
+    return true;
+}
+
 // Long list of equally sized items that moves enough bytes to pay for staging
 // its table: the items themselves (not cut into tiles) go to device memory and the row kernel
 // above works on them.  Returns false if the list does not qualify.  (Lists that still fit the
@@ -769,7 +856,10 @@ bool launch_uniform_rows(const Item *items, size_t n, const dl_launch_shape &sh,
     // of which the ones without a destination are dead weight at the rate wavefronts can be started.
     const bool fused = std::is_same<Item, dl_fused_item>::value;
     const uint32_t split = c.fan_split ? sh.split : fused ? DL_TABLE_ROWS_SPLIT : 1u;
-    const uint32_t threads = c.block_threads ? c.block_threads : fused && !c.fan_split ? DL_TABLE_ROWS_THREADS : 256u;
+    // Plain items: one wavefront per workgroup as in shorter lists, but not where every workgroup first fetches its entry
+    // of a pushed table (512 blocks of 512 KiB: 97.6 us with four wavefronts, 101 with one; of 1 MiB, staged: 195 and 176).
+    const bool staged = items[0].bytes * n * 2u >= UNIFORM_ROWS_STAGE_BYTES;
+    const uint32_t threads = c.block_threads ? c.block_threads : fused && !c.fan_split ? DL_TABLE_ROWS_THREADS : staged && !fused ? 64u : 256u;
     if (threads > 512u || threads % (64u * split) || ((threads / 64u / split) & (threads / 64u / split - 1u)))
         return false;  // whole sub-groups of a power-of-two number of wavefronts
     if (n * sizeof(Item) > RING_SLOT_BYTES) return false;
@@ -1099,6 +1189,10 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
         return launch_klist<Item, NBIG>(items, n, tile_end, sh, stream, arm);
     }
     *launched = true;
+    if constexpr (!std::is_same<Item, dl_fused_item>::value) {
+        int rc = DL_OK;
+        if (!arm && !dl_debug_lose_armed() && launch_offsets(items, n, sh, stream, &rc)) return rc;  // (the hook is for a table)
+    }
     return launch_table(items, n, sh, stream, arm);
 }
 

@@ -149,3 +149,53 @@ def test_token_dispatch_in_a_graph(ref):
         for j, w in enumerate(ref.token_dispatch(ins, row, dest)):
             got = d_out[j].host()
             assert np.array_equal(got[:w.size], w) and not got[w.size:].any() and d_out[j].guards_intact(), (replay, j)
+
+
+def _scattered(n, nb, align, seed):
+    """n disjoint (first, second) offsets of nb bytes in one arena, at odd places if align is 1."""
+    rng = np.random.default_rng(seed)
+    slot = (nb + 31 + 127) // 128 * 128
+    at = rng.permutation(2 * n + 5)[:2 * n] * slot
+    if align == 1:
+        at = at + rng.integers(0, 32, 2 * n)
+    arena = rng.integers(0, 256, (2 * n + 5) * slot, dtype=np.uint8)
+    return arena, [(int(a), int(b), nb) for a, b in zip(at[:n], at[n:])]
+
+
+# equal copies and swaps beyond the 64 of a short list: offsets in the kernel arguments (256 and 480 of them), in several
+# launches where each moves 64 MiB, else a table
+@pytest.mark.parametrize("align", [128, 1])
+@pytest.mark.parametrize("n,nb", [(65, 16), (65, 100000), (256, 4096), (257, 1000), (480, 5000), (481, 5000), (600, 131072), (500, 15)])
+@pytest.mark.parametrize("op", ["copy", "swap"])
+def test_equal_copies_by_offsets(ref, op, n, nb, align):
+    arena, descs = _scattered(n, nb, align, seed=n + nb)
+    d = DevBuf(arena.size, fill=arena)
+    want = arena.copy()
+    if op == "copy":
+        want = ref.batch_copy([want], [(0, s, 0, t, m) for s, t, m in descs])[0]
+        dl.dl_batch_copy([(d.ptr(s), d.ptr(t), m) for s, t, m in descs], stream())
+    else:
+        for s, t, m in descs:
+            want[s:s + m], want[t:t + m] = arena[t:t + m], arena[s:s + m]
+        dl.dl_batch_swap([(d.ptr(s), d.ptr(t), m) for s, t, m in descs], stream())
+    sync()
+    assert np.array_equal(d.host(), want) and d.guards_intact()
+
+
+def test_equal_copies_in_a_graph(ref):
+    import torch
+    arena, descs = _scattered(300, 3000, 1, seed=3)
+    d = DevBuf(arena.size, fill=arena)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        dl.dl_batch_copy([(d.ptr(s), d.ptr(t), m) for s, t, m in descs], torch.cuda.current_stream())
+    for replay in range(4):
+        now = np.random.default_rng(replay).integers(0, 256, arena.size, dtype=np.uint8)
+        d.view().copy_(torch.from_numpy(now))
+        sync()
+        g.replay()
+        torch.cuda.synchronize()
+        want = ref.batch_copy([now], [(0, s, 0, t, m) for s, t, m in descs])[0]
+        assert np.array_equal(d.host(), want) and d.guards_intact(), replay
