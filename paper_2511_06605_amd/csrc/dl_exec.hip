@@ -497,6 +497,7 @@ constexpr uint64_t FAN_WAVE_MIN_BYTES = 3ull << 20;         // bytes moved above
 constexpr uint64_t UNIFORM_ROWS_MIN_BYTES = 4ull << 20;  // source bytes from which a uniform long list takes the row kernel
 constexpr uint64_t UNIFORM_ROWS_STAGE_BYTES = 768ull << 20;  // bytes moved (read + written) from which its table is staged even where it could be pushed
 constexpr uint64_t OFFSETS_MIN_BYTES = 64ull << 20;  // bytes moved per launch where a long uniform list takes several instead of a table
+constexpr uint64_t ARMED_ROWS_MAX_BYTES = 32ull << 20;  // bytes moved up to which an armed kernel that does not wait takes the row path for more than eight items
 constexpr size_t TABLE_STAGE_MIN = 512;          // tables at least this long are staged in device memory first
 constexpr size_t RING_SLOTS = 4;
 constexpr size_t RING_SLOT_BYTES = DL_RING_SLOT_BYTES;
@@ -1169,7 +1170,12 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
         // row path: a short list (found by a few scalar compares; bisecting a long one per wavefront
         // measured slower than the general path) and a tile that is exactly one 1 KiB row per
         // wavefront of a sub-group
-        sh.rows = n <= (size_t)NMAX_SMALL && sh.tile_bytes == 16u * (sh.block_threads / sh.split) &&
+        // ... or, armed, a list of any length, where few wavefronts are in flight: a waiting kernel, whose grid is capped
+        // (all-to-all of 128 / 512 KiB chunks between eight ranks, trigger to done and the call: 21.9 / 44.4 us on the general
+        // path, 19.6 / 35.4 this way; all-gather of 480 KiB over 16 ranks 54.8 : 45.7), and a short request without a
+        // doorbell (64 chunks of 16 KiB 15.3 : 14.7; with a full grid and 64 MiB moved 25.4 : 25.6, 138 MB 40.8 : 41.6)
+        const bool armed_rows = arm && ((!arm->nowait && !sh.chain) || total * (1ull + kmax) <= ARMED_ROWS_MAX_BYTES);
+        sh.rows = (n <= (size_t)NMAX_SMALL || armed_rows) && sh.tile_bytes == 16u * (sh.block_threads / sh.split) &&
                   !(sh.max_blocks && !arm);
         // ... or, one-shot, a longer list whose items are about equally long: item by item on a
         // two-dimensional grid (see dl_exec_rows2d_kernel), while at most a fifth of its workgroups find nothing to do

@@ -199,3 +199,39 @@ def test_equal_copies_in_a_graph(ref):
         torch.cuda.synchronize()
         want = ref.batch_copy([now], [(0, s, 0, t, m) for s, t, m in descs])[0]
         assert np.array_equal(d.host(), want) and d.guards_intact(), replay
+
+
+# armed and signalled requests of more than eight items take the row path; below and above 32 MiB moved without a doorbell
+@pytest.mark.parametrize("mode", [dl.DL_MODE_PRELAUNCH, dl.DL_MODE_SIGNAL])
+@pytest.mark.parametrize("op,ranks,n", [("alltoall", 8, 100), ("alltoall", 8, 4097), ("alltoall", 8, 256 * KiB - 1), ("alltoall", 8, 256 * KiB + 16),
+                                        ("alltoall", 5, 70001), ("inplace", 8, 1000), ("inplace", 8, 600 * KiB + 3), ("allgather", 9, 5001),
+                                        ("allgather", 16, 40000), ("allgather", 16, 200003)])
+def test_armed_lists_on_the_row_path(ref, mode, op, ranks, n):
+    dl.dl_prelaunch_start()
+    try:
+        dl.dl_set_mode(mode)
+        C = inputs.uniform_chunks(ranks, n)
+        if op == "allgather":
+            ins = inputs.allgather_inputs(ranks, n, seed=n)
+            want = ref.allgather(ins)
+        else:
+            ins = inputs.alltoall_inputs(C, seed=n, kind="u8")
+            want = ref.alltoall(ins, C)
+        d_in = [DevBuf(a.size, fill=a, shift=n % 7) for a in ins]
+        d_out = d_in if op == "inplace" else [DevBuf(w.size, shift=n % 3) for w in want]
+        sync()
+        p, q = [b.ptr() for b in d_in], [b.ptr() for b in d_out]
+        if op == "allgather":
+            dl.dl_allgather(p, q, n)
+        elif op == "alltoall":
+            dl.dl_alltoall(p, q, C)
+        else:
+            dl.dl_alltoall_inplace(p, n)
+        if mode == dl.DL_MODE_PRELAUNCH:
+            dl.dl_trigger()
+        dl.dl_wait()
+        for got, w in zip(d_out, want):
+            assert np.array_equal(got.host(), w) and got.guards_intact()
+    finally:
+        dl.dl_set_mode(dl.DL_MODE_ONESHOT)
+        dl.dl_prelaunch_stop()
