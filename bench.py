@@ -35,7 +35,7 @@ HBM_PEAK_GBS = 8000.0
 # for a plain copy of known size.  Valid only for the kernel sources whose digest is given; with
 # any other sources the figure is reported as null until the counters are taken again.
 KERNEL_SOURCES = ["dl_work.h", "dl_device.h", "dl_exec.hip"]
-MEASURED_TRAFFIC = {"sources_sha256": "75a52d98d113b89d66940941dec8f515c05644e8ee7db06877cba48dfc5a87d6", "bytes_per_rank": 64 * MiB, "bytes_per_launch": 4831886239}
+MEASURED_TRAFFIC = {"sources_sha256": "f182a2f77e32febefafcf362be89fb10e88d9daf8c2b468956c860cc33afd878", "bytes_per_rank": 64 * MiB, "bytes_per_launch": 4831892879}
 
 
 def kernel_sources_digest() -> str:
@@ -514,7 +514,7 @@ def other_operations(dl, benchaid, inputs, torch, stream, ag_reqs, ag_bufs, ag_s
 
 def pmc_case(args, dl, benchaid, torch, stream) -> int:
     """A few launches of the dominant kernel (all-gather at the largest sweep
-    point: dl_exec_rows_kernel<dl_fused_item,...>) and of a plain copy of known
+    point: dl_exec_pairs_kernel) and of a plain copy of known
     size (dl_exec_rows_kernel<dl_plain_item,...>: reads 1 GiB, writes 1 GiB) so
     that counter readings of the first can be scaled by those of the second."""
     B = args.max_bytes
@@ -525,8 +525,8 @@ def pmc_case(args, dl, benchaid, torch, stream) -> int:
     a = torch.randint(0, 256, (n,), dtype=torch.uint8, device="cuda")
     b = torch.empty(n, dtype=torch.uint8, device="cuda")
     cp = benchaid.copy_list_request([(a.data_ptr(), b.data_ptr(), n)], benchaid.OP_BATCH)
-    # the calibration copy with ordinary loads and stores, like the kernel that is being calibrated (a plain list
-    # of this size would use streaming ones by default)
+    # the calibration copy with ordinary loads and streamed stores, like the kernel that is being calibrated (a plain
+    # list of this size would use streaming loads and write-through stores by default)
     dl.dl_set_config(stream_plain_min_bytes=(1 << 64) - 1)
     stream.synchronize()
     for _ in range(args.warmup + args.steps):
@@ -759,7 +759,7 @@ def main() -> int:
                    "W": W, "calls_per_step": len(sizes), "bytes_per_step": step_bytes, "mode": "oneshot"},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": "dl_exec_rows_kernel<dl_fused_item, 8, 0, true>",
+                     "kernel": "dl_exec_pairs_kernel<8, 0, true>",
                      "launch": f"all-gather {big // MiB} MiB/rank: {ag_bytes(big)} B in {big_ms * 1e3:.1f} us "
                                f"(mean of {len(events)} launches, HIP events)"},
     }

@@ -497,7 +497,7 @@ int dl_init(int device)
     g_dl.mode = DL_MODE_ONESHOT;
     g_dl.validate = 0;
     g_dl.cfg = dl_config{};
-    g_dl.cfg.nontemporal_min_bytes = ~0ull;  // streaming hints measured slower: off unless asked for
+    g_dl.cfg.nontemporal_min_bytes = ~0ull;  // hints on both sides measured slower than on the side that needs them: off unless asked for
     g_dl.cfg.write_through_max_bytes = 144ull << 20;  // all-gather of 2 MiB per rank over 8 ranks
     g_dl.cfg.armed_chain_min_bytes = 256ull << 20;    // what the Infinity Cache holds; all-gather: from 4 MiB per rank over 8 ranks
     g_dl.cfg.stream_plain_min_bytes = 96ull << 20;    // a source of 48 MiB: all-to-all of 768 KiB chunks between 8 ranks

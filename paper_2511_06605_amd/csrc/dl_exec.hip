@@ -5,7 +5,8 @@
 //
 // Short lists travel by value in the kernel-argument segment, so the device
 // needs no extra memory round trip to find its work: workgroup b finds its
-// (item, tile) from an inclusive prefix sum of tile counts.  Long lists are cut
+// (item, tile) from an inclusive prefix sum of tile counts.  Long lists of equal
+// plain copies travel there as offsets.  Other long lists are cut
 // into one-tile entries on the host and become a table, workgroup b taking
 // entry b: written straight into device memory through the BAR where that is
 // possible (see push_acquire), else into a pinned host ring (and copied to
@@ -843,9 +844,9 @@ bool launch_offsets(const Item *items, size_t n, const dl_launch_shape &sh, hipS
 
 // Long list of equally sized items that moves enough bytes to pay for staging
 // its table: the items themselves (not cut into tiles) go to device memory and the row kernel
-// above works on them.  Returns false if the list does not qualify.  (Lists that still fit the
-// kernel arguments, such as the 64 chunks of a uniform all-to-all, were 5-25 % slower this way than
-// on the general path and do not come here.)
+// above works on them.  Returns false if the list does not qualify.  (Lists that fit the kernel arguments,
+// such as the 64 chunks of a uniform all-to-all, and equal plain copies at offsets that do, see launch_offsets,
+// never come here: from there they need no table.)
 template <class Item>
 bool launch_uniform_rows(const Item *items, size_t n, const dl_launch_shape &sh, hipStream_t stream, int *rc)
 {
@@ -1211,13 +1212,12 @@ uint32_t floor_pow2(uint64_t v)
 
 }  // namespace
 
-// Tile, workgroup size and fan split for a request.  Measured on MI355X
-// (all-gather of 8 .. 64 MiB per rank, 1:1 copies of 2 GiB): the finest cut
-// wins, with 256-thread workgroups in which every wavefront moves one 1 KiB row
-// with one 16-byte load and at most two stores per lane.  So a fan-out of 5..8
-// takes 1 KiB tiles shared out over four wavefronts, 3..4 takes 2 KiB tiles and
-// two sub-groups, 1:1 and 1:2 copies take 4 KiB tiles.  Larger tiles, larger or
-// smaller workgroups, capped grids and streaming hints were all slower.
+// Tile, workgroup size and fan split for a request.  The finest cut wins: every wavefront moves one 1 KiB row with
+// one 16-byte load per lane; larger tiles and capped grids were slower at every size.  What is chosen here is the
+// shape of requests that last as long as a launch does: there a row's stores are shared out, at most two per lane, over
+// the four wavefronts of a workgroup (a fan-out of 5..8: 1 KiB tiles; 3..4: 2 KiB tiles and two sub-groups; 1:1
+// and 1:2 copies: 4 KiB tiles).  Larger copies with several destinations get their shape where they are launched
+// (FAN_WAVE_MIN_BYTES, dl_pair_body), larger plain ones below.
 dl_launch_shape dl_choose_shape(uint64_t src_bytes, uint64_t max_item_bytes, uint32_t max_k)
 {
     const dl_config &c = g_dl.cfg;
