@@ -85,6 +85,8 @@ DL_HD uint64_t dl_pair_blocks(const dl_fused_item &it)
 
 // Row and pair of destinations of that kernel's workgroup `local` of an item of `rows` rows and `pairs` (1..4) pairs:
 // the rows in chunks of DL_PAIR_ROWS, a chunk's rows for the first pair, then for the second, ...  False: past the item.
+// All-gather of 32 / 64 MiB per rank over eight ranks with chunks of 1024 rows 414 / 865 us, of 4096 370 / 747, of 8192
+// 375 / 748, of 16 384 370 / 740, of 32 768 (as much source as the eight L2s hold) 419 / 842.
 constexpr uint32_t DL_PAIR_ROWS = 4096;
 
 DL_HD bool dl_pair_locate(uint32_t local, uint32_t rows, uint32_t pairs, uint32_t *row, uint32_t *pair)
