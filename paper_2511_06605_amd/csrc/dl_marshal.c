@@ -7,8 +7,9 @@
  *
  * Arguments as the functions of binding.py take them: an address is an int, None (null) or an object with data_ptr();
  * a stream an int, None or an object with cuda_stream.  Every sequence is taken as a tuple first, so nothing that
- * runs in between (data_ptr() of a foreign class) can change what is being read.  The lock of the interpreter is
- * released for the call into the library.
+ * runs in between (data_ptr() of a foreign class) can change what is being read, and the tuple is kept until the library
+ * has returned: it may hold the only reference to a buffer (an iterator that makes tensors as it goes).  The lock of the
+ * interpreter is released for the call into the library.
  */
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
@@ -92,37 +93,35 @@ static int to_stream(PyObject *x, void **out)
     return rc;
 }
 
-/* A sequence's values in an array: the caller's `room` of ON_STACK entries, or allocated (free_values). */
+/* A sequence's values in an array: the caller's `room` of ON_STACK entries, or allocated; and what they are the
+ * values of, for as long as the addresses are in use (free_values gives both up). */
 typedef struct {
     uint64_t *v;
     Py_ssize_t n;
+    PyObject *owners;
     uint64_t room[ON_STACK];
 } values;
 
 static void free_values(values *a)
 {
     if (a->v != a->room) PyMem_Free(a->v);
-}
-
-static int to_values(PyObject *seq, values *a, int (*convert)(PyObject *, uint64_t *))
-{
     a->v = a->room;
     a->n = 0;
-    PyObject *t = PySequence_Tuple(seq);
-    if (!t) return -1;
-    const Py_ssize_t n = PyTuple_GET_SIZE(t);
+    Py_CLEAR(a->owners);
+}
+
+/* `a` is empty (free_values) before; to be given up by the caller in any case */
+static int to_values(PyObject *seq, values *a, int (*convert)(PyObject *, uint64_t *))
+{
+    if (!(a->owners = PySequence_Tuple(seq))) return -1;
+    const Py_ssize_t n = PyTuple_GET_SIZE(a->owners);
     if (n > ON_STACK && !(a->v = PyMem_New(uint64_t, n))) {
         a->v = a->room;
-        Py_DECREF(t);
         PyErr_NoMemory();
         return -1;
     }
     for (; a->n < n; ++a->n)
-        if (convert(PyTuple_GET_ITEM(t, a->n), a->v + a->n) < 0) {
-            Py_DECREF(t);
-            return -1;
-        }
-    Py_DECREF(t);
+        if (convert(PyTuple_GET_ITEM(a->owners, a->n), a->v + a->n) < 0) return -1;
     return 0;
 }
 
@@ -183,12 +182,11 @@ static PyObject *m_alltoall(PyObject *self, PyObject *const *args, Py_ssize_t n)
     for (Py_ssize_t i = 0; i < PyTuple_GET_SIZE(rows); ++i) {
         PyObject *r = PyTuple_GET_ITEM(rows, i);
         free_values(&row);
-        row.v = row.room;
-        row.n = 1;
         if (!PyLong_CheckExact(r) && PyObject_HasAttrString(r, "__len__")) {
             if (to_values(r, &row, to_u64) < 0) goto done;
-        } else if (to_u64(r, row.room) < 0) {
-            goto done;
+        } else {
+            if (to_u64(r, row.room) < 0) goto done;
+            row.n = 1;
         }
         if (have + row.n <= need) memcpy(chunks + have, row.v, (size_t)row.n * sizeof *chunks);
         have += row.n;

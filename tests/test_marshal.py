@@ -166,3 +166,73 @@ def test_small_calls_and_errors(calls):
         with pytest.raises((TypeError, ValueError)):
             m.allgather(*args)
     assert len(seen) == 3
+
+
+class Block:
+    """A buffer from an allocator that hands the lowest free address out, as a caching allocator does."""
+    live = set()
+
+    def __init__(self):
+        self.p = next(a for a in range(0x1000, 1 << 20, 0x1000) if a not in Block.live)
+        Block.live.add(self.p)
+
+    def __del__(self):
+        Block.live.discard(self.p)
+
+    def data_ptr(self):
+        return self.p
+
+
+def fresh(n):
+    return (Block() for _ in range(n))
+
+
+@pytest.mark.parametrize("call", [
+    lambda m: m.allgather(fresh(3), fresh(3), 16, None),
+    lambda m: m.allgather(fresh(70), fresh(70), 16, None),                          # more than fits the stack
+    lambda m: m.alltoall(fresh(2), fresh(2), [[1, 2], [3, 4]], None),
+    lambda m: m.alltoall_inplace(fresh(4), 16, None),
+    lambda m: m.broadcast(Block(), fresh(3), 16, None),
+    lambda m: m.batch_copy(((Block(), Block(), 5) for _ in range(3)), None),
+    lambda m: m.token_dispatch(fresh(2), fresh(2), [2, 1], 16, np.zeros((3, 2), np.uint8), None),
+    lambda m: m.token_dispatch_device(fresh(2), fresh(2), [2, 1], 16, Block(), None)])
+def test_buffers_outlive_the_call(calls, call):
+    """Buffers that only the argument refers to (made by an iterator) are alive, each at an address of its own, while
+    the library runs, and given up afterwards."""
+    m, _ = calls
+    Block.live.clear()
+    during = []
+    m.bind([ctypes.cast(f, vp).value for f in watchers(m, during)])
+    assert call(m) == -5
+    (used, live), = during
+    assert len(set(used)) == len(used) and set(used) <= live
+    assert not Block.live
+
+
+_watchers = []
+
+
+def watchers(m, during):
+    """Entry points that note the addresses they are given and what is alive at that time."""
+    def words(p, n):
+        return [ctypes.cast(p, ctypes.POINTER(u64))[i] for i in range(n)]
+
+    args = {
+        "dl_allgather": ([vp, vp, ctypes.c_int, sz, vp], lambda i, o, W, b, s: words(i, W) + words(o, W)),
+        "dl_alltoall": ([vp, vp, ctypes.c_int, vp, vp], lambda i, o, W, c, s: words(i, W) + words(o, W)),
+        "dl_alltoall_inplace": ([vp, ctypes.c_int, sz, vp], lambda b, W, c, s: words(b, W)),
+        "dl_broadcast": ([vp, vp, ctypes.c_int, sz, vp], lambda a, d, k, b, s: [a] + words(d, k)),
+        "dl_batch_copy": ([vp, sz, vp], lambda p, n, s: [words(p, 3 * n)[3 * i + q] for i in range(n) for q in (0, 1)]),
+        "dl_token_dispatch": ([vp, vp, ctypes.c_int, vp, sz, vp, vp], lambda i, o, W, t, r, d, s: words(i, W) + words(o, W)),
+        "dl_token_dispatch_device": ([vp, vp, ctypes.c_int, vp, sz, vp, vp], lambda i, o, W, t, r, d, s: words(i, W) + words(o, W) + [d]),
+    }
+
+    def watch(f):
+        def g(*a):
+            during.append((f(*a), set(Block.live)))
+            return -5
+        return g
+
+    _watchers[:] = [ctypes.CFUNCTYPE(ctypes.c_int, *args[n][0])(watch(args[n][1])) if n in args else ctypes.CFUNCTYPE(ctypes.c_int)(lambda: -5)
+                    for n in m.NAMES]
+    return _watchers
