@@ -358,6 +358,13 @@ def dl_alltoall_inplace(bufs, chunk_bytes: int, stream=None) -> None:
     _check(_native().alltoall_inplace(bufs, chunk_bytes, stream), "dl_alltoall_inplace")
 
 
+def _mask_bytes(dest) -> bytes:
+    """A routing mask of any form, one byte per (token, rank)."""
+    if hasattr(dest, "tobytes"):
+        return (dest != 0).astype("uint8").tobytes()
+    return bytes(bytearray(int(v) != 0 for row in dest for v in row))
+
+
 def _dispatch_args(ins, outs, tokens, dest):
     ins, outs = list(ins), list(outs)
     W = len(ins)
@@ -365,8 +372,7 @@ def _dispatch_args(ins, outs, tokens, dest):
         raise ValueError("need W send buffers, W receive buffers and W token counts")
     tok = (ctypes.c_uint32 * W)(*[int(t) for t in tokens])
     total = sum(int(t) for t in tokens)
-    flat = bytes(bytearray(int(v) != 0 for row in dest for v in row)) if not hasattr(dest, "tobytes") else \
-        (dest != 0).astype("uint8").tobytes()
+    flat = _mask_bytes(dest)
     if len(flat) != total * W:
         raise ValueError("dest must have one entry per (token, rank)")
     d = (ctypes.c_uint8 * max(len(flat), 1)).from_buffer_copy(flat or b"\0")
@@ -381,9 +387,8 @@ def dl_batch_fanout(items, stream=None) -> None:
 
 def dl_token_dispatch(ins, outs, tokens, row_bytes: int, dest, stream=None) -> None:
     status = _native().token_dispatch(ins, outs, tokens, row_bytes, dest, stream)
-    if status is NotImplemented:  # dest is no contiguous buffer of bytes: make one
-        a, b, W, tok, d = _dispatch_args(ins, outs, tokens, dest)
-        status = lib().dl_token_dispatch(a, b, W, tok, int(row_bytes), d, _stream(stream))
+    if status is NotImplemented:  # dest is no contiguous buffer of bytes (and nothing else has been looked at): make one
+        status = _native().token_dispatch(ins, outs, tokens, row_bytes, _mask_bytes(dest), stream)
     _check(status, "dl_token_dispatch")
 
 

@@ -284,7 +284,7 @@ static PyObject *m_batch_copy_static(PyObject *self, PyObject *const *args, Py_s
 static PyObject *m_batch_swap(PyObject *self, PyObject *const *args, Py_ssize_t n) { return triples(args, n, "batch_swap", 2); }
 
 /* The mask: a device address (on_device), or a C-contiguous buffer of one byte per (token, rank).  NotImplemented: the
- * host mask is not such a buffer, and the caller makes one of it. */
+ * host mask is not such a buffer; no other argument has been read, and the caller makes a buffer of it. */
 static PyObject *dispatch(PyObject *const *args, Py_ssize_t n, const char *what, int on_device)
 {
     values in = {.v = in.room}, out = {.v = out.room}, tok = {.v = tok.room};
@@ -295,7 +295,18 @@ static PyObject *dispatch(PyObject *const *args, Py_ssize_t n, const char *what,
     PyObject *res = NULL;
     int rc;
     if (want(n, 6, what) < 0) return NULL;
-    if (to_values(args[0], &in, to_address) < 0 || to_values(args[1], &out, to_address) < 0 ||
+    if (!on_device) {
+        if (PyObject_GetBuffer(args[4], &view, PyBUF_C_CONTIGUOUS | PyBUF_FORMAT) < 0) {
+            PyErr_Clear();
+            return Py_NewRef(Py_NotImplemented);
+        }
+        if (view.itemsize != 1 || (view.format && !strchr("Bb?c", view.format[0]))) {
+            res = Py_NewRef(Py_NotImplemented);
+            goto done;
+        }
+        mask = (uint64_t)(uintptr_t)view.buf;
+    }
+    if (to_values(args[0], &in, to_address) < 0 || to_values(args[1], &out, to_address) < 0 || PyObject_Size(args[2]) < 0 ||
         to_values(args[2], &tok, to_u64) < 0)
         goto done;
     if (in.n != out.n || in.n != tok.n) {
@@ -310,22 +321,9 @@ static PyObject *dispatch(PyObject *const *args, Py_ssize_t n, const char *what,
     if (to_u64(args[3], &row) < 0) goto done;
     if (on_device) {
         if (to_address(args[4], &mask) < 0) goto done;
-    } else {
-        if (PyObject_GetBuffer(args[4], &view, PyBUF_C_CONTIGUOUS | PyBUF_FORMAT) < 0) {
-            PyErr_Clear();
-            view.obj = NULL;
-            res = Py_NewRef(Py_NotImplemented);
-            goto done;
-        }
-        if (view.itemsize != 1 || (view.format && !strchr("Bb?c", view.format[0]))) {
-            res = Py_NewRef(Py_NotImplemented);
-            goto done;
-        }
-        if ((uint64_t)view.len != total * (uint64_t)in.n) {
-            PyErr_SetString(PyExc_ValueError, "dest must have one entry per (token, rank)");
-            goto done;
-        }
-        mask = (uint64_t)(uintptr_t)view.buf;
+    } else if ((uint64_t)view.len != total * (uint64_t)in.n) {
+        PyErr_SetString(PyExc_ValueError, "dest must have one entry per (token, rank)");
+        goto done;
     }
     if (to_stream(args[5], &stream) < 0) goto done;
     Py_BEGIN_ALLOW_THREADS

@@ -236,3 +236,25 @@ def watchers(m, during):
     _watchers[:] = [ctypes.CFUNCTYPE(ctypes.c_int, *args[n][0])(watch(args[n][1])) if n in args else ctypes.CFUNCTYPE(ctypes.c_int)(lambda: -5)
                     for n in m.NAMES]
     return _watchers
+
+
+@pytest.mark.parametrize("form", [lambda m: m, lambda m: m.tolist(), lambda m: m.astype(np.int64), np.asfortranarray, lambda m: iter(m.tolist()),
+                                  lambda m: np.repeat(m, 2, axis=1)[:, ::2]])
+@pytest.mark.parametrize("buffers", [iter, list])
+def test_any_form_of_mask_with_iterators_for_the_buffers(calls, form, buffers):
+    """Whatever form the mask has, the buffers may come from iterators, which can be read once only."""
+    m, seen = calls
+    mask = np.array([[3, 0], [0, 1], [5, 7]], dtype=np.uint8)
+    with pytest.raises(binding.DlError):                                            # (the stub's -5)
+        binding.dl_token_dispatch(buffers([1, 2]), buffers([3, 4]), [2, 1], 16, form(mask), 9)
+    (got,) = seen
+    assert got[:6] == ("dl_token_dispatch", [1, 2], [3, 4], [2, 1], 16, got[5]) and got[6] == 9
+    assert [v != 0 for v in got[7]] == (mask != 0).ravel().tolist()
+
+
+def test_token_counts_are_a_sequence(calls):
+    m, seen = calls
+    for mask in (bytes(6), [[0, 1]] * 3):
+        with pytest.raises(TypeError):
+            binding.dl_token_dispatch([1, 2], [3, 4], iter([2, 1]), 16, mask, None)
+    assert not seen
