@@ -288,7 +288,7 @@ static PyObject *m_batch_swap(PyObject *self, PyObject *const *args, Py_ssize_t 
 static PyObject *dispatch(PyObject *const *args, Py_ssize_t n, const char *what, int on_device)
 {
     values in = {.v = in.room}, out = {.v = out.room}, tok = {.v = tok.room};
-    uint32_t count[ON_STACK];
+    uint32_t on_stack[ON_STACK], *count = on_stack;
     uint64_t row, mask = 0, total = 0;
     Py_buffer view = {.obj = NULL};
     void *stream;
@@ -313,11 +313,14 @@ static PyObject *dispatch(PyObject *const *args, Py_ssize_t n, const char *what,
         PyErr_SetString(PyExc_ValueError, "need W send buffers, W receive buffers and W token counts");
         goto done;
     }
-    if (in.n > ON_STACK) {  /* more ranks than the library takes */
-        res = PyLong_FromLong(DL_ERR_INVALID);
+    if (tok.n > ON_STACK && !(count = PyMem_New(uint32_t, tok.n))) {
+        PyErr_NoMemory();
         goto done;
     }
-    for (Py_ssize_t i = 0; i < tok.n; ++i) total += count[i] = (uint32_t)tok.v[i];
+    for (Py_ssize_t i = 0; i < tok.n; ++i) {
+        total += tok.v[i];  /* the count as it was given: one that 32 bits do not hold goes with no mask */
+        count[i] = (uint32_t)tok.v[i];
+    }
     if (to_u64(args[3], &row) < 0) goto done;
     if (on_device) {
         if (to_address(args[4], &mask) < 0) goto done;
@@ -333,6 +336,7 @@ static PyObject *dispatch(PyObject *const *args, Py_ssize_t n, const char *what,
     res = PyLong_FromLong(rc);
 done:
     if (view.obj) PyBuffer_Release(&view);
+    if (count != on_stack) PyMem_Free(count);
     free_values(&in);
     free_values(&out);
     free_values(&tok);

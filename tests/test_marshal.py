@@ -258,3 +258,15 @@ def test_token_counts_are_a_sequence(calls):
         with pytest.raises(TypeError):
             binding.dl_token_dispatch([1, 2], [3, 4], iter([2, 1]), 16, mask, None)
     assert not seen
+
+
+def test_dispatch_of_unlikely_counts_and_ranks(calls):
+    """Counts beyond 32 bits do not match a mask that their remainders would; any number of ranks reaches the library."""
+    m, seen = calls
+    with pytest.raises(ValueError):
+        m.token_dispatch([1, 2], [3, 4], [2 ** 32 + 2, 1], 16, np.zeros((3, 2), np.uint8), None)
+    assert not seen
+    W = list(range(1, 71))
+    assert m.token_dispatch(W, W, [1] * 70, 16, np.ones((70, 70), np.uint8), None) == -5
+    assert m.token_dispatch_device(W, W, [1] * 70, 16, 2 ** 62, None) == -5
+    assert [c[1:5] for c in seen] == [(W, W, [1] * 70, 16)] * 2
