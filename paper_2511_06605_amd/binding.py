@@ -276,7 +276,8 @@ def dl_shutdown() -> None:
 
 
 def dl_set_mode(mode: int) -> None:
-    _check(_native().set_mode(mode), "dl_set_mode")
+    status = _native().set_mode(mode)
+    _check(lib().dl_set_mode(mode) if status is NotImplemented else status, "dl_set_mode")
 
 
 def dl_get_mode() -> int:
@@ -413,12 +414,14 @@ def dl_last_ticket() -> int:
 
 def dl_trigger(ticket: int | None = None) -> None:
     t = dl_last_ticket() if ticket is None else ticket
-    _check(_native().trigger(t), "dl_trigger")
+    status = _native().trigger(t)
+    _check(lib().dl_trigger(t) if status is NotImplemented else status, "dl_trigger")
 
 
 def dl_wait(ticket: int | None = None, timeout_ns: int = 5_000_000_000) -> None:
     t = dl_last_ticket() if ticket is None else ticket
-    _check(_native().wait(t, timeout_ns), "dl_wait")
+    status = _native().wait(t, timeout_ns)
+    _check(lib().dl_wait(t, timeout_ns) if status is NotImplemented else status, "dl_wait")
 
 
 def dl_wait_armed(ticket: int | None = None, timeout_ns: int = 5_000_000_000) -> None:

@@ -349,11 +349,28 @@ static PyObject *m_token_dispatch_device(PyObject *self, PyObject *const *args, 
     return dispatch(args, n, "token_dispatch_device", 1);
 }
 
+/* Modes and tickets are whole numbers: an int or what stands for one (__index__).  Nothing else is converted here;
+ * NotImplemented leaves it to the ctypes entry point, which refuses a text or a fraction and takes its own integers. */
+static int to_whole(PyObject *x, uint64_t *out, PyObject **other)
+{
+    if (PyLong_CheckExact(x)) return to_u64(x, out);
+    if (!PyIndex_Check(x)) {
+        *other = Py_NewRef(Py_NotImplemented);
+        return -1;
+    }
+    PyObject *n = PyNumber_Index(x);
+    if (!n) return -1;
+    const int rc = to_u64(n, out);
+    Py_DECREF(n);
+    return rc;
+}
+
 static PyObject *m_set_mode(PyObject *self, PyObject *const *args, Py_ssize_t n)
 {
+    PyObject *other = NULL;
     uint64_t mode;
     int rc;
-    if (want(n, 1, "set_mode") < 0 || to_u64(args[0], &mode) < 0) return NULL;
+    if (want(n, 1, "set_mode") < 0 || to_whole(args[0], &mode, &other) < 0) return other;
     UNLOCKED(rc, lib.set_mode((int)mode))
     return PyLong_FromLong(rc);
 }
@@ -368,18 +385,20 @@ static PyObject *m_last_ticket(PyObject *self, PyObject *const *args, Py_ssize_t
 
 static PyObject *m_trigger(PyObject *self, PyObject *const *args, Py_ssize_t n)
 {
+    PyObject *other = NULL;
     uint64_t t;
     int rc;
-    if (want(n, 1, "trigger") < 0 || to_u64(args[0], &t) < 0) return NULL;
+    if (want(n, 1, "trigger") < 0 || to_whole(args[0], &t, &other) < 0) return other;
     UNLOCKED(rc, lib.trigger(t))
     return PyLong_FromLong(rc);
 }
 
 static PyObject *m_wait(PyObject *self, PyObject *const *args, Py_ssize_t n)
 {
+    PyObject *other = NULL;
     uint64_t t, ns;
     int rc;
-    if (want(n, 2, "wait") < 0 || to_u64(args[0], &t) < 0 || to_u64(args[1], &ns) < 0) return NULL;
+    if (want(n, 2, "wait") < 0 || to_whole(args[0], &t, &other) < 0 || to_whole(args[1], &ns, &other) < 0) return other;
     UNLOCKED(rc, lib.wait(t, ns))
     return PyLong_FromLong(rc);
 }

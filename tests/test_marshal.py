@@ -270,3 +270,19 @@ def test_dispatch_of_unlikely_counts_and_ranks(calls):
     assert m.token_dispatch(W, W, [1] * 70, 16, np.ones((70, 70), np.uint8), None) == -5
     assert m.token_dispatch_device(W, W, [1] * 70, 16, 2 ** 62, None) == -5
     assert [c[1:5] for c in seen] == [(W, W, [1] * 70, 16)] * 2
+
+
+@pytest.mark.parametrize("bad", ["0", 1.0, 1.9, b"1", (1,), np.float64(2.0)])
+def test_modes_and_tickets_are_whole_numbers(calls, bad):
+    """What is no whole number is refused, not converted; ctypes' own integers are taken as by the entry points."""
+    m, seen = calls
+    for call in (binding.dl_set_mode, binding.dl_trigger, binding.dl_wait, lambda v: binding.dl_wait(1, v)):
+        with pytest.raises(ctypes.ArgumentError):
+            call(bad)
+    assert not seen
+    for f, args in ((m.set_mode, (1,)), (m.trigger, (2,)), (m.wait, (3, 4))):
+        assert f(*args) == -5 and f(*(np.int32(a) for a in args)) == -5 and f(True, *args[1:]) == -5
+        assert f(ctypes.c_int(1), *args[1:]) is NotImplemented
+    assert [c[1] for c in seen] == [1, 1, 1, 2, 2, 1, 3, 3, 1]
+    with pytest.raises(binding.DlError):                                            # the library's own refusal: taken as 1 << 20
+        binding.dl_set_mode(ctypes.c_int(1 << 20))
