@@ -68,7 +68,16 @@ static int to_address(PyObject *x, uint64_t *out)
     PyObject *p = PyObject_CallMethodNoArgs(x, s_data_ptr);
     if (!p) {
         if (!PyErr_ExceptionMatches(PyExc_AttributeError)) return -1;
-        PyErr_Clear();
+        /* no such method, or one that failed with this error itself? */
+        PyObject *type, *value, *trace;
+        PyErr_Fetch(&type, &value, &trace);
+        if (PyObject_HasAttr(x, s_data_ptr)) {
+            PyErr_Restore(type, value, trace);
+            return -1;
+        }
+        Py_XDECREF(type);
+        Py_XDECREF(value);
+        Py_XDECREF(trace);
         return to_u64(x, out);
     }
     const int rc = to_u64(p, out);

@@ -286,3 +286,21 @@ def test_modes_and_tickets_are_whole_numbers(calls, bad):
     assert [c[1] for c in seen] == [1, 1, 1, 2, 2, 1, 3, 3, 1]
     with pytest.raises(binding.DlError):                                            # the library's own refusal: taken as 1 << 20
         binding.dl_set_mode(ctypes.c_int(1 << 20))
+
+
+def test_an_attribute_error_inside_data_ptr_is_the_callers_to_see(calls):
+    """It does not turn the object into a number (a one-element tensor's value is not its address)."""
+    m, seen = calls
+
+    class Lost:
+        def data_ptr(self):
+            return self.storage
+
+        def __index__(self):
+            return 7
+
+    for call in (lambda: m.allgather([Lost()], [1], 1, None), lambda: m.broadcast(Lost(), [1], 1, None),
+                 lambda: m.batch_copy([(1, Lost(), 3)], None), lambda: m.token_dispatch_device([1], [2], [1], 1, Lost(), None)):
+        with pytest.raises(AttributeError, match="storage"):
+            call()
+    assert not seen
