@@ -187,9 +187,13 @@ def lib() -> ctypes.CDLL:
         fn = getattr(L, name)
         fn.restype = res
         fn.argtypes = args
-    from . import _marshal as m  # built next to the library (build.py)
+    try:
+        from . import _marshal as m  # built next to the library (build.py)
+    except ImportError:
+        from . import marshal_ctypes as m  # not for this Python: the same calls with ctypes objects
     m.bind(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in m.NAMES)
-    _lib, _marshal = L, m
+    _marshal = m  # first: another thread that finds _lib set goes on to use it
+    _lib = L
     return L
 
 

@@ -27,6 +27,9 @@ class Stream:
     cuda_stream = 0xABC0
 
 
+stubs = {}  # the entry points that `calls` put in place, by name
+
+
 @pytest.fixture()
 def calls():
     """Binds the module to stubs that note their arguments as Python values; the real entry points afterwards."""
@@ -71,6 +74,8 @@ def calls():
         else:
             keep.append(ctypes.CFUNCTYPE(ctypes.c_int, *kinds[name][0])(note(name, kinds[name][1])))
     m.bind([ctypes.cast(f, vp).value for f in keep])
+    stubs.clear()
+    stubs.update(zip(m.NAMES, keep))
     yield m, seen
     m.bind([ctypes.cast(getattr(L, n), vp).value for n in m.NAMES])
 
@@ -304,3 +309,59 @@ def test_an_attribute_error_inside_data_ptr_is_the_callers_to_see(calls):
         with pytest.raises(AttributeError, match="storage"):
             call()
     assert not seen
+
+
+def test_the_calls_made_with_ctypes_objects(calls, monkeypatch):
+    """marshal_ctypes.py, for a Python without the extension, hands the entry points the same."""
+    from types import SimpleNamespace
+
+    from paper_2511_06605_amd import marshal_ctypes
+    m, seen = calls
+    monkeypatch.setattr(binding, "_lib", SimpleNamespace(**stubs))
+    B = [Tensor(2 ** 63), 1, 2, 3]
+    descs = [(0x10, Tensor(0x20), 3), [Tensor(5), None, np.int32(9)]]
+    mask = np.array([[3, 0], [0, 1], [5, 7]], dtype=np.uint8)
+    table = [("allgather", lambda: (iter(A), iter(B), np.int64(4096), Stream())), ("allgather", lambda: ([], [], 0, None)),
+             ("alltoall", lambda: ([8, 9], [10, 11], [[1, 2], [3, 2 ** 40]], 3)), ("alltoall_inplace", lambda: (iter(A), 2 ** 33, 4)),
+             ("broadcast", lambda: (Tensor(0x99), iter(A), 1, None)), ("batch_copy", lambda: (iter(descs), 5)),
+             ("batch_copy_static", lambda: (descs, 5)), ("batch_swap", lambda: (descs, None)),
+             ("token_dispatch", lambda: (iter([1, 2]), iter([3, 4]), [2, 1], 16, mask != 0, 9)),
+             ("token_dispatch_device", lambda: (iter([1, 2]), iter([3, 4]), [2, 1], 16, Tensor(2 ** 62), 9)),
+             ("set_mode", lambda: (3,)), ("trigger", lambda: (2 ** 64 - 1,)), ("wait", lambda: (3, 4))]
+    for name, args in table:
+        assert getattr(m, name)(*args()) == -5 and getattr(marshal_ctypes, name)(*args()) == -5
+        native, other = seen[-2:]
+        if name == "token_dispatch":  # the address of the mask is its own
+            native, other = ([v for q, v in enumerate(c) if q != 5] for c in (native, other))
+        assert native == other, name
+    assert m.last_ticket() == marshal_ctypes.last_ticket()
+    assert {n[3:] for n in stubs} <= set(dir(marshal_ctypes))
+    with pytest.raises(ValueError):
+        marshal_ctypes.allgather([1], [1, 2], 1, None)
+
+
+def test_the_library_is_built_where_python_has_no_headers(tmp_path, monkeypatch, capsys):
+    """The library first, whatever becomes of the extension; no headers or no C compiler: the library alone."""
+    from paper_2511_06605_amd import build as b
+    ran = []
+    monkeypatch.setattr(b, "_run", lambda cmd, verbose: ran.append(cmd))
+    monkeypatch.setattr(b, "HERE", str(tmp_path))
+    monkeypatch.setattr(b, "MARSHAL", str(tmp_path / "_marshal.so"))
+    assert b.build() == b.LIB
+    assert [c[-1] for c in ran] == [b.LIB, b.MARSHAL]
+    ran.clear()
+    monkeypatch.setattr(b.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    assert b.build() == b.LIB
+    assert [c[-1] for c in ran] == [b.LIB] and "headers" in capsys.readouterr().err
+
+
+def test_without_the_extension_the_package_uses_ctypes(monkeypatch):
+    from paper_2511_06605_amd import marshal_ctypes
+    import paper_2511_06605_amd
+    import sys
+    monkeypatch.setitem(sys.modules, "paper_2511_06605_amd._marshal", None)         # import raises ImportError
+    monkeypatch.delattr(paper_2511_06605_amd, "_marshal", raising=False)
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_marshal", None)
+    assert binding._native() is marshal_ctypes and binding._lib is not None
+    assert binding.dl_last_ticket() == 0
