@@ -340,7 +340,6 @@ int dl_dispatch_on_device(const void *const *in, void *const *out, int W, const 
         if ((tokens[i] && !in[i]) || !out[i]) return DL_OK;  // the host lowering reports what is wrong
     }
     if (total == 0 || total < min_tokens || total >= (1ull << 21)) return DL_OK;  // (a grid has at most 65535 rows of workgroups)
-    if (dl_debug_lose_armed() && total <= DISPATCH_GROUPS * GROUP) return DL_OK;  // the hook loses tables; the host lowering makes one
 
     dispatch_list p;
     dispatch_shape sh;

@@ -1198,7 +1198,7 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
     *launched = true;
     if constexpr (!std::is_same<Item, dl_fused_item>::value) {
         int rc = DL_OK;
-        if (!arm && !dl_debug_lose_armed() && launch_offsets(items, n, sh, stream, &rc)) return rc;  // (the hook is for a table)
+        if (!arm && launch_offsets(items, n, sh, stream, &rc)) return rc;
     }
     return launch_table(items, n, sh, stream, arm);
 }
@@ -1387,7 +1387,6 @@ dl_pushed dl_push_kernel_args(uint64_t stamp)
 char *dl_push_acquire(size_t bytes, hipStream_t stream, int *rc) { return push_acquire(bytes, stream, rc); }
 uint64_t dl_push_seal(char *slot) { return push_seal(slot); }
 int dl_push_commit(hipStream_t stream) { return push_commit(stream, 0); }
-bool dl_debug_lose_armed() { return g_debug_lose_tries != 0; }
 
 bool dl_device_error_pending() { return g_lost && __atomic_load_n(g_lost, __ATOMIC_ACQUIRE) != 0; }
 

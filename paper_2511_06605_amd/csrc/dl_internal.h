@@ -134,7 +134,6 @@ constexpr size_t DL_RING_SLOT_BYTES = 1u << 20;
 //                    the one stream besides the default stream that cannot go away between two calls
 //   dl_push_kernel_args  what the kernel that reads the slot gets: the stamp, how often to look for it, where to
 //                    report that it never came (stamp 0: a kernel whose table did not go this way)
-//   dl_debug_lose_armed  the test hook waits for a table (dl_debug_lose_next_table)
 //   dl_device_error_pending  a kernel has reported such a loss and dl_last_device_error() has not been called since
 char *dl_push_acquire(size_t bytes, hipStream_t stream, int *rc);
 uint64_t dl_push_seal(char *slot);
@@ -143,7 +142,6 @@ dl_pushed dl_push_kernel_args(uint64_t stamp);
 bool dl_device_error_pending();
 void dl_ring_forget_armed();
 void dl_ring_own_stream(hipStream_t stream);
-bool dl_debug_lose_armed();
 
 // dl_exec.hip: the table kernel over m plain copies of at most entry_bytes (< 2^32) each that are already in device
 // memory (entry b is workgroup b's), with the cache policy that suits `moved` bytes read + written.

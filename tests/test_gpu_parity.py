@@ -509,9 +509,9 @@ def test_batch_copy_with_and_without_broadcast_inference(ref, cfg, infer):
 @pytest.mark.parametrize("n,nb", [(9, 8 * MiB), (64, 1 * MiB), (65, 1 * MiB), (200, 512 * KiB), (70, 100 * KiB),
                                   (100, 4 * MiB)])
 def test_long_lists_of_equal_large_copies(ref, n, nb):
-    """Lists of equal, aligned, large copies: up to 64 of them travel in the kernel arguments, longer lists take the
-    row kernel over a table in device memory (written there by the host, or, when the request moves 768 MiB or more
-    as the last case does, staged by a kernel in front); every byte of the arena is compared."""
+    """Lists of equal, aligned, large copies, which travel in the kernel arguments: up to 64 of them as they are, longer
+    lists as offsets (the lists that do need a table: test_equal_copies_from_a_staged_table); every byte of the arena is
+    compared."""
     run_batch(ref, n, nb, 2 * n * nb + 64 * MiB, seed=n, align=4096)
 
 
@@ -790,7 +790,7 @@ def test_a_table_that_never_completes_is_reported_and_nothing_is_copied(ref, kin
     assert dl.dl_last_device_error() == dl.DL_OK
     W = 8
     if kind == "token_dispatch":
-        counts, row = [80] * W, 512      # 640 tokens: lowered on the device, and on the host still one table slot
+        counts, row = [300] * W, 512     # 2400 tokens: more than the kernel arguments hold
         ins = inputs.token_rows(W, counts, row, seed=5, kind="u8")
         dest = inputs.moe_token_destinations(W, counts, seed=6, n_experts=256, top_k=8)
         want = ref.token_dispatch(ins, row, dest)
@@ -801,8 +801,9 @@ def test_a_table_that_never_completes_is_reported_and_nothing_is_copied(ref, kin
         def issue():
             dl.dl_token_dispatch([b.ptr() for b in d_in], [b.ptr() for b in outs], counts, row, dest, stream())
     else:
-        n, nb = (200, 16 * KiB) if kind == "rows_table" else (300, 5000)
-        arena, descs = inputs.b2b_batch(n, nb, 32 * MiB, seed=n, align=256 if kind == "rows_table" else 1)
+        # equal copies: more than fit the kernel arguments as offsets, too small for several launches
+        arena, descs = inputs.b2b_batch(500, 16 * KiB, 64 * MiB, seed=500) if kind == "rows_table" else \
+            inputs.mixed_batch(300, 5000, 8 * MiB, seed=300)
         want = [ref.batch_copy([arena.copy()], [(0, s, 0, d, m) for s, d, m in descs])[0]]
         outs = [DevBuf(arena.size, fill=arena)]
         before = [arena]
@@ -833,6 +834,44 @@ def test_a_table_that_never_completes_is_reported_and_nothing_is_copied(ref, kin
         assert np.array_equal(d.host(), w) and d.guards_intact()
 
 
+def test_requests_without_a_table_do_not_heed_the_lost_table_hook(ref):
+    """Equal copies at offsets and a token dispatch of 640 tokens travel in the kernel arguments: with the hook armed
+    they run as ever, and the next table, of unequal copies, is the one that is lost."""
+    W, counts, row = 8, [80] * 8, 512
+    ins = inputs.token_rows(W, counts, row, seed=5, kind="u8")
+    dest = inputs.moe_token_destinations(W, counts, seed=6, n_experts=256, top_k=8)
+    want = ref.token_dispatch(ins, row, dest)
+    d_in = [DevBuf(a.size, fill=a) for a in ins]
+    outs = [DevBuf(w.size) for w in want]
+    arena, descs = inputs.b2b_batch(200, 16 * KiB, 32 * MiB, seed=200)
+    d = DevBuf(arena.size, fill=arena)
+    arena2, descs2 = inputs.mixed_batch(300, 5000, 8 * MiB, seed=301)
+    d2 = DevBuf(arena2.size, fill=arena2)
+
+    def copy(buf, ds):
+        dl.dl_batch_copy([(buf.ptr(int(s)), buf.ptr(int(t)), int(m)) for s, t, m in ds], stream())
+
+    assert dl.dl_last_device_error() == dl.DL_OK
+    _lose_next_table()
+    try:
+        dl.dl_token_dispatch([b.ptr() for b in d_in], [b.ptr() for b in outs], counts, row, dest, stream())
+        copy(d, descs)
+        sync()
+        if os.environ.get("DL_TEST_CONFIG") and lib_error_pending():
+            pytest.skip("with these forced tunables one of the requests has a table")
+        assert dl.dl_last_device_error() == dl.DL_OK
+        copy(d2, descs2)
+        sync()
+    finally:
+        dl.dl_debug_lose_next_table(0)
+        lost = dl.dl_last_device_error()
+    assert lost == dl.DL_ERR_LOST
+    for b, w in zip(outs, want):
+        assert np.array_equal(b.host(), w) and b.guards_intact()
+    assert np.array_equal(d.host(), ref.batch_copy([arena.copy()], [(0, s, 0, t, m) for s, t, m in descs])[0]) and d.guards_intact()
+    assert np.array_equal(d2.host(), arena2)
+
+
 def _hip_runtime():
     """The HIP runtime this process has loaded already (the one that owns every stream here)."""
     import ctypes
@@ -846,7 +885,8 @@ def _hip_runtime():
 def test_table_memory_is_reused_after_the_callers_stream_is_gone(ref, cfg, push):
     """A long-list request on a stream of the caller's, which the caller destroys once it has synchronised; then
     enough long-list requests on the default stream that every table slot is used again.  The library must not
-    touch the dead stream (its event was recorded while the stream was alive)."""
+    touch the dead stream (its event was recorded while the stream was alive).  The copies of a request have unequal
+    lengths: equal ones travel in the kernel arguments and use no table."""
     import ctypes
     import torch
     cfg(table_push=push)
@@ -857,8 +897,10 @@ def test_table_memory_is_reused_after_the_callers_stream_is_gone(ref, cfg, push)
     rng = np.random.default_rng(5)
     cases = []
     for r in range(71):
-        n = int(rng.integers(70, 300))
-        arena, descs = inputs.b2b_batch(n, int(rng.choice([512, 3000, 16 * KiB])), 16 * MiB, seed=100 + r)
+        n = int(rng.integers(80, 300))
+        arena, descs = inputs.mixed_batch(n, int(rng.choice([512, 3000, 16 * KiB])), 16 * MiB, seed=100 + r)
+        lengths = descs[:, 2][descs[:, 2] > 0]
+        assert len(lengths) > 64 and len(set(lengths.tolist())) > 1, "a request that needs no table"
         cases.append((arena, DevBuf(arena.size, fill=arena), descs))
     torch.cuda.synchronize()
 
