@@ -493,7 +493,6 @@ template <> struct list_cap<dl_fused_item> { static constexpr int big = 32; };
 
 constexpr uint32_t DL_UROWS_MAX_ITEMS = 65535;    // a grid's second dimension goes no further
 constexpr uint64_t TABLE_ENTRIES_TARGET = 8192;  // table kernels: aim for at most this many one-tile entries
-constexpr uint64_t PLAIN_WAVE_MIN_BYTES = 48ull << 20;  // bytes moved (read + written) from which a list of plain copies takes one-wavefront workgroups
 constexpr uint64_t FAN_WAVE_MIN_BYTES = 3ull << 20;         // bytes moved above which a copy with several destinations takes one wavefront per row
 constexpr uint64_t UNIFORM_ROWS_MIN_BYTES = 4ull << 20;  // source bytes from which a uniform long list takes the row kernel
 constexpr uint64_t UNIFORM_ROWS_STAGE_BYTES = 768ull << 20;  // bytes moved (read + written) from which its table is staged even where it could be pushed
@@ -1228,11 +1227,7 @@ dl_launch_shape dl_choose_shape(uint64_t src_bytes, uint64_t max_item_bytes, uin
     const uint64_t moved = src_bytes * (1ull + max_k);  // upper bound on bytes read + written
     uint32_t tile = c.tile_bytes;
     uint32_t most = 256u;  // threads of a workgroup
-    // Plain copies beyond the launch-bound sizes: a workgroup is one wavefront that moves one row, so consecutive
-    // rows of the address stream go to different XCDs.  All-to-all between eight ranks with 512 KiB / 1 MiB / 4 MiB chunks,
-    // 256 threads against 64: 10.8 / 26.6 / 83.4 us against 10.6 / 24.0 / 79.7; at 256 KiB chunks (32 MiB moved)
-    // the larger workgroup is 1-3 % ahead when the buffers are in the caches and 8 % behind when they are not.
-    if (max_k == 1 && tile == 0 && c.block_threads == 0 && moved >= PLAIN_WAVE_MIN_BYTES) most = 64u;
+    if (max_k == 1 && tile == 0 && c.block_threads == 0) most = dl_plain_threads(moved, c.max_blocks != 0);
     if (tile == 0) tile = 16u * most / split;
     sh.tile_bytes = tile;
     uint32_t bt = c.block_threads;

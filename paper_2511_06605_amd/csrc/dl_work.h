@@ -76,6 +76,20 @@ DL_HD uint64_t dl_item_tiles(const Item &it, uint32_t tile_bytes)
     return span / tile_bytes + (span % tile_bytes ? 1u : 0u);
 }
 
+// Threads of a workgroup that moves plain copies, where the caller has not fixed them.  Beyond the launch-bound sizes
+// a workgroup is one wavefront that moves one row, so consecutive rows of the address stream go to different XCDs.
+// All-to-all between eight ranks with 512 KiB / 1 MiB / 4 MiB chunks, 256 threads against 64: 10.8 / 26.6 / 83.4 us
+// against 10.6 / 24.0 / 79.7; at 256 KiB chunks (32 MiB moved) the larger workgroup is 1-3 % ahead when the buffers are in
+// the caches and 8 % behind when they are not.  Not where the caller caps the number of workgroups (capped): there each
+// makes many passes, and with a quarter of the wavefronts the 512 KiB / 2 MiB chunks took 51.9 / 250 us against 16.1 / 57.9
+// (512 workgroups) and 16.1 / 78.4 against 8.8 / 36.2 (2048).
+constexpr uint64_t DL_PLAIN_WAVE_MIN_BYTES = 48ull << 20;  // bytes moved (read + written)
+
+DL_HD uint32_t dl_plain_threads(uint64_t moved, bool capped)
+{
+    return moved >= DL_PLAIN_WAVE_MIN_BYTES && !capped ? 64u : 256u;
+}
+
 // Rows of 1 KiB that an item takes on that grid, and workgroups of the kernel that writes its destinations in pairs.
 DL_HD uint32_t dl_pair_rows(uint64_t bytes, uint32_t shift) { return (uint32_t)((bytes + shift + 1023u) >> 10); }
 DL_HD uint64_t dl_pair_blocks(const dl_fused_item &it)

@@ -30,6 +30,9 @@ int main()
     for (uint64_t bytes = 1; bytes < 5000; ++bytes)
         for (uint32_t shift = 0; shift < DL_CUT; ++shift)
             if (dl_pair_rows(bytes, shift) != (shift + bytes - 1) / 1024 + 1) return 3;
+    // a capped grid keeps its wavefronts, whatever the request moves
+    for (uint64_t moved = 1; moved < 1ull << 40; moved *= 2)
+        if (dl_plain_threads(moved, true) != 256u || dl_plain_threads(moved, false) != (moved < 48ull << 20 ? 256u : 64u)) return 4;
     std::puts("ok");
     return 0;
 }
