@@ -182,6 +182,45 @@ def test_equal_copies_by_offsets(ref, op, n, nb, align):
     assert np.array_equal(d.host(), want) and d.guards_intact()
 
 
+# too many for a few launches with offsets and for a table that the host pushes: the table is staged.  Below and above
+# the 768 MiB moved from which a workgroup is one wavefront
+@pytest.mark.parametrize("align", [128, 1])
+@pytest.mark.parametrize("n,nb", [(2800, 4096), (5200, 65536 + 2048), (6200, 65536)])
+def test_equal_copies_from_a_staged_table(ref, n, nb, align):
+    nb += 0 if align == 128 else 3
+    per = -(-n // (-(-n // 480)))
+    assert n * 24 > 64 * KiB and 2 * nb * per < 64 * MiB, "a list that needs no staged table"
+    arena, descs = _scattered(n, nb, align, seed=n + nb)
+    d = DevBuf(arena.size, fill=arena)
+    want = ref.batch_copy([arena], [(0, s, 0, t, m) for s, t, m in descs])[0]
+    dl.dl_batch_copy([(d.ptr(s), d.ptr(t), m) for s, t, m in descs], stream())
+    sync()
+    assert np.array_equal(d.host(), want) and d.guards_intact()
+
+
+@pytest.mark.parametrize("align", [16, 1])
+def test_equal_copies_far_apart(ref, align):
+    """Addresses more than 4 GiB apart: 32-bit offsets hold them in units of 16 bytes, where all agree modulo 16; else
+    the list takes a table."""
+    import torch
+    n, nb, span = 70, 1008, 4608 * MiB
+    rng = np.random.default_rng(align)
+    arena = torch.zeros(span, dtype=torch.uint8, device="cuda")
+    at = np.sort(rng.permutation(span // 4096 - 2)[:2 * n]) * 4096 + (rng.integers(0, 64, 2 * n) if align == 1 else 16)
+    at[0], at[-1] = align, span - nb - align
+    src, dst = at[rng.permutation(n) * 2], at[rng.permutation(n) * 2 + 1]
+    data = [rng.integers(0, 256, nb, dtype=np.uint8) for _ in range(n)]
+    for s, x in zip(src, data):
+        arena[int(s):int(s) + nb].copy_(torch.from_numpy(x))
+    p = arena.data_ptr()
+    dl.dl_batch_copy([(p + int(s), p + int(t), nb) for s, t in zip(src, dst)], stream())
+    sync()
+    for s, t, x in zip(src, dst, data):
+        assert np.array_equal(arena[int(t):int(t) + nb].cpu().numpy(), x) and np.array_equal(arena[int(s):int(s) + nb].cpu().numpy(), x)
+        if int(t) + nb + 8 <= span:
+            assert not arena[int(t) - 8:int(t)].any() and not arena[int(t) + nb:int(t) + nb + 8].any()
+
+
 def test_equal_copies_in_a_graph(ref):
     import torch
     arena, descs = _scattered(300, 3000, 1, seed=3)
