@@ -24,7 +24,6 @@ constexpr int DISPATCH_W = 8;              // ranks this path handles: exactly 8
 constexpr uint32_t GROUP = 64;             // tokens whose places one wavefront's ballots tell apart
 constexpr uint32_t DISPATCH_GROUPS = 32;   // groups per launch with the mask in the kernel arguments (3.2 KiB of the 4 KiB they may take)
 constexpr uint32_t MAX_WAVES = 8;          // wavefronts of a workgroup
-constexpr int ROWS_PER_WAVE = 2;           // 1 KiB rows in flight per wavefront
 
 struct dispatch_args {
     const char *in[DISPATCH_W];
@@ -49,44 +48,43 @@ struct dispatch_list {
 static_assert(sizeof(dispatch_list) <= 4096, "kernel arguments");
 static_assert(sizeof(dispatch_group) % 16 == 0, "whole words");
 
-// What one wavefront copies of a token's row: 1 KiB rows `row0`, row0 + stride, ..., ROWS_PER_WAVE of them.
-// On the grid (see dl_rows_body) every row is loaded once, into registers, as soon as the token is known; the loads are
-// in flight while the wavefront finds out where the row goes (128 tokens per rank, mask on the device: 18.1 -> 16.4 us).
-// Off the grid the destinations lie differently against each other, and stores across 16-byte boundaries go to
-// memory in pieces; there each destination is a plain copy cut on its own grid, whose loads after the first one hit
-// the caches (rows of 14 338 bytes, 512 tokens per rank: 103 us with one load and unaligned stores, 76 this way).
-template <int POL, bool ON_GRID>
+// Where the row of token `token` (< a.tokens) begins: its rank is the last one that starts at or before it.
+__device__ __forceinline__ const char *dl_dispatch_source(const dispatch_args &a, uint32_t token)
+{
+    const char *src = a.in[0];
+    uint32_t first = 0;
+#pragma unroll
+    for (int r = 1; r < DISPATCH_W; ++r)
+        if (a.first_token[r] <= token) {
+            src = a.in[r];
+            first = a.first_token[r];
+        }
+    return src + (uint64_t)(token - first) * a.row_bytes;
+}
+
+// On the grid (see dl_rows_body): what one wavefront copies of a token's row, 1 KiB rows `row0`, row0 + stride, ...,
+// ROWS of them.  Every row is loaded once, into registers, as soon as the token is known; the loads are in
+// flight while the wavefront finds out where the row goes (128 tokens per rank, mask on the device: 18.1 -> 16.4 us).
+template <int POL, int ROWS>
 struct dispatch_row {
     const char *src;
     uint64_t bytes;
     uint32_t row0, stride;
-    dl_u32x4 v[ON_GRID ? ROWS_PER_WAVE : 1];
+    dl_u32x4 v[ROWS];
 
     __device__ __forceinline__ uint64_t byte(int i) const
     {
         return ((uint64_t)(row0 + (uint32_t)i * stride) << 10) + ((threadIdx.x & 63u) << 4);
     }
-    // token < a.tokens
     __device__ __forceinline__ void load(const dispatch_args &a, uint32_t token, uint32_t first_row)
     {
-        // the token's rank is the last one that starts at or before it
-        src = a.in[0];
-        uint32_t first = 0;
-#pragma unroll
-        for (int r = 1; r < DISPATCH_W; ++r)
-            if (a.first_token[r] <= token) {
-                src = a.in[r];
-                first = a.first_token[r];
-            }
-        src += (uint64_t)(token - first) * a.row_bytes;
+        src = dl_dispatch_source(a, token);
         bytes = a.row_bytes;
         row0 = first_row;
         stride = a.token_waves;
-        if constexpr (ON_GRID) {
 #pragma unroll
-            for (int i = 0; i < ROWS_PER_WAVE; ++i)
-                if (byte(i) < bytes) v[i] = dl_ld16<POL>(src + byte(i));
-        }
+        for (int i = 0; i < ROWS; ++i)
+            if (byte(i) < bytes) v[i] = dl_ld16<POL>(src + byte(i));
     }
     // The token is number `in_group` of the 64 whose ranks the lanes hold in `mine`; `taken(j)` rows were placed in
     // receive buffer j before the group.
@@ -99,19 +97,45 @@ struct dispatch_row {
             const uint64_t votes = __ballot((mine >> j) & 1u);
             if (!((votes >> in_group) & 1u)) continue;
             char *const d = a.out[j] + (uint64_t)(taken(j) + (uint32_t)__popcll(votes & before)) * bytes;
-            if constexpr (ON_GRID) {
 #pragma unroll
-                for (int i = 0; i < ROWS_PER_WAVE; ++i)
-                    if (byte(i) < bytes) dl_st16<POL>(d + byte(i), v[i]);
-            } else {
-                const dl_plain_item it{src, d, bytes};
-                for (int i = 0; i < ROWS_PER_WAVE; ++i) dl_plain_row<POL, false>(it, row0 + (uint32_t)i * stride);
-            }
+            for (int i = 0; i < ROWS; ++i)
+                if (byte(i) < bytes) dl_st16<POL>(d + byte(i), v[i]);
         }
     }
 };
 
+// Off the grid the destinations of a row lie differently against each other, and stores across 16-byte boundaries go to
+// memory in pieces (rows of 14 338 bytes, 512 tokens per rank: 103 us with one load and unaligned stores), so every 1 KiB
+// row is one plain copy per destination, each cut on its own grid; its loads after the first one hit the caches.
+// What a small request takes here is instructions: a row and a destination are about a hundred of them, of one wavefront
+// and fetched anew by every kernel.  So the destinations are a loop that is not unrolled, over those that the token goes
+// to (mask on the host, 8 tokens per rank, rows of 14 338 / 16 400 bytes: 10.0 / 7.5 us unrolled eightfold, 7.2 / 5.5 as
+// a loop; four or eight destinations' loads in flight together: 9.6 / 7.3, and 102 instead of 79 us at 512 per rank).
+// Called by a wavefront for rows row0, row0 + a.token_waves, ..., ROWS of them, of token `token`, number `in_group` of
+// the 64 whose ranks the lanes hold in `mine`; `taken(j)` rows were placed in receive buffer j before the group.
+template <int POL, int ROWS, class Taken>
+__device__ __forceinline__ void dl_dispatch_off_grid(const dispatch_args &a, uint32_t token, uint32_t in_group, uint32_t row0, uint32_t mine,
+                                                     Taken taken)
+{
+    const char *const src = dl_dispatch_source(a, token);
+    const uint64_t before = (1ull << in_group) - 1ull, bytes = a.row_bytes;
+    const uint32_t ranks = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)in_group);
+#pragma unroll 1
+    for (uint32_t left = ranks; left; left &= left - 1u) {
+        const uint32_t j = (uint32_t)__builtin_ctz(left);
+        const uint64_t votes = __ballot((mine >> j) & 1u);
+        const dl_plain_item it{src, a.out[j] + (uint64_t)(taken(j) + (uint32_t)__popcll(votes & before)) * bytes, bytes};
+#pragma unroll 1
+        for (int i = 0; i < ROWS; ++i) {
+            const uint64_t row = row0 + (uint32_t)i * a.token_waves;
+            if ((row << 10) >= bytes + DL_CUT) break;  // past the end wherever on its grid the copy begins
+            dl_plain_row<POL, false>(it, row);
+        }
+    }
+}
+
 // Wavefront -> its token of the workgroup, and its first row.
+template <int ROWS>
 __device__ __forceinline__ void dl_dispatch_place(const dispatch_args &a, uint32_t *token_in_wg, uint32_t *row0)
 {
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -121,27 +145,32 @@ __device__ __forceinline__ void dl_dispatch_place(const dispatch_args &a, uint32
         ++t;
     }
     *token_in_wg = t;
-    *row0 = blockIdx.x * a.token_waves * ROWS_PER_WAVE + w;
+    *row0 = blockIdx.x * a.token_waves * ROWS + w;
 }
 
-template <int POL, bool ON_GRID>
+template <int POL, bool ON_GRID, int ROWS>
 __global__ void __launch_bounds__(64 * MAX_WAVES) dl_dispatch_list_kernel(const dispatch_list p)
 {
     uint32_t t, row0;
-    dl_dispatch_place(p.a, &t, &row0);
+    dl_dispatch_place<ROWS>(p.a, &t, &row0);
     const uint32_t first = blockIdx.y * p.a.wg_tokens;  // within this launch
     const dispatch_group &g = p.group[first / GROUP];
     const uint32_t token = p.a.token0 + first + t;
     if (token >= p.a.tokens) return;
     const uint32_t mine = g.ranks[threadIdx.x & 63u];
-    dispatch_row<POL, ON_GRID> row;
-    row.load(p.a, token, row0);
-    row.store(p.a, (first + t) % GROUP, mine, [&](int j) { return g.taken[j]; });
+    const auto taken = [&](uint32_t j) { return g.taken[j]; };
+    if constexpr (ON_GRID) {
+        dispatch_row<POL, ROWS> row;
+        row.load(p.a, token, row0);
+        row.store(p.a, (first + t) % GROUP, mine, taken);
+    } else {
+        dl_dispatch_off_grid<POL, ROWS>(p.a, token, (first + t) % GROUP, row0, mine, taken);
+    }
 }
 
 // The groups in device memory, written there by the host through the BAR just before the launch: read past the caches,
 // once the slot's stamp has been seen (see dl_pushed_entry in the row kernels), and handed on through LDS.
-template <int POL, bool ON_GRID>
+template <int POL, bool ON_GRID, int ROWS>
 __global__ void __launch_bounds__(64 * MAX_WAVES) dl_dispatch_pushed_kernel(const dispatch_args a, const dispatch_group *groups,
                                                                             const dl_pushed ps)
 {
@@ -149,7 +178,7 @@ __global__ void __launch_bounds__(64 * MAX_WAVES) dl_dispatch_pushed_kernel(cons
     __shared__ uint64_t raw[WORDS];
     __shared__ uint32_t sealed;
     uint32_t t, row0;
-    dl_dispatch_place(a, &t, &row0);
+    dl_dispatch_place<ROWS>(a, &t, &row0);
     const uint32_t first = blockIdx.y * a.wg_tokens;
     const bool valid = first + t < a.tokens;  // uniform over the wavefront
     if (threadIdx.x == 0) sealed = dl_pushed_sealed(groups, ps) ? 1u : 0u;
@@ -159,13 +188,18 @@ __global__ void __launch_bounds__(64 * MAX_WAVES) dl_dispatch_pushed_kernel(cons
         return;
     }
     if (threadIdx.x < WORDS) raw[threadIdx.x] = dl_ld<DL_POL_COHERENT>(dl_global<uint64_t>(groups + first / GROUP) + threadIdx.x);
-    dispatch_row<POL, ON_GRID> row;
-    if (valid) row.load(a, first + t, row0);
+    dispatch_row<POL, ROWS> row;
+    if constexpr (ON_GRID)
+        if (valid) row.load(a, first + t, row0);
     __syncthreads();
     if (!valid) return;
     const dispatch_group &g = *reinterpret_cast<const dispatch_group *>(raw);
     const uint32_t mine = g.ranks[threadIdx.x & 63u];
-    row.store(a, (first + t) % GROUP, mine, [&](int j) { return (uint32_t)__builtin_amdgcn_readfirstlane(g.taken[j]); });
+    const auto taken = [&](uint32_t j) { return (uint32_t)__builtin_amdgcn_readfirstlane(g.taken[j]); };
+    if constexpr (ON_GRID)
+        row.store(a, (first + t) % GROUP, mine, taken);
+    else
+        dl_dispatch_off_grid<POL, ROWS>(a, first + t, (first + t) % GROUP, row0, mine, taken);
 }
 
 // Every byte of a mask word to 0 or 1.
@@ -177,14 +211,14 @@ __device__ __forceinline__ uint64_t dl_mask_fold(uint64_t w)
     return w & 0x0101010101010101ull;
 }
 
-template <int POL, bool ON_GRID>
+template <int POL, bool ON_GRID, int ROWS>
 __global__ void __launch_bounds__(64 * MAX_WAVES) dl_dispatch_mask_kernel(const dispatch_args a, const uint8_t *__restrict__ mask)
 {
     __shared__ uint32_t part[MAX_WAVES][4];
     const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t waves = blockDim.x >> 6;
     uint32_t t, row0;
-    dl_dispatch_place(a, &t, &row0);
+    dl_dispatch_place<ROWS>(a, &t, &row0);
     const uint32_t first = blockIdx.y * a.wg_tokens;
     const uint32_t group0 = first & ~(GROUP - 1u);  // the same for the whole workgroup: wg_tokens divides GROUP
     const bool valid = first + t < a.tokens;  // uniform over the wavefront
@@ -196,26 +230,30 @@ __global__ void __launch_bounds__(64 * MAX_WAVES) dl_dispatch_mask_kernel(const 
     constexpr uint32_t BATCH = 4;
     const uint32_t step = 2u * blockDim.x;
     dl_u32x4 w[BATCH];
+    // (a thread past the end loads the first two words instead, so that no branch keeps the loads apart)
     const auto fetch = [&](uint32_t i) {
 #pragma unroll
-        for (uint32_t u = 0; u < BATCH; ++u) {
-            w[u] = dl_u32x4{0, 0, 0, 0};
-            if (i + u * step < group0) w[u] = dl_ld16<DL_POL_WT>((const char *)mask + 8ull * (i + u * step));
-        }
+        for (uint32_t u = 0; u < BATCH; ++u) w[u] = dl_ld16<DL_POL_WT>((const char *)mask + 8ull * (i + u * step < group0 ? i + u * step : 0u));
     };
     uint64_t sum = 0;
-    const auto add = [&] {
+    const auto add = [&](uint32_t i) {
 #pragma unroll
-        for (uint32_t u = 0; u < BATCH; ++u)
-            sum += dl_mask_fold(w[u].x | ((uint64_t)w[u].y << 32)) + dl_mask_fold(w[u].z | ((uint64_t)w[u].w << 32));
+        for (uint32_t u = 0; u < BATCH; ++u) {
+            const uint64_t two = dl_mask_fold(w[u].x | ((uint64_t)w[u].y << 32)) + dl_mask_fold(w[u].z | ((uint64_t)w[u].w << 32));
+            sum += i + u * step < group0 ? two : 0u;
+        }
     };
-    fetch(2u * threadIdx.x);
-    dispatch_row<POL, ON_GRID> row;
-    if (valid) row.load(a, first + t, row0);  // behind the mask's first loads: those come back first
-    add();
-    for (uint32_t i = 2u * threadIdx.x + BATCH * step; i < group0; i += BATCH * step) {
-        fetch(i);
-        add();
+    const uint32_t i0 = 2u * threadIdx.x;
+    if (group0) fetch(i0);
+    dispatch_row<POL, ROWS> row;
+    if constexpr (ON_GRID)
+        if (valid) row.load(a, first + t, row0);  // behind the mask's first loads: those come back first
+    if (group0) {
+        add(i0);
+        for (uint32_t i = BATCH * step; i < group0; i += BATCH * step) {
+            fetch(i + i0);
+            add(i + i0);
+        }
     }
     // to 16 bits a column, two columns a word: columns 0|2, 1|3, 4|6, 5|7
     const uint32_t lo = (uint32_t)sum, hi = (uint32_t)(sum >> 32);
@@ -227,21 +265,28 @@ __global__ void __launch_bounds__(64 * MAX_WAVES) dl_dispatch_mask_kernel(const 
         if (lane == 0) part[wave][q] = c[q];
     }
     __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    // over the wavefronts, and to four columns a word in their order: uniform, and picked by a shift (an array that the
+    // column indexes would be kept in memory, and everything that depends on it counted as different for every lane)
+    const auto column_pair = [&](int q) {
         uint32_t s = 0;
         for (uint32_t w = 0; w < waves; ++w) s += part[w][q];
-        c[q] = __builtin_amdgcn_readfirstlane(s);
-    }
+        return (uint32_t)__builtin_amdgcn_readfirstlane(s);
+    };
+    const auto four = [&](int q) {
+        const uint32_t even = column_pair(q), odd = column_pair(q + 1);
+        return (uint64_t)((even & 0xFFFFu) | (odd << 16)) | (uint64_t)((even >> 16) | (odd & 0xFFFF0000u)) << 32;
+    };
+    const uint64_t columns0 = four(0), columns4 = four(2);
+    const auto taken = [&](uint32_t j) { return (uint32_t)((j < 4u ? columns0 : columns4) >> (16u * (j & 3u))) & 0xFFFFu; };
     const uint64_t bits = dl_mask_fold(own);
     uint32_t mine = 0;
 #pragma unroll
     for (int j = 0; j < DISPATCH_W; ++j) mine |= ((uint32_t)(bits >> (8 * j)) & 1u) << j;
     if (!valid) return;
-    row.store(a, first + t - group0, mine, [&](int j) {
-        const uint32_t both = c[(j >> 2) * 2 + (j & 1)];
-        return (j & 2) ? both >> 16 : both & 0xFFFFu;
-    });
+    if constexpr (ON_GRID)
+        row.store(a, first + t - group0, mine, taken);
+    else
+        dl_dispatch_off_grid<POL, ROWS>(a, first + t, first + t - group0, row0, mine, taken);
 }
 
 // How far behind a DL_CUT boundary the first destination of a row can lie: rows stand whole multiples of
@@ -263,17 +308,30 @@ bool rows_on_grid(const void *const *in, void *const *out, int W, size_t row_byt
     return m == 0 && (row_bytes & 15u) == 0 && worst_shift(out, W, row_bytes) == 0;
 }
 
-// What both kernels are told, and their grid: a token's rows are shared out over up to MAX_WAVES wavefronts (a longer
+// What the kernels are told, and their grid: a token's rows are shared out over up to MAX_WAVES wavefronts (a longer
 // row takes several workgroups, blockIdx.x); short rows put several tokens into a workgroup.
 struct dispatch_shape {
     uint32_t grid_x;
     uint32_t threads;
     int policy;
     bool on_grid;
+    int rows;  // of a wavefront, in flight together
 };
 
+// Calls f with the cache policy, whether all lies on the grid, and the rows of a wavefront as compile-time constants.
+template <class F>
+void with_instance(const dispatch_shape &sh, F f)
+{
+    dl_with_policy_and_grid(sh.policy, sh.on_grid, [&](auto pol, auto og) {
+        if (sh.rows == 1)
+            f(pol, og, std::integral_constant<int, 1>{});
+        else
+            f(pol, og, std::integral_constant<int, 2>{});
+    });
+}
+
 int dispatch_setup(const void *const *in, void *const *out, const uint32_t *tokens, uint64_t total, size_t row_bytes,
-                   dispatch_args *a, dispatch_shape *sh)
+                   bool mask_on_device, dispatch_args *a, dispatch_shape *sh)
 {
     uint32_t first = 0;
     for (int i = 0; i < DISPATCH_W; ++i) {
@@ -287,12 +345,6 @@ int dispatch_setup(const void *const *in, void *const *out, const uint32_t *toke
     a->row_bytes = row_bytes;
     const uint64_t rows = (row_bytes + worst_shift(out, DISPATCH_W, row_bytes) + 1023u) >> 10;
     if (rows * total >= (1ull << 30)) return DL_ERR_INVALID;  // beyond a grid
-    const uint32_t per_wg = MAX_WAVES * ROWS_PER_WAVE;
-    sh->grid_x = (uint32_t)((rows + per_wg - 1) / per_wg);
-    a->token_waves = (uint32_t)((rows + sh->grid_x * ROWS_PER_WAVE - 1) / (sh->grid_x * ROWS_PER_WAVE));
-    a->wg_tokens = 1;
-    while (2u * a->wg_tokens * a->token_waves <= MAX_WAVES) a->wg_tokens *= 2;
-    sh->threads = 64u * a->wg_tokens * a->token_waves;
     sh->on_grid = rows_on_grid(in, out, DISPATCH_W, row_bytes);
     // Cache policy by an upper bound of what is moved (every token to every rank; top-8 of 256 experts: two thirds of
     // that), at the lines of the fan-outs of a list: write-through stores, with streaming loads, streamed output.
@@ -301,6 +353,25 @@ int dispatch_setup(const void *const *in, void *const *out, const uint32_t *toke
     const dl_config &c = g_dl.cfg;
     sh->policy = bound >= c.nontemporal_min_bytes ? DL_POL_STREAM
                  : bound > c.write_through_max_bytes ? DL_POL_STREAM_OUT : bound >= DL_FAN_STREAM_IN_MIN_BYTES ? DL_POL_STREAM_IN : DL_POL_WT;
+    // Rows of a wavefront, wavefronts of a workgroup.  Off the grid, rows that one workgroup can hold: a row per wavefront
+    // while the chip has room for all of them (8 tokens of 14 338 bytes per rank 7.2 us against 10.5 with two), else two
+    // (1024 per rank, sources not in the caches: 184 us against 202).  Longer rows: four wavefronts of a row each
+    // (16 400 bytes, 1024 per rank, likewise 189 us against 228 with eight of two; 300 000 bytes, 32 per rank 65 against 75).
+    const uint64_t in_one = 2u * MAX_WAVES;
+    uint32_t waves = MAX_WAVES;
+    sh->rows = 2;
+    if (!sh->on_grid && rows > in_one) {
+        waves = 4;
+        sh->rows = 1;
+    } else if (!sh->on_grid && (rows == 1 || rows * total <= 8192u)) {
+        sh->rows = 1;
+    }
+    const uint32_t per_wg = waves * (uint32_t)sh->rows;
+    sh->grid_x = (uint32_t)((rows + per_wg - 1) / per_wg);
+    a->token_waves = (uint32_t)((rows + sh->grid_x * sh->rows - 1) / (sh->grid_x * sh->rows));
+    a->wg_tokens = 1;
+    while (2u * a->wg_tokens * a->token_waves <= waves) a->wg_tokens *= 2;
+    sh->threads = 64u * a->wg_tokens * a->token_waves;
     return DL_OK;
 }
 
@@ -324,6 +395,25 @@ void pack_group(dispatch_group *g, const uint8_t *mask, uint32_t m, uint32_t (&p
     for (int j = 0; j < DISPATCH_W; ++j) placed[j] += (uint32_t)(acc >> (8 * j)) & 0xFFu;
 }
 
+// A few tokens off the grid are lowered on the host (a list in the kernel arguments or a short table): the destinations
+// of a row in turn, with their edges, keep one wavefront busy for longer than the host needs for so few items.  Rows of
+// 1000 / 14 338 / 16 400 bytes, 1, 4, 16 and 32 tokens per rank: on the host 2.7, 3.1, 5.2 and 7.6 us whatever the
+// length, placed on the device 6.7 / 6.9 / 5.2, 7.1 / 7.3 / 5.5, 7.6 / 7.6 / 6.5 and 7.4 / 8.7 / 7.2; at 64 per rank
+// 11 to 16 on the host, 7.6 / 11.8 / 12 here.
+constexpr uint64_t OFF_GRID_MIN_TOKENS = 256;
+
+// A table cannot be captured into a graph, the kernel arguments can (32 items fit either way).
+bool capturing(hipStream_t stream)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (!stream) return false;  // the default stream cannot be captured
+    if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
 }  // namespace
 
 int dl_dispatch_on_device(const void *const *in, void *const *out, int W, const uint32_t *tokens, size_t row_bytes,
@@ -343,8 +433,9 @@ int dl_dispatch_on_device(const void *const *in, void *const *out, int W, const 
 
     dispatch_list p;
     dispatch_shape sh;
-    int rc = dispatch_setup(in, out, tokens, total, row_bytes, &p.a, &sh);
+    int rc = dispatch_setup(in, out, tokens, total, row_bytes, false, &p.a, &sh);
     if (rc != DL_OK) return rc;
+    if (!sh.on_grid && total < OFF_GRID_MIN_TOKENS && !(total > 32u && capturing(stream))) return DL_OK;
     const uint64_t groups = (total + GROUP - 1) / GROUP;
     char *pushed = nullptr;
     if (groups > DISPATCH_GROUPS) {
@@ -364,8 +455,8 @@ int dl_dispatch_on_device(const void *const *in, void *const *out, int W, const 
         }
         const dl_pushed ps = dl_push_kernel_args(dl_push_seal(pushed));
         const dim3 grid(sh.grid_x, (uint32_t)((total + p.a.wg_tokens - 1) / p.a.wg_tokens));
-        dl_with_policy_and_grid(sh.policy, sh.on_grid, [&](auto pol, auto og) {
-            hipLaunchKernelGGL((dl_dispatch_pushed_kernel<decltype(pol)::value, decltype(og)::value>), grid, dim3(sh.threads), 0,
+        with_instance(sh, [&](auto pol, auto og, auto rows) {
+            hipLaunchKernelGGL((dl_dispatch_pushed_kernel<decltype(pol)::value, decltype(og)::value, decltype(rows)::value>), grid, dim3(sh.threads), 0,
                                stream, p.a, (const dispatch_group *)pushed, ps);
         });
         DL_HIP(hipGetLastError());
@@ -380,8 +471,8 @@ int dl_dispatch_on_device(const void *const *in, void *const *out, int W, const 
         p.a.token0 = (uint32_t)(g0 * GROUP);
         const uint64_t n = (g1 * GROUP < total ? g1 * GROUP : total) - g0 * GROUP;
         const dim3 grid(sh.grid_x, (uint32_t)((n + p.a.wg_tokens - 1) / p.a.wg_tokens));
-        dl_with_policy_and_grid(sh.policy, sh.on_grid, [&](auto pol, auto og) {
-            hipLaunchKernelGGL((dl_dispatch_list_kernel<decltype(pol)::value, decltype(og)::value>), grid, dim3(sh.threads), 0, stream, p);
+        with_instance(sh, [&](auto pol, auto og, auto rows) {
+            hipLaunchKernelGGL((dl_dispatch_list_kernel<decltype(pol)::value, decltype(og)::value, decltype(rows)::value>), grid, dim3(sh.threads), 0, stream, p);
         });
         DL_HIP(hipGetLastError());
     }
@@ -407,11 +498,11 @@ extern "C" int dl_token_dispatch_device(const void *const *in, void *const *out,
     if (total > DL_DISPATCH_DEVICE_MAX_TOKENS) return DL_ERR_CAPACITY;
     dispatch_args a;
     dispatch_shape sh;
-    const int rc = dispatch_setup(in, out, tokens, total, row_bytes, &a, &sh);
+    const int rc = dispatch_setup(in, out, tokens, total, row_bytes, true, &a, &sh);
     if (rc != DL_OK) return rc;
     const dim3 grid(sh.grid_x, (uint32_t)((total + a.wg_tokens - 1) / a.wg_tokens));
-    dl_with_policy_and_grid(sh.policy, sh.on_grid, [&](auto pol, auto og) {
-        hipLaunchKernelGGL((dl_dispatch_mask_kernel<decltype(pol)::value, decltype(og)::value>), grid, dim3(sh.threads), 0,
+    with_instance(sh, [&](auto pol, auto og, auto rows) {
+        hipLaunchKernelGGL((dl_dispatch_mask_kernel<decltype(pol)::value, decltype(og)::value, decltype(rows)::value>), grid, dim3(sh.threads), 0,
                            (hipStream_t)stream, a, dest_device);
     });
     DL_HIP(hipGetLastError());

@@ -115,7 +115,10 @@ def _dispatch(ref, counts, row, seed, entry, shift=0, top_k=4):
 @pytest.mark.parametrize("counts,row,shift", [
     ([8] * 8, 2048, 0), ([8] * 7 + [7], 4096, 0), ([9, 8, 8, 8, 8, 8, 8, 8], 6144, 0), ([3, 0, 0, 70, 1, 0, 0, 9], 10240, 0),
     ([20] * 8, 14336, 0), ([20] * 8, 16384, 0), ([6] * 8, 16384 + 128, 0), ([5] * 8, 50000, 3), ([256] * 8, 256, 0),
-    ([255] * 7 + [264], 1024, 1), ([257, 256, 256, 256, 256, 256, 256, 256], 1040, 0), ([900, 0, 1, 800, 64, 63, 65, 700], 384, 5)])
+    ([255] * 7 + [264], 1024, 1), ([257, 256, 256, 256, 256, 256, 256, 256], 1040, 0), ([900, 0, 1, 800, 64, 63, 65, 700], 384, 5),
+    # off the grid: below and from 256 tokens; one and two rows per wavefront; longer than a workgroup holds
+    ([31] * 7 + [38], 1000, 3), ([32] * 8, 1000, 3), ([64] * 8, 14338, 0), ([70] * 8, 14338, 2), ([33] * 8, 16400, 0), ([600] * 8, 2050, 1),
+    ([40] * 8, 33000, 7), ([400, 0, 300, 1, 2, 700, 0, 65], 17, 0)])
 def test_token_dispatch_shapes(ref, counts, row, shift, entry, push):
     dl.dl_set_config(table_push=push)
     try:
@@ -149,6 +152,34 @@ def test_token_dispatch_in_a_graph(ref):
         for j, w in enumerate(ref.token_dispatch(ins, row, dest)):
             got = d_out[j].host()
             assert np.array_equal(got[:w.size], w) and not got[w.size:].any() and d_out[j].guards_intact(), (replay, j)
+
+
+@pytest.mark.parametrize("tokens", [4, 20, 60])  # on the host: a list in the kernel arguments; a table; here the kernel
+def test_token_dispatch_off_the_grid_in_a_graph(ref, tokens):
+    """A captured dispatch has no table, however few its tokens are."""
+    import torch
+    counts, row = [tokens] * W, 1003
+    ins = inputs.token_rows(W, counts, row, seed=2)
+    dest = inputs.moe_token_destinations(W, counts, seed=3, n_experts=64, top_k=4)
+    want = ref.token_dispatch(ins, row, dest)
+    d_in = [DevBuf(a.size, fill=a, shift=1) for a in ins]
+    d_out = [DevBuf(w.size, shift=3) for w in want]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        dl.dl_token_dispatch([b.ptr() for b in d_in], [b.ptr() for b in d_out], counts, row, dest, torch.cuda.current_stream())
+    arena, descs = inputs.mixed_batch(300, 3000, 4 * MiB, seed=9)
+    other = DevBuf(arena.size, fill=arena)
+    for replay in range(4):
+        for b in d_out:
+            b.view().zero_()
+        dl.dl_batch_copy([(other.ptr(int(s)), other.ptr(int(t)), int(m)) for s, t, m in descs], stream())  # a table in between
+        sync()
+        g.replay()
+        torch.cuda.synchronize()
+        for b, w in zip(d_out, want):
+            assert np.array_equal(b.host(), w) and b.guards_intact(), replay
 
 
 def _scattered(n, nb, align, seed):
