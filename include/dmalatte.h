@@ -497,8 +497,10 @@ int dl_token_dispatch(const void *const *in, void *const *out, int W, const uint
  * (token, rank), non-zero = send), same result, but dest_device is a device
  * pointer (8-byte aligned) and nothing of the mask crosses the host link: one
  * launch on `stream`, ordered behind whatever produced the mask there, counts
- * and copies.  Always executed as in DL_MODE_ONESHOT; it uses no memory of the
- * library's and may be captured into a HIP graph (a replay reads the mask anew).  The host does not learn how many rows each rank
+ * and copies (a request of some hundred MiB takes two, which hand the counts on in
+ * the library's table memory).  Always executed as in DL_MODE_ONESHOT; it may be
+ * captured into a HIP graph (one launch and no memory of the library's then; a
+ * replay reads the mask anew).  The host does not learn how many rows each rank
  * receives: out[j] must have room for what the mask sends it (at most all
  * tokens).  Rows and buffers may have any length and alignment.  Limits:
  * exactly 8 ranks (DL_ERR_INVALID otherwise); at most

@@ -6,7 +6,7 @@
 //     tokens (control work, Sec. III-B2, done where the mask is); both travel in the kernel arguments (up to 2048
 //     tokens), or through the BAR, or, where that way is not open, in the arguments of several launches;
 //   - the mask in device memory: every workgroup counts the tokens in front of its own group itself (at most 80 KiB
-//     of mask, which the L2 holds).
+//     of mask, which the L2 holds); or, for a large request, a first kernel packs the groups (see PACK_FIRST_BYTES).
 // Inside a group of 64 the places come from one ballot per rank.
 //
 // Before, a kernel built a table of 88-byte items from the mask (and another counted for it) and the row kernel for
@@ -148,24 +148,39 @@ __device__ __forceinline__ void dl_dispatch_place(const dispatch_args &a, uint32
     *row0 = blockIdx.x * a.token_waves * ROWS + w;
 }
 
+// A wavefront's rows of token `token`, whose group's record is g.
+template <int POL, bool ON_GRID, int ROWS>
+__device__ __forceinline__ void dl_dispatch_group_rows(const dispatch_args &a, const dispatch_group &g, uint32_t token, uint32_t row0)
+{
+    const uint32_t mine = g.ranks[threadIdx.x & 63u];
+    const auto taken = [&](uint32_t j) { return g.taken[j]; };
+    if constexpr (ON_GRID) {
+        dispatch_row<POL, ROWS> row;
+        row.load(a, token, row0);
+        row.store(a, token % GROUP, mine, taken);
+    } else {
+        dl_dispatch_off_grid<POL, ROWS>(a, token, token % GROUP, row0, mine, taken);
+    }
+}
+
 template <int POL, bool ON_GRID, int ROWS>
 __global__ void __launch_bounds__(64 * MAX_WAVES) dl_dispatch_list_kernel(const dispatch_list p)
 {
     uint32_t t, row0;
     dl_dispatch_place<ROWS>(p.a, &t, &row0);
     const uint32_t first = blockIdx.y * p.a.wg_tokens;  // within this launch
-    const dispatch_group &g = p.group[first / GROUP];
     const uint32_t token = p.a.token0 + first + t;
-    if (token >= p.a.tokens) return;
-    const uint32_t mine = g.ranks[threadIdx.x & 63u];
-    const auto taken = [&](uint32_t j) { return g.taken[j]; };
-    if constexpr (ON_GRID) {
-        dispatch_row<POL, ROWS> row;
-        row.load(p.a, token, row0);
-        row.store(p.a, (first + t) % GROUP, mine, taken);
-    } else {
-        dl_dispatch_off_grid<POL, ROWS>(p.a, token, (first + t) % GROUP, row0, mine, taken);
-    }
+    if (token < p.a.tokens) dl_dispatch_group_rows<POL, ON_GRID, ROWS>(p.a, p.group[first / GROUP], token, row0);
+}
+
+// The groups in device memory, written there by the kernel in front (dl_dispatch_pack_kernel).
+template <int POL, bool ON_GRID, int ROWS>
+__global__ void __launch_bounds__(64 * MAX_WAVES) dl_dispatch_packed_kernel(const dispatch_args a, const dispatch_group *__restrict__ groups)
+{
+    uint32_t t, row0;
+    dl_dispatch_place<ROWS>(a, &t, &row0);
+    const uint32_t token = blockIdx.y * a.wg_tokens + t;
+    if (token < a.tokens) dl_dispatch_group_rows<POL, ON_GRID, ROWS>(a, groups[token / GROUP], token, row0);
 }
 
 // The groups in device memory, written there by the host through the BAR just before the launch: read past the caches,
@@ -211,82 +226,113 @@ __device__ __forceinline__ uint64_t dl_mask_fold(uint64_t w)
     return w & 0x0101010101010101ull;
 }
 
+// The mask in device memory: how many rows the tokens in front of a group take in each receive buffer, and the ranks of
+// the group's own token `lane` (0 past the last one).  Counted by the whole workgroup; `between` runs behind the first
+// loads, which are in flight meanwhile.
+struct dispatch_counts {
+    uint64_t columns0, columns4;  // 16 bits a rank
+    uint32_t mine;
+
+    __device__ __forceinline__ uint32_t taken(uint32_t j) const
+    {
+        // (an array that j indexes would be kept in memory, and all that depends on it counted as different for every lane)
+        return (uint32_t)((j < 4u ? columns0 : columns4) >> (16u * (j & 3u))) & 0xFFFFu;
+    }
+    template <class Between>
+    __device__ __forceinline__ void count(const uint8_t *mask, uint32_t tokens, uint32_t group0, Between between)
+    {
+        __shared__ uint32_t part[MAX_WAVES][4];
+        const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const uint32_t waves = blockDim.x >> 6;
+        const DL_GLOBAL uint64_t *words = dl_global<uint64_t>(mask);
+        const uint64_t own = group0 + lane < tokens ? words[group0 + lane] : 0ull;
+        // two tokens per 16-byte load, BATCH loads in flight; a thread sums at most DL_DISPATCH_DEVICE_MAX_TOKENS / 64
+        // words, so a byte of the sum does not overflow
+        static_assert(DL_DISPATCH_DEVICE_MAX_TOKENS / 64 <= 255, "bytewise sums");
+        constexpr uint32_t BATCH = 4;
+        const uint32_t step = 2u * blockDim.x, i0 = 2u * threadIdx.x;
+        dl_u32x4 w[BATCH];
+        // (a thread past the end loads the first two words instead, so that no branch keeps the loads apart)
+        const auto fetch = [&](uint32_t i) {
+#pragma unroll
+            for (uint32_t u = 0; u < BATCH; ++u) w[u] = dl_ld16<DL_POL_WT>((const char *)mask + 8ull * (i + u * step < group0 ? i + u * step : 0u));
+        };
+        uint64_t sum = 0;
+        const auto add = [&](uint32_t i) {
+#pragma unroll
+            for (uint32_t u = 0; u < BATCH; ++u) {
+                const uint64_t two = dl_mask_fold(w[u].x | ((uint64_t)w[u].y << 32)) + dl_mask_fold(w[u].z | ((uint64_t)w[u].w << 32));
+                sum += i + u * step < group0 ? two : 0u;
+            }
+        };
+        if (group0) fetch(i0);
+        between();
+        if (group0) {
+            add(i0);
+            for (uint32_t i = BATCH * step; i < group0; i += BATCH * step) {
+                fetch(i + i0);
+                add(i + i0);
+            }
+        }
+        // to 16 bits a column, two columns a word: columns 0|2, 1|3, 4|6, 5|7
+        const uint32_t lo = (uint32_t)sum, hi = (uint32_t)(sum >> 32);
+        uint32_t c[4] = {lo & 0x00FF00FFu, (lo >> 8) & 0x00FF00FFu, hi & 0x00FF00FFu, (hi >> 8) & 0x00FF00FFu};
+        static_assert(DL_DISPATCH_DEVICE_MAX_TOKENS < 65536, "16-bit counts");
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            for (int o = 32; o; o >>= 1) c[q] += __shfl_xor(c[q], o);
+            if (lane == 0) part[wave][q] = c[q];
+        }
+        __syncthreads();
+        // over the wavefronts, and to four columns a word in their order
+        const auto column_pair = [&](int q) {
+            uint32_t s = 0;
+            for (uint32_t w = 0; w < waves; ++w) s += part[w][q];
+            return (uint32_t)__builtin_amdgcn_readfirstlane(s);
+        };
+        const auto four = [&](int q) {
+            const uint32_t even = column_pair(q), odd = column_pair(q + 1);
+            return (uint64_t)((even & 0xFFFFu) | (odd << 16)) | (uint64_t)((even >> 16) | (odd & 0xFFFF0000u)) << 32;
+        };
+        columns0 = four(0);
+        columns4 = four(2);
+        const uint64_t bits = dl_mask_fold(own);
+        mine = 0;
+#pragma unroll
+        for (int j = 0; j < DISPATCH_W; ++j) mine |= ((uint32_t)(bits >> (8 * j)) & 1u) << j;
+    }
+};
+
 template <int POL, bool ON_GRID, int ROWS>
 __global__ void __launch_bounds__(64 * MAX_WAVES) dl_dispatch_mask_kernel(const dispatch_args a, const uint8_t *__restrict__ mask)
 {
-    __shared__ uint32_t part[MAX_WAVES][4];
-    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t waves = blockDim.x >> 6;
     uint32_t t, row0;
     dl_dispatch_place<ROWS>(a, &t, &row0);
     const uint32_t first = blockIdx.y * a.wg_tokens;
     const uint32_t group0 = first & ~(GROUP - 1u);  // the same for the whole workgroup: wg_tokens divides GROUP
     const bool valid = first + t < a.tokens;  // uniform over the wavefront
-    const DL_GLOBAL uint64_t *words = dl_global<uint64_t>(mask);
-    const uint64_t own = group0 + lane < a.tokens ? words[group0 + lane] : 0ull;
-    // the tokens before the group, two per 16-byte load, BATCH loads in flight; a thread sums at most
-    // DL_DISPATCH_DEVICE_MAX_TOKENS / 64 words, so a byte of the sum does not overflow
-    static_assert(DL_DISPATCH_DEVICE_MAX_TOKENS / 64 <= 255, "bytewise sums");
-    constexpr uint32_t BATCH = 4;
-    const uint32_t step = 2u * blockDim.x;
-    dl_u32x4 w[BATCH];
-    // (a thread past the end loads the first two words instead, so that no branch keeps the loads apart)
-    const auto fetch = [&](uint32_t i) {
-#pragma unroll
-        for (uint32_t u = 0; u < BATCH; ++u) w[u] = dl_ld16<DL_POL_WT>((const char *)mask + 8ull * (i + u * step < group0 ? i + u * step : 0u));
-    };
-    uint64_t sum = 0;
-    const auto add = [&](uint32_t i) {
-#pragma unroll
-        for (uint32_t u = 0; u < BATCH; ++u) {
-            const uint64_t two = dl_mask_fold(w[u].x | ((uint64_t)w[u].y << 32)) + dl_mask_fold(w[u].z | ((uint64_t)w[u].w << 32));
-            sum += i + u * step < group0 ? two : 0u;
-        }
-    };
-    const uint32_t i0 = 2u * threadIdx.x;
-    if (group0) fetch(i0);
     dispatch_row<POL, ROWS> row;
-    if constexpr (ON_GRID)
-        if (valid) row.load(a, first + t, row0);  // behind the mask's first loads: those come back first
-    if (group0) {
-        add(i0);
-        for (uint32_t i = BATCH * step; i < group0; i += BATCH * step) {
-            fetch(i + i0);
-            add(i + i0);
-        }
-    }
-    // to 16 bits a column, two columns a word: columns 0|2, 1|3, 4|6, 5|7
-    const uint32_t lo = (uint32_t)sum, hi = (uint32_t)(sum >> 32);
-    uint32_t c[4] = {lo & 0x00FF00FFu, (lo >> 8) & 0x00FF00FFu, hi & 0x00FF00FFu, (hi >> 8) & 0x00FF00FFu};
-    static_assert(DL_DISPATCH_DEVICE_MAX_TOKENS < 65536, "16-bit counts");
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        for (int o = 32; o; o >>= 1) c[q] += __shfl_xor(c[q], o);
-        if (lane == 0) part[wave][q] = c[q];
-    }
-    __syncthreads();
-    // over the wavefronts, and to four columns a word in their order: uniform, and picked by a shift (an array that the
-    // column indexes would be kept in memory, and everything that depends on it counted as different for every lane)
-    const auto column_pair = [&](int q) {
-        uint32_t s = 0;
-        for (uint32_t w = 0; w < waves; ++w) s += part[w][q];
-        return (uint32_t)__builtin_amdgcn_readfirstlane(s);
-    };
-    const auto four = [&](int q) {
-        const uint32_t even = column_pair(q), odd = column_pair(q + 1);
-        return (uint64_t)((even & 0xFFFFu) | (odd << 16)) | (uint64_t)((even >> 16) | (odd & 0xFFFF0000u)) << 32;
-    };
-    const uint64_t columns0 = four(0), columns4 = four(2);
-    const auto taken = [&](uint32_t j) { return (uint32_t)((j < 4u ? columns0 : columns4) >> (16u * (j & 3u))) & 0xFFFFu; };
-    const uint64_t bits = dl_mask_fold(own);
-    uint32_t mine = 0;
-#pragma unroll
-    for (int j = 0; j < DISPATCH_W; ++j) mine |= ((uint32_t)(bits >> (8 * j)) & 1u) << j;
+    dispatch_counts c;
+    c.count(mask, a.tokens, group0, [&] {
+        if constexpr (ON_GRID)
+            if (valid) row.load(a, first + t, row0);  // behind the mask's first loads: those come back first
+    });
     if (!valid) return;
+    const auto taken = [&](uint32_t j) { return c.taken(j); };
     if constexpr (ON_GRID)
-        row.store(a, first + t - group0, mine, taken);
+        row.store(a, first + t - group0, c.mine, taken);
     else
-        dl_dispatch_off_grid<POL, ROWS>(a, first + t, first + t - group0, row0, mine, taken);
+        dl_dispatch_off_grid<POL, ROWS>(a, first + t, first + t - group0, row0, c.mine, taken);
+}
+
+// One workgroup per group: its record, for dl_dispatch_packed_kernel.
+__global__ void __launch_bounds__(64 * MAX_WAVES) dl_dispatch_pack_kernel(const uint8_t *__restrict__ mask, uint32_t tokens, dispatch_group *groups)
+{
+    dispatch_counts c;
+    c.count(mask, tokens, blockIdx.x * GROUP, [] {});
+    dispatch_group &g = groups[blockIdx.x];
+    if (threadIdx.x < GROUP) g.ranks[threadIdx.x] = (uint8_t)c.mine;
+    if (threadIdx.x < (uint32_t)DISPATCH_W) g.taken[threadIdx.x] = c.taken(threadIdx.x);
 }
 
 // How far behind a DL_CUT boundary the first destination of a row can lie: rows stand whole multiples of
@@ -315,7 +361,8 @@ struct dispatch_shape {
     uint32_t threads;
     int policy;
     bool on_grid;
-    int rows;  // of a wavefront, in flight together
+    bool long_rows;  // longer than a workgroup holds
+    int rows;        // of a wavefront, in flight together
 };
 
 // Calls f with the cache policy, whether all lies on the grid, and the rows of a wavefront as compile-time constants.
@@ -360,10 +407,19 @@ int dispatch_setup(const void *const *in, void *const *out, const uint32_t *toke
     const uint64_t in_one = 2u * MAX_WAVES;
     uint32_t waves = MAX_WAVES;
     sh->rows = 2;
-    if (!sh->on_grid && rows > in_one) {
+    sh->long_rows = rows > in_one;
+    if (!sh->on_grid && sh->long_rows) {
         waves = 4;
         sh->rows = 1;
     } else if (!sh->on_grid && (rows == 1 || rows * total <= 8192u)) {
+        sh->rows = 1;
+    } else if (sh->on_grid && sh->policy == DL_POL_STREAM_OUT && !mask_on_device) {
+        // Large requests on the grid: two wavefronts of a row each.  Consecutive rows then go to different XCDs, and fewer
+        // destinations are written at once by each.  Rows of 14 336 bytes, 512 / 1024 per rank 58.5 / 140 us with eight
+        // wavefronts of two rows, 54.6 / 125 this way; of 64 KiB, sources not in the caches, 256 / 512 / 1024 per rank
+        // 163 / 320 / 638 and 141 / 278 / 564.  Smaller requests stay: 128 per rank of 14 336 bytes 13.0 and 17.9.
+        // (Not where every workgroup counts the mask: four times as many workgroups, 512 per rank of 64 KiB 378 us.)
+        waves = 2;
         sh->rows = 1;
     }
     const uint32_t per_wg = waves * (uint32_t)sh->rows;
@@ -401,6 +457,16 @@ void pack_group(dispatch_group *g, const uint8_t *mask, uint32_t m, uint32_t (&p
 // length, placed on the device 6.7 / 6.9 / 5.2, 7.1 / 7.3 / 5.5, 7.6 / 7.6 / 6.5 and 7.4 / 8.7 / 7.2; at 64 per rank
 // 11 to 16 on the host, 7.6 / 11.8 / 12 here.
 constexpr uint64_t OFF_GRID_MIN_TOKENS = 256;
+
+// A large request whose mask is in device memory packs the groups first, in a launch of their own, so that the kernel
+// that copies need not count: it can then have many small workgroups (see dispatch_setup).  That costs 5 us, and pays from
+// the sizes (every token to every rank) below.  One launch : two, sources not in the caches: 14 336 bytes, 700 / 1024 per
+// rank (689 / 1008 MiB by this measure) 82 : 86 and 139 : 131 us; 64 KiB, 128 / 256 / 1024 (576 / 1152 / 4608 MiB) 68.5 :
+// 69.1, 162 : 148 and 634 : 582; off the grid 16 400 bytes, 128 / 256 / 1024 (144 / 288 / 1153 MiB) 28.3 : 29.7, 49.8 :
+// 47.6 and 255 : 194, 14 338 bytes, 512 / 1024 (504 / 1008 MiB) 83.7 : 83.6 and 200 : 188.
+constexpr uint64_t PACK_FIRST_BYTES = 900ull << 20;
+constexpr uint64_t PACK_FIRST_OFF_GRID_BYTES = 256ull << 20;  // rows longer than a workgroup holds
+static_assert((DL_DISPATCH_DEVICE_MAX_TOKENS + GROUP - 1) / GROUP * sizeof(dispatch_group) <= DL_RING_SLOT_BYTES, "groups of the largest request");
 
 // A table cannot be captured into a graph, the kernel arguments can (32 items fit either way).
 bool capturing(hipStream_t stream)
@@ -479,8 +545,9 @@ int dl_dispatch_on_device(const void *const *in, void *const *out, int W, const 
     return DL_OK;
 }
 
-// Token dispatch with the routing mask in device memory (dl_token_dispatch_device): one launch on the caller's
-// stream, nothing of the request but the kernel arguments comes from the host, and no memory of the library's is used.
+// Token dispatch with the routing mask in device memory (dl_token_dispatch_device): on the caller's stream, and nothing
+// of the request but the kernel arguments comes from the host.  One launch, which uses no memory of the library's; or two
+// with the groups in its table memory, if the request is large, the stream is not being captured and that memory is free.
 extern "C" int dl_token_dispatch_device(const void *const *in, void *const *out, int W, const uint32_t *tokens,
                                         size_t row_bytes, const uint8_t *dest_device, void *stream)
 {
@@ -498,14 +565,35 @@ extern "C" int dl_token_dispatch_device(const void *const *in, void *const *out,
     if (total > DL_DISPATCH_DEVICE_MAX_TOKENS) return DL_ERR_CAPACITY;
     dispatch_args a;
     dispatch_shape sh;
-    const int rc = dispatch_setup(in, out, tokens, total, row_bytes, true, &a, &sh);
+    hipStream_t hs = (hipStream_t)stream;
+    int rc = dispatch_setup(in, out, tokens, total, row_bytes, true, &a, &sh);
     if (rc != DL_OK) return rc;
+    size_t slot;
+    dispatch_group *groups = nullptr;
+    const uint64_t bound = total * row_bytes * (1u + DISPATCH_W);  // (see dispatch_setup)
+    if ((bound >= PACK_FIRST_BYTES || (!sh.on_grid && sh.long_rows && bound >= PACK_FIRST_OFF_GRID_BYTES)) && !capturing(hs))
+        groups = (dispatch_group *)dl_scratch_acquire(&slot);
+    if (groups) {
+        rc = dispatch_setup(in, out, tokens, total, row_bytes, false, &a, &sh);
+        if (rc != DL_OK) return rc;
+        hipLaunchKernelGGL(dl_dispatch_pack_kernel, dim3((uint32_t)((total + GROUP - 1) / GROUP)), dim3(64 * MAX_WAVES), 0, hs, dest_device,
+                           (uint32_t)total, groups);
+        DL_HIP(hipGetLastError());
+    }
     const dim3 grid(sh.grid_x, (uint32_t)((total + a.wg_tokens - 1) / a.wg_tokens));
     with_instance(sh, [&](auto pol, auto og, auto rows) {
-        hipLaunchKernelGGL((dl_dispatch_mask_kernel<decltype(pol)::value, decltype(og)::value, decltype(rows)::value>), grid, dim3(sh.threads), 0,
-                           (hipStream_t)stream, a, dest_device);
+        if (groups)
+            hipLaunchKernelGGL((dl_dispatch_packed_kernel<decltype(pol)::value, decltype(og)::value, decltype(rows)::value>), grid,
+                               dim3(sh.threads), 0, hs, a, (const dispatch_group *)groups);
+        else
+            hipLaunchKernelGGL((dl_dispatch_mask_kernel<decltype(pol)::value, decltype(og)::value, decltype(rows)::value>), grid,
+                               dim3(sh.threads), 0, hs, a, dest_device);
     });
     DL_HIP(hipGetLastError());
+    if (groups) {
+        rc = dl_scratch_release(slot, hs);
+        if (rc != DL_OK) return rc;
+    }
     t_dl_last.mode = DL_MODE_ONESHOT;
     return DL_OK;
 }

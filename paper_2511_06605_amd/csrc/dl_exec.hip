@@ -1349,6 +1349,24 @@ int dl_launch_plain_table(const dl_plain_item *dev_items, uint32_t m, uint32_t e
     return DL_OK;
 }
 
+void *dl_scratch_acquire(size_t *slot)
+{
+    if (!g_ring.base) return nullptr;
+    const size_t s = g_ring.next % RING_SLOTS;
+    if (g_ring.used[s] && wait_for_readers(g_ring.ev[s], g_ring.armed[s]) != DL_OK) return nullptr;
+    ++g_ring.next;
+    g_ring.armed[s] = 0;
+    *slot = s;
+    return g_ring.dev + s * RING_SLOT_BYTES;
+}
+
+int dl_scratch_release(size_t slot, hipStream_t stream)
+{
+    DL_HIP(hipEventRecord(g_ring.ev[slot], stream));
+    g_ring.used[slot] = true;
+    return DL_OK;
+}
+
 void dl_ring_forget_armed()
 {
     for (size_t s = 0; s < RING_SLOTS; ++s) g_ring.armed[s] = 0;

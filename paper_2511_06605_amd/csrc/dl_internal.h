@@ -119,7 +119,12 @@ constexpr uint32_t DL_TABLE_ROWS_SPLIT = 2;
 constexpr uint32_t DL_TABLE_ROWS_THREADS = 128;
 
 // dl_exec.hip: the staging ring: pinned host slots of this size, each with a device mirror.
+//   dl_scratch_acquire  the next slot's mirror, for kernels that are launched next to write and read; its previous user
+//                       has finished.  Null: there is none, or a request that nobody has triggered yet holds it
+//   dl_scratch_release  the slot is in use until all that is enqueued on `stream` so far has finished
 constexpr size_t DL_RING_SLOT_BYTES = 1u << 20;
+void *dl_scratch_acquire(size_t *slot);
+int dl_scratch_release(size_t slot, hipStream_t stream);
 // dl_exec.hip: short tables written by the host straight into device memory (through the BAR).
 //   dl_push_acquire  a slot for `bytes` (at most DL_PUSH_PAYLOAD_BYTES) that a kernel launched on `stream` next
 //                    will read, or null if that way is not open (no such BAR, switched off, too long);

@@ -118,7 +118,11 @@ def _dispatch(ref, counts, row, seed, entry, shift=0, top_k=4):
     ([255] * 7 + [264], 1024, 1), ([257, 256, 256, 256, 256, 256, 256, 256], 1040, 0), ([900, 0, 1, 800, 64, 63, 65, 700], 384, 5),
     # off the grid: below and from 256 tokens; one and two rows per wavefront; longer than a workgroup holds
     ([31] * 7 + [38], 1000, 3), ([32] * 8, 1000, 3), ([64] * 8, 14338, 0), ([70] * 8, 14338, 2), ([33] * 8, 16400, 0), ([600] * 8, 2050, 1),
-    ([40] * 8, 33000, 7), ([400, 0, 300, 1, 2, 700, 0, 65], 17, 0)])
+    ([40] * 8, 33000, 7), ([400, 0, 300, 1, 2, 700, 0, 65], 17, 0),
+    # on the grid, 144 MiB and more by the measure of the rule: rows of one and of several workgroups
+    ([300] * 8, 8192, 0), ([300, 301, 299, 310, 290, 300, 300, 301], 7296, 0), ([120] * 8, 20480 + 128, 0), ([13] * 8, 160 * KiB + 1152, 0),
+    # the mask on the device and the groups packed first: on the grid from 900 MiB, off it long rows from 256 MiB
+    ([100] * 8, 131200, 0), ([231, 230, 229, 230, 230, 230, 230, 232], 16400, 0)])
 def test_token_dispatch_shapes(ref, counts, row, shift, entry, push):
     dl.dl_set_config(table_push=push)
     try:
@@ -127,10 +131,10 @@ def test_token_dispatch_shapes(ref, counts, row, shift, entry, push):
         dl.dl_set_config(table_push=1)
 
 
-def test_token_dispatch_in_a_graph(ref):
+@pytest.mark.parametrize("counts,row", [([40] * 8, 3072), ([230] * 8, 16400)])
+def test_token_dispatch_in_a_graph(ref, counts, row):
     """The mask on the device: one launch, captured once; every replay follows the mask of the moment."""
     import torch
-    counts, row = [40] * W, 3072
     ins = inputs.token_rows(W, counts, row, seed=1)
     d_in = [DevBuf(a.size, fill=a) for a in ins]
     d_out = [DevBuf(sum(counts) * row) for _ in range(W)]
@@ -152,6 +156,28 @@ def test_token_dispatch_in_a_graph(ref):
         for j, w in enumerate(ref.token_dispatch(ins, row, dest)):
             got = d_out[j].host()
             assert np.array_equal(got[:w.size], w) and not got[w.size:].any() and d_out[j].guards_intact(), (replay, j)
+
+
+def test_large_token_dispatches_on_changing_streams(ref):
+    """Masks on the device, groups packed in the table memory: twelve requests (the memory has four slots) on three
+    streams without any synchronisation in between, each with a mask and outputs of its own."""
+    import torch
+    counts, row = [230] * W, 16400
+    ins = inputs.token_rows(W, counts, row, seed=4)
+    d_in = [DevBuf(a.size, fill=a) for a in ins]
+    streams = [torch.cuda.current_stream(), torch.cuda.Stream(), torch.cuda.Stream()]
+    cases = []
+    for r in range(12):
+        dest = inputs.moe_token_destinations(W, counts, seed=60 + r, n_experts=64, top_k=2)
+        outs = [DevBuf(max(1, int(n)) * row) for n in dest.astype(bool).sum(axis=0)]
+        cases.append((dest, torch.from_numpy(dest).cuda(), outs))
+    torch.cuda.synchronize()
+    for r, (_, mask, outs) in enumerate(cases):
+        dl.dl_token_dispatch_device([b.ptr() for b in d_in], [b.ptr() for b in outs], counts, row, mask, streams[r % 3])
+    torch.cuda.synchronize()
+    for r, (dest, _, outs) in enumerate(cases):
+        for j, w in enumerate(ref.token_dispatch(ins, row, dest)):
+            assert np.array_equal(outs[j].host(), w) and outs[j].guards_intact(), (r, j)
 
 
 @pytest.mark.parametrize("tokens", [4, 20, 60])  # on the host: a list in the kernel arguments; a table; here the kernel
