@@ -697,8 +697,8 @@ __device__ __forceinline__ void dl_rows_body(const Item &it, uint32_t tile, uint
 // the fewer streams are written at once: with all eight destinations of an all-gather in flight together 64 MiB per
 // rank took 781 us, and 810 to 965 when the buffers lay badly against each other; in pairs 740, however they lie.
 // The row is loaded once per pair, and all but the first of these loads hit the L2: workgroups are dealt round-robin
-// to the eight XCDs and a chunk's pairs are a multiple of eight workgroups apart, so a row always goes to the same
-// XCD, whose share of a 4 MiB chunk is 512 KiB (1, 4 and 16 MiB chunks were within 1 % of each other).
+// to the eight XCDs and a chunk's pairs are a multiple of eight workgroups apart (see dl_pair_locate), so a row always goes
+// to the same XCD, whose share of a 4 MiB chunk is 512 KiB.
 // `local`: the workgroup's index within the item.  Destinations in their own order, the unused ones null.
 template <int POL, bool ON_GRID>
 __device__ __forceinline__ void dl_pair_body(const dl_fused_item &it, uint32_t local)

@@ -7,23 +7,39 @@
 
 int main()
 {
-    const uint32_t sizes[] = {1, 2, 4095, 4096, 4097, 8191, 8192, 8193, 12288, 20000};
+    std::vector<uint32_t> sizes = {4089, 4095, 4096, 4097, 8191, 8192, 8193, 12288, 20000, 20001};
+    for (uint32_t rows = 1; rows < 600; ++rows) sizes.push_back(rows);
     for (uint32_t rows : sizes)
         for (uint32_t pairs = 1; pairs <= 4; ++pairs) {
             std::vector<int> seen((size_t)rows * pairs, 0);
-            for (uint32_t b = 0; b < rows * pairs; ++b) {
+            std::vector<uint32_t> xcd(rows, ~0u);
+            dl_fused_item item{};
+            item.bytes = (uint64_t)rows << 10;
+            item.k = 2 * pairs;
+            const uint64_t blocks = dl_pair_blocks(item);
+            if (blocks % 8) return 5;
+            uint64_t idle = 0;
+            for (uint32_t b = 0; b < blocks; ++b) {
                 uint32_t row = ~0u, pair = ~0u;
-                if (!dl_pair_locate(b, rows, pairs, &row, &pair) || row >= rows || pair >= pairs || seen[(size_t)pair * rows + row]++) {
+                if (!dl_pair_locate(b, rows, pairs, &row, &pair)) {
+                    ++idle;
+                    continue;
+                }
+                if (row >= rows || pair >= pairs || seen[(size_t)pair * rows + row]++) {
                     std::printf("rows %u pairs %u block %u: row %u pair %u\n", rows, pairs, b, row, pair);
                     return 1;
                 }
+                // the workgroups of a row's pairs are dealt to the same one of eight XCDs
+                if (xcd[row] == ~0u) xcd[row] = b % 8;
+                if (xcd[row] != b % 8) {
+                    std::printf("rows %u pairs %u row %u: XCDs %u and %u\n", rows, pairs, row, xcd[row], b % 8);
+                    return 2;
+                }
             }
-            // the workgroups of a row's pairs stay on one of eight XCDs where whole chunks allow it
-            for (uint32_t b = 0; b + 4096 < rows * pairs && rows % 4096 == 0; ++b) {
-                uint32_t r0, p0, r1, p1;
-                dl_pair_locate(b, rows, pairs, &r0, &p0);
-                dl_pair_locate(b + 4096, rows, pairs, &r1, &p1);
-                if (p1 == p0 + 1 && r0 != r1) return 2;
+            if (idle != blocks - (uint64_t)rows * pairs || idle > 7u * pairs) return 6;
+            for (uint32_t b = (uint32_t)blocks; b < blocks + 10000; b += 9) {  // past the item
+                uint32_t row, pair;
+                if (dl_pair_locate(b, rows, pairs, &row, &pair)) return 7;
             }
         }
     // shifts move an item over its grid: the number of rows is that of the bytes it touches
