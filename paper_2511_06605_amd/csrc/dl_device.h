@@ -33,7 +33,8 @@ constexpr int DL_UNROLL = 4;
 // Cache policy of the copy loop's loads and stores.
 //  STREAM_OUT  ordinary loads, non-temporal write-through stores: copies with several destinations whose output
 //           outgrows the on-die caches.  What is written does not push out the sources, which are read several times.
-//  STREAM   non-temporal hint on both: kept as a tunable.
+//  STREAM   non-temporal hint on both: lists of plain copies that are neither cut into rows nor off the grid, from 512 MiB
+//           moved (see plain_policy), and what the caller asks for.
 //  STREAM_IN  non-temporal loads, write-through stores: lists of plain copies too large for the on-die caches to
 //           hold both sides.  The loads pass the Infinity Cache by, so the sources do not push out what is being
 //           written, and whoever reads the result next finds the tail of it there.  All-to-all between eight ranks,

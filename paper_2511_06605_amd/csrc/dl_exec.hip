@@ -496,6 +496,7 @@ constexpr uint64_t TABLE_ENTRIES_TARGET = 8192;  // table kernels: aim for at mo
 constexpr uint64_t FAN_WAVE_MIN_BYTES = 3ull << 20;         // bytes moved above which a copy with several destinations takes one wavefront per row
 constexpr uint64_t UNIFORM_ROWS_MIN_BYTES = 4ull << 20;  // source bytes from which a uniform long list takes the row kernel
 constexpr uint64_t UNIFORM_ROWS_STAGE_BYTES = 768ull << 20;  // bytes moved (read + written) from which its table is staged even where it could be pushed
+constexpr uint64_t STREAM_BOTH_MIN_BYTES = 512ull << 20;  // bytes moved from which lists of plain copies outside the row path stream both sides
 constexpr uint64_t OFFSETS_MIN_BYTES = 64ull << 20;  // bytes moved per launch where a long uniform list takes several instead of a table
 constexpr uint64_t ARMED_ROWS_MAX_BYTES = 32ull << 20;  // bytes moved up to which an armed kernel that does not wait takes the row path for more than eight items
 constexpr size_t TABLE_STAGE_MIN = 512;          // tables at least this long are staged in device memory first
@@ -771,6 +772,33 @@ int stage_slot(size_t s, uint64_t bytes, hipStream_t stream)
     return launch_klist<dl_plain_item, NMAX_SMALL>(&stage, 1, &stage_tiles, ssh, stream, nullptr);
 }
 
+// The cache policy of a list of plain copies or swaps that choose_shape gave streaming loads, once it is known how it is
+// executed (rows: by the row path with the list in the kernel arguments).
+//  - Where a source and its destination differ modulo 16 (aligned: no item's do), the loads of neighbouring lanes and
+//    rows meet inside 16-byte words, and a streaming load leaves nothing of them in a cache: it pays only where the rows of
+//    an item are in flight together.  Lists of unequal copies, 181 / 755 MiB moved, one buffer set / three in turn,
+//    write-through stores alone against streaming loads: 24.8 / 34.3 and 135 / 134 us against 32.6 / 34.5 and
+//    143 / 143; 100 of them (a table), 201 MiB 27.4 / 45.4 against 39.1 / 47.0; 1000 equal ones of 60 KiB 20.1 / 27.3
+//    against 27.9 / 27.9; swaps, 224 and 896 MiB 30.1 / 40.1 and 153 / 155 against 37.2 / 43.6 and 160 / 161.
+//  - Else, lists that do not take the row path do best with the hint on both sides from 512 MiB moved: all-to-all of
+//    unequal chunks, 518 / 1036 MiB moved 88.3 / 174 us against 92.5 / 182; 8000 equal copies of 60 KiB 172 : 182, a
+//    table of 300 unequal ones, 584 MiB 124 : 128 (with one buffer set 123 : 119).
+template <class Item>
+int plain_policy(int policy, bool rows, bool aligned, uint64_t moved)
+{
+    if (policy != DL_POL_STREAM_IN) return policy;
+    if (!aligned) return rows && !std::is_same<Item, dl_swap_item>::value ? DL_POL_STREAM_IN : DL_POL_WT;
+    return !rows && moved >= STREAM_BOTH_MIN_BYTES ? DL_POL_STREAM : DL_POL_STREAM_IN;
+}
+
+template <class Item>
+bool all_aligned(const Item *items, size_t n)
+{
+    for (size_t i = 0; i < n; ++i)
+        if (((uint64_t)items[i].src ^ (uint64_t)items[i].dst) & 15u) return false;
+    return true;
+}
+
 // Equally long plain copies or swaps that do not fit a dl_klist but whose offsets do fit the kernel arguments (up to
 // 480): one launch and nothing else.  Returns false if the list does not qualify (and nothing was enqueued).
 template <class Item, int NMAX>
@@ -804,7 +832,7 @@ bool launch_offsets(const Item *items, size_t n, const dl_launch_shape &sh, hipS
     if (launches > 1 && 2u * items[0].bytes * per < OFFSETS_MIN_BYTES) return false;
     // the addresses relative to the lowest one of each side: 16-byte units if all of them agree modulo 16, else bytes
     const char *src = items[0].src, *src_hi = src, *dst = items[0].dst, *dst_hi = dst;
-    uint64_t apart = 0, any_src = 0, any_dst = 0;
+    uint64_t apart = 0, any_src = 0, any_dst = 0, across = 0;
     uint32_t worst = 0;  // how far behind its grid the worst first destination lies
     const uint64_t bytes = items[0].bytes;
     for (size_t i = 0; i < n; ++i) {
@@ -816,6 +844,7 @@ bool launch_offsets(const Item *items, size_t n, const dl_launch_shape &sh, hipS
         dst_hi = it.dst > dst_hi ? it.dst : dst_hi;
         any_src |= (uint64_t)it.src;
         any_dst |= (uint64_t)it.dst;
+        across |= (uint64_t)it.src ^ (uint64_t)it.dst;
         apart |= ((uint64_t)it.src ^ (uint64_t)items[0].src) | ((uint64_t)it.dst ^ (uint64_t)items[0].dst);
         const uint32_t shift = dl_item_shift(it);
         worst = shift > worst ? shift : worst;
@@ -831,12 +860,13 @@ bool launch_offsets(const Item *items, size_t n, const dl_launch_shape &sh, hipS
     head.dst = (char *)dst;
     head.bytes = bytes;
     head.wpg_log2 = log2u(threads / 64u);
+    const int policy = plain_policy<Item>(sh.policy, true, (across & 15u) == 0, 2u * bytes * n);
     *rc = DL_OK;
     for (size_t i = 0; i < n && *rc == DL_OK; i += per) {
         const size_t m = n - i < per ? n - i : per;
         *rc = m <= (size_t)SMALL
-                  ? launch_offsets_sized<Item, SMALL>(items + i, m, head, (uint32_t)width, threads, sh.policy, on_grid, stream)
-                  : launch_offsets_sized<Item, BIG>(items + i, m, head, (uint32_t)width, threads, sh.policy, on_grid, stream);
+                  ? launch_offsets_sized<Item, SMALL>(items + i, m, head, (uint32_t)width, threads, policy, on_grid, stream)
+                  : launch_offsets_sized<Item, BIG>(items + i, m, head, (uint32_t)width, threads, policy, on_grid, stream);
     }
     return true;
 }
@@ -857,19 +887,20 @@ bool launch_uniform_rows(const Item *items, size_t n, const dl_launch_shape &sh,
     // of which the ones without a destination are dead weight at the rate wavefronts can be started.
     const bool fused = std::is_same<Item, dl_fused_item>::value;
     const uint32_t split = c.fan_split ? sh.split : fused ? DL_TABLE_ROWS_SPLIT : 1u;
-    // Plain items: one wavefront per workgroup as in shorter lists, but not where every workgroup first fetches its entry
-    // of a pushed table (512 blocks of 512 KiB: 97.6 us with four wavefronts, 101 with one; of 1 MiB, staged: 195 and 176).
-    const bool staged = items[0].bytes * n * 2u >= UNIFORM_ROWS_STAGE_BYTES;
-    const uint32_t threads = c.block_threads ? c.block_threads : fused && !c.fan_split ? DL_TABLE_ROWS_THREADS : staged && !fused ? 64u : 256u;
-    if (threads > 512u || threads % (64u * split) || ((threads / 64u / split) & (threads / 64u / split - 1u)))
-        return false;  // whole sub-groups of a power-of-two number of wavefronts
     if (n * sizeof(Item) > RING_SLOT_BYTES) return false;
     const uint64_t bytes = items[0].bytes;
-    uint32_t kmax = 1;
+    uint32_t kmax = 1, worst = 0;  // how far behind its grid the worst first destination lies
+    uint64_t any_src = 0, across = 0;
     for (size_t i = 0; i < n; ++i) {
         if (items[i].bytes != bytes) return false;
         if (item_k(items[i]) > kmax) kmax = item_k(items[i]);
+        const uint32_t shift = dl_item_shift(items[i]);
+        worst = shift > worst ? shift : worst;
+        any_src |= (uint64_t)items[i].src;
+        if constexpr (!std::is_same<Item, dl_fused_item>::value) across |= (uint64_t)items[i].src ^ (uint64_t)items[i].dst;
     }
+    const bool on_grid = worst == 0 && (any_src & 3u) == 0 && (bytes & 15u) == 0;  // (item_on_grid for all)
+    const bool aligned = (across & 15u) == 0;
     // a table that needs staging must move enough bytes to pay for it; one written through the BAR needs none.
     // But every workgroup that reads a pushed table looks for the stamp and fetches its entry past the caches, two
     // round trips that cost a large request 12 % of its kernel time, against 4 us for the staging kernel and the
@@ -877,14 +908,17 @@ bool launch_uniform_rows(const Item *items, size_t n, const dl_launch_shape &sh,
     const bool pushable = g_ring.push && c.table_push && n * sizeof(Item) <= PUSH_PAYLOAD_BYTES &&
                           bytes * n * (1u + kmax) < UNIFORM_ROWS_STAGE_BYTES;
     if (!pushable && bytes * n < UNIFORM_ROWS_MIN_BYTES) return false;
+    // Plain items: one wavefront per workgroup as in shorter lists of that size, but not where every workgroup first
+    // fetches its entry of a pushed table, unless the loads are unaligned.  Four wavefronts against one, three buffer
+    // sets in turn: staged, 3000 / 8000 / 20 000 copies of 60 KiB 72.5 / 176 / 436 us against 72.1 / 173 / 427,
+    // unaligned 77.1 / 194 and 72.6 / 184; pushed, 1000 copies 22.2 against 23.3, unaligned 30.6 against 27.3.
+    const bool waves = !fused && (!pushable || !aligned) && dl_plain_threads(2u * bytes * n, false) == 64u;
+    const uint32_t threads = c.block_threads ? c.block_threads : fused && !c.fan_split ? DL_TABLE_ROWS_THREADS : waves ? 64u : 256u;
+    if (threads > 512u || threads % (64u * split) || ((threads / 64u / split) & (threads / 64u / split - 1u)))
+        return false;  // whole sub-groups of a power-of-two number of wavefronts
+    const int policy = fused ? sh.policy : plain_policy<Item>(sh.policy, false, aligned, 2u * bytes * n);
     const uint32_t tile = 16u * threads / split;  // one 1 KiB row per wavefront of a sub-group
-    uint64_t tpi = 0;  // of the item that lies worst on its grid; the others leave a workgroup without work
-    bool on_grid = true;
-    for (size_t i = 0; i < n; ++i) {
-        const uint64_t t = dl_item_tiles(items[i], tile);
-        if (t > tpi) tpi = t;
-        on_grid = on_grid && item_on_grid(items[i]);
-    }
+    const uint64_t tpi = (bytes + worst + tile - 1u) / tile;  // of the item that lies worst on its grid; the others leave a workgroup without work
     if (tpi * n >= (1ull << 30) || tpi >= (1ull << 31) || n > DL_UROWS_MAX_ITEMS) return false;
 
     char *pushed = pushable ? push_acquire(n * sizeof(Item), stream, rc) : nullptr;
@@ -918,7 +952,7 @@ bool launch_uniform_rows(const Item *items, size_t n, const dl_launch_shape &sh,
         dslot = (const Item *)(g_ring.dev + s * RING_SLOT_BYTES);
     }
     const dl_pushed ps = dl_push_kernel_args(stamp);
-    dl_with_policy_and_grid(sh.policy, on_grid, [&](auto pol, auto og) {
+    dl_with_policy_and_grid(policy, on_grid, [&](auto pol, auto og) {
         if (pushed)
             hipLaunchKernelGGL((dl_exec_urows_kernel<Item, decltype(pol)::value, true, decltype(og)::value>),
                                dim3((uint32_t)tpi, (uint32_t)n), dim3(threads), 0, stream, dslot,
@@ -951,6 +985,13 @@ int launch_table(const Item *items, size_t n, dl_launch_shape sh, hipStream_t st
     if (!arm) {
         int rc = DL_OK;
         if (launch_uniform_rows(items, n, sh, stream, &rc)) return rc;
+    }
+    if constexpr (!std::is_same<Item, dl_fused_item>::value) {
+        if (sh.policy == DL_POL_STREAM_IN) {
+            uint64_t moved = 0;
+            for (size_t i = 0; i < n; ++i) moved += 2u * items[i].bytes;
+            sh.policy = plain_policy<Item>(sh.policy, false, all_aligned(items, n), moved);
+        }
     }
     const size_t cap = RING_SLOT_BYTES / sizeof(Item);
     auto entries = [&](uint32_t tile) {  // one per tile of the first destination's grid, like everywhere
@@ -1158,15 +1199,18 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
                 if (moved >= DL_FAN_STREAM_IN_MIN_BYTES) sh.policy = DL_POL_STREAM_IN;
             }
         }
-        for (;;) {
-            uint64_t acc = 0;
-            for (size_t i = 0; i < n; ++i) {
-                acc += dl_item_tiles(items[i], sh.tile_bytes);
-                tile_end[i] = acc;
+        const auto count_tiles = [&] {
+            for (;;) {
+                uint64_t acc = 0;
+                for (size_t i = 0; i < n; ++i) {
+                    acc += dl_item_tiles(items[i], sh.tile_bytes);
+                    tile_end[i] = acc;
+                }
+                if (acc < (1ull << 30)) break;
+                sh.tile_bytes *= 2;  // keep the grid inside the launch limit
             }
-            if (acc < (1ull << 30)) break;
-            sh.tile_bytes *= 2;  // keep the grid inside the launch limit
-        }
+        };
+        count_tiles();
         // row path: a short list (found by a few scalar compares; bisecting a long one per wavefront
         // measured slower than the general path) and a tile that is exactly one 1 KiB row per
         // wavefront of a sub-group
@@ -1188,6 +1232,17 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
             if (widest * n <= tile_end[n - 1] + tile_end[n - 1] / 4 && widest < (1ull << 31)) {
                 sh.rows = true;
                 sh.rows2d_width = (uint32_t)widest;
+            }
+        }
+        if constexpr (!std::is_same<Item, dl_fused_item>::value) {
+            if (!arm && sh.policy == DL_POL_STREAM_IN) {
+                sh.policy = plain_policy<Item>(sh.policy, sh.rows, all_aligned(items, n), 2u * total);
+                if (sh.policy == DL_POL_STREAM && sh.block_threads == 64u && sh.tile_bytes == 1024u) {
+                    // (four wavefronts: 88.3 / 174 us at 518 / 1036 MiB moved, one 90.3 / 178)
+                    sh.block_threads = 256u;
+                    sh.tile_bytes = 4096u;
+                    count_tiles();
+                }
             }
         }
         *launched = true;

@@ -26,7 +26,7 @@ def library():
 
 # 48 MiB and 96 MiB: 64 chunks of 384 and 768 KiB read and written, 28 swaps of 877.7 and 1755.4 KiB
 @pytest.mark.parametrize("op,c", [("alltoall", c) for c in (384 * KiB - 16, 384 * KiB, 384 * KiB + 17, 768 * KiB - 1, 768 * KiB)] +
-                         [("inplace", c) for c in (877 * KiB, 878 * KiB + 5, 1755 * KiB + 16, 1756 * KiB)])
+                         [("inplace", c) for c in (877 * KiB, 878 * KiB + 5, 1755 * KiB + 16, 1756 * KiB, 1757 * KiB + 5)])
 def test_plain_lists_around_their_size_rules(ref, op, c):
     W = 8
     C = inputs.uniform_chunks(W, c)
@@ -42,6 +42,26 @@ def test_plain_lists_around_their_size_rules(ref, op, c):
     sync()
     for got, w in zip(d_out, want):
         assert np.array_equal(got.host(), w) and got.guards_intact()
+
+
+# unequal copies, in the kernel arguments and from a table: streaming loads from 96 MiB, both sides from 512 MiB, neither
+# where addresses and lengths are off the grid
+@pytest.mark.parametrize("align", [128, 1])
+@pytest.mark.parametrize("n,total", [(20, 50 * MiB), (20, 270 * MiB), (100, 50 * MiB), (100, 270 * MiB)])
+def test_unequal_copies_around_their_size_rules(ref, n, total, align):
+    rng = np.random.default_rng(n + total)
+    size = rng.integers(total // n // 8, 2 * total // n, n) // 16 * 16 + (0 if align == 128 else rng.integers(0, 16, n))
+    at = np.cumsum((np.concatenate([[0], size, size]) + 255) // 128 * 128)
+    src, dst = at[:n], at[n:2 * n]
+    if align == 1:
+        src, dst = src + rng.integers(0, 64, n), dst + rng.integers(0, 64, n)
+    arena = rng.integers(0, 256, int(at[-1]) + 256, dtype=np.uint8)
+    d = DevBuf(arena.size, fill=arena)
+    descs = [(int(s), int(t), int(m)) for s, t, m in zip(src, dst, size)]
+    want = ref.batch_copy([arena], [(0, s, 0, t, m) for s, t, m in descs])[0]
+    dl.dl_batch_copy([(d.ptr(s), d.ptr(t), m) for s, t, m in descs], stream())
+    sync()
+    assert np.array_equal(d.host(), want) and d.guards_intact()
 
 
 def _fanout(sizes, shifts, seed):
