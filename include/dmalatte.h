@@ -436,8 +436,8 @@ typedef struct dl_config {
     uint32_t infer_broadcast;    /* 1: dl_batch_copy merges copies that share source and size into read-once/write-k copies; default 1 */
     uint32_t device_lowering;    /* 1: dl_token_dispatch (W = 8, one-shot mode, validation off; DL_MODE_AUTO: 512 tokens or more) sends only the mask to the device, which places the rows itself; default 1 */
     uint32_t table_push;         /* 1: the table of a long list (more copies than fit the kernel arguments) is written by the host straight into device memory, through the BAR, when the device exposes one that covers its memory and the table is short enough; 0: always through pinned host memory; default 1 */
-    uint64_t write_through_max_bytes; /* requests moving at most this many bytes (read + written) use write-through stores, larger ones streaming stores; default 144 MiB */
-    uint64_t stream_plain_min_bytes;  /* lists of plain 1:1 copies and swaps (all-to-all, batches) moving at least this many bytes (a swap's two ranges counted once each) use streaming loads, so that what is read does not push what is written out of the on-die caches; default 96 MiB; UINT64_MAX = never */
+    uint64_t write_through_max_bytes; /* requests moving at most this many bytes (read + written) use write-through stores; above, copies with several destinations use streaming stores, and lists of plain copies ordinary ones up to stream_plain_min_bytes; default 144 MiB */
+    uint64_t stream_plain_min_bytes;  /* lists of plain 1:1 copies and swaps (all-to-all, batches) moving at least this many bytes (a swap's two ranges counted once each) use streaming loads and write-through stores, so that what is read does not push what is written out of the on-die caches, where that pays: not for most lists whose sources and destinations differ modulo 16, nor on a grid capped below 1024 workgroups; from 512 MiB some stream both sides; default 96 MiB; UINT64_MAX = never */
     uint64_t armed_chain_min_bytes;   /* prelaunch mode: a request moving more than this many bytes waits in a one-workgroup gate kernel and copies with a full-grid kernel enqueued behind it, instead of waiting and copying with one capped grid; ignored when armed_blocks is set; default 256 MiB */
 } dl_config;
 

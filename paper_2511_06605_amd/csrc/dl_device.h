@@ -35,6 +35,8 @@ constexpr int DL_UNROLL = 4;
 //           outgrows the on-die caches.  What is written does not push out the sources, which are read several times.
 //  STREAM   non-temporal hint on both: lists of plain copies that are neither cut into rows nor off the grid, from 512 MiB
 //           moved (see plain_policy), and what the caller asks for.
+//  PLAIN    ordinary loads and stores (write-back L2): lists of plain copies between the lines of the other
+//           policies, where the caller has moved those apart.
 //  STREAM_IN  non-temporal loads, write-through stores: lists of plain copies too large for the on-die caches to
 //           hold both sides.  The loads pass the Infinity Cache by, so the sources do not push out what is being
 //           written, and whoever reads the result next finds the tail of it there.  All-to-all between eight ranks,
@@ -51,7 +53,7 @@ constexpr int DL_UNROLL = 4;
 //           write-back before the completion word.  A wavefront that used this policy
 //           must execute dl_drain_stores() before it signals anything: the compiler
 //           does not count the stores issued from inline assembly.
-enum : int { DL_POL_STREAM_OUT = 0, DL_POL_STREAM = 1, DL_POL_WT = 2, DL_POL_COHERENT = 3, DL_POL_STREAM_IN = 4 };
+enum : int { DL_POL_STREAM_OUT = 0, DL_POL_STREAM = 1, DL_POL_WT = 2, DL_POL_COHERENT = 3, DL_POL_STREAM_IN = 4, DL_POL_PLAIN = 5 };
 
 template <int POL, typename V>
 __device__ __forceinline__ V dl_ld(const DL_GLOBAL V *p)
@@ -844,6 +846,7 @@ inline void dl_with_policy(int policy, F f)
     case DL_POL_STREAM: f(std::integral_constant<int, DL_POL_STREAM>{}); break;
     case DL_POL_WT: f(std::integral_constant<int, DL_POL_WT>{}); break;
     case DL_POL_STREAM_IN: f(std::integral_constant<int, DL_POL_STREAM_IN>{}); break;
+    case DL_POL_PLAIN: f(std::integral_constant<int, DL_POL_PLAIN>{}); break;
     default: f(std::integral_constant<int, DL_POL_STREAM_OUT>{}); break;
     }
 }

@@ -1235,6 +1235,12 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
             }
         }
         if constexpr (!std::is_same<Item, dl_fused_item>::value) {
+            // Few workgroups have few loads in flight, and a streaming load takes longer to come back: all-to-all between eight
+            // ranks, 2 MiB chunks, 128 / 512 workgroups, one buffer set / three in turn 171 / 240 and 57 / 77 us, with
+            // streaming loads 259 / 260 and 79 / 80; with 2048 they are ahead again (50 : 44 with three).
+            if (!arm && sh.policy == DL_POL_STREAM_IN && sh.max_blocks && sh.max_blocks < 1024u && tile_end[n - 1] > sh.max_blocks &&
+                2u * total < STREAM_BOTH_MIN_BYTES)
+                sh.policy = 2u * total <= g_dl.cfg.write_through_max_bytes ? DL_POL_WT : DL_POL_PLAIN;
             if (!arm && sh.policy == DL_POL_STREAM_IN) {
                 sh.policy = plain_policy<Item>(sh.policy, sh.rows, all_aligned(items, n), 2u * total);
                 if (sh.policy == DL_POL_STREAM && sh.block_threads == 64u && sh.tile_bytes == 1024u) {
@@ -1309,7 +1315,7 @@ dl_launch_shape dl_choose_shape(uint64_t src_bytes, uint64_t max_item_bytes, uin
     const bool plain_stream = max_k == 1 && moved >= c.stream_plain_min_bytes;
     sh.policy = moved >= c.nontemporal_min_bytes ? DL_POL_STREAM
                 : plain_stream                   ? DL_POL_STREAM_IN
-                : moved <= c.write_through_max_bytes ? DL_POL_WT : DL_POL_STREAM_OUT;
+                : moved <= c.write_through_max_bytes ? DL_POL_WT : max_k == 1 ? DL_POL_PLAIN : DL_POL_STREAM_OUT;
     return sh;
 }
 

@@ -180,6 +180,16 @@ def test_capped_grid_workgroups_stride_over_tiles(ref, cfg, cap):
     run_batch(ref, 5, 200000, 8 * MiB, seed=cap + 3, align=16)
 
 
+@pytest.mark.parametrize("wt_max", [0, 1 << 62])
+def test_capped_grid_with_the_policies_of_large_lists(ref, cfg, wt_max):
+    """The size from which plain lists get streaming loads set to one byte: a capped grid keeps write-through or
+    ordinary stores."""
+    cfg(max_blocks=33, stream_plain_min_bytes=1, write_through_max_bytes=wt_max)
+    run_alltoall(ref, inputs.uniform_chunks(8, 40000), seed=38, kind="u8")
+    run_alltoall(ref, inputs.random_chunks(7, 100000, seed=39, zero_frac=0.1), seed=40)
+    run_batch(ref, 60, 30001, 32 * MiB, seed=41, align=1)
+
+
 def test_allgather_nontemporal_path(ref, cfg):
     cfg(nontemporal_min_bytes=0)
     run_allgather(ref, 8, 300001, seed=8)
