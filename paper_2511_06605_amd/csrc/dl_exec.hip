@@ -1398,11 +1398,12 @@ int dl_standby_launch(void *rec_mem, const dl_arm *a, hipStream_t stream)
     return DL_OK;
 }
 
-int dl_launch_plain_table(const dl_plain_item *dev_items, uint32_t m, uint32_t entry_bytes, uint64_t moved, hipStream_t stream)
+int dl_launch_plain_table(const dl_plain_item *dev_items, uint32_t m, uint32_t entry_bytes, uint64_t moved, bool aligned,
+                          hipStream_t stream)
 {
     if (m == 0) return DL_OK;
-    const dl_launch_shape sh = dl_choose_shape(moved / 2, entry_bytes, 1);  // for the cache policy
-    dl_with_policy(sh.policy, [&](auto pol) {
+    const int policy = plain_policy<dl_plain_item>(dl_choose_shape(moved / 2, entry_bytes, 1).policy, false, aligned, moved);
+    dl_with_policy(policy, [&](auto pol) {
         hipLaunchKernelGGL((dl_exec_table_kernel<dl_plain_item, decltype(pol)::value, false>), dim3(m), dim3(256), 0,
                            stream, dev_items, m, 1u, dl_push_kernel_args(0));
     });

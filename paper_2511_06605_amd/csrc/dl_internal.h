@@ -149,8 +149,10 @@ void dl_ring_forget_armed();
 void dl_ring_own_stream(hipStream_t stream);
 
 // dl_exec.hip: the table kernel over m plain copies of at most entry_bytes (< 2^32) each that are already in device
-// memory (entry b is workgroup b's), with the cache policy that suits `moved` bytes read + written.
-int dl_launch_plain_table(const dl_plain_item *dev_items, uint32_t m, uint32_t entry_bytes, uint64_t moved, hipStream_t stream);
+// memory (entry b is workgroup b's), with the cache policy that suits `moved` bytes read + written.  aligned: every
+// copy's source and destination agree modulo 16.
+int dl_launch_plain_table(const dl_plain_item *dev_items, uint32_t m, uint32_t entry_bytes, uint64_t moved, bool aligned,
+                          hipStream_t stream);
 
 // dl_static.hip: the address of this device's copy of the static table (dl_batch_copy_static).
 int dl_static_init(int device);

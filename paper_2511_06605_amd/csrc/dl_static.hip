@@ -56,11 +56,12 @@ extern "C" int dl_batch_copy_static(const dl_copy_desc *desc, size_t n, void *st
     hipStream_t hs = (hipStream_t)stream;
 
     // pass 1: what there is to move, and the tile that cuts it into few enough entries
-    uint64_t total = 0, biggest = 0;
+    uint64_t total = 0, biggest = 0, across = 0;
     for (size_t i = 0; i < n; ++i) {
         if (desc[i].bytes == 0 || desc[i].src == desc[i].dst) continue;
         if (!desc[i].src || !desc[i].dst) return DL_ERR_INVALID;
         total += desc[i].bytes;
+        across |= (uint64_t)desc[i].src ^ (uint64_t)desc[i].dst;
         if (desc[i].bytes > biggest) biggest = desc[i].bytes;
     }
     if (total == 0) return DL_OK;
@@ -109,5 +110,5 @@ extern "C" int dl_batch_copy_static(const dl_copy_desc *desc, size_t n, void *st
     }
     const int rc = flush();
     if (rc != DL_OK) return rc;
-    return dl_launch_plain_table(table, m, (uint32_t)tile, 2 * total, hs);
+    return dl_launch_plain_table(table, m, (uint32_t)tile, 2 * total, (across & 15u) == 0, hs);
 }
