@@ -33,8 +33,8 @@ constexpr int DL_UNROLL = 4;
 // Cache policy of the copy loop's loads and stores.
 //  STREAM_OUT  ordinary loads, non-temporal write-through stores: copies with several destinations whose output
 //           outgrows the on-die caches.  What is written does not push out the sources, which are read several times.
-//  STREAM   non-temporal hint on both: lists of plain copies that are neither cut into rows nor off the grid, from 512 MiB
-//           moved (see plain_policy), and what the caller asks for.
+//  STREAM   non-temporal hint on both: from 512 MiB moved, lists of plain copies outside the row path whose sources and
+//           destinations agree modulo 16 (see plain_policy); and what the caller asks for.
 //  PLAIN    ordinary loads and stores (write-back L2): lists of plain copies between the lines of the other
 //           policies, where the caller has moved those apart.
 //  STREAM_IN  non-temporal loads, write-through stores: lists of plain copies too large for the on-die caches to

@@ -1,10 +1,11 @@
 // Token dispatch placed on the device (Sec. IV-B: a token that goes to several experts is one source with several
 // destinations).  Receive buffers are packed in token order, so where a token's row lands is a count: of the tokens
-// before it that go to the same rank.  No copy list exists anywhere; every workgroup works out the places of its own
-// tokens and copies their rows, in one launch:
+// before it that go to the same rank.  No copy list exists; every workgroup works out the places of its own tokens and
+// copies their rows, in one launch:
 //   - the mask on the host: the host packs it to a byte per token and counts the rows taken before every group of 64
 //     tokens (control work, Sec. III-B2, done where the mask is); both travel in the kernel arguments (up to 2048
-//     tokens), or through the BAR, or, where that way is not open, in the arguments of several launches;
+//     tokens), or through the BAR, or, where that way is not open, in the arguments of several launches.  (Fewer than 256
+//     tokens off the grid are lowered to a list on the host after all, see OFF_GRID_MIN_TOKENS);
 //   - the mask in device memory: every workgroup counts the tokens in front of its own group itself (at most 80 KiB
 //     of mask, which the L2 holds); or, for a large request, a first kernel packs the groups (see PACK_FIRST_BYTES).
 // Inside a group of 64 the places come from one ballot per rank.
@@ -495,7 +496,9 @@ int dl_dispatch_on_device(const void *const *in, void *const *out, int W, const 
         total += tokens[i];
         if ((tokens[i] && !in[i]) || !out[i]) return DL_OK;  // the host lowering reports what is wrong
     }
-    if (total == 0 || total < min_tokens || total >= (1ull << 21)) return DL_OK;  // (a grid has at most 65535 rows of workgroups)
+    // (a grid has at most 2048 tokens from the kernel arguments or 43 648 through the BAR; from 2^21 on, which would be a
+    // thousand launches, a request goes the way of any long list)
+    if (total == 0 || total < min_tokens || total >= (1ull << 21)) return DL_OK;
 
     dispatch_list p;
     dispatch_shape sh;

@@ -1193,9 +1193,14 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
                 sh.split = 1;
                 sh.block_threads = on_grid ? 64u : 512u;
                 sh.tile_bytes = 16u * sh.block_threads;
-                // With one load per row the loads can be streaming ones (see DL_POL_STREAM_IN), from the size at which
-                // output and sources no longer share the caches: 72 MiB moved 10.70 us either way, 84 MiB 14.7 -> 15.1,
-                // 90 MiB (3 MiB per rank over five) 18.3 -> 15.6, 108 MiB 21.3 -> 19.0.
+                // With one load per row the loads can be streaming ones (see DL_POL_STREAM_IN).  What they give depends on
+                // what the calls before left in the Infinity Cache, which a request does not tell: buffers that all fit it, or
+                // far exceed it, see no difference; a few sets that together are about its size do.  Over eight / five / two ranks,
+                // write-through stores alone : streaming loads as well, 96 MiB moved, one buffer set 11.9 : 12.0, 11.3 :
+                // 11.3, 11.9 : 15.2 us, two in turn 12.0 : 12.4, 12.5 : 17.2, 12.9 : 13.8, three 16.0 : 16.2, 16.7 : 15.2,
+                // 15.5 : 14.0, eight 19.9 : 20.0, 19.2 : 19.2, 18.3 : 17.5; 128 MiB, two 15.5 : 15.6, 21.3 : 20.3, 19.4 : 17.4,
+                // three 25.7 : 24.6, 25.0 : 23.6, 23.6 : 18.8.  The line is where three sets in turn begin to gain (88 MiB
+                // over five ranks 16.1 : 14.9, 80 MiB 13.6 : 13.8 and over eight 10.5 : 13.1).
                 if (moved >= DL_FAN_STREAM_IN_MIN_BYTES) sh.policy = DL_POL_STREAM_IN;
             }
         }
@@ -1304,14 +1309,19 @@ dl_launch_shape dl_choose_shape(uint64_t src_bytes, uint64_t max_item_bytes, uin
     sh.block_threads = bt;
     sh.split = split;
     sh.max_blocks = c.max_blocks;
-    // Above write_through_max_bytes copies with several destinations stream their output (see DL_POL_STREAM_OUT).
-    // All-gather over eight ranks, call alone / call and a kernel that reads all of the output, write-through against
-    // streamed: 1 MiB per rank (72 MiB moved) 11.2 / 32.2 against 13.9 / 40.2 us, 2 MiB 31.1 / 67.6 against 27.1 /
-    // 74.3, 2.5 MiB 36.0 / 87.2 against 30.9 / 85.7, 4 MiB 53.3 / 126 against 46.7 / 131, 8 MiB 102 / 259 against 82 / 240.
+    // Above write_through_max_bytes copies with several destinations stream their output (see DL_POL_STREAM_OUT) and are
+    // written in pairs.  All-gather over eight ranks, three buffer sets in turn, call alone / call and a kernel that reads all of the
+    // output: ordinary stores by four wavefronts per row 2.5 MiB per rank 35.3 / 147 us, 3 MiB 41.1 / 157, 4 MiB 53.4 /
+    // 180, 6 MiB 76.7 / 238, 8 MiB 102 / 289; write-through by one 34.9 / 144, 41.1 / 154, 55.2 / 177, 82.4 / 234, 111 /
+    // 288; streamed in pairs 26.0 / 150, 30.8 / 160, 43.3 / 184, 62.4 / 224, 80.9 / 264.  So up to some 300 MiB moved the
+    // reader pays 2 % of its own time for the quarter that the call gains, and with one buffer set that fits the Infinity Cache
+    // the call itself loses (2.5 MiB: 23.7, 20.5 and 27.4 us); above, both gain.
     // Streaming hints on both sides where the caller asks for them.  Streaming loads with write-through stores for
-    // lists of plain copies from 96 MiB moved (a third of the Infinity Cache read, see DL_POL_STREAM_IN): with
-    // 64 MiB moved the call and a kernel that reads its output take 27.2 us against 26.3 without, with 128 MiB 40.7
-    // against 42.3.  Copies with several destinations load a row from several wavefronts and lose 10 % with them.
+    // lists of plain copies from 96 MiB moved, that is 48 MiB read (see DL_POL_STREAM_IN).  All-to-all between eight ranks,
+    // write-through stores alone : streaming loads as well, one buffer set / three / eight in turn: 80 MiB 10.8 : 11.3,
+    // 12.9 : 12.1, 15.5 : 14.8 us, 96 MiB 12.7 : 13.1, 16.0 : 14.3, 18.1 : 17.4, 128 MiB 16.8 : 17.5, 23.2 : 18.3, 23.3 :
+    // 22.4, 192 MiB 24.1 : 25.6, 33.5 : 30.0, 33.4 : 31.8; 64 MiB 8.8 : 10.0, 9.1 : 10.1, 12.7 : 10.6.  Lists that this does
+    // not hold for: see plain_policy.
     const bool plain_stream = max_k == 1 && moved >= c.stream_plain_min_bytes;
     sh.policy = moved >= c.nontemporal_min_bytes ? DL_POL_STREAM
                 : plain_stream                   ? DL_POL_STREAM_IN
