@@ -16,6 +16,7 @@ from gpu_util import DevBuf, stream, sync
 pytestmark = pytest.mark.gpu
 
 VALIDATE_ALL = os.environ.get("DL_TEST_VALIDATE") == "1"
+FORCED = bool(os.environ.get("DL_TEST_CONFIG")) or VALIDATE_ALL   # settings that send requests other ways
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -796,7 +797,7 @@ def test_a_table_that_never_completes_is_reported_and_nothing_is_copied(ref, kin
     """The kernel of a long list is told (by the test hook) a stamp that its table's slot will never hold, and
     three looks: every workgroup gives up its bounded wait and leaves.  The call has returned DL_OK long before;
     the loss shows in dl_last_device_error(), every operation refuses until it has been read, no destination
-    byte has changed, and the same request issued again gives the checker's result."""
+    byte has changed, and the same request issued again gives the oracle's result."""
     assert dl.dl_last_device_error() == dl.DL_OK
     W = 8
     if kind == "token_dispatch":
@@ -828,8 +829,8 @@ def test_a_table_that_never_completes_is_reported_and_nothing_is_copied(ref, kin
     finally:
         dl.dl_debug_lose_next_table(0)    # taken back if no table took it
     sync()
-    if os.environ.get("DL_TEST_CONFIG") and not lib_error_pending():
-        pytest.skip("with these forced tunables the request's table does not go through the BAR")
+    if FORCED and not lib_error_pending():
+        pytest.skip("with these forced settings the request's table does not go through the BAR")
     with pytest.raises(dl.DlError) as refused:
         issue()
     assert refused.value.status == dl.DL_ERR_LOST
@@ -865,13 +866,17 @@ def test_requests_without_a_table_do_not_heed_the_lost_table_hook(ref):
     _lose_next_table()
     try:
         dl.dl_token_dispatch([b.ptr() for b in d_in], [b.ptr() for b in outs], counts, row, dest, stream())
-        copy(d, descs)
-        sync()
-        if os.environ.get("DL_TEST_CONFIG") and lib_error_pending():
-            pytest.skip("with these forced tunables one of the requests has a table")
+        for request in (None, descs):
+            if request is not None:
+                copy(d, request)
+            sync()
+            if FORCED and lib_error_pending():
+                pytest.skip("with these forced settings one of the requests has a table")
         assert dl.dl_last_device_error() == dl.DL_OK
         copy(d2, descs2)
         sync()
+        if FORCED and not lib_error_pending():
+            pytest.skip("with these forced settings the list's table does not go through the BAR")
     finally:
         dl.dl_debug_lose_next_table(0)
         lost = dl.dl_last_device_error()
