@@ -18,6 +18,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <type_traits>
 #include <vector>
 
@@ -497,6 +498,8 @@ constexpr uint64_t FAN_WAVE_MIN_BYTES = 3ull << 20;         // bytes moved above
 constexpr uint64_t UNIFORM_ROWS_MIN_BYTES = 4ull << 20;  // source bytes from which a uniform long list takes the row kernel
 constexpr uint64_t UNIFORM_ROWS_STAGE_BYTES = 768ull << 20;  // bytes moved (read + written) from which its table is staged even where it could be pushed
 constexpr uint64_t STREAM_BOTH_MIN_BYTES = 512ull << 20;  // bytes moved from which lists of plain copies outside the row path stream both sides
+constexpr uint64_t OFF_GRID_MIN_BYTES = 24ull << 20;  // bytes moved from which plain copies off the grid take workgroups of eight rows
+constexpr uint64_t RAGGED_GRID = 768;  // workgroups of a two-dimensional grid that may be mostly idle
 constexpr uint64_t OFFSETS_MIN_BYTES = 64ull << 20;  // bytes moved per launch where a long uniform list takes several instead of a table
 constexpr uint64_t ARMED_ROWS_MAX_BYTES = 32ull << 20;  // bytes moved up to which an armed kernel that does not wait takes the row path for more than eight items
 constexpr size_t TABLE_STAGE_MIN = 512;          // tables at least this long are staged in device memory first
@@ -537,6 +540,14 @@ template <class Item>
 inline bool item_on_grid(const Item &it)
 {
     return dl_item_shift(it) == 0 && (it.bytes & 15u) == 0 && ((uint64_t)it.src & 3u) == 0;
+}
+
+template <class Item>
+bool all_on_grid(const Item *items, size_t n)
+{
+    for (size_t i = 0; i < n; ++i)
+        if (!item_on_grid(items[i])) return false;
+    return true;
 }
 
 inline uint32_t log2u(uint32_t v)
@@ -610,8 +621,7 @@ int launch_klist(const Item *items, size_t n, const uint64_t *tile_end, const dl
         p.item[i] = items[i];
     }
     for (size_t i = n; i < (size_t)NMAX; ++i) p.tile_end[i] = 0xFFFFFFFFu;  // the device compares without looking at n
-    bool on_grid = true;
-    for (size_t i = 0; i < n; ++i) on_grid = on_grid && item_on_grid(items[i]);
+    const bool on_grid = all_on_grid(items, n);
     if constexpr (std::is_same<Item, dl_fused_item>::value) {
         if (sh.pairs) {  // (tile_end counts workgroups: one per row and pair of destinations)
             const uint32_t blocks = (uint32_t)tile_end[n - 1];
@@ -1134,6 +1144,8 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
     }
     if (total == 0) return DL_OK;
     dl_launch_shape sh = dl_choose_shape(total, biggest, kmax);
+    // one-shot requests, where the caller has not fixed the shape
+    const bool free_shape = !arm && !g_dl.cfg.tile_bytes && !g_dl.cfg.block_threads && !g_dl.cfg.fan_split && !sh.max_blocks;
     if (arm && !arm->nowait && g_dl.cfg.armed_blocks == 0) {
         // prelaunch mode, and the caller has not fixed the waiting grid: large requests wait in a gate kernel
         uint64_t moved = 0;
@@ -1163,13 +1175,22 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
         }
     }
 
+    if constexpr (std::is_same<Item, dl_plain_item>::value) {
+        // Copies off the grid, below the sizes that stream: eight rows to a workgroup, whose unaligned loads and partly
+        // written lines then meet in one compute unit.  All-to-all, one buffer set / three / sets that fit no cache, 64 or
+        // 256 threads against 512: 5 ranks of 500 003 bytes (25 MB moved) 4.12 / 5.22 / 5.65 : 4.05 / 5.17 / 5.55 us,
+        // 12 of 140 001 6.31 / 7.82 / 10.3 : 5.47 / 7.70 / 10.2, 8 of 420 001 8.43 / 9.91 / 11.8 : 6.49 / 9.23 / 12.5, 15 of
+        // 164 228 12.3 / 13.5 / 15.7 : 11.1 / 12.1 / 16.0; smaller ones +-5 % by how their last tile falls; larger ones one row
+        // each, as any list (8 ranks of 2 MiB and 3 bytes, three sets 44.4 : 45.1).
+        if (free_shape && sh.policy == DL_POL_WT && 2u * total >= OFF_GRID_MIN_BYTES && biggest >= 8192u && !all_on_grid(items, n)) {
+            sh.block_threads = 512u;
+            sh.tile_bytes = 8192u;
+        }
+    }
     constexpr int NBIG = list_cap<Item>::big;
     if (n <= (size_t)NBIG) {
         uint64_t tile_end[NBIG];
         if constexpr (std::is_same<Item, dl_fused_item>::value) {
-            // one-shot requests, where the caller has not fixed the shape
-            const dl_config &c = g_dl.cfg;
-            const bool free_shape = !arm && !c.tile_bytes && !c.block_threads && !c.fan_split && !sh.max_blocks;
             const uint64_t moved = total * (1ull + kmax);
             if (free_shape && sh.policy == DL_POL_STREAM_OUT) {  // the output outgrows the caches
                 uint64_t acc = 0;
@@ -1188,8 +1209,7 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
                 // 2 MiB to seven others 3.86 / 5.38 : 3.51 / 4.52; of 1 MiB and 5 bytes over five ranks 5.95 / 9.15 : 5.36 / 8.11.
                 // A workgroup is that one wavefront, or eight where loads are shifted (1 MiB + 5 over eight
                 // ranks: 11.6 us with one, 11.4 with eight, 13.0 with four; 1 MiB: 10.7, 10.6, 11.3).
-                bool on_grid = true;
-                for (size_t i = 0; i < n; ++i) on_grid = on_grid && item_on_grid(items[i]);
+                const bool on_grid = all_on_grid(items, n);
                 sh.split = 1;
                 sh.block_threads = on_grid ? 64u : 512u;
                 sh.tile_bytes = 16u * sh.block_threads;
@@ -1226,17 +1246,42 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
         const bool armed_rows = arm && ((!arm->nowait && !sh.chain) || total * (1ull + kmax) <= ARMED_ROWS_MAX_BYTES);
         sh.rows = (n <= (size_t)NMAX_SMALL || armed_rows) && sh.tile_bytes == 16u * (sh.block_threads / sh.split) &&
                   !(sh.max_blocks && !arm);
-        // ... or, one-shot, a longer list whose items are about equally long: item by item on a
-        // two-dimensional grid (see dl_exec_rows2d_kernel), while at most a fifth of its workgroups find nothing to do
-        if (n > (size_t)NMAX_SMALL && !arm && !sh.max_blocks && sh.tile_bytes == 16u * (sh.block_threads / sh.split)) {
-            uint64_t widest = 0;
-            for (size_t i = 0; i < n; ++i) {
-                const uint64_t t = i ? tile_end[i] - tile_end[i - 1] : tile_end[0];
-                if (t > widest) widest = t;
+        // ... or, one-shot, a longer list item by item on a two-dimensional grid (see dl_exec_rows2d_kernel), unless too many of
+        // its workgroups find nothing to do: a fifth of them; for plain copies and swaps below the sizes that stream, in
+        // workgroups of four rows, three fifths, or whatever a grid of RAGGED_GRID workgroups holds.  Chunks of a
+        // mixture-of-experts exchange between eight ranks, three buffer sets in turn, one tile after the other with a search : item by
+        // item: 16 tokens per rank of 4 KiB 2.80 : 2.52 us, 24 of 8 KiB 5.73 : 4.83, 24 of 14 KiB 8.8 : 8.0 (sets that
+        // fit no cache 11.8 : 10.4), 40 of 10 KiB 9.5 : 9.3, one buffer set 7.8 : 6.6.  Lengths drawn from 1 byte to
+        // 40 000: 12 / 30 / 64 copies 2.48 : 2.25, 2.60 : 2.46, 2.67 : 2.64; to 256 KiB (a grid of 2048 / 4096) 32 / 64
+        // copies 2.56 : 2.81, 2.74 : 3.35.
+        if (n > (size_t)NMAX_SMALL && !arm && !sh.max_blocks) {
+            const auto grid_if_even = [&](uint64_t spare) -> uint64_t {  // workgroups of the grid, if `spare` is enough; else 0
+                uint64_t widest = 0;
+                for (size_t i = 0; i < n; ++i) {
+                    const uint64_t t = i ? tile_end[i] - tile_end[i - 1] : tile_end[0];
+                    if (t > widest) widest = t;
+                }
+                return widest * n <= tile_end[n - 1] + spare && widest < (1ull << 31) ? widest * n : 0;
+            };
+            uint64_t grid = 0;
+            if (sh.tile_bytes == 16u * (sh.block_threads / sh.split)) grid = grid_if_even(tile_end[n - 1] / 4);
+            if constexpr (!std::is_same<Item, dl_fused_item>::value) {
+                if (!grid && free_shape && sh.policy == DL_POL_WT) {
+                    const dl_launch_shape before = sh;
+                    if (sh.block_threads == 64u && biggest >= 4096u) sh.block_threads = 256u;
+                    sh.tile_bytes = 16u * sh.block_threads;
+                    count_tiles();
+                    const uint64_t tiles = tile_end[n - 1];
+                    grid = grid_if_even(std::max(tiles + tiles / 2, RAGGED_GRID > tiles ? RAGGED_GRID - tiles : 0));
+                    if (!grid) {
+                        sh = before;
+                        count_tiles();
+                    }
+                }
             }
-            if (widest * n <= tile_end[n - 1] + tile_end[n - 1] / 4 && widest < (1ull << 31)) {
+            if (grid) {
                 sh.rows = true;
-                sh.rows2d_width = (uint32_t)widest;
+                sh.rows2d_width = (uint32_t)(grid / n);
             }
         }
         if constexpr (!std::is_same<Item, dl_fused_item>::value) {

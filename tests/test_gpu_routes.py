@@ -64,6 +64,35 @@ def test_unequal_copies_around_their_size_rules(ref, n, total, align):
     assert np.array_equal(d.host(), want) and d.guards_intact()
 
 
+# lists of 9..64 copies item by item or tile by tile: lengths that fill the two-dimensional grid to a fifth, two fifths or
+# hardly at all, a grid of 768 workgroups and one more, items shorter than a tile; off the grid around 24 and 96 MiB moved
+@pytest.mark.parametrize("lens,align", [
+    ([4096 * 8] * 8 + [4096 * 20] * 4, 128), ([4096 * 8] * 8 + [4096 * 21] * 4, 128), ([4096 * 100] + [4096 * 40] * 20, 128),
+    ([4096 * 100] + [4096 * 39] * 20, 128), ([4096 * 64] + [100] * 11, 128), ([4096 * 64] + [100] * 12, 128),
+    ([4096 * 63 + 1] + [1] * 11, 1), ([1500 + i for i in range(40)], 1), ([1024, 1, 1023] * 9, 128), ([64 * KiB, 1] * 32, 1),
+    ([640 * KiB] * 20, 1), ([12 * MiB // 20 - 1] * 20, 1), ([12 * MiB // 20] * 20, 1), ([48 * MiB // 20] * 20, 1),
+    ([48 * MiB // 20 + 100] * 20, 1), ([12 * MiB // 100 + 1] * 100, 1), ([6 * MiB, 3 * MiB, 5 * MiB + 1], 1)])
+def test_copies_item_by_item_or_tile_by_tile(ref, lens, align):
+    rng = np.random.default_rng(len(lens) + lens[0])
+    at = np.cumsum([0] + [(m + 255) // 128 * 128 for m in lens * 2])
+    off = rng.integers(0, 64, 2 * len(lens)) if align == 1 else np.zeros(2 * len(lens), dtype=np.int64)
+    arena = rng.integers(0, 256, int(at[-1]) + 256, dtype=np.uint8)
+    n = len(lens)
+    descs = [(int(at[i] + off[i]), int(at[n + i] + off[n + i]), m) for i, m in enumerate(lens)]
+    for swap in (False, True):
+        d = DevBuf(arena.size, fill=arena)
+        if swap:
+            want = arena.copy()
+            for s, t, m in descs:
+                want[s:s + m], want[t:t + m] = arena[t:t + m], arena[s:s + m]
+            dl.dl_batch_swap([(d.ptr(s), d.ptr(t), m) for s, t, m in descs], stream())
+        else:
+            want = ref.batch_copy([arena], [(0, s, 0, t, m) for s, t, m in descs])[0]
+            dl.dl_batch_copy([(d.ptr(s), d.ptr(t), m) for s, t, m in descs], stream())
+        sync()
+        assert np.array_equal(d.host(), want) and d.guards_intact()
+
+
 def _fanout(sizes, shifts, seed):
     """Read-once/write-k items, item i of sizes[i] = (bytes, k) bytes, with its buffers moved by the given shifts."""
     rng = np.random.default_rng(seed)
