@@ -25,6 +25,9 @@ constexpr int DISPATCH_W = 8;              // ranks this path handles: exactly 8
 constexpr uint32_t GROUP = 64;             // tokens whose places one wavefront's ballots tell apart
 constexpr uint32_t DISPATCH_GROUPS = 32;   // groups per launch with the mask in the kernel arguments (3.2 KiB of the 4 KiB they may take)
 constexpr uint32_t MAX_WAVES = 8;          // wavefronts of a workgroup
+constexpr uint64_t ALONE_MAX_TOKENS = 512;     // tokens up to which a workgroup is one wavefront (see dispatch_setup),
+constexpr uint64_t ALONE_LIST_MAX_ROWS = 3400; // ... and 1 KiB rows, with the mask on the host
+constexpr uint64_t ALONE_MASK_MAX_ROWS = 8192; // ... and in device memory
 
 struct dispatch_args {
     const char *in[DISPATCH_W];
@@ -389,6 +392,10 @@ template <class F>
 void with_instance(const dispatch_shape &sh, F f)
 {
     dl_with_policy_and_grid(sh.policy, sh.on_grid, [&](auto pol, auto og) {
+        if constexpr (decltype(og)::value) {  // off the grid a wavefront's rows are a loop, and two of them enough
+            if (sh.rows == 3) return f(pol, og, std::integral_constant<int, 3>{});
+            if (sh.rows == 4) return f(pol, og, std::integral_constant<int, 4>{});
+        }
         if (sh.rows == 1)
             f(pol, og, std::integral_constant<int, 1>{});
         else
@@ -419,7 +426,7 @@ int dispatch_setup(const void *const *in, void *const *out, const uint32_t *toke
     const dl_config &c = g_dl.cfg;
     sh->policy = bound >= c.nontemporal_min_bytes ? DL_POL_STREAM
                  : bound > c.write_through_max_bytes ? DL_POL_STREAM_OUT : bound >= DL_FAN_STREAM_IN_MIN_BYTES ? DL_POL_STREAM_IN : DL_POL_WT;
-    // Rows of a wavefront, wavefronts of a workgroup.  Off the grid, rows that one workgroup can hold: a row per wavefront
+    // Rows of a wavefront, (at most) wavefronts of a workgroup.  Off the grid, rows that one workgroup can hold: a row per wavefront
     // while the chip has room for all of them (8 tokens of 14 338 bytes per rank 7.2 us against 10.5 with two), else two
     // (1024 per rank, sources not in the caches: 184 us against 202).  Longer rows: four wavefronts of a row each
     // (16 400 bytes, 1024 per rank, likewise 189 us against 228 with eight of two; 300 000 bytes, 32 per rank 65 against 75).
@@ -430,9 +437,9 @@ int dispatch_setup(const void *const *in, void *const *out, const uint32_t *toke
     if (!sh->on_grid && sh->long_rows) {
         waves = 4;
         sh->rows = 1;
-    } else if (!sh->on_grid && (rows == 1 || rows * total <= 8192u)) {
-        sh->rows = 1;
-    } else if (sh->on_grid && sh->policy == DL_POL_STREAM_OUT && !mask_on_device) {
+    } else if (!sh->on_grid) {
+        if (rows == 1 || rows * total <= 8192u) sh->rows = 1;
+    } else if (sh->policy == DL_POL_STREAM_OUT && !mask_on_device) {
         // Large requests on the grid: two wavefronts of a row each.  Consecutive rows then go to different XCDs, and fewer
         // destinations are written at once by each.  Rows of 14 336 bytes, 512 / 1024 per rank 58.5 / 140 us with eight
         // wavefronts of two rows, 54.6 / 125 this way; of 64 KiB, sources not in the caches, 256 / 512 / 1024 per rank
@@ -440,6 +447,32 @@ int dispatch_setup(const void *const *in, void *const *out, const uint32_t *toke
         // (Not where every workgroup counts the mask: four times as many workgroups, 512 per rank of 64 KiB 378 us.)
         waves = 2;
         sh->rows = 1;
+    } else if (sh->policy == DL_POL_WT && total <= ALONE_MAX_TOKENS &&
+               rows * total <= (mask_on_device ? ALONE_MASK_MAX_ROWS : total < ALONE_MAX_TOKENS ? ALONE_LIST_MAX_ROWS : 1024u)) {
+        // Small: a wavefront by itself, so that nothing waits for a neighbour and a wavefront has the fewest instructions
+        // to fetch.  Eight wavefronts of two rows : this, three buffer sets in turn, mask on the host, 16 / 40 tokens per rank of
+        // 4 KiB 3.13 : 2.59 and 3.28 : 3.17 us, of 8 KiB 3.30 : 2.82 and 3.95 : 3.85, of 10 KiB 3.11 : 3.07 and 4.69 : 4.19;
+        // more rows gain only while the buffers are in the caches (40 per rank of 14 KiB 5.93 : 5.22, else 6.87 : 7.09, 57
+        // of 10 KiB 5.54 : 5.31 and 6.5 : 7.5), more tokens share their group's record better (64 / 128 per rank of 4 KiB 3.55 : 3.61 and 4.94 : 5.03).
+        // Mask on the device, 16 / 64 per rank of 4 KiB 4.96 : 4.01 and 5.41 : 4.96, of 8 KiB 5.12 : 4.23 and 6.90 : 6.34, of
+        // 14 KiB 6.19 : 4.71 and 10.3 : 9.2 (with two rows; 9.7 with one); there every wavefront counts the mask for itself
+        // (128 of 4 KiB 6.8 : 7.3), and 512 tokens of 20 rows take 12.5 : 13.1.
+        waves = 1;
+        sh->rows = mask_on_device && rows * total > 5120u ? 2 : 1;
+    } else if (sh->policy != DL_POL_STREAM && rows > 4u && rows <= in_one) {
+        // Between: up to four rows of a wavefront in flight together.  Three sets in turn, mask on the host, 192 / 256 per
+        // rank of 8 KiB 12.5 / 16.8 : 12.1 / 15.9 us, 128 / 192 of 10 KiB 10.8 / 16.3 : 10.4 / 15.3, 128 of 14 KiB 14.9 : 14.1
+        // (one set or sets that fit no cache +-3 %; 384 of 4 KiB 13.3 : 15.9 and 64 of 20 KiB 11.0 : 11.6, which stay).  Mask on the
+        // device: 13 rows and more likewise while sources stream (128 of 14 KiB 16.5 : 15.9; 512 59.8 : 60.8), and 9 to 12
+        // rows, whose five or six wavefronts of two lie badly on four SIMDs, by four of three (192 / 384 / 512 of 10 KiB
+        // 19.6 / 35.2 / 45.7 : 17.0 / 33.5 / 44.6; 768, in sets that fit no cache, 75.5 : 79.3).
+        if (!mask_on_device ? sh->policy == DL_POL_STREAM_IN : rows >= 13u && sh->policy != DL_POL_STREAM_OUT) {
+            waves = 4;
+            sh->rows = 4;
+        } else if (mask_on_device && rows >= 9u && rows <= 12u && bound < (512ull << 20)) {
+            waves = 4;
+            sh->rows = 3;
+        }
     }
     const uint32_t per_wg = waves * (uint32_t)sh->rows;
     sh->grid_x = (uint32_t)((rows + per_wg - 1) / per_wg);

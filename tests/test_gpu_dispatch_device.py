@@ -84,6 +84,18 @@ def test_rows_and_buffers_of_any_length_and_alignment(ref, counts, row, top_k, s
     run(ref, counts, row, seed=row + sum(counts), top_k=top_k, shifts=shifts, check_host_entry=True)
 
 
+# A workgroup of one wavefront with one row or two, of four with three or four rows, of eight with two: 511 / 512 / 513
+# tokens, 1024 / 1025, 3400, 5120 and 8192 rows of 1 KiB and one token more, rows of one to eighteen KiB that fill a
+# workgroup's share or not, 88 MiB and 144 MiB by the bound that the cache policy goes by.
+@pytest.mark.parametrize("counts,row", [
+    ([64] * 7 + [63], 16), ([64] * 8, 2048), ([64] * 7 + [65], 1024), ([64] * 7 + [64], 2 * 1024 + 16), ([0] * 7 + [340], 10240), ([341] + [0] * 7, 10240),
+    ([64] * 8, 10240), ([64] * 7 + [63], 10 * 1024 + 16), ([64] * 8, 16384), ([65] + [0] * 6 + [450], 16384), ([120] * 8, 9 * 1024 + 128),
+    ([150] * 8, 12288), ([130] * 8, 12 * 1024 + 128), ([110] * 8, 14336), ([100] * 8, 16384), ([110] * 8, 16 * 1024 + 128), ([180] * 8, 14336), ([160] * 8, 11 * 1024), ([260] * 8, 5 * 1024), ([400] * 8, 4096),
+    ([1] * 8, 3 * 1024)])
+def test_shapes_of_a_workgroup(ref, counts, row):
+    run(ref, counts, row, seed=sum(counts) + row, check_host_entry=True)
+
+
 def test_mask_produced_on_the_stream_just_before(ref):
     """The mask is written by a kernel on the same stream and the dispatch follows without a synchronisation in
     between: the three launches are ordered behind it.  Twice, with the mask buffer reused."""
