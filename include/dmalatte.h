@@ -73,7 +73,8 @@ typedef enum dl_status {
 typedef enum dl_mode {
     DL_MODE_ONESHOT = 0,   /* one kernel launch per call, ordered on `stream` */
     DL_MODE_PRELAUNCH = 1, /* one armed kernel per call, started by dl_trigger() */
-    DL_MODE_SIGNAL = 2,    /* one kernel launch per call that starts at once and writes a completion word: the
+    DL_MODE_SIGNAL = 2,    /* a kernel per call that starts at once and writes a completion word (where much is
+                              moved, a second one behind it does): the
                               request has a ticket, dl_wait() observes its end without a stream synchronisation */
     DL_MODE_STANDBY = 3,   /* small requests are handed to a kernel that is already waiting on the device: no
                               launch between the call and the copy (see "standby mode" below); the rest run as in
@@ -256,7 +257,8 @@ int dl_alltoall_inplace(void *const *buf, int W, size_t chunk_bytes, void *strea
  *                  longer than dl_config.arm_timeout_us), or DL_ERR_TIMEOUT
  *                  (the host gave up waiting; ns == 0 polls once).
  *   dl_wait_armed(t, ns) returns once request t's kernel is resident and
- *                  polling (used to time trigger -> completion).
+ *                  polling (used to time trigger -> completion); for a request
+ *                  without a doorbell (signal mode) once it has finished.
  * Requests on one stream run in ticket order.  The armed kernel occupies its
  * stream until it is triggered, cancelled or expires; later work on that
  * stream waits for it.  At most 64 requests may be armed and unfinished.
@@ -288,10 +290,11 @@ int dl_alltoall_inplace(void *const *buf, int W, size_t chunk_bytes, void *strea
  * with DL_ERR_INVALID in this mode.  An empty request enqueues nothing and
  * takes no ticket.
  *
- * DL_MODE_SIGNAL is the same kernel without the doorbell: it copies as soon as
- * it starts (still in order on its stream), and the last workgroup writes the
+ * DL_MODE_SIGNAL is the same without the doorbell: the kernel copies as soon as
+ * it starts (still in order on its stream), and its last workgroup writes the
  * completion word (the analogue of the sync command that ends a queue of
- * copies, paper Sec. III-B2).  dl_wait() on its ticket returns about 3 us
+ * copies, paper Sec. III-B2); a request that moves 12 MiB or more is an ordinary
+ * one-shot kernel and a second one, behind it on the stream, that writes the word.  dl_wait() on its ticket returns about 3 us
  * earlier than a stream synchronisation would for the same kernel.
  *
  * Standby mode (DL_MODE_STANDBY) is prelaunch for requests that are not known

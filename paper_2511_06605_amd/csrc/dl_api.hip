@@ -308,7 +308,7 @@ int run_in_mode(void *stream, Launch launch)
     }
     bool launched = false;
     const int rc = launch(hs, armp, &launched);
-    if (armp && rc == DL_OK && launched) dl_armed_commit(g_dl.armed_words);
+    if (armp && rc == DL_OK && launched) dl_armed_commit(g_dl.armed_words, g_dl.armed_counted, armp->nowait != 0);
     return rc;
 }
 

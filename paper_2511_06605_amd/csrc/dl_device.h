@@ -42,10 +42,13 @@ constexpr int DL_UNROLL = 4;
 //           written, and whoever reads the result next finds the tail of it there.  All-to-all between eight ranks,
 //           2 MiB chunks (256 MiB moved): 48.1 us with ordinary loads and stores, 40.8 with the hint on both, 41.6
 //           this way; followed by a kernel that reads all of the output: 86.2, 83.6 and 68.4 us.
-//  WT       ordinary loads, write-through 16-byte stores: nothing is left dirty in the
+//  WT       ordinary loads, write-through stores: nothing is left dirty in the
 //           L2 for the end of the kernel to write back, which shortens small and
 //           medium requests by 10-15 % and costs nothing until the output outgrows
 //           the on-die caches.
+//  The stores of all of these but PLAIN are at system scope (agent scope takes the same time, between -1 and +2 % over 25
+//  requests of 0.1 MB to 5 GB): once a wavefront's memory counter has drained, or its kernel has ended, what it wrote is
+//  where the host, another device and every later kernel see it, so a signalled request can use them too.
 //  COHERENT every load and store at system scope: loads never hit a stale cache
 //           line, stores are written through and are visible to the whole system once
 //           the wavefront's memory counter has drained.  Used by the armed kernels,
@@ -74,19 +77,17 @@ __device__ __forceinline__ V dl_ld(const DL_GLOBAL V *p)
 template <int POL, typename V>
 __device__ __forceinline__ void dl_st(DL_GLOBAL V *p, V v)
 {
-    if constexpr (POL == DL_POL_STREAM)
-        __builtin_nontemporal_store(v, p);
     // The s_nop after each store: a store of more than 8 bytes must not be followed directly by a
     // vector ALU write to its data registers (the hardware reads them a cycle late).  The compiler
     // pads its own stores for this, but it cannot see that the assembly below is one, and it is free
     // to reuse v's registers in the very next instruction.
-    else if constexpr (POL == DL_POL_STREAM_OUT && sizeof(V) == 16)
-        asm volatile("global_store_dwordx4 %0, %1, off sc1 nt\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
+    if constexpr ((POL == DL_POL_STREAM_OUT || POL == DL_POL_STREAM) && sizeof(V) == 16)
+        asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
     else if constexpr ((POL == DL_POL_WT || POL == DL_POL_STREAM_IN) && sizeof(V) == 16)
-        asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
+        asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
     else if constexpr (POL == DL_POL_COHERENT && sizeof(V) == 16)
         asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
-    else if constexpr (POL == DL_POL_COHERENT)
+    else if constexpr (POL != DL_POL_PLAIN)
         __hip_atomic_store((V *)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     else
         *p = v;
@@ -123,12 +124,10 @@ template <int POL>
 __device__ __forceinline__ void dl_st16(char *p, dl_u32x4 v)
 {
     DL_GLOBAL dl_u32x4u *q = (DL_GLOBAL dl_u32x4u *)(uint64_t)p;
-    if constexpr (POL == DL_POL_STREAM)
-        __builtin_nontemporal_store(v, q);
-    else if constexpr (POL == DL_POL_STREAM_OUT)  // (the s_nop: see dl_st)
-        asm volatile("global_store_dwordx4 %0, %1, off sc1 nt\n\ts_nop 1" : : "v"(q), "v"(v) : "memory");
+    if constexpr (POL == DL_POL_STREAM_OUT || POL == DL_POL_STREAM)  // (the s_nop: see dl_st)
+        asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt\n\ts_nop 1" : : "v"(q), "v"(v) : "memory");
     else if constexpr (POL == DL_POL_WT || POL == DL_POL_STREAM_IN)
-        asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(q), "v"(v) : "memory");
+        asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" : : "v"(q), "v"(v) : "memory");
     else if constexpr (POL == DL_POL_COHERENT)
         asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" : : "v"(q), "v"(v) : "memory");
     else
@@ -756,73 +755,96 @@ __device__ __forceinline__ void dl_run_rows(const dl_klist<Item, NMAX> &p, uint3
 // wavefront takes up to R global tiles per pass (b0, b0 + stride, ...; those below `total`), issues the loads
 // of all of them, waits once and stores.  Rows and lanes as in dl_rows_body, with one sub-group per workgroup
 // (every wavefront stores its row to all of the item's destinations).  b0 < total.  Not for swaps.
+// prepare() works out what is moved, and may run before the sources may be read; run() moves it.
 // spare: 16 readable bytes of device memory, for the lanes that have no vector of their own to load.
+template <int R, class Item, int NMAX>
+struct dl_coherent_rows {
+    static_assert(!std::is_same<Item, dl_swap_item>::value, "a swap has two loads per row already");
+    uint32_t d[R], kind[R];
+    uint64_t row[R], byte[R];
+    bool whole[R];
+    const char *from[R];
+
+    __device__ __forceinline__ void prepare(const dl_klist<Item, NMAX> &p, uint32_t b0, uint32_t stride, uint32_t total, const void *spare)
+    {
+        const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const uint32_t lane = threadIdx.x & 63u;
+        const uint32_t wl = p.wpg_log2;
+        uint32_t first;
+        const uint32_t d0 = dl_find_item(p, b0, &first);
+        // what a lane without a vector loads instead: the first 16 bytes of tile b0's item, if it has that many
+        const char *const safe = p.item[d0].bytes >= 16u ? p.item[d0].src : (const char *)spare;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t b = b0 + (uint32_t)r * stride;
+            d[r] = p.n;
+            kind[r] = DL_ROW_NONE;
+            row[r] = 0;
+            byte[r] = 0;
+            whole[r] = false;
+            from[r] = safe;
+            if (b < total && b >= b0) {  // (b >= b0: no wrap-around)
+                d[r] = dl_find_item(p, b, &first);
+                if (d[r] < p.n) {
+                    const Item &it = p.item[d[r]];
+                    row[r] = ((uint64_t)(b - first) << wl) + (wave & ((1u << wl) - 1u));
+                    const uint32_t shift = dl_item_shift(it);
+                    byte[r] = ((row[r] << 10) - shift) + (lane << 4);
+                    kind[r] = dl_row_kind(dl_item_ragged(it), shift, it.bytes, row[r]);
+                    whole[r] = dl_lane_whole(byte[r], it.bytes, kind[r]);
+                    if (whole[r]) from[r] = it.src + byte[r];
+                }
+            }
+        }
+    }
+
+    __device__ __forceinline__ void run(const dl_klist<Item, NMAX> &p) const
+    {
+        const uint32_t lane = threadIdx.x & 63u;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (kind[r] != DL_ROW_EDGE) continue;  // the bytes in front of and behind the item's whole vectors
+            const Item &it = p.item[d[r]];
+            dl_row_edges(dl_item_shift(it), it.bytes, row[r], lane, [&](uint64_t i) {
+                const uint8_t x = dl_ld<DL_POL_COHERENT>(dl_global<uint8_t>(it.src) + i);
+                if constexpr (std::is_same<Item, dl_plain_item>::value) {
+                    dl_st<DL_POL_COHERENT>(dl_global<uint8_t>(it.dst) + i, x);
+                } else {
+                    for (uint32_t q = 0; q < (uint32_t)DL_FAN; ++q) {
+                        char *dq = it.dst[q];  // filled from the front, the rest null
+                        if (!dq) break;
+                        dl_st<DL_POL_COHERENT>(dl_global<uint8_t>(dq) + i, x);
+                    }
+                }
+            });
+        }
+        dl_u32x4 v[R];
+        dl_ld_many<DL_POL_COHERENT, R>(v, from);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (!whole[r]) continue;
+            const Item &it = p.item[d[r]];
+            if constexpr (std::is_same<Item, dl_plain_item>::value) {
+                dl_st16<DL_POL_COHERENT>(it.dst + byte[r], v[r]);
+            } else {
+#pragma unroll
+                for (uint32_t q = 0; q < (uint32_t)DL_FAN; ++q) {
+                    char *dq = it.dst[q];  // filled from the front, the rest null
+                    if (!dq) break;
+                    dl_st16<DL_POL_COHERENT>(dq + byte[r], v[r]);
+                }
+            }
+        }
+    }
+};
+
 template <int R, class Item, int NMAX>
 __device__ __forceinline__ void dl_run_rows_coherent(const dl_klist<Item, NMAX> &p, uint32_t b0, uint32_t stride,
                                                      uint32_t total, const void *spare)
 {
-    static_assert(!std::is_same<Item, dl_swap_item>::value, "a swap has two loads per row already");
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wl = p.wpg_log2;
-    uint32_t first;
-    const uint32_t d0 = dl_find_item(p, b0, &first);
-    // what a lane without a vector loads instead: the first 16 bytes of tile b0's item, if it has that many
-    const char *const safe = p.item[d0].bytes >= 16u ? p.item[d0].src : (const char *)spare;
-    uint32_t d[R];
-    uint64_t byte[R];
-    bool whole[R];
-    const char *from[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const uint32_t b = b0 + (uint32_t)r * stride;
-        d[r] = p.n;
-        byte[r] = 0;
-        whole[r] = false;
-        from[r] = safe;
-        if (b < total && b >= b0) {  // (b >= b0: no wrap-around)
-            d[r] = dl_find_item(p, b, &first);
-            if (d[r] < p.n) {
-                const Item &it = p.item[d[r]];
-                const uint64_t row = ((uint64_t)(b - first) << wl) + (wave & ((1u << wl) - 1u));
-                const uint32_t shift = dl_item_shift(it);
-                byte[r] = ((row << 10) - shift) + (lane << 4);
-                const uint32_t kind = dl_row_kind(dl_item_ragged(it), shift, it.bytes, row);
-                whole[r] = dl_lane_whole(byte[r], it.bytes, kind);
-                if (whole[r]) from[r] = it.src + byte[r];
-                if (kind == DL_ROW_EDGE)  // the bytes in front of and behind the item's whole vectors
-                    dl_row_edges(shift, it.bytes, row, lane, [&](uint64_t i) {
-                        const uint8_t x = dl_ld<DL_POL_COHERENT>(dl_global<uint8_t>(it.src) + i);
-                        if constexpr (std::is_same<Item, dl_plain_item>::value) {
-                            dl_st<DL_POL_COHERENT>(dl_global<uint8_t>(it.dst) + i, x);
-                        } else {
-                            for (uint32_t q = 0; q < (uint32_t)DL_FAN; ++q) {
-                                char *dq = it.dst[q];  // filled from the front, the rest null
-                                if (!dq) break;
-                                dl_st<DL_POL_COHERENT>(dl_global<uint8_t>(dq) + i, x);
-                            }
-                        }
-                    });
-            }
-        }
-    }
-    dl_u32x4 v[R];
-    dl_ld_many<DL_POL_COHERENT, R>(v, from);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        if (!whole[r]) continue;
-        const Item &it = p.item[d[r]];
-        if constexpr (std::is_same<Item, dl_plain_item>::value) {
-            dl_st16<DL_POL_COHERENT>(it.dst + byte[r], v[r]);
-        } else {
-#pragma unroll
-            for (uint32_t q = 0; q < (uint32_t)DL_FAN; ++q) {
-                char *dq = it.dst[q];  // filled from the front, the rest null
-                if (!dq) break;
-                dl_st16<DL_POL_COHERENT>(dq + byte[r], v[r]);
-            }
-        }
-    }
+    dl_coherent_rows<R, Item, NMAX> rows;
+    rows.prepare(p, b0, stride, total, spare);
+    rows.run(p);
 }
 
 // Global tile b of a list, any alignment and tile size: find its item, then

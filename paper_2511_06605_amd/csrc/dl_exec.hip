@@ -153,14 +153,54 @@ __global__ void __launch_bounds__(512) dl_exec_table_kernel(const Item *__restri
 
 enum : uint32_t { DL_GO_WAIT = 0, DL_GO_RUN = 1, DL_GO_SKIP = 2 };
 
-// Housekeeping of a request, done by one thread where its stores' round trips delay nothing: clear the
-// counters that the slot's next request will count on, and tell the host that the kernel is resident.
-__device__ __forceinline__ void dl_arm_housekeeping(const dl_arm &a)
+// First thing in a kernel that may count its workgroups in: the counters that the slot's next request that counts will
+// use, one lane each.  The stores are in flight beside the wait and the copy.
+__device__ __forceinline__ void dl_arm_clear(const dl_arm &a)
 {
-    for (uint32_t g = 0; a.arrive_clear && g <= DL_ARM_GROUPS; ++g)
-        __hip_atomic_store((uint32_t *)((char *)a.arrive_clear + g * DL_ARM_STRIDE), 0u, __ATOMIC_RELAXED,
+    static_assert(DL_ARM_GROUPS < 64, "one lane per counter");
+    if (a.arrive_clear && blockIdx.x == 0 && threadIdx.x <= DL_ARM_GROUPS)
+        __hip_atomic_store((uint32_t *)((char *)a.arrive_clear + threadIdx.x * DL_ARM_STRIDE), 0u, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Tells the host that a kernel that waits is on the device.
+__device__ __forceinline__ void dl_arm_resident(const dl_arm &a)
+{
     __hip_atomic_store(a.armed, a.ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Phase stamps of a request that waits for no doorbell.
+__device__ __forceinline__ void dl_arm_stamp_begin(const dl_arm &a)
+{
+    if (a.trace_host && blockIdx.x == 0 && threadIdx.x == 0) {
+        const uint64_t t = (uint64_t)wall_clock64();
+        __hip_atomic_store(a.trace_host, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(a.trace_host + 1, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+// One thread polls the doorbell (system-scope loads past every cache: device memory, or host memory over the link) until
+// it has been rung for this ticket, the request is cancelled or the limit runs out.  t0: when the kernel began to wait.
+__device__ __forceinline__ uint32_t dl_arm_poll(const dl_arm &a, uint64_t t0, bool pause)
+{
+    for (uint32_t spins = 1;; ++spins) {
+        // doorbell and cancel word sit side by side in one aligned 16 bytes: one read over the link
+        // (each is an aligned 8-byte word that the host writes with one store, so neither can tear)
+        const dl_u32x4 w = dl_ld<DL_POL_COHERENT>(dl_global<dl_u32x4>(a.bell));
+        const uint64_t bell = (uint64_t)w.x | ((uint64_t)w.y << 32);
+        const uint64_t cancel = (uint64_t)w.z | ((uint64_t)w.w << 32);
+        if (cancel >= a.ticket) return DL_GO_SKIP;
+        if (bell >= a.ticket) return DL_GO_RUN;
+        if ((spins & 3u) == 0 && (uint64_t)wall_clock64() - t0 > a.limit_ticks) return DL_GO_SKIP;
+        if (spins >= a.max_spins) return DL_GO_SKIP;
+        if (pause) __builtin_amdgcn_s_sleep(8);
+    }
+}
+
+__device__ __forceinline__ void dl_arm_stamp(const dl_arm &a, int which)
+{
+    if (a.trace_host && blockIdx.x == 0)
+        __hip_atomic_store(a.trace_host + which, (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Returns DL_GO_RUN once the doorbell has been rung for this ticket, DL_GO_SKIP
@@ -168,52 +208,29 @@ __device__ __forceinline__ void dl_arm_housekeeping(const dl_arm &a)
 __device__ __forceinline__ uint32_t dl_arm_wait(const dl_arm &a)
 {
     __shared__ uint32_t s_go;
+    dl_arm_clear(a);
     if (a.nowait && a.gated) {
         // uniform over the grid: the waiting was done by the gate kernel that ran before this one on the stream
         // (see dl_arm_gate_kernel); what it decided lies in the slot's first flag
         if (threadIdx.x == 0) {
             const uint64_t g = __hip_atomic_load(a.go, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             s_go = (g >> 2) == a.ticket ? (uint32_t)(g & 3u) : (uint32_t)DL_GO_SKIP;
-            if (a.trace_host && blockIdx.x == 0 && s_go == DL_GO_RUN)
-                __hip_atomic_store(a.trace_host + 1, (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            if (s_go == DL_GO_RUN) dl_arm_stamp(a, 1);
         }
         __syncthreads();
         return s_go;
     }
-    if (a.nowait) {  // uniform over the grid: started without a doorbell; housekeeping follows the copy
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            if (a.trace_host) {
-                const uint64_t t = (uint64_t)wall_clock64();
-                __hip_atomic_store(a.trace_host, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-                __hip_atomic_store(a.trace_host + 1, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            }
-        }
+    if (a.nowait) {  // uniform over the grid: started without a doorbell
+        dl_arm_stamp_begin(a);
         return DL_GO_RUN;
     }
     if (threadIdx.x == 0) {
         uint32_t go = DL_GO_SKIP;
         const uint64_t t0 = wall_clock64();
-        if (blockIdx.x == 0) dl_arm_housekeeping(a);  // before the wait: off the critical path
+        if (blockIdx.x == 0) dl_arm_resident(a);  // before the wait: off the critical path
         if (a.direct || blockIdx.x == 0) {
-            // poll the doorbell (system-scope loads past every cache: device memory, or host memory over the link)
-            for (uint32_t spins = 1;; ++spins) {
-                // doorbell and cancel word sit side by side in one aligned 16 bytes: one read over the link
-                // (each is an aligned 8-byte word that the host writes with one store, so neither can tear)
-                const dl_u32x4 w = dl_ld<DL_POL_COHERENT>(dl_global<dl_u32x4>(a.bell));
-                const uint64_t bell = (uint64_t)w.x | ((uint64_t)w.y << 32);
-                const uint64_t cancel = (uint64_t)w.z | ((uint64_t)w.w << 32);
-                if (cancel >= a.ticket) break;
-                if (bell >= a.ticket) {
-                    go = DL_GO_RUN;
-                    if (a.trace_host && blockIdx.x == 0)
-                        __hip_atomic_store(a.trace_host, (uint64_t)wall_clock64(), __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_SYSTEM);
-                    break;
-                }
-                if ((spins & 3u) == 0 && (uint64_t)wall_clock64() - t0 > a.limit_ticks) break;
-                if (spins >= a.max_spins) break;
-                if (blockIdx.x && !a.direct) __builtin_amdgcn_s_sleep(8);
-            }
+            go = dl_arm_poll(a, t0, blockIdx.x && !a.direct);
+            if (go == DL_GO_RUN) dl_arm_stamp(a, 0);
             if (!a.direct) {
                 // pass the word on: one flag per group of workgroups, each in its own cache line
                 // (the flag carries everything the others need, so it is not ordered against anything)
@@ -236,8 +253,7 @@ __device__ __forceinline__ uint32_t dl_arm_wait(const dl_arm &a)
                 if (spins >= a.max_spins) break;
             }
         }
-        if (a.trace_host && blockIdx.x == 0 && go == DL_GO_RUN)  // the polling workgroup is the first to begin its copy
-            __hip_atomic_store(a.trace_host + 1, (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        if (go == DL_GO_RUN) dl_arm_stamp(a, 1);  // the polling workgroup is the first to begin its copy
         s_go = go;
     }
     __syncthreads();
@@ -257,20 +273,15 @@ __device__ __forceinline__ uint32_t dl_arm_wait(const dl_arm &a)
 // the host and to every later kernel, and relaxed counters suffice.  (With
 // ordinary stores each workgroup had to write the L2 back before counting
 // itself in; that serialised per XCD and cost ~0.5 us per workgroup.)
-__device__ __forceinline__ void dl_arm_finish(const dl_arm &a, uint32_t go)
+__device__ __forceinline__ void dl_arm_report(const dl_arm &a, uint32_t go)
 {
-    // without a doorbell there was no wait to hide the housekeeping behind: its stores go out behind the copy's
-    // and share their round trip
-    if (a.nowait && blockIdx.x == 0 && threadIdx.x == 0) dl_arm_housekeeping(a);
-    dl_drain_stores();
-    __syncthreads();
-    if (threadIdx.x == 0 && a.own_word) {
+    if (a.own_word) {
         // a small grid: the host waits for one word per workgroup, no count in between
         __hip_atomic_store(a.done + blockIdx.x, a.ticket | (go == DL_GO_RUN ? 0ull : DL_DONE_SKIPPED), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_SYSTEM);
         return;
     }
-    if (threadIdx.x == 0) {
+    {
         const uint32_t grid = gridDim.x;
         const bool flat = grid <= DL_ARM_FLAT_MAX;  // few enough to count at one word without queueing there
         const uint32_t groups = flat ? grid : DL_ARM_GROUPS;
@@ -307,6 +318,13 @@ __device__ __forceinline__ void dl_arm_finish(const dl_arm &a, uint32_t go)
     }
 }
 
+__device__ __forceinline__ void dl_arm_finish(const dl_arm &a, uint32_t go)
+{
+    dl_drain_stores();
+    __syncthreads();
+    if (threadIdx.x == 0) dl_arm_report(a, go);
+}
+
 // Gate of a large prelaunched request.  A grid that waits for a doorbell must stay small (see armed_grid), and a
 // small grid is what bounds a large copy.  So the waiting is done by this kernel, one workgroup, and the copy by
 // an ordinary signal-style kernel with a full grid that is enqueued behind it on the same stream: it starts when
@@ -318,6 +336,121 @@ __global__ void __launch_bounds__(64) dl_arm_gate_kernel(const dl_arm a)
     const uint32_t go = dl_arm_wait(a);
     if (threadIdx.x == 0)
         __hip_atomic_store(a.go, (a.ticket << 2) | (uint64_t)go, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A signalled request on the row path: no doorbell, a workgroup per tile, then the report.  A kernel of its own, because what
+// it takes beyond a one-shot kernel's time is instruction fetch and round trips: nothing of the waiting kernels' code is in
+// the way, and the loads are ordinary ones (whoever wrote the sources did so before the launch).
+template <class Item, int NMAX, bool ON_GRID>
+__global__ void __launch_bounds__(512) dl_signal_rows_kernel(const dl_klist<Item, NMAX> p, const dl_arm a)
+{
+    dl_arm_clear(a);
+    dl_arm_stamp_begin(a);
+    dl_run_rows<DL_POL_WT, ON_GRID>(p, blockIdx.x);
+    dl_arm_finish(a, DL_GO_RUN);
+}
+
+// Completion of a large signalled request: the copy is an ordinary one-shot kernel (whose stores are at system scope), and this
+// one, behind it on the stream, reports.
+__global__ void __launch_bounds__(64) dl_signal_done_kernel(uint64_t *done, uint64_t ticket)
+{
+    if (threadIdx.x == 0) __hip_atomic_store(done, ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// A waiting request of at most one tile per workgroup, each of which polls the doorbell itself.  Whatever the copy needs is
+// worked out before the wait, so that behind it there are a load, the stores and the report, in few instructions: what
+// counts there is instruction fetch and round trips.
+template <class Item, int NMAX, bool ON_GRID>
+__global__ void __launch_bounds__(1024) dl_armed_rows_kernel(const dl_klist<Item, NMAX> p, const dl_arm a)
+{
+    constexpr int K = std::is_same<Item, dl_plain_item>::value ? 1 : DL_FAN;
+    __shared__ uint32_t s_go;
+    const uint64_t t0 = wall_clock64();
+    dl_arm_clear(a);
+    if (blockIdx.x == 0 && threadIdx.x == 0) dl_arm_resident(a);
+    uint32_t first;
+    const uint32_t d = dl_find_item(p, blockIdx.x, &first);  // (< p.n: the grid is as long as the list has tiles)
+    const Item &it = p.item[d];
+    const char *const src = it.src;
+    const uint64_t bytes = it.bytes;
+    char *dst[K];
+#pragma unroll
+    for (int q = 0; q < K; ++q) dst[q] = (char *)dl_item_dst(it, (uint32_t)q);  // filled from the front, the rest null
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wl = p.wpg_log2;
+    const uint64_t row = ((uint64_t)(blockIdx.x - first) << wl) + (wave & ((1u << wl) - 1u));
+    const uint32_t shift = ON_GRID ? 0u : dl_item_shift(it);
+    const uint32_t kind = ON_GRID ? (uint32_t)DL_ROW_PLAIN : dl_row_kind(dl_item_ragged(it), shift, bytes, row);
+    const uint64_t byte = ((row << 10) - shift) + (lane << 4);
+    const bool whole = dl_lane_whole(byte, bytes, kind);
+    asm volatile("" ::"s"(src), "s"(dst[0]), "s"(dst[K - 1]), "v"(byte));
+    if (threadIdx.x == 0) {
+        const uint32_t go = dl_arm_poll(a, t0, false);
+        if (go == DL_GO_RUN) {
+            dl_arm_stamp(a, 0);
+            dl_arm_stamp(a, 1);
+        }
+        s_go = go;
+    }
+    __syncthreads();
+    const uint32_t go = s_go;
+    if (go == DL_GO_RUN) {
+        if (kind == DL_ROW_EDGE)
+            dl_row_edges(shift, bytes, row, lane, [&](uint64_t i) {
+                const uint8_t x = dl_ld<DL_POL_COHERENT>(dl_global<uint8_t>(src) + i);
+#pragma unroll 1
+                for (int q = 0; q < K; ++q) {
+                    char *dq = (char *)dl_item_dst(it, (uint32_t)q);
+                    if (!dq) break;
+                    dl_st<DL_POL_COHERENT>(dl_global<uint8_t>(dq) + i, x);
+                }
+            });
+        if (whole) {
+            const dl_u32x4 v = dl_ld16<DL_POL_COHERENT>(src + byte);
+#pragma unroll
+            for (int q = 0; q < K; ++q) {
+                if (!dst[q]) break;
+                dl_st16<DL_POL_COHERENT>(dst[q] + byte, v);
+            }
+        }
+    }
+    dl_arm_finish(a, go);
+}
+
+// The same for a request of more tiles than the waiting grid has workgroups: R tiles a pass, the first pass's worked out
+// before the wait.  Two a pass for up to two passes of sixteen wavefronts, else four (all-gather over eight ranks, sixteen wavefronts a workgroup, trigger
+// to done and the call: 1 MiB per rank 24.6 us with two, 26.1 with four; 2 MiB 56.8 and 47.7).
+template <class Item, int NMAX, int R>
+__global__ void __launch_bounds__(1024) dl_armed_passes_kernel(const dl_klist<Item, NMAX> p, const dl_arm a)
+{
+    __shared__ uint32_t s_go;
+    const uint64_t t0 = wall_clock64();
+    dl_arm_clear(a);
+    if (blockIdx.x == 0 && threadIdx.x == 0) dl_arm_resident(a);
+    const uint32_t grid = gridDim.x, total = p.tile_end[p.n - 1];
+    dl_coherent_rows<R, Item, NMAX> rows;
+    rows.prepare(p, blockIdx.x, grid, total, a.go);
+    {
+        uint64_t touched = 0;  // so that the destinations are in the scalar cache behind the wait
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (rows.d[r] < p.n) touched += (uint64_t)dl_item_dst(p.item[rows.d[r]], 0) + (uint64_t)dl_item_dst(p.item[rows.d[r]], DL_FAN - 1);
+        asm volatile("" ::"s"(touched));
+    }
+    if (threadIdx.x == 0) {
+        const uint32_t go = dl_arm_poll(a, t0, false);
+        if (go == DL_GO_RUN) {
+            dl_arm_stamp(a, 0);
+            dl_arm_stamp(a, 1);
+        }
+        s_go = go;
+    }
+    __syncthreads();
+    const uint32_t go = s_go;
+    if (go == DL_GO_RUN) {
+        rows.run(p);
+        for (uint32_t b = blockIdx.x + R * grid; b < total; b += R * grid) dl_run_rows_coherent<R>(p, b, grid, total, a.go);
+    }
+    dl_arm_finish(a, go);
 }
 
 template <class Item, int NMAX, bool ROWS>
@@ -369,10 +502,6 @@ struct dl_standby_rec {
     uint64_t activation;  // which arming of this pool slot the record is for (the executor's doorbell value)
     uint64_t *done;       // the request's completion words (host-coherent): one per tile up to DL_DONE_WORDS tiles, else one
     uint64_t arrivals;    // written as 0; requests of more than DL_DONE_WORDS tiles count their workgroups in here
-    // The ticket's slot has two sets of arrival counters that its requests use in turn, each clearing the set it
-    // does not use (see dl_arm).  A request served here counts nothing there, but it keeps that chain: this is
-    // the set it clears.
-    uint32_t *arrive_clear;
     uint64_t plain;       // 1: `copies` holds the request (up to 64 plain copies); 0: `list` (up to 8 read-once/write-k items)
     union {
         dl_klist<dl_fused_item, 8> list;
@@ -407,10 +536,6 @@ __global__ void __launch_bounds__(DL_STANDBY_THREADS) dl_standby_kernel(dl_stand
     if (!ok) return;  // not the announced record: touch nothing (the host's wait for the request times out)
     const uint32_t tiles = rec.copies.tile_end[rec.list.n - 1];
     if (blockIdx.x >= tiles) return;
-    if (blockIdx.x == 0 && threadIdx.x == 0)  // in flight beside the copy, drained with it before the completion word
-        for (uint32_t g = 0; rec.arrive_clear && g <= DL_ARM_GROUPS; ++g)
-            __hip_atomic_store((uint32_t *)((char *)rec.arrive_clear + g * DL_ARM_STRIDE), 0u, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
     if (rec.plain)
         dl_run_rows<DL_POL_COHERENT>(rec.copies, blockIdx.x);
     else
@@ -499,6 +624,8 @@ constexpr uint64_t UNIFORM_ROWS_MIN_BYTES = 4ull << 20;  // source bytes from wh
 constexpr uint64_t UNIFORM_ROWS_STAGE_BYTES = 768ull << 20;  // bytes moved (read + written) from which its table is staged even where it could be pushed
 constexpr uint64_t STREAM_BOTH_MIN_BYTES = 512ull << 20;  // bytes moved from which lists of plain copies outside the row path stream both sides
 constexpr uint64_t OFF_GRID_MIN_BYTES = 24ull << 20;  // bytes moved from which plain copies off the grid take workgroups of eight rows
+constexpr uint32_t SIGNAL_MAX_BLOCKS = 32768;  // the arrival counters keep 16 bits for the count
+constexpr uint64_t SIGNAL_DONE_MIN_BYTES = 12ull << 20;  // bytes moved from which a signalled request is a one-shot kernel and one that reports
 constexpr uint64_t RAGGED_GRID = 768;  // workgroups of a two-dimensional grid that may be mostly idle
 constexpr uint64_t OFFSETS_MIN_BYTES = 64ull << 20;  // bytes moved per launch where a long uniform list takes several instead of a table
 constexpr uint64_t ARMED_ROWS_MAX_BYTES = 32ull << 20;  // bytes moved up to which an armed kernel that does not wait takes the row path for more than eight items
@@ -642,11 +769,26 @@ int launch_klist(const Item *items, size_t n, const uint64_t *tile_end, const dl
             const int rc = launch_gate(a, stream);
             if (rc != DL_OK) return rc;
         }
-        const uint32_t g = armed_grid(grid, sh.block_threads, !a.nowait);
+        const bool signal = sh.rows && a.nowait && !a.gated && !g_dl.cfg.armed_blocks && grid <= SIGNAL_MAX_BLOCKS;
+        const uint32_t g = signal ? grid : armed_grid(grid, sh.block_threads, !a.nowait);
         a.direct = g <= a.direct_max ? 1u : 0u;
         a.own_word = g <= DL_DONE_WORDS && !a.trace_host ? 1u : 0u;  // the stamps come from the last arriver
         g_dl.armed_words = a.own_word ? g : 1u;
-        if (sh.rows)
+        g_dl.armed_counted = !a.own_word;
+        if (signal && on_grid)
+            hipLaunchKernelGGL((dl_signal_rows_kernel<Item, NMAX, true>), dim3(g), dim3(sh.block_threads), 0, stream, p, a);
+        else if (signal)
+            hipLaunchKernelGGL((dl_signal_rows_kernel<Item, NMAX, false>), dim3(g), dim3(sh.block_threads), 0, stream, p, a);
+        else if (sh.rows && !a.nowait && a.direct && sh.split == 1 && (grid <= 4u * g || sh.block_threads > 512u) && !std::is_same<Item, dl_swap_item>::value) {
+            if constexpr (!std::is_same<Item, dl_swap_item>::value) {
+                const bool four = grid > 4u * g || (grid > 2u * g && (grid <= 2u * g + g / 2u || sh.block_threads <= 512u));
+                const auto kernel = g < grid ? four ? dl_armed_passes_kernel<Item, NMAX, 4> : dl_armed_passes_kernel<Item, NMAX, 2>
+                                    : on_grid ? dl_armed_rows_kernel<Item, NMAX, true> : dl_armed_rows_kernel<Item, NMAX, false>;
+                hipLaunchKernelGGL(kernel, dim3(g), dim3(sh.block_threads), 0, stream, p, a);
+            }
+        } else if (sh.block_threads > 512u)
+            return DL_ERR_INVALID;  // not for the kernels below (and no shape rule asks for it)
+        else if (sh.rows)
             hipLaunchKernelGGL((dl_armed_list_kernel<Item, NMAX, true>), dim3(g), dim3(sh.block_threads), 0, stream, p, a);
         else
             hipLaunchKernelGGL((dl_armed_list_kernel<Item, NMAX, false>), dim3(g), dim3(sh.block_threads), 0, stream, p, a);
@@ -1094,6 +1236,7 @@ int launch_table(const Item *items, size_t n, dl_launch_shape sh, hipStream_t st
             a.direct = g <= a.direct_max ? 1u : 0u;
             a.own_word = g <= DL_DONE_WORDS && !a.trace_host ? 1u : 0u;
             g_dl.armed_words = a.own_word ? g : 1u;
+            g_dl.armed_counted = !a.own_word;
             if (pushed)
                 hipLaunchKernelGGL((dl_armed_table_kernel<Item, true>), dim3(g), dim3(sh.block_threads), 0, stream, slot,
                                    (uint32_t)m, sh.split, ps, a);
@@ -1145,6 +1288,35 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
     if (total == 0) return DL_OK;
     dl_launch_shape sh = dl_choose_shape(total, biggest, kmax);
     // one-shot requests, where the caller has not fixed the shape
+    // A signalled request that moves more than a little is an ordinary one-shot request, and a kernel of one workgroup behind
+    // it reports: the copy then has a full grid, loads that the caches may serve and no count at its end, for the second
+    // launch's 2 us.  Issue to done and the call, one kernel : two, all-gather over eight ranks 128 / 256 KiB per rank 11.6 / 12.5 :
+    // 11.6 / 12.3 us, 1 / 2 MiB 19.4 / 39.4 : 19.2 / 36.2, over sixteen 1 / 2 MiB 66 / 122 : 55 / 100; all-to-all over eight of
+    // 64 KiB chunks (8 MiB moved) 12.0 : 12.4, 128 / 256 KiB 13.0 / 16.9 : 12.4 / 15.2, 1 MiB 37.1 : 30.0.  (Not with stores that
+    // stay in the L2, nor where the caller has fixed the armed grid or wants the phase stamps.)
+    if (arm && arm->nowait && !arm->trace_host && !g_dl.cfg.armed_blocks && sh.policy != DL_POL_PLAIN && !sh.max_blocks) {
+        uint64_t moved = 0;
+        for (size_t i = 0; i < n; ++i)
+            moved += items[i].bytes * (std::is_same<Item, dl_swap_item>::value ? 4ull : 1ull + item_k(items[i]));
+        if (moved >= SIGNAL_DONE_MIN_BYTES) {
+            // (not what needs a table: a kernel that gave up on its table would be reported as done)
+            int rc = DL_OK;
+            bool sent = false;
+            if (n <= (size_t)list_cap<Item>::big)
+                rc = exec_list(items, n, stream, nullptr, &sent);
+            else if constexpr (!std::is_same<Item, dl_fused_item>::value)
+                sent = launch_offsets(items, n, sh, stream, &rc);
+            if (rc != DL_OK) return rc;
+            if (sent) {
+                hipLaunchKernelGGL(dl_signal_done_kernel, dim3(1), dim3(64), 0, stream, arm->done, arm->ticket);
+                DL_HIP(hipGetLastError());
+                g_dl.armed_words = 1;
+                g_dl.armed_counted = false;
+                *launched = true;
+                return DL_OK;
+            }
+        }
+    }
     const bool free_shape = !arm && !g_dl.cfg.tile_bytes && !g_dl.cfg.block_threads && !g_dl.cfg.fan_split && !sh.max_blocks;
     if (arm && !arm->nowait && g_dl.cfg.armed_blocks == 0) {
         // prelaunch mode, and the caller has not fixed the waiting grid: large requests wait in a gate kernel
@@ -1172,6 +1344,23 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
         if (sh.block_threads == 256u && t4 > ARMED_DIRECT_MAX && 3u * t8 <= 2u * t4) {
             sh.tile_bytes = 8192;
             sh.block_threads = 512;
+        }
+        // A waiting grid is capped in workgroups, so where eight wavefronts each would make several passes it takes sixteen:
+        // only in the kernels whose workgroups all poll the doorbell themselves, the others being built for 512 threads.
+        // All-gather over eight ranks, trigger to done and the call, 256 KiB / 1 MiB per rank 16.6 / 25.3 us with eight,
+        // 15.4 / 24.6 with sixteen.
+        if (!std::is_same<Item, dl_swap_item>::value && !arm->nowait && !sh.chain && !g_dl.cfg.armed_blocks && sh.block_threads == 512u &&
+            n <= (size_t)list_cap<Item>::big && armed_grid(t8, 512u, true) <= arm->direct_max) {
+            // ... and where the larger tiles do not leave a few workgroups with a quarter more rows than before (over fifteen
+            // ranks, 132 919 bytes per rank: 3 tiles of 16 KiB at most instead of 4 of 8, 20.7 us with eight, 21.6 with sixteen),
+            // nor many passes of unaligned loads (over eight, 1 500 003 bytes 40.2 : 44.7; over twelve, 1 MiB 61.5 : 53.1)
+            uint64_t t16 = 0;
+            for (size_t i = 0; i < n; ++i) t16 += dl_item_tiles(items[i], 16384);
+            const uint64_t g = armed_grid(t8, 512u, true), most8 = (t8 + g - 1) / g, most16 = (t16 + g - 1) / g;
+            if (t8 > g && 8u * most16 <= 5u * most8 && (t16 <= 4u * g || all_on_grid(items, n))) {
+                sh.tile_bytes = 16384;
+                sh.block_threads = 1024;
+            }
         }
     }
 
@@ -1409,7 +1598,7 @@ uint64_t standby_list(dl_klist<Item, NMAX> &l, size_t n, uint32_t max_tiles, Get
 }
 
 uint32_t dl_standby_fill(void *rec_mem, const dl_plan_item *items, size_t n, uint64_t activation, uint64_t ticket,
-                         uint64_t *done, uint32_t *arrive_clear, uint32_t max_tiles)
+                         uint64_t *done, uint32_t max_tiles)
 {
     const dl_config &c = g_dl.cfg;
     if (n == 0 || n > 64 || c.tile_bytes || c.block_threads || c.max_blocks || c.armed_blocks) return 0;
@@ -1433,7 +1622,6 @@ uint32_t dl_standby_fill(void *rec_mem, const dl_plan_item *items, size_t n, uin
     r.ticket_front = r.ticket_back = ticket;
     r.activation = activation;
     r.done = done;
-    r.arrive_clear = arrive_clear;
     r.arrivals = 0;
     // The record may live in device memory mapped write-combined: plain 8-byte stores in ascending order, of the
     // part that this kind of list uses and of the closing ticket.

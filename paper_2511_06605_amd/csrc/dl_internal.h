@@ -34,7 +34,8 @@ struct dl_state {
     int validate = 0;
     int last_hip = 0;
     int trace = 0;  // armed kernels record phase stamps
-    uint32_t armed_words = 0;  // completion words the armed kernel launched last reports in (see dl_arm::own_word)
+    uint32_t armed_words = 0;    // completion words the armed kernel launched last reports in (see dl_arm::own_word)
+    bool armed_counted = false;  // it counts its workgroups in (see dl_arm::arrive)
     dl_config cfg{};
 };
 extern dl_state g_dl;
@@ -67,12 +68,12 @@ struct dl_launch_shape {
 struct dl_arm {
     const uint64_t *bell;  // bell[0] = doorbell, bell[1] = cancel; both only ever grow.  Host-coherent memory, or device memory that the host writes through the BAR
     uint64_t *done;        // host-coherent: completion word of this ticket's slot
-    uint64_t *armed;       // host-coherent: "resident and polling" word of this ticket's slot
+    uint64_t *armed;       // host-coherent: "resident and polling" word of this ticket's slot; written by kernels that wait
     uint64_t *go;          // device: fan-out flags of this ticket's slot, one per group, DL_ARM_STRIDE bytes apart
     uint32_t *arrive;      // device: arrival counters of this slot: one per group, then the top one, same spacing
-    // A slot has two sets of counters, used by its requests in turn.  A request leaves its set as counted
-    // (no reset on the way to the completion word) and clears the other one before it waits: that set's last
-    // user has finished, and its next user is armed only after this request has.
+    // A slot has two sets of counters, used in turn by those of its requests that count.  Such a request leaves its
+    // set as counted (no reset on the way to the completion word) and clears the other one, if an earlier request has
+    // counted there (else null): that request has finished, and the set's next user is armed only after this one has.
     uint32_t *arrive_clear;
     uint64_t ticket;
     uint64_t limit_ticks;   // give up this long after becoming resident
@@ -177,10 +178,9 @@ constexpr uint32_t DL_STANDBY_IDLE_US = 2000;  // an executor that has waited th
 // dl_exec.hip: write the record of a request that fits an executor (at most 8 items, or at most 64 that are all
 // plain copies, and max_tiles tiles; default tunables) and return the number of completion words it will report in (one per tile up to DL_DONE_WORDS tiles,
 // else one, counted at the record, which must then be in device memory); 0 if it does not fit.  Launch an
-// executor that will read that record.  arrive_clear: the counter set of the ticket's slot that the request is
-// to clear (see dl_arm).
+// executor that will read that record.
 uint32_t dl_standby_fill(void *rec_mem, const dl_plan_item *items, size_t n, uint64_t activation, uint64_t ticket,
-                         uint64_t *done, uint32_t *arrive_clear, uint32_t max_tiles);
+                         uint64_t *done, uint32_t max_tiles);
 int dl_standby_launch(void *rec_mem, const dl_arm *a, hipStream_t stream);
 // dl_prelaunch.hip: hand the request to a waiting executor if it fits and one is fresh; *taken says whether.
 int dl_standby_try(const dl_plan_item *items, size_t n, bool *taken);
@@ -195,4 +195,6 @@ void *dl_bar_memory(size_t bytes);
 bool dl_armed_ready();
 bool dl_armed_untriggered(uint64_t ticket);  // armed, neither triggered nor cancelled, and not finished
 int dl_armed_begin(dl_arm *arm, hipStream_t *stream);  // next ticket's words; picks the library stream if *stream is null
-void dl_armed_commit(uint32_t done_words);             // the ticket of the last dl_armed_begin was launched and reports in that many words
+// The ticket of the last dl_armed_begin was launched and reports in that many words; counted: see dl_arm::arrive; at_once: it
+// waits for no doorbell and does not say when it is resident.
+void dl_armed_commit(uint32_t done_words, bool counted, bool at_once);

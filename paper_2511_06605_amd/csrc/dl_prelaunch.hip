@@ -58,6 +58,8 @@ struct arm_state {
     uint64_t seq = 0;  // last ticket issued
     uint64_t session = 0;  // which prelaunch session this is (tickets start over with each)
     uint32_t words[SLOTS] = {};  // completion words that the slot's current request reports in
+    bool at_once[SLOTS] = {};    // that request waits for no doorbell: it does not say that it is resident, only that it is done
+    uint8_t counted[SLOTS] = {};  // 1 + the slot's set of counters that a request has counted in and none has cleared since; 0: both are clear
     // standby pool: a stream per executor, when the executor armed last was armed, the ticket the slot served
     // last, and the slot that takes the next request
     bool standby = false;
@@ -125,6 +127,9 @@ void arm_limits(dl_arm *arm, uint32_t limit_us)
     arm->max_spins = (limit_us + 5000u) * 10u;
 }
 
+// The set of a slot's arrival counters (see dl_arm) that its next request may count in.
+uint32_t clear_set(uint32_t slot) { return g_arm.counted[slot] == 1u ? 1u : 0u; }
+
 uint64_t drain_ns() { return ((uint64_t)g_dl.cfg.arm_timeout_us + 5000ull) * 1000ull + 2000000000ull; }
 
 }  // namespace
@@ -175,9 +180,9 @@ int dl_armed_begin(dl_arm *arm, hipStream_t *stream)
     arm->gated = 0;
     arm->armed = &g_arm.host->armed[slot];
     arm->go = (uint64_t *)g_arm.dev->go[slot];
-    const uint32_t set = (uint32_t)(ticket / SLOTS) & 1u;
+    const uint32_t set = clear_set(slot);
     arm->arrive = (uint32_t *)g_arm.dev->arrive[slot][set];
-    arm->arrive_clear = (uint32_t *)g_arm.dev->arrive[slot][set ^ 1u];
+    arm->arrive_clear = g_arm.counted[slot] ? (uint32_t *)g_arm.dev->arrive[slot][set ^ 1u] : nullptr;
     arm->ticket = ticket;
     arm_limits(arm, g_dl.cfg.arm_timeout_us);
     arm->direct = 0;
@@ -337,15 +342,13 @@ int dl_standby_try(const dl_plan_item *items, size_t n, bool *taken)
     // caller that comes back faster than the launch gap waits here for what it would have waited for anyway.
     if (wait_word(&g_arm.host->sb_resident[e], g_sb_act[e], 20000ull, nullptr) != DL_OK) return DL_OK;
     // a request of more tiles than completion words counts its workgroups in at the record: device memory only
-    const uint32_t set = (uint32_t)(ticket / SLOTS) & 1u;  // as in dl_armed_begin: this ticket's set; it clears the other
     const uint32_t words = dl_standby_fill(standby_rec(e), items, n, g_sb_act[e], ticket, g_arm.host->done[slot],
-                                           (uint32_t *)g_arm.dev->arrive[slot][set ^ 1u],
                                            g_sb_rec_dev ? DL_STANDBY_GRID : DL_DONE_WORDS);
     if (words == 0) return DL_OK;
     standby_store(standby_bell(e), g_sb_act[e]);  // the executor's doorbell, behind its record
     const bool in_time = now_ns() - g_arm.sb_armed_at[e] + 100000ull < g_arm.sb_limit_ns[e];
     __atomic_store_n(&g_arm.host->armed[slot], ticket, __ATOMIC_RELAXED);             // it was resident already
-    dl_armed_commit(words);
+    dl_armed_commit(words, false, false);
     g_arm.sb_ticket[e] = ticket;
     g_arm.sb_next = (e + 1) % DL_STANDBY_POOL;
     if (in_time) {
@@ -359,10 +362,6 @@ int dl_standby_try(const dl_plan_item *items, size_t n, bool *taken)
     DL_HIP(hipStreamSynchronize(g_arm.sb_stream[e]));
     const int served = wait_done(ticket, 0, nullptr);
     if (served != DL_OK) {
-        // what the executor would have done for the slot besides copying: clear the other set of counters
-        DL_HIP(hipMemsetAsync(g_arm.dev->arrive[slot][set ^ 1u], 0, sizeof g_arm.dev->arrive[slot][set ^ 1u],
-                              g_arm.sb_stream[e]));
-        DL_HIP(hipStreamSynchronize(g_arm.sb_stream[e]));
         for (uint32_t w = 0; w < words; ++w)
             __atomic_store_n(&g_arm.host->done[slot][w], ticket, __ATOMIC_RELEASE);
     }
@@ -370,10 +369,13 @@ int dl_standby_try(const dl_plan_item *items, size_t n, bool *taken)
     return standby_arm(e);
 }
 
-void dl_armed_commit(uint32_t done_words)
+void dl_armed_commit(uint32_t done_words, bool counted, bool at_once)
 {
     ++g_arm.seq;
-    g_arm.words[g_arm.seq % SLOTS] = done_words >= 1 && done_words <= DL_DONE_WORDS ? done_words : 1u;
+    const uint32_t slot = (uint32_t)(g_arm.seq % SLOTS);
+    g_arm.at_once[slot] = at_once;
+    if (counted) g_arm.counted[slot] = (uint8_t)(1u + clear_set(slot));
+    g_arm.words[slot] = done_words >= 1 && done_words <= DL_DONE_WORDS ? done_words : 1u;
     t_dl_last.session = g_arm.session;  // the calling thread's most recent request
     t_dl_last.ticket = g_arm.seq;
 }
@@ -538,14 +540,21 @@ int dl_trigger(uint64_t ticket)
 // and trigger requests meanwhile.  (The words live until dl_prelaunch_stop, which must not run beside a wait.)
 int dl_wait_armed(uint64_t ticket, uint64_t timeout_ns)
 {
-    const uint64_t *word;
+    const uint64_t *words;
+    uint32_t count = 1;
     {
         DL_LOCKED;
         if (!g_arm.started) return DL_ERR_STATE;
         if (ticket == 0 || ticket > g_arm.seq) return DL_ERR_INVALID;
-        word = &g_arm.host->armed[ticket % SLOTS];
+        const uint32_t slot = (uint32_t)(ticket % SLOTS);
+        words = &g_arm.host->armed[slot];
+        if (g_arm.at_once[slot]) {
+            if (g_arm.seq - ticket >= SLOTS) return DL_OK;  // its slot has been reused since, which waited for it
+            words = g_arm.host->done[slot];
+            count = g_arm.words[slot] ? g_arm.words[slot] : 1u;
+        }
     }
-    return wait_word(word, ticket, timeout_ns, nullptr);
+    return wait_words(words, count, ticket, timeout_ns, nullptr);
 }
 
 int dl_wait(uint64_t ticket, uint64_t timeout_ns)

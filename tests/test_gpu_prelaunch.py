@@ -223,6 +223,65 @@ def test_batch_swap_armed_twice_restores(ref, armed):
     assert np.array_equal(d.host(), arena) and d.guards_intact()
 
 
+def test_slots_reused_by_requests_that_count_and_that_do_not(ref, armed):
+    """400 requests, so that every slot is used six times, in no particular order of what reports: a completion word per
+    workgroup, a count in one of the slot's two sets of counters (which the next request that counts clears), a kernel
+    behind the copy; armed or at once."""
+    W = 8
+    rng = np.random.default_rng(11)
+    sizes = [512, 4 * KiB + 3, 64 * KiB, 100 * KiB, 170 * KiB + 5, 256 * KiB, 1 * MiB + 16]
+    ins = {B: inputs.allgather_inputs(W, B, seed=B) for B in sizes}
+    d_in = {B: [DevBuf(B, fill=a) for a in ins[B]] for B in sizes}
+    d_out = {B: [DevBuf(W * B) for _ in range(W)] for B in sizes}
+    sync()
+    try:
+        for it in range(400):
+            B, at_once = sizes[rng.integers(len(sizes))], bool(rng.integers(2))
+            dl.dl_set_mode(dl.DL_MODE_SIGNAL if at_once else dl.DL_MODE_PRELAUNCH)
+            dl.dl_allgather([b.ptr() for b in d_in[B]], [b.ptr() for b in d_out[B]], B)
+            if rng.integers(4) == 0 and at_once:
+                dl.dl_wait_armed()      # a request without a doorbell: waits for its end
+            if not at_once:
+                dl.dl_trigger()
+            dl.dl_wait()
+            if it % 40 == 0:
+                got = d_out[B][it // 40 % W]
+                assert np.array_equal(got.host(), np.concatenate(ins[B])) and got.guards_intact(), f"request {it}, {B} bytes"
+    finally:
+        dl.dl_set_mode(dl.DL_MODE_PRELAUNCH)
+    for B in sizes:
+        for r, w in zip(d_out[B], ref.allgather(ins[B])):
+            assert np.array_equal(r.host(), w) and r.guards_intact()
+
+
+# at once: one kernel, or (from 12 MiB moved) an ordinary one and a second that reports; lists in the kernel arguments of
+# either, as offsets, in a table; armed: a tile per workgroup and several, of eight and of sixteen wavefronts
+@pytest.mark.parametrize("own_stream", [True, False])
+@pytest.mark.parametrize("mode", [dl.DL_MODE_SIGNAL, dl.DL_MODE_PRELAUNCH])
+@pytest.mark.parametrize("n,size,off", [
+    (1, 6 * MiB - 16, 0), (1, 6 * MiB, 0), (1, 6 * MiB + 1, 3), (8, 768 * KiB, 0), (8, 128 * KiB, 0), (8, 129 * KiB + 16, 0), (8, 1 * MiB, 5), (8, 4 * MiB, 0),
+    (30, 40 * KiB + 7, 1), (30, 140 * KiB + 7, 1), (64, 96 * KiB, 0), (64, 96 * KiB - 128, 0), (100, 61440, 0), (100, 63 * KiB, 9), (300, 40000, 0)])
+def test_copies_around_the_armed_shapes(ref, armed, n, size, off, mode, own_stream):
+    rng = np.random.default_rng(n + size)
+    slot = (size + 511) // 256 * 256
+    arena = rng.integers(0, 256, 2 * n * slot + 512, dtype=np.uint8)
+    at = rng.permutation(2 * n)
+    shift = rng.integers(0, off + 1, 2 * n)
+    descs = [(int(at[i]) * slot + int(shift[i]), int(at[n + i]) * slot + int(shift[n + i]), size) for i in range(n)]
+    want = ref.batch_copy([arena], [(0, s, 0, d, m) for s, d, m in descs])[0]
+    d = DevBuf(arena.size, fill=arena)
+    sync()
+    dl.dl_set_mode(mode)
+    try:
+        dl.dl_batch_copy([(d.ptr(s), d.ptr(t), m) for s, t, m in descs], None if own_stream else stream())
+        if mode == dl.DL_MODE_PRELAUNCH:
+            dl.dl_trigger()
+        dl.dl_wait()
+    finally:
+        dl.dl_set_mode(dl.DL_MODE_PRELAUNCH)
+    assert np.array_equal(d.host(), want) and d.guards_intact()
+
+
 def test_sources_written_after_arming_are_seen(ref, armed):
     """The point of prelaunch: the request is armed first, its inputs are
     produced afterwards, and only then is the doorbell rung.  The same device
