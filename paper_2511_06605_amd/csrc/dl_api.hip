@@ -172,6 +172,34 @@ long lower_batch_inferred(const dl_copy_desc *desc, size_t n, sink &s)
     return (long)m;
 }
 
+// The usual batch, in which no two copies read the same range: straight to the plain copies that lower_batch or
+// lower_batch_inferred (infer) would come to, without their 88-byte items in between.  -1 where there is something to infer
+// or to refuse, else the number of copies in `out`.
+long lower_batch_plain(const dl_copy_desc *desc, size_t n, bool infer, std::vector<dl_plain_item> &out)
+{
+    static std::vector<uint32_t> slots;  // open addressing over the copies so far, by source: index + 1, 0 = empty
+    size_t want = 16, m = 0;
+    while (want < 2 * n) want *= 2;
+    if (infer) slots.assign(want, 0);
+    if (out.size() < n) out.resize(n);
+    for (size_t i = 0; i < n; ++i) {
+        const dl_copy_desc &d = desc[i];
+        if (d.bytes == 0) continue;
+        if (!d.src || !d.dst) return -1;
+        if (d.src == d.dst) continue;
+        if (infer) {
+            size_t q = (size_t)(((uint64_t)d.src * 0x9E3779B97F4A7C15ull) >> 20) & (want - 1);
+            for (; slots[q]; q = (q + 1) & (want - 1)) {
+                const dl_plain_item &it = out[slots[q] - 1];
+                if (it.src == d.src && it.bytes == d.bytes) return -1;
+            }
+            slots[q] = (uint32_t)m + 1;
+        }
+        out[m++] = {(const char *)d.src, (char *)d.dst, d.bytes};
+    }
+    return (long)m;
+}
+
 // One read-once/write-k item per token that has a destination; receive buffers
 // fill up in token order.
 long lower_token_dispatch(const void *const *in, void *const *out, int W, const uint32_t *tokens, size_t row,
@@ -393,6 +421,18 @@ int execute_in(int mode, const dl_plan_item *items, size_t n, void *stream)
             return dl_exec_plain(g_plain.data(), n, hs, armp, launched);
         }
         return dl_exec_fused(reinterpret_cast<const dl_fused_item *>(items), n, hs, armp, launched);
+    });
+}
+
+// The first n plain copies in g_plain, in a mode that takes them as they are.
+int execute_plain(size_t n, void *stream)
+{
+    if (!g_dl.inited) return DL_ERR_STATE;
+    if (dl_device_error_pending()) return DL_ERR_LOST;
+    if (n == 0) return DL_OK;
+    t_dl_last.mode = g_dl.mode;
+    return run_in_mode(stream, [&](hipStream_t hs, const dl_arm *armp, bool *launched) {
+        return dl_exec_plain(g_plain.data(), n, hs, armp, launched);
     });
 }
 
@@ -654,6 +694,12 @@ int dl_parse_config(const char *text, dl_config *cfg)
 int dl_batch_copy(const dl_copy_desc *desc, size_t n, void *stream)
 {
     DL_LOCKED;
+    // (the hazard check, and the modes that look at the lowered list first, want the other form)
+    const bool as_is = !g_dl.validate && (g_dl.mode == DL_MODE_ONESHOT || g_dl.mode == DL_MODE_PRELAUNCH || g_dl.mode == DL_MODE_SIGNAL);
+    if (as_is && n > 1 && n < (1u << 30) && desc) {
+        const long m = lower_batch_plain(desc, n, g_dl.cfg.infer_broadcast != 0, g_plain);
+        if (m >= 0) return execute_plain((size_t)m, stream);
+    }
     if (g_dl.cfg.infer_broadcast && n > 1)
         return lower_and_execute([&](sink &s) { return lower_batch_inferred(desc, n, s); }, stream, DL_OP_BATCH);
     return lower_and_execute([&](sink &s) { return lower_batch(desc, n, s); }, stream, DL_OP_BATCH);

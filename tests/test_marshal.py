@@ -130,6 +130,31 @@ def test_triples(calls, call, name):
     assert len(seen) == 3
 
 
+# integers read where they lie: none to three digits of 30 bits, signs, what is no exact int, not a triple or no tuple, at the
+# front of a list and behind others
+@pytest.mark.parametrize("call,name", [("batch_copy", "dl_batch_copy"), ("batch_swap", "dl_batch_swap")])
+def test_triples_of_integers(calls, call, name):
+    m, seen = calls
+    edges = [0, 1, 2 ** 30 - 1, 2 ** 30, 2 ** 47 + 5, 2 ** 60 - 1, 2 ** 60, 2 ** 63, 2 ** 64 - 1, 2 ** 70 + 3, -1, -2 ** 31, True]
+    plain = [(v, 2 ** 40 + v, 7) for v in edges if v is not True]
+    odd = [(True, 1, 2), [1, 2, 3], (Tensor(0x99), 4, 5), (np.int64(6), 7, np.uint8(8)), (None, 1, 2), range(3)]
+    mask = 2 ** 64 - 1
+
+    def words(t):
+        return tuple((binding._addr(v) or 0) & mask if i < 2 else int(v) & mask for i, v in enumerate(t))
+
+    for descs in [plain, plain[:5], *([o] + plain[:3] for o in odd), *(plain[:3] + [o] + plain[3:] for o in odd)]:
+        for form in (list, tuple, iter):
+            seen.clear()
+            assert getattr(m, call)(form(descs), None) == -5
+            assert seen == [(name, [words(t) for t in descs], 0)]
+    for bad in (plain[:2] + [(1, 2)], [(1, 2, 3, 4)], [(1, 2, 3), 5], [(1, 2, "x")], [("x", 1, 2)]):
+        seen.clear()
+        with pytest.raises((TypeError, ValueError)):
+            getattr(m, call)(bad, None)
+        assert not seen
+
+
 def test_dispatch_masks(calls):
     m, seen = calls
     mask = np.arange(6, dtype=np.uint8).reshape(3, 2)
