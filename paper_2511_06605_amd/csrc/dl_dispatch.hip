@@ -69,7 +69,10 @@ __device__ __forceinline__ const char *dl_dispatch_source(const dispatch_args &a
 // On the grid (see dl_rows_body): what one wavefront copies of a token's row, 1 KiB rows `row0`, row0 + stride, ...,
 // ROWS of them.  Every row is loaded once, into registers, as soon as the token is known; the loads are in
 // flight while the wavefront finds out where the row goes (128 tokens per rank, mask on the device: 18.1 -> 16.4 us).
-template <int POL, int ROWS>
+// AHEAD: what decides where the row goes comes from memory too, and is worked on before the row is waited for.  Then every
+// lane loads, past the row's end its first 16 bytes: with loads that some path leaves out the compiler cannot tell how many
+// are outstanding, and waits for the row together with whatever was asked for in front of it.
+template <int POL, int ROWS, bool AHEAD = false>
 struct dispatch_row {
     const char *src;
     uint64_t bytes;
@@ -88,7 +91,7 @@ struct dispatch_row {
         stride = a.token_waves;
 #pragma unroll
         for (int i = 0; i < ROWS; ++i)
-            if (byte(i) < bytes) v[i] = dl_ld16<POL>(src + byte(i));
+            if (AHEAD || byte(i) < bytes) v[i] = dl_ld16<POL>(src + (byte(i) < bytes ? byte(i) : 0));
     }
     // The token is number `in_group` of the 64 whose ranks the lanes hold in `mine`; `taken(j)` rows were placed in
     // receive buffer j before the group.
@@ -96,15 +99,34 @@ struct dispatch_row {
     __device__ __forceinline__ void store(const dispatch_args &a, uint32_t in_group, uint32_t mine, Taken taken) const
     {
         const uint64_t before = (1ull << in_group) - 1ull;
+        char *d[DISPATCH_W];
+        if constexpr (AHEAD) {
+#pragma unroll
+            for (int j = 0; j < DISPATCH_W; ++j) {
+                const uint64_t votes = __ballot((mine >> j) & 1u);
+                d[j] = (votes >> in_group) & 1u ? a.out[j] + (uint64_t)(taken(j) + (uint32_t)__popcll(votes & before)) * bytes : nullptr;
+            }
+            arrived();
+        }
 #pragma unroll
         for (int j = 0; j < DISPATCH_W; ++j) {
-            const uint64_t votes = __ballot((mine >> j) & 1u);
-            if (!((votes >> in_group) & 1u)) continue;
-            char *const d = a.out[j] + (uint64_t)(taken(j) + (uint32_t)__popcll(votes & before)) * bytes;
+            if constexpr (AHEAD) {
+                if (!d[j]) continue;
+            } else {
+                const uint64_t votes = __ballot((mine >> j) & 1u);
+                if (!((votes >> in_group) & 1u)) continue;
+                d[j] = a.out[j] + (uint64_t)(taken(j) + (uint32_t)__popcll(votes & before)) * bytes;
+            }
 #pragma unroll
             for (int i = 0; i < ROWS; ++i)
-                if (byte(i) < bytes) dl_st16<POL>(d + byte(i), v[i]);
+                if (byte(i) < bytes) dl_st16<POL>(d[j] + byte(i), v[i]);
         }
+    }
+    // One wait for the whole row: at each use it would be waited for together with the stores in between.
+    __device__ __forceinline__ void arrived() const
+    {
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) asm volatile("" ::"v"(v[i]));
     }
 };
 
@@ -221,13 +243,24 @@ __global__ void __launch_bounds__(64 * MAX_WAVES) dl_dispatch_pushed_kernel(cons
         dl_dispatch_off_grid<POL, ROWS>(a, first + t, (first + t) % GROUP, row0, mine, taken);
 }
 
-// Every byte of a mask word to 0 or 1.
-__device__ __forceinline__ uint64_t dl_mask_fold(uint64_t w)
+// Every byte of half a mask word to 0 or 1: adding 0x7f to its low seven bits carries into the eighth unless they are 0.
+// keep: what of the result counts.
+__device__ __forceinline__ uint32_t dl_mask_fold(uint32_t w, uint32_t keep = 0x01010101u)
 {
-    w |= w >> 4;
-    w |= w >> 2;
-    w |= w >> 1;
-    return w & 0x0101010101010101ull;
+    return (((w & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w) >> 7 & keep;
+}
+
+// Sum over the wavefront, which lane 63 has: within rows of 16 lanes by shifts, then from row to row, all in the vector ALU
+// (shuffles go through the LDS, whose pipe the wavefronts of a compute unit share).
+__device__ __forceinline__ uint32_t dl_wave_sum63(uint32_t x)
+{
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);  // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);  // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);  // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);  // row_shr:8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);  // row_bcast:15
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);  // row_bcast:31
+    return x;
 }
 
 // The mask in device memory: how many rows the tokens in front of a group take in each receive buffer, and the ranks of
@@ -262,60 +295,78 @@ struct dispatch_counts {
         __shared__ uint32_t part[MAX_WAVES][4];
         const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const uint32_t waves = blockDim.x >> 6;
-        const DL_GLOBAL uint64_t *words = dl_global<uint64_t>(mask);
-        const uint64_t own = group0 + lane < tokens ? words[group0 + lane] : 0ull;
-        // two tokens per 16-byte load, BATCH loads in flight; a thread sums at most DL_DISPATCH_DEVICE_MAX_TOKENS / 64
+        // (the last group's lanes past the last token read that one's word)
+        uint64_t own = dl_global<uint64_t>(mask)[group0 + lane < tokens ? group0 + lane : tokens - 1u];
+        // two tokens per 16-byte load, up to BATCH loads in flight; a thread sums at most DL_DISPATCH_DEVICE_MAX_TOKENS / 64
         // words, so a byte of the sum does not overflow
         static_assert(DL_DISPATCH_DEVICE_MAX_TOKENS / 64 <= 255, "bytewise sums");
-        constexpr uint32_t BATCH = 4;
+        constexpr uint32_t BATCH = 6;
         const uint32_t step = 2u * blockDim.x, i0 = 2u * threadIdx.x;
         dl_u32x4 w[BATCH];
-        const auto fetch = [&](uint32_t i) {
+        // Lanes past the group's beginning load the mask's first words (group0 is a multiple of GROUP: there are any) and count none
+        // of them, loads that no lane needs are left out for all: whether a load is outstanding then depends on no lane.
+        const auto fetch = [&](uint32_t base) {
 #pragma unroll
             for (uint32_t u = 0; u < BATCH; ++u) {
-                w[u] = dl_u32x4{0, 0, 0, 0};
-                if (i + u * step < group0) w[u] = dl_ld16<DL_POL_WT>((const char *)mask + 8ull * (i + u * step));
+                const uint32_t i = base + i0 + u * step;
+                if (base + u * step < group0) w[u] = dl_ld16<DL_POL_WT>((const char *)mask + 8ull * (i < group0 ? i : 0u));
             }
         };
-        uint64_t sum = 0;
-        const auto add = [&] {
+        uint32_t lo = 0, hi = 0;
+        const auto add = [&](uint32_t base) {
 #pragma unroll
-            for (uint32_t u = 0; u < BATCH; ++u)
-                sum += dl_mask_fold(w[u].x | ((uint64_t)w[u].y << 32)) + dl_mask_fold(w[u].z | ((uint64_t)w[u].w << 32));
+            for (uint32_t u = 0; u < BATCH; ++u) {
+                if (base + u * step >= group0) break;
+                const uint32_t keep = base + i0 + u * step < group0 ? 0x01010101u : 0u;
+                lo += dl_mask_fold(w[u].x, keep) + dl_mask_fold(w[u].z, keep);
+                hi += dl_mask_fold(w[u].y, keep) + dl_mask_fold(w[u].w, keep);
+            }
         };
-        fetch(i0);
+        fetch(0);
         between();
-        add();
-        for (uint32_t i = i0 + BATCH * step; i < group0; i += BATCH * step) {
-            fetch(i);
-            add();
+        add(0);
+        for (uint32_t base = BATCH * step; base < group0; base += BATCH * step) {
+            fetch(base);
+            add(base);
         }
         // to 16 bits a rank, two ranks a word
-        const uint32_t lo = (uint32_t)sum, hi = (uint32_t)(sum >> 32);
         c[0] = lo & 0x00FF00FFu;
         c[1] = (lo >> 8) & 0x00FF00FFu;
         c[2] = hi & 0x00FF00FFu;
         c[3] = (hi >> 8) & 0x00FF00FFu;
         static_assert(DL_DISPATCH_DEVICE_MAX_TOKENS < 65536, "16-bit counts");
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            for (int o = 32; o; o >>= 1) c[q] += __shfl_xor(c[q], o);
-            if (lane == 0) part[wave][q] = c[q];
-        }
-        __syncthreads();
+        for (int q = 0; q < 4; ++q) c[q] = dl_wave_sum63(c[q]);
+        if (waves == 1u) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            uint32_t s = 0;
-            for (uint32_t w = 0; w < waves; ++w) s += part[w][q];
-            c[q] = __builtin_amdgcn_readfirstlane(s);
-        }
-        const uint64_t bits = dl_mask_fold(own);
-        mine = 0;
+            for (int q = 0; q < 4; ++q) c[q] = (uint32_t)__builtin_amdgcn_readlane((int)c[q], 63);
+        } else {
+            if (lane == 63u) {
 #pragma unroll
-        for (int j = 0; j < DISPATCH_W; ++j) mine |= ((uint32_t)(bits >> (8 * j)) & 1u) << j;
+                for (int q = 0; q < 4; ++q) part[wave][q] = c[q];
+            }
+            __syncthreads();
+            // a lane per word, rows of four wavefronts summed by shifts
+            static_assert(MAX_WAVES * 4 <= 32, "two rows of lanes");
+            uint32_t x = lane < 4u * waves ? part[lane >> 2][lane & 3u] : 0u;
+            x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);  // row_shr:4
+            x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);  // row_shr:8
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                c[q] = (uint32_t)__builtin_amdgcn_readlane((int)x, 12 + q) + (uint32_t)__builtin_amdgcn_readlane((int)x, 28 + q);
+        }
+        asm volatile("" : "+v"(own));  // not looked at (and so waited for) earlier
+        const uint32_t low = dl_mask_fold((uint32_t)own), high = dl_mask_fold((uint32_t)(own >> 32));
+        // four low bits into the top four: the multiplication moves bit 8 j to bit 24 + j
+        mine = group0 + lane < tokens ? ((low * 0x01020408u) >> 24 & 0xFu) | ((high * 0x01020408u) >> 20 & 0xF0u) : 0u;
     }
 };
 
+// What bounds it beyond its bytes: the counting, by every workgroup, in front of the first store.  It runs while the row is on
+// its way, in the vector ALU alone (shuffles of a whole compute unit's wavefronts kept the LDS busy for 1 us a pass).  Row
+// waited for first and sums by shuffles : this, one mask and set of buffers after the other in a graph, 2 / 16 / 64 tokens per
+// rank of 4 KiB 4.2 / 4.3 / 5.2 : 2.9 / 3.2 / 4.1 us, of 14 KiB 4.2 / 5.1 / 9.2 : 2.9 / 3.9 / 8.3; in a stream of launches 128 /
+// 253 per rank of 4 KiB 7.3 / 9.9 : 6.9 / 8.7, 192 / 253 / 512 of 14 KiB 25.6 / 32.1 / 59.3 : 23.0 / 29.2 / 57.1 (6.4 TB/s).
 template <int POL, bool ON_GRID, int ROWS>
 __global__ void __launch_bounds__(64 * MAX_WAVES) dl_dispatch_mask_kernel(const dispatch_args a, const uint8_t *__restrict__ mask)
 {
@@ -332,11 +383,15 @@ __global__ void __launch_bounds__(64 * MAX_WAVES) dl_dispatch_mask_kernel(const 
                      "s"(a.out[6]), "s"(a.out[7]), "s"(a.row_bytes), "s"(a.first_token[1]), "s"(a.first_token[2]),
                      "s"(a.first_token[3]), "s"(a.first_token[4]), "s"(a.first_token[5]), "s"(a.first_token[6]),
                      "s"(a.first_token[7]));
-    dispatch_row<POL, ROWS> row;
+    dispatch_row<POL, ROWS, true> row;
     dispatch_counts c;
     c.count(mask, a.tokens, group0, [&] {
-        if constexpr (ON_GRID)
-            if (valid) row.load(a, first + t, row0);  // behind the mask's first loads: those come back first
+        if constexpr (ON_GRID) {
+            row.load(a, valid ? first + t : a.tokens - 1u, row0);  // behind the mask's first loads: those come back first, and are counted meanwhile
+            // ... but where the loads stream, all rows of a workgroup are waited for here: loads in one burst and stores in the
+            // next are then the faster order (see dispatch_setup)
+            if constexpr (POL == DL_POL_STREAM_IN) row.arrived();
+        }
     });
     if (!valid) return;
     if constexpr (ON_GRID) {
@@ -459,13 +514,24 @@ int dispatch_setup(const void *const *in, void *const *out, const uint32_t *toke
         // (128 of 4 KiB 6.8 : 7.3), and 512 tokens of 20 rows take 12.5 : 13.1.
         waves = 1;
         sh->rows = mask_on_device && rows * total > 5120u ? 2 : 1;
+    } else if (mask_on_device && sh->policy == DL_POL_STREAM_IN && rows >= 3u && rows <= in_one) {
+        // Where sources stream, four wavefronts of up to four rows, all loaded before any is stored (see dl_dispatch_mask_kernel).
+        // Eight of two, the counting behind the loads in time : eight of two, loads in a burst : this, and last this with
+        // stores as soon as a row is there, three sets in turn: 334 / 430 / 512 per rank of 4 KiB 12.1 / 14.9 / 16.8 : 12.0 / 15.6 /
+        // 18.1 : 11.0 / 14.1 / 16.2 : 10.8 / 16.7 / 18.5 us, 170 / 220 / 253 of 8 KiB 12.3 / 15.1 / 16.7 : 12.0 / 15.6 / 17.4 :
+        // 11.1 / 14.0 / 15.7 : 10.9 / 15.8 / 16.7, 128 / 192 of 10 KiB (four wavefronts of three, then) 12.1 / 16.4 : 10.7 /
+        // 16.4 : 10.8 / 15.6 : 10.4 / 17.5, 112 / 128 of 14 KiB (four of four) 14.1 / 15.7 : 12.7 / 14.1 : 12.7 / 14.2 : 13.5 /
+        // 15.0; 450 / 590 of 3 KiB 12.5 / 17.6 before, 11.6 / 16.1 this way.  (Outside this range of sizes, the other way round: 150
+        // of 14 KiB 18.7 without the burst, 19.8 with it.  Shorter rows stay with eight of two: 700 of 2 KiB 13.4, 14.0 with four.)
+        waves = 4;
+        sh->rows = rows < 4u ? (int)rows : 4;
     } else if (sh->policy != DL_POL_STREAM && rows > 4u && rows <= in_one) {
         // Between: up to four rows of a wavefront in flight together.  Three sets in turn, mask on the host, 192 / 256 per
         // rank of 8 KiB 12.5 / 16.8 : 12.1 / 15.9 us, 128 / 192 of 10 KiB 10.8 / 16.3 : 10.4 / 15.3, 128 of 14 KiB 14.9 : 14.1
         // (one set or sets that fit no cache +-3 %; 384 of 4 KiB 13.3 : 15.9 and 64 of 20 KiB 11.0 : 11.6, which stay).  Mask on the
-        // device: 13 rows and more likewise while sources stream (128 of 14 KiB 16.5 : 15.9; 512 59.8 : 60.8), and 9 to 12
-        // rows, whose five or six wavefronts of two lie badly on four SIMDs, by four of three (192 / 384 / 512 of 10 KiB
-        // 19.6 / 35.2 / 45.7 : 17.0 / 33.5 / 44.6; 768, in sets that fit no cache, 75.5 : 79.3).
+        // device, less than what streams: 13 rows and more likewise (512 of 14 KiB, which stream, 59.8 : 60.8), and 9 to 12
+        // rows, whose five or six wavefronts of two lie badly on four SIMDs, by four of three (384 / 512 of 10 KiB
+        // 35.2 / 45.7 : 33.5 / 44.6; 768, in sets that fit no cache, 75.5 : 79.3).
         if (!mask_on_device ? sh->policy == DL_POL_STREAM_IN : rows >= 13u && sh->policy != DL_POL_STREAM_OUT) {
             waves = 4;
             sh->rows = 4;

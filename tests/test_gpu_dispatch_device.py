@@ -96,6 +96,17 @@ def test_shapes_of_a_workgroup(ref, counts, row):
     run(ref, counts, row, seed=sum(counts) + row, check_host_entry=True)
 
 
+# The mask's counting: every value of a byte that is not 0, groups in front of which one wavefront or eight count, a load of
+# all lanes or of some, more loads than are in flight together (3072 tokens by four wavefronts, 6144 by eight); the last
+# workgroup with tokens past the end; ranks without tokens at either end; 88 and 144 MiB by the bound that the policy goes by.
+@pytest.mark.parametrize("counts,row", [
+    ([8] * 8, 1024), ([9] * 7 + [2], 512), ([0, 0, 129, 0, 0, 0, 0, 0], 4096), ([0] * 7 + [511], 256), ([600, 0, 0, 0, 0, 0, 0, 0], 3072), ([78] * 8, 5120),
+    ([313] * 8, 4096), ([313] * 7 + [312], 4096), ([392] * 7 + [397], 4096), ([512] * 8, 4096), ([513] + [512] * 7, 4096), ([157] * 8, 8192), ([220] * 7 + [3], 7 * 1024 + 16),
+    ([410] * 8, 9 * 1024), ([800] * 8, 2048), ([0, 1279, 1281, 1280, 1280, 1280, 2560, 1280], 16)])
+def test_counting_the_mask(ref, counts, row):
+    run(ref, counts, row, seed=sum(counts) + row, top_k=64, mask_value=[1, 0x80, 255, 2, 0x7F, 0x10, 3, 0xFE], drop=7)
+
+
 def test_mask_produced_on_the_stream_just_before(ref):
     """The mask is written by a kernel on the same stream and the dispatch follows without a synchronisation in
     between: the three launches are ordered behind it.  Twice, with the mask buffer reused."""
