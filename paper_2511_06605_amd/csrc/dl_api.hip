@@ -111,6 +111,13 @@ long lower_batch(const dl_copy_desc *desc, size_t n, sink &s)
     return (long)s.n;
 }
 
+// Where the search for a copy's range begins in a table of slots; of address and length, since a batch may cut one buffer
+// into prefixes (1 000 copies of one source, each of another length: 6 us to lower, and 360 by the address alone).
+inline uint64_t range_hash(const dl_copy_desc &d)
+{
+    return (((uint64_t)d.src * 0x9E3779B97F4A7C15ull) ^ ((uint64_t)d.bytes * 0xC2B2AE3D27D4EB4Full)) >> 20;
+}
+
 // dl_batch_copy with broadcast inference (Sec. VI): copies with the same source
 // address and the same byte count become one read-once/write-k item, in order of
 // first appearance, at most DL_PLAN_FANOUT destinations per item.
@@ -147,8 +154,7 @@ long lower_batch_inferred(const dl_copy_desc *desc, size_t n, sink &s)
         if (d.bytes == 0) continue;
         if (!d.src || !d.dst) return DL_ERR_INVALID;
         if (d.src == d.dst) continue;
-        const uint64_t h = ((uint64_t)d.src * 0x9E3779B97F4A7C15ull) ^ ((uint64_t)d.bytes * 0xC2B2AE3D27D4EB4Full);
-        size_t q = (size_t)(h >> 20) & (want - 1);
+        size_t q = (size_t)range_hash(d) & (want - 1);
         for (;;) {
             const uint32_t g = slots[q];
             if (g == 0) {  // first copy from this (src, bytes)
@@ -177,7 +183,7 @@ long lower_batch_inferred(const dl_copy_desc *desc, size_t n, sink &s)
 // or to refuse, else the number of copies in `out`.
 long lower_batch_plain(const dl_copy_desc *desc, size_t n, bool infer, std::vector<dl_plain_item> &out)
 {
-    static std::vector<uint32_t> slots;  // open addressing over the copies so far, by source: index + 1, 0 = empty
+    static std::vector<uint32_t> slots;  // open addressing over the copies so far: index + 1, 0 = empty
     size_t want = 16, m = 0;
     while (want < 2 * n) want *= 2;
     if (infer) slots.assign(want, 0);
@@ -188,7 +194,7 @@ long lower_batch_plain(const dl_copy_desc *desc, size_t n, bool infer, std::vect
         if (!d.src || !d.dst) return -1;
         if (d.src == d.dst) continue;
         if (infer) {
-            size_t q = (size_t)(((uint64_t)d.src * 0x9E3779B97F4A7C15ull) >> 20) & (want - 1);
+            size_t q = (size_t)range_hash(d) & (want - 1);
             for (; slots[q]; q = (q + 1) & (want - 1)) {
                 const dl_plain_item &it = out[slots[q] - 1];
                 if (it.src == d.src && it.bytes == d.bytes) return -1;
