@@ -546,10 +546,10 @@ int dl_wait_armed(uint64_t ticket, uint64_t timeout_ns)
         DL_LOCKED;
         if (!g_arm.started) return DL_ERR_STATE;
         if (ticket == 0 || ticket > g_arm.seq) return DL_ERR_INVALID;
+        if (g_arm.seq - ticket >= SLOTS) return DL_OK;  // its slot has been reused since, which waited for it
         const uint32_t slot = (uint32_t)(ticket % SLOTS);
         words = &g_arm.host->armed[slot];
-        if (g_arm.at_once[slot]) {
-            if (g_arm.seq - ticket >= SLOTS) return DL_OK;  // its slot has been reused since, which waited for it
+        if (g_arm.at_once[slot]) {  // (the slot's present request is this one)
             words = g_arm.host->done[slot];
             count = g_arm.words[slot] ? g_arm.words[slot] : 1u;
         }

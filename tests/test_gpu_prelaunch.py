@@ -223,6 +223,34 @@ def test_batch_swap_armed_twice_restores(ref, armed):
     assert np.array_equal(d.host(), arena) and d.guards_intact()
 
 
+def test_wait_armed_on_a_finished_ticket_whose_slot_is_armed_again(ref, armed):
+    """A request without a doorbell leaves no word that it was resident.  64 tickets later its slot belongs to a request that
+    is armed behind another one and not resident: a wait for the old ticket ends at once all the same."""
+    src, dst = DevBuf(4 * KiB, fill=np.arange(4 * KiB, dtype=np.uint8)), DevBuf(4 * KiB)
+    sync()
+    dl.dl_set_mode(dl.DL_MODE_SIGNAL)
+    try:
+        tickets = []
+        for _ in range(63):
+            dl.dl_batch_copy([(src.ptr(), dst.ptr(), 4 * KiB)])
+            tickets.append(dl.dl_last_ticket())
+        dl.dl_wait()
+    finally:
+        dl.dl_set_mode(dl.DL_MODE_PRELAUNCH)
+    for _ in range(2):  # on the same stream: the second one starts behind the first, which nobody has triggered
+        dl.dl_batch_copy([(src.ptr(), dst.ptr(), 4 * KiB)])
+    newest = dl.dl_last_ticket()
+    assert newest == tickets[0] + 64
+    with pytest.raises(dl.DlError) as e:
+        dl.dl_wait_armed(newest, 0)
+    assert e.value.status == dl.DL_ERR_TIMEOUT
+    dl.dl_wait_armed(tickets[0], 0)
+    dl.dl_wait_armed(tickets[1], 0)  # its slot is still its own: finished
+    dl.dl_trigger(newest)
+    dl.dl_wait(newest)
+    assert np.array_equal(dst.host(), src.host()) and dst.guards_intact()
+
+
 def test_slots_reused_by_requests_that_count_and_that_do_not(ref, armed):
     """400 requests, so that every slot is used six times, in no particular order of what reports: a completion word per
     workgroup, a count in one of the slot's two sets of counters (which the next request that counts clears), a kernel
