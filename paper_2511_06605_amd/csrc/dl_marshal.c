@@ -46,11 +46,13 @@ _Static_assert(sizeof(dl_copy_desc) == 24 && sizeof(dl_swap_desc) == 24, "three 
 
 static PyObject *s_data_ptr, *s_cuda_stream;
 
-/* The value of an exact int of at most two digits (60 bits: every address and length there is), read where it lies.
- * 0: x is something else. */
-#if PY_VERSION_HEX < 0x030C0000
-#include <longintrepr.h>
-_Static_assert(PyLong_SHIFT == 30, "two digits, 60 bits");
+/* The value of an exact int of at most two digits of 30 bits (every address and length there is), read where it lies, for the
+ * Pythons whose ints are known to lie that way.  0: x is something else. */
+#if PY_VERSION_HEX < 0x030A0000
+#include <longintrepr.h> /* later Python.h includes it, from 3.11 on under another name */
+#endif
+#if PY_VERSION_HEX < 0x030C0000 && PyLong_SHIFT == 30
+enum { PLAIN_INTS = 1 };
 static inline int plain_int(PyObject *x, uint64_t *out)
 {
     if (!PyLong_CheckExact(x)) return 0;
@@ -67,6 +69,7 @@ static inline int plain_int(PyObject *x, uint64_t *out)
     return 1;
 }
 #else
+enum { PLAIN_INTS = 0 };
 static inline int plain_int(PyObject *x, uint64_t *out) { return 0; }
 #endif
 
@@ -288,7 +291,7 @@ static PyObject *triples(PyObject *const *args, Py_ssize_t n, const char *what, 
     /* a list or tuple of tuples of ints, as most are, is read where it lies (nothing else runs meanwhile, and ints keep no
      * buffer alive); with anything else in it, from its beginning as below */
     Py_ssize_t read = 0;
-    if (PyList_CheckExact(args[0]) || PyTuple_CheckExact(args[0])) {
+    if (PLAIN_INTS && (PyList_CheckExact(args[0]) || PyTuple_CheckExact(args[0]))) {
         const Py_ssize_t size = PySequence_Fast_GET_SIZE(args[0]);
         PyObject *const *const items = PySequence_Fast_ITEMS(args[0]);
         if (!(w = PyMem_New(uint64_t, 3 * (size ? size : 1)))) return PyErr_NoMemory();

@@ -2,11 +2,16 @@
 in their place (no GPU, no library call)."""
 
 import ctypes
+import os
+import re
+import shutil
+import subprocess
+import sysconfig
 
 import numpy as np
 import pytest
 
-from paper_2511_06605_amd import binding
+from paper_2511_06605_amd import binding, build
 
 vp, sz, u64, u32 = ctypes.c_void_p, ctypes.c_size_t, ctypes.c_uint64, ctypes.c_uint32
 PP = ctypes.POINTER(vp)
@@ -390,3 +395,32 @@ def test_without_the_extension_the_package_uses_ctypes(monkeypatch):
     monkeypatch.setattr(binding, "_marshal", None)
     assert binding._native() is marshal_ctypes and binding._lib is not None
     assert binding.dl_last_ticket() == 0
+
+
+# Python.h includes longintrepr.h from 3.10 on and by another name from 3.11; a Python may be built with digits of 15 bits; from
+# 3.12 on an int lies differently
+@pytest.mark.parametrize("minor,bits,in_place", [(9, 30, True), (10, 30, True), (10, 15, False), (11, 30, True), (11, 15, False), (12, 30, False)])
+def test_builds_for_other_pythons(tmp_path, minor, bits, in_place):
+    here = sysconfig.get_paths()["include"]
+    cc = next(filter(None, map(shutil.which, ("gcc", "cc"))), None)
+    if not cc or sysconfig.get_python_version() != "3.10" or not os.path.exists(os.path.join(here, "longintrepr.h")):
+        pytest.skip("needs a C compiler and the headers of Python 3.10, from which the others are made")
+    inc = tmp_path / "include"
+    shutil.copytree(here, inc)
+
+    def edit(name, pattern, by):
+        text, n = re.subn(pattern, by, (inc / name).read_text())
+        assert n == 1, (name, pattern)
+        (inc / name).write_text(text)
+
+    edit("patchlevel.h", r"(#define PY_MINOR_VERSION\s+)\d+", rf"\g<1>{minor}")
+    if minor < 10:
+        edit("Python.h", r'#include "longintrepr.h"\n', "")
+    if minor > 10:
+        edit("Python.h", r'#include "longintrepr.h"', '#include "cpython/longintrepr.h"')
+        shutil.move(inc / "longintrepr.h", inc / "cpython" / "longintrepr.h")
+    probe = tmp_path / "probe.c"
+    probe.write_text(f'#include "{os.path.join(build.CSRC, "dl_marshal.c")}"\n'
+                     f'_Static_assert((PY_VERSION_HEX >> 16 & 0xFF) == {minor} && PLAIN_INTS == {int(in_place)}, "which Pythons are read in place");\n')
+    r = subprocess.run([cc, "-std=c11", "-fsyntax-only", "-Wall", f"-DPYLONG_BITS_IN_DIGIT={bits}", "-I" + str(inc), str(probe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
