@@ -264,8 +264,8 @@ __device__ __forceinline__ uint32_t dl_wave_sum63(uint32_t x)
 }
 
 // The mask in device memory: how many rows the tokens in front of a group take in each receive buffer, and the ranks of
-// the group's own token `lane` (0 past the last one).  Counted by the whole workgroup; `between` runs behind the first
-// loads, which are in flight meanwhile.
+// the group's own token `lane` (0 past the last one).  Counted by the whole workgroup; `rows` runs behind the first
+// loads, which are in flight meanwhile, or (ROWS_FIRST) in front of them.
 struct dispatch_counts {
     uint32_t c[4];  // 16 bits a rank: ranks 0|2, 1|3, 4|6, 5|7
     uint32_t mine;
@@ -289,8 +289,8 @@ struct dispatch_counts {
         };
         return packed{four(c[0], c[1]), four(c[2], c[3])};
     }
-    template <class Between>
-    __device__ __forceinline__ void count(const uint8_t *mask, uint32_t tokens, uint32_t group0, Between between)
+    template <bool ROWS_FIRST, class Rows>
+    __device__ __forceinline__ void count(const uint8_t *mask, uint32_t tokens, uint32_t group0, Rows rows)
     {
         __shared__ uint32_t part[MAX_WAVES][4];
         const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -322,8 +322,9 @@ struct dispatch_counts {
                 hi += dl_mask_fold(w[u].y, keep) + dl_mask_fold(w[u].w, keep);
             }
         };
+        if constexpr (ROWS_FIRST) rows();
         fetch(0);
-        between();
+        if constexpr (!ROWS_FIRST) rows();
         add(0);
         for (uint32_t base = BATCH * step; base < group0; base += BATCH * step) {
             fetch(base);
@@ -385,12 +386,18 @@ __global__ void __launch_bounds__(64 * MAX_WAVES) dl_dispatch_mask_kernel(const 
                      "s"(a.first_token[7]));
     dispatch_row<POL, ROWS, true> row;
     dispatch_counts c;
-    c.count(mask, a.tokens, group0, [&] {
+    // The rows are loaded behind the mask's first loads: those come back first, and are counted meanwhile.  But where the loads
+    // stream, all rows of a workgroup are waited for there: loads in one burst and stores in the next are then the faster order
+    // (see dispatch_setup).  With eight wavefronts of two rows, rows of up to 2 KiB and of more than 16, the burst lies in front
+    // of the mask's loads, which held some rows up until others were being stored.  Behind : in front, one buffer set / three / sets
+    // that fit no cache, 650 per rank of 2 KiB 11.1 / 12.8 / 15.6 : 11.2 / 11.5 / 14.2 us, 900 14.3 / 18.9 / 22.6 : 14.5 / 16.7 / 19.7; 75 of
+    // 18 KiB 11.4 / 12.5 / 14.2 : 11.5 / 11.8 / 14.2, 85 12.2 / 14.5 / 16.9 : 12.5 / 14.6 / 17.2, 56 of 32 KiB 13.3 / 15.9 / 19.0 : 13.3 / 14.6 /
+    // 18.2 (without a burst 650 of 2 KiB 10.9 / 13.6 / 15.8, 85 of 18 KiB 12.5 / 15.2 / 18.1, 56 of 32 KiB 13.4 / 17.1 / 20.9).
+    constexpr bool BURST = POL == DL_POL_STREAM_IN;
+    c.count<BURST && ROWS == 2>(mask, a.tokens, group0, [&] {
         if constexpr (ON_GRID) {
-            row.load(a, valid ? first + t : a.tokens - 1u, row0);  // behind the mask's first loads: those come back first, and are counted meanwhile
-            // ... but where the loads stream, all rows of a workgroup are waited for here: loads in one burst and stores in the
-            // next are then the faster order (see dispatch_setup)
-            if constexpr (POL == DL_POL_STREAM_IN) row.arrived();
+            row.load(a, valid ? first + t : a.tokens - 1u, row0);
+            if constexpr (BURST) row.arrived();
         }
     });
     if (!valid) return;
@@ -406,7 +413,7 @@ __global__ void __launch_bounds__(64 * MAX_WAVES) dl_dispatch_mask_kernel(const 
 __global__ void __launch_bounds__(64 * MAX_WAVES) dl_dispatch_pack_kernel(const uint8_t *__restrict__ mask, uint32_t tokens, dispatch_group *groups)
 {
     dispatch_counts c;
-    c.count(mask, tokens, blockIdx.x * GROUP, [] {});
+    c.count<false>(mask, tokens, blockIdx.x * GROUP, [] {});
     dispatch_group &g = groups[blockIdx.x];
     if (threadIdx.x < GROUP) g.ranks[threadIdx.x] = (uint8_t)c.mine;
     if (threadIdx.x < (uint32_t)DISPATCH_W) g.taken[threadIdx.x] = c.pack().taken(threadIdx.x);
@@ -522,7 +529,7 @@ int dispatch_setup(const void *const *in, void *const *out, const uint32_t *toke
         // 11.1 / 14.0 / 15.7 : 10.9 / 15.8 / 16.7, 128 / 192 of 10 KiB (four wavefronts of three, then) 12.1 / 16.4 : 10.7 /
         // 16.4 : 10.8 / 15.6 : 10.4 / 17.5, 112 / 128 of 14 KiB (four of four) 14.1 / 15.7 : 12.7 / 14.1 : 12.7 / 14.2 : 13.5 /
         // 15.0; 450 / 590 of 3 KiB 12.5 / 17.6 before, 11.6 / 16.1 this way.  (Outside this range of sizes, the other way round: 150
-        // of 14 KiB 18.7 without the burst, 19.8 with it.  Shorter rows stay with eight of two: 700 of 2 KiB 13.4, 14.0 with four.)
+        // of 14 KiB 18.7 without the burst, 19.8 with it.  Shorter rows stay with eight of two: 700 of 2 KiB 13.4, 14.0 with four, before the burst lay where it does.)
         waves = 4;
         sh->rows = rows < 4u ? (int)rows : 4;
     } else if (sh->policy != DL_POL_STREAM && rows > 4u && rows <= in_one) {
