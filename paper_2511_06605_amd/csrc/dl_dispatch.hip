@@ -510,12 +510,15 @@ int dispatch_setup(const void *const *in, void *const *out, const uint32_t *toke
         waves = 2;
         sh->rows = 1;
     } else if (sh->policy == DL_POL_WT && total <= ALONE_MAX_TOKENS &&
-               rows * total <= (mask_on_device ? ALONE_MASK_MAX_ROWS : total < ALONE_MAX_TOKENS ? ALONE_LIST_MAX_ROWS : 1024u)) {
+               rows * total <= (mask_on_device ? ALONE_MASK_MAX_ROWS : ALONE_LIST_MAX_ROWS)) {
         // Small: a wavefront by itself, so that nothing waits for a neighbour and a wavefront has the fewest instructions
-        // to fetch.  Eight wavefronts of two rows : this, three buffer sets in turn, mask on the host, 16 / 40 tokens per rank of
-        // 4 KiB 3.13 : 2.59 and 3.28 : 3.17 us, of 8 KiB 3.30 : 2.82 and 3.95 : 3.85, of 10 KiB 3.11 : 3.07 and 4.69 : 4.19;
-        // more rows gain only while the buffers are in the caches (40 per rank of 14 KiB 5.93 : 5.22, else 6.87 : 7.09, 57
-        // of 10 KiB 5.54 : 5.31 and 6.5 : 7.5), more tokens share their group's record better (64 / 128 per rank of 4 KiB 3.55 : 3.61 and 4.94 : 5.03).
+        // to fetch.  Eight wavefronts of two rows : this, mask on the host, in a graph: up to a row for each of the chip's 1024 SIMDs
+        // always (64 tokens per rank of 2 KiB 2.87 : 2.52 us, 32 of 4 KiB 2.90 : 2.52, 16 of 8 KiB 2.94 : 2.53), up to two with sets that
+        // fit no cache (48 of 3 KiB 3.95 : 3.69, 40 and 64 of 4 KiB 4.32 : 3.78 and 4.65 : 4.42, 40 of 5 KiB 4.21 : 4.06) and rows of 8 KiB and more
+        // (24 of 8 KiB 3.07 : 2.98, 20 of 12 KiB 3.20 : 3.08), while shorter rows in the caches, which then go two by two in one
+        // round, lose (48 of 3 KiB 2.67 : 2.89, 64 of 4 KiB 3.22 : 3.30, 40 of 5 KiB 2.88 : 3.10); beyond that mostly again (64 of 6 KiB
+        // 3.93 : 3.85 and 5.52 : 5.30, 40 of 8 KiB 3.63 : 3.57 and 5.15 : 4.85, 40 of 10 KiB 4.44 : 3.94 and 6.02 : 5.48), to 3400 rows
+        // (56 of 8 KiB 4.32 : 4.32, 44 of 10 KiB 4.55 : 4.55; 57 of 10 KiB, three sets in turn, 6.5 : 7.5); 128 of 4 KiB 4.94 : 5.03.
         // Mask on the device, 16 / 64 per rank of 4 KiB 4.96 : 4.01 and 5.41 : 4.96, of 8 KiB 5.12 : 4.23 and 6.90 : 6.34, of
         // 14 KiB 6.19 : 4.71 and 10.3 : 9.2 (with two rows; 9.7 with one); there every wavefront counts the mask for itself
         // (128 of 4 KiB 6.8 : 7.3), and 512 tokens of 20 rows take 12.5 : 13.1.

@@ -88,7 +88,7 @@ def test_rows_and_buffers_of_any_length_and_alignment(ref, counts, row, top_k, s
 # tokens, 1024 / 1025, 3400, 5120 and 8192 rows of 1 KiB and one token more, rows of one to eighteen KiB that fill a
 # workgroup's share or not, 88 MiB and 144 MiB by the bound that the cache policy goes by.
 @pytest.mark.parametrize("counts,row", [
-    ([64] * 7 + [63], 16), ([64] * 8, 2048), ([64] * 7 + [65], 1024), ([64] * 7 + [64], 2 * 1024 + 16), ([0] * 7 + [340], 10240), ([341] + [0] * 7, 10240),
+    ([64] * 7 + [63], 16), ([64] * 8, 2048), ([64] * 8, 6144), ([64] * 8, 7 * 1024), ([64] * 7 + [65], 1024), ([64] * 7 + [64], 2 * 1024 + 16), ([0] * 7 + [340], 10240), ([341] + [0] * 7, 10240),
     ([64] * 8, 10240), ([64] * 7 + [63], 10 * 1024 + 16), ([64] * 8, 16384), ([65] + [0] * 6 + [450], 16384), ([120] * 8, 9 * 1024 + 128),
     ([150] * 8, 12288), ([130] * 8, 12 * 1024 + 128), ([110] * 8, 14336), ([100] * 8, 16384), ([110] * 8, 16 * 1024 + 128), ([180] * 8, 14336), ([160] * 8, 11 * 1024), ([260] * 8, 5 * 1024), ([400] * 8, 4096),
     ([1] * 8, 3 * 1024)])
