@@ -417,8 +417,9 @@ __global__ void __launch_bounds__(1024) dl_armed_rows_kernel(const dl_klist<Item
 }
 
 // The same for a request of more tiles than the waiting grid has workgroups: R tiles a pass, the first pass's worked out
-// before the wait.  Two a pass for up to two passes of sixteen wavefronts, else four (all-gather over eight ranks, sixteen wavefronts a workgroup, trigger
-// to done and the call: 1 MiB per rank 24.6 us with two, 26.1 with four; 2 MiB 56.8 and 47.7).
+// before the wait.  R is two while two passes are enough for sixteen wavefronts a workgroup, one pass for eight, else four
+// (all-gather, trigger to done and the call, sixteen wavefronts, two : four, 608 / 640 / 768 KiB per rank over eight ranks, 2.4 to 3 tiles a
+// workgroup, 21.5 / 21.4 / 21.9 : 21.7 / 21.7 / 22.3 us, 1 MiB over five 19.1 : 19.3 and over eight, 4 tiles, 25.0 : 26.2; 2 MiB 56.8 : 47.7).
 template <class Item, int NMAX, int R>
 __global__ void __launch_bounds__(1024) dl_armed_passes_kernel(const dl_klist<Item, NMAX> p, const dl_arm a)
 {
@@ -781,7 +782,7 @@ int launch_klist(const Item *items, size_t n, const uint64_t *tile_end, const dl
             hipLaunchKernelGGL((dl_signal_rows_kernel<Item, NMAX, false>), dim3(g), dim3(sh.block_threads), 0, stream, p, a);
         else if (sh.rows && !a.nowait && a.direct && sh.split == 1 && (grid <= 4u * g || sh.block_threads > 512u) && !std::is_same<Item, dl_swap_item>::value) {
             if constexpr (!std::is_same<Item, dl_swap_item>::value) {
-                const bool four = grid > 4u * g || (grid > 2u * g && (grid <= 2u * g + g / 2u || sh.block_threads <= 512u));
+                const bool four = grid > (sh.block_threads > 512u ? 4u : 2u) * g;  // (see dl_armed_passes_kernel)
                 const auto kernel = g < grid ? four ? dl_armed_passes_kernel<Item, NMAX, 4> : dl_armed_passes_kernel<Item, NMAX, 2>
                                     : on_grid ? dl_armed_rows_kernel<Item, NMAX, true> : dl_armed_rows_kernel<Item, NMAX, false>;
                 hipLaunchKernelGGL(kernel, dim3(g), dim3(sh.block_threads), 0, stream, p, a);
