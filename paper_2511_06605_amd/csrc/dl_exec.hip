@@ -37,11 +37,12 @@ __global__ void __launch_bounds__(512) dl_exec_rows_kernel(const dl_klist<Item, 
 // eight ranks): a two-dimensional grid, blockIdx.y the item, blockIdx.x the tile within it, so nothing is
 // searched and nothing divided.  The grid is as wide as the longest item; a workgroup beyond its item's last
 // row leaves at once (the host takes this path only while few workgroups are wasted that way).  Consecutive
-// workgroups walk along one item, so the chip-wide stream of addresses stays sequential.
-template <class Item, int NMAX, int POL, bool ON_GRID>
+// workgroups walk along one item, so the chip-wide stream of addresses stays sequential (EIGHTHS: see dl_eighths_tile).
+template <class Item, int NMAX, int POL, bool ON_GRID, bool EIGHTHS = false>
 __global__ void __launch_bounds__(512) dl_exec_rows2d_kernel(const dl_klist<Item, NMAX> p)
 {
-    dl_rows_body<POL, ON_GRID>(p.item[blockIdx.y], blockIdx.x, p.wpg_log2, p.split_log2);
+    const uint32_t tile = EIGHTHS ? dl_eighths_tile(blockIdx.x, gridDim.x) : blockIdx.x;
+    dl_rows_body<POL, ON_GRID>(p.item[blockIdx.y], tile, p.wpg_log2, p.split_log2);
 }
 
 // Large copies with several destinations, written two destinations at a time (see dl_pair_body).
@@ -96,7 +97,7 @@ __global__ void __launch_bounds__(512) dl_exec_urows_kernel(const Item *__restri
 // written, so the two round trips in front of every row of a pushed table (stamp, entry) are gone: 256 copies of 64 KiB
 // 7.4 us of kernel, now 6.2 (10.4 -> 9.8 us a call); of 256 KiB 28.5 -> 21.6 us, of 1 MiB 97.3 -> 85.7 us, where one-wavefront
 // workgroups count as well.
-template <class Item, int NMAX, int POL, bool ON_GRID>
+template <class Item, int NMAX, int POL, bool ON_GRID, bool EIGHTHS = false>
 __global__ void __launch_bounds__(512) dl_exec_offsets_kernel(const dl_offset_list<NMAX> p)
 {
     const uint32_t d = blockIdx.y;
@@ -104,7 +105,7 @@ __global__ void __launch_bounds__(512) dl_exec_offsets_kernel(const dl_offset_li
     it.src = p.src + ((uint64_t)p.at[d].src << p.unit_log2);
     it.dst = p.dst + ((uint64_t)p.at[d].dst << p.unit_log2);
     it.bytes = p.bytes;
-    dl_rows_body<POL, ON_GRID>(it, blockIdx.x, p.wpg_log2, 0u);
+    dl_rows_body<POL, ON_GRID>(it, EIGHTHS ? dl_eighths_tile(blockIdx.x, gridDim.x) : blockIdx.x, p.wpg_log2, 0u);
 }
 
 // General path: any tile size, one workgroup per tile.
@@ -624,7 +625,7 @@ constexpr uint64_t FAN_WAVE_MIN_BYTES = 3ull << 20;         // bytes moved above
 constexpr uint64_t UNIFORM_ROWS_MIN_BYTES = 4ull << 20;  // source bytes from which a uniform long list takes the row kernel
 constexpr uint64_t UNIFORM_ROWS_STAGE_BYTES = 768ull << 20;  // bytes moved (read + written) from which its table is staged even where it could be pushed
 constexpr uint64_t STREAM_BOTH_MIN_BYTES = 512ull << 20;  // bytes moved from which lists of plain copies outside the row path stream both sides
-constexpr uint64_t OFF_GRID_MIN_BYTES = 24ull << 20;  // bytes moved from which plain copies off the grid take workgroups of eight rows
+constexpr uint64_t OFF_GRID_MIN_BYTES = 24ull << 20;  // bytes moved from which plain copies off the grid keep rows next to each other together
 constexpr uint32_t SIGNAL_MAX_BLOCKS = 32768;  // the arrival counters keep 16 bits for the count
 constexpr uint64_t SIGNAL_DONE_MIN_BYTES = 12ull << 20;  // bytes moved from which a signalled request is a one-shot kernel and one that reports
 constexpr uint64_t RAGGED_GRID = 768;  // workgroups of a two-dimensional grid that may be mostly idle
@@ -793,6 +794,10 @@ int launch_klist(const Item *items, size_t n, const uint64_t *tile_end, const dl
             hipLaunchKernelGGL((dl_armed_list_kernel<Item, NMAX, true>), dim3(g), dim3(sh.block_threads), 0, stream, p, a);
         else
             hipLaunchKernelGGL((dl_armed_list_kernel<Item, NMAX, false>), dim3(g), dim3(sh.block_threads), 0, stream, p, a);
+    } else if (sh.rows && sh.rows2d_width && sh.eighths) {
+        if constexpr (std::is_same<Item, dl_plain_item>::value)
+            hipLaunchKernelGGL((dl_exec_rows2d_kernel<Item, NMAX, DL_POL_WT, false, true>), dim3((uint32_t)dl_eighths_width(sh.rows2d_width), (uint32_t)n),
+                               dim3(sh.block_threads), 0, stream, p);
     } else if (sh.rows && sh.rows2d_width) {
         dl_with_policy_and_grid(sh.policy, on_grid, [&](auto pol, auto og) {
             hipLaunchKernelGGL((dl_exec_rows2d_kernel<Item, NMAX, decltype(pol)::value, decltype(og)::value>),
@@ -956,7 +961,7 @@ bool all_aligned(const Item *items, size_t n)
 // 480): one launch and nothing else.  Returns false if the list does not qualify (and nothing was enqueued).
 template <class Item, int NMAX>
 int launch_offsets_sized(const Item *items, size_t n, const dl_offset_head &head, uint32_t width, uint32_t threads, int policy,
-                         bool on_grid, hipStream_t stream)
+                         bool on_grid, bool eighths, hipStream_t stream)
 {
     dl_offset_list<NMAX> p;
     static_cast<dl_offset_head &>(p) = head;
@@ -964,10 +969,15 @@ int launch_offsets_sized(const Item *items, size_t n, const dl_offset_head &head
         p.at[i].src = (uint32_t)((uint64_t)(items[i].src - head.src) >> head.unit_log2);
         p.at[i].dst = (uint32_t)((uint64_t)(items[i].dst - head.dst) >> head.unit_log2);
     }
-    dl_with_policy_and_grid(policy, on_grid, [&](auto pol, auto og) {
-        hipLaunchKernelGGL((dl_exec_offsets_kernel<Item, NMAX, decltype(pol)::value, decltype(og)::value>), dim3(width, (uint32_t)n),
-                           dim3(threads), 0, stream, p);
-    });
+    if (eighths) {
+        if constexpr (std::is_same<Item, dl_plain_item>::value)
+            hipLaunchKernelGGL((dl_exec_offsets_kernel<Item, NMAX, DL_POL_WT, false, true>), dim3((uint32_t)dl_eighths_width(width), (uint32_t)n),
+                               dim3(threads), 0, stream, p);
+    } else
+        dl_with_policy_and_grid(policy, on_grid, [&](auto pol, auto og) {
+            hipLaunchKernelGGL((dl_exec_offsets_kernel<Item, NMAX, decltype(pol)::value, decltype(og)::value>), dim3(width, (uint32_t)n),
+                               dim3(threads), 0, stream, p);
+        });
     DL_HIP(hipGetLastError());
     return DL_OK;
 }
@@ -1018,8 +1028,8 @@ bool launch_offsets(const Item *items, size_t n, const dl_launch_shape &sh, hipS
     for (size_t i = 0; i < n && *rc == DL_OK; i += per) {
         const size_t m = n - i < per ? n - i : per;
         *rc = m <= (size_t)SMALL
-                  ? launch_offsets_sized<Item, SMALL>(items + i, m, head, (uint32_t)width, threads, policy, on_grid, stream)
-                  : launch_offsets_sized<Item, BIG>(items + i, m, head, (uint32_t)width, threads, policy, on_grid, stream);
+                  ? launch_offsets_sized<Item, SMALL>(items + i, m, head, (uint32_t)width, threads, policy, on_grid, sh.eighths, stream)
+                  : launch_offsets_sized<Item, BIG>(items + i, m, head, (uint32_t)width, threads, policy, on_grid, sh.eighths, stream);
     }
     return true;
 }
@@ -1288,7 +1298,6 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
     }
     if (total == 0) return DL_OK;
     dl_launch_shape sh = dl_choose_shape(total, biggest, kmax);
-    // one-shot requests, where the caller has not fixed the shape
     // A signalled request that moves more than a little is an ordinary one-shot request, and a kernel of one workgroup behind
     // it reports: the copy then has a full grid, loads that the caches may serve and no count at its end, for the second
     // launch's 2 us.  Issue to done and the call, one kernel : two, all-gather over eight ranks 128 / 256 KiB per rank 11.6 / 12.5 :
@@ -1318,6 +1327,7 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
             }
         }
     }
+    // one-shot requests, where the caller has not fixed the shape
     const bool free_shape = !arm && !g_dl.cfg.tile_bytes && !g_dl.cfg.block_threads && !g_dl.cfg.fan_split && !sh.max_blocks;
     if (arm && !arm->nowait && g_dl.cfg.armed_blocks == 0) {
         // prelaunch mode, and the caller has not fixed the waiting grid: large requests wait in a gate kernel
@@ -1366,15 +1376,25 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
     }
 
     if constexpr (std::is_same<Item, dl_plain_item>::value) {
-        // Copies off the grid, below the sizes that stream: eight rows to a workgroup, whose unaligned loads and partly
-        // written lines then meet in one compute unit.  All-to-all, one buffer set / three / sets that fit no cache, 64 or
-        // 256 threads against 512: 5 ranks of 500 003 bytes (25 MB moved) 4.12 / 5.22 / 5.65 : 4.05 / 5.17 / 5.55 us,
-        // 12 of 140 001 6.31 / 7.82 / 10.3 : 5.47 / 7.70 / 10.2, 8 of 420 001 8.43 / 9.91 / 11.8 : 6.49 / 9.23 / 12.5, 15 of
-        // 164 228 12.3 / 13.5 / 15.7 : 11.1 / 12.1 / 16.0; smaller ones +-5 % by how their last tile falls; larger ones one row
-        // each, as any list (8 ranks of 2 MiB and 3 bytes, three sets 44.4 : 45.1).
+        // Copies off the grid, below the sizes that stream.  Rows next to each other share the lines that their unaligned
+        // loads and partly written ends lie in.  Up to 48 MiB moved eight rows to a workgroup, so that they meet in one compute
+        // unit: all-to-all, one buffer set / three / sets that fit no cache, 256 threads : 512, 5 ranks of 500 003 bytes (25 MB moved)
+        // 3.73 / 4.89 / 7.55 : 3.62 / 4.79 / 7.34 us, 12 of 140 001 5.88 / 7.50 / 10.3 : 5.13 / 7.26 / 10.1, 8 of 300 007 4.72 / 7.08 /
+        // 9.94 : 4.64 / 6.94 / 9.85; by how the last tile of a copy falls 16 of 90 001 5.70 / 8.30 / 11.1 : 5.82 / 8.29 / 10.7, 20 of
+        // 60 003 6.02 / 8.69 / 11.9 : 6.73 / 8.60 / 11.4.  Beyond, where workgroups are one wavefront, an eighth of the copy to every
+        // XCD, so that they meet in one L2; 512 threads have the better figures while all is in the caches, and lose to what was there
+        // before where nothing is.  Rows in turn : 512 threads : eighths, 8 of 420 001 7.95 / 9.55 / 11.58 : 6.10 / 8.91 / 12.2 : 7.47 /
+        // 9.03 / 11.4, 8 of 524 291 10.2 / 11.2 / 13.5 : 9.0 / 10.6 / 14.0 : 9.3 / 10.8 / 13.3, 15 of 164 228 12.1 / 13.3 / 15.4 : 10.7 /
+        // 11.7 / 15.6 : 11.1 / 12.0 / 14.5, 2 of 9 000 001 11.5 / 11.6 / 14.3 : 11.3 / 11.7 / 14.9 : 10.7 / 11.1 / 14.1.  (Cold sets do not
+        // want more loads in flight: two rows per wavefront 7.0 / 9.4 / 13.4 for the first of these; nor 512 threads with rows in turn,
+        // 7.3 / 9.5 / 12.9, or in eighths, 6.9 / 9.4 / 12.2.  Larger ones in turn, as any list: 8 of 2 MiB and 3 bytes.)
         if (free_shape && sh.policy == DL_POL_WT && 2u * total >= OFF_GRID_MIN_BYTES && biggest >= 8192u && !all_on_grid(items, n)) {
-            sh.block_threads = 512u;
-            sh.tile_bytes = 8192u;
+            if (sh.block_threads == 64u) {
+                sh.eighths = true;
+            } else {
+                sh.block_threads = 512u;
+                sh.tile_bytes = 8192u;
+            }
         }
     }
     constexpr int NBIG = list_cap<Item>::big;
@@ -1444,7 +1464,7 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
         // fit no cache 11.8 : 10.4), 40 of 10 KiB 9.5 : 9.3, one buffer set 7.8 : 6.6.  Lengths drawn from 1 byte to
         // 40 000: 12 / 30 / 64 copies 2.48 : 2.25, 2.60 : 2.46, 2.67 : 2.64; to 256 KiB (a grid of 2048 / 4096) 32 / 64
         // copies 2.56 : 2.81, 2.74 : 3.35.
-        if (n > (size_t)NMAX_SMALL && !arm && !sh.max_blocks) {
+        if ((n > (size_t)NMAX_SMALL || sh.eighths) && !arm && !sh.max_blocks) {
             const auto grid_if_even = [&](uint64_t spare) -> uint64_t {  // workgroups of the grid, if `spare` is enough; else 0
                 uint64_t widest = 0;
                 for (size_t i = 0; i < n; ++i) {
@@ -1456,7 +1476,7 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
             uint64_t grid = 0;
             if (sh.tile_bytes == 16u * (sh.block_threads / sh.split)) grid = grid_if_even(tile_end[n - 1] / 4);
             if constexpr (!std::is_same<Item, dl_fused_item>::value) {
-                if (!grid && free_shape && sh.policy == DL_POL_WT) {
+                if (!grid && n > (size_t)NMAX_SMALL && free_shape && sh.policy == DL_POL_WT) {
                     const dl_launch_shape before = sh;
                     if (sh.block_threads == 64u && biggest >= 4096u) sh.block_threads = 256u;
                     sh.tile_bytes = 16u * sh.block_threads;
@@ -1472,6 +1492,7 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
             if (grid) {
                 sh.rows = true;
                 sh.rows2d_width = (uint32_t)(grid / n);
+                if (sh.block_threads != 64u) sh.eighths = false;
             }
         }
         if constexpr (!std::is_same<Item, dl_fused_item>::value) {

@@ -61,6 +61,7 @@ struct dl_launch_shape {
     bool chain = false;   // prelaunch mode, a large request: a one-workgroup gate kernel waits, the copy kernel follows it on the stream
     bool pairs = false;   // read-once/write-k items written two destinations at a time (see dl_pair_body)
     uint32_t rows2d_width = 0;  // row path on a two-dimensional grid (item by item), this many tiles wide; 0: one-dimensional
+    bool eighths = false;       // on that grid an item's tiles in the order of dl_eighths_tile
 };
 
 // What an armed (prelaunched) kernel needs to wait for its doorbell and to

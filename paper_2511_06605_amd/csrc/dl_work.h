@@ -90,6 +90,11 @@ DL_HD uint32_t dl_plain_threads(uint64_t moved, bool capped)
     return moved >= DL_PLAIN_WAVE_MIN_BYTES && !capped ? 64u : 256u;
 }
 
+// Workgroups of an item, a multiple of eight, and the tile of one of them where tiles next to each other share lines: the eight
+// XCDs, to which workgroups are dealt in turn, take an eighth of the item each.
+DL_HD uint64_t dl_eighths_width(uint64_t tiles) { return (tiles + 7u) & ~(uint64_t)7u; }
+DL_HD uint32_t dl_eighths_tile(uint32_t wg, uint32_t width) { return (wg & 7u) * (width >> 3) + (wg >> 3); }
+
 // Rows of 1 KiB that an item takes on that grid, and workgroups of the kernel that writes its destinations in pairs:
 // as many for every pair, a multiple of eight (see dl_pair_locate).
 DL_HD uint32_t dl_pair_rows(uint64_t bytes, uint32_t shift) { return (uint32_t)((bytes + shift + 1023u) >> 10); }

@@ -1,5 +1,5 @@
 // Every workgroup of the kernel that writes destinations in pairs gets a row and a pair of its own, and together they
-// take every row of an item once for every pair.
+// take every row of an item once for every pair.  The workgroups of an item taken by eighths have a tile each.
 #include <cstdio>
 #include <vector>
 
@@ -42,6 +42,16 @@ int main()
                 if (dl_pair_locate(b, rows, pairs, &row, &pair)) return 7;
             }
         }
+    for (uint32_t tiles = 1; tiles < 3000; ++tiles) {
+        const uint32_t width = (uint32_t)dl_eighths_width(tiles);
+        std::vector<int> seen(width, 0);
+        if (width < tiles || width > tiles + 7) return 8;
+        for (uint32_t b = 0; b < width; ++b) {
+            const uint32_t t = dl_eighths_tile(b, width);
+            if (t >= width || seen[t]++) return 9;
+            if (t / (width / 8) != b % 8) return 10;  // an XCD's tiles lie together
+        }
+    }
     // shifts move an item over its grid: the number of rows is that of the bytes it touches
     for (uint64_t bytes = 1; bytes < 5000; ++bytes)
         for (uint32_t shift = 0; shift < DL_CUT; ++shift)

@@ -65,13 +65,15 @@ def test_unequal_copies_around_their_size_rules(ref, n, total, align):
 
 
 # lists of 9..64 copies item by item or tile by tile: lengths that fill the two-dimensional grid to a fifth, two fifths or
-# hardly at all, a grid of 768 workgroups and one more, items shorter than a tile; off the grid around 24 and 96 MiB moved
+# hardly at all, a grid of 768 workgroups and one more, items shorter than a tile; off the grid around 24, 48 and 96 MiB moved, where an
+# item is taken by eighths: items of a multiple of eight rows and not, shorter than eight rows, one alone
 @pytest.mark.parametrize("lens,align", [
     ([4096 * 8] * 8 + [4096 * 20] * 4, 128), ([4096 * 8] * 8 + [4096 * 21] * 4, 128), ([4096 * 100] + [4096 * 40] * 20, 128),
     ([4096 * 100] + [4096 * 39] * 20, 128), ([4096 * 64] + [100] * 11, 128), ([4096 * 64] + [100] * 12, 128),
     ([4096 * 63 + 1] + [1] * 11, 1), ([1500 + i for i in range(40)], 1), ([1024, 1, 1023] * 9, 128), ([64 * KiB, 1] * 32, 1),
     ([640 * KiB] * 20, 1), ([12 * MiB // 20 - 1] * 20, 1), ([12 * MiB // 20] * 20, 1), ([48 * MiB // 20] * 20, 1),
-    ([48 * MiB // 20 + 100] * 20, 1), ([12 * MiB // 100 + 1] * 100, 1), ([6 * MiB, 3 * MiB, 5 * MiB + 1], 1)])
+    ([48 * MiB // 20 + 100] * 20, 1), ([24 * MiB // 20 - 1] * 20, 1), ([24 * MiB // 20 + 1] * 20, 1), ([4 * MiB] * 6, 1), ([4 * MiB + 5] * 7, 1), ([25 * MiB + 1], 1),
+    ([24 * MiB // 40 + 1000] * 39 + [3 * KiB], 1), ([24 * MiB // 300 + 1] * 300, 1), ([55 * KiB + 3] * 480, 1), ([12 * MiB // 100 + 1] * 100, 1), ([6 * MiB, 3 * MiB, 5 * MiB + 1], 1)])
 def test_copies_item_by_item_or_tile_by_tile(ref, lens, align):
     rng = np.random.default_rng(len(lens) + lens[0])
     at = np.cumsum([0] + [(m + 255) // 128 * 128 for m in lens * 2])
