@@ -254,32 +254,47 @@ def test_wait_armed_on_a_finished_ticket_whose_slot_is_armed_again(ref, armed):
 def test_slots_reused_by_requests_that_count_and_that_do_not(ref, armed):
     """400 requests, so that every slot is used six times, in no particular order of what reports: a completion word per
     workgroup, a count in one of the slot's two sets of counters (which the next request that counts clears), a kernel
-    behind the copy; armed or at once."""
+    behind the copy; armed or at once.  A size's sources change from one of its requests to the next, and every result is
+    looked at as soon as the request is reported, one rank's in host memory, without a wait for its stream: a request that is
+    reported too early, or never copied, has left what the one before wrote."""
+    import torch
     W = 8
     rng = np.random.default_rng(11)
+    # eight-row tiles: 8, 16 (a word each); 64 (one count); 104, 168 (two levels of them); over the cap of a waiting grid
     sizes = [512, 4 * KiB + 3, 64 * KiB, 100 * KiB, 170 * KiB + 5, 256 * KiB, 1 * MiB + 16]
-    ins = {B: inputs.allgather_inputs(W, B, seed=B) for B in sizes}
-    d_in = {B: [DevBuf(B, fill=a) for a in ins[B]] for B in sizes}
-    d_out = {B: [DevBuf(W * B) for _ in range(W)] for B in sizes}
+    ins = {B: [inputs.allgather_inputs(W, B, seed=2 * B + v) for v in range(2)] for B in sizes}
+    d_in = {B: [[DevBuf(B, fill=a) for a in v] for v in ins[B]] for B in sizes}
+    want = {B: [np.concatenate(v) for v in ins[B]] for B in sizes}
+    d_want = {B: [torch.from_numpy(v).cuda() for v in want[B]] for B in sizes}
+    for B in sizes:
+        for v in range(2):
+            assert np.array_equal(ref.allgather(ins[B][v])[0], want[B][v]) and not np.array_equal(want[B][0], want[B][1])
+    d_out = {B: [DevBuf(W * B) for _ in range(W - 1)] for B in sizes}
+    h_out = {B: torch.zeros(W * B, dtype=torch.uint8, pin_memory=True) for B in sizes}
+    turn = dict.fromkeys(sizes, 0)
+    reused = {(B, at_once): 0 for B in sizes for at_once in (False, True)}
     sync()
     try:
         for it in range(400):
             B, at_once = sizes[rng.integers(len(sizes))], bool(rng.integers(2))
+            turn[B] ^= 1
+            v = turn[B]
             dl.dl_set_mode(dl.DL_MODE_SIGNAL if at_once else dl.DL_MODE_PRELAUNCH)
-            dl.dl_allgather([b.ptr() for b in d_in[B]], [b.ptr() for b in d_out[B]], B)
+            dl.dl_allgather([b.ptr() for b in d_in[B][v]], [b.ptr() for b in d_out[B]] + [h_out[B].data_ptr()], B)
             if rng.integers(4) == 0 and at_once:
                 dl.dl_wait_armed()      # a request without a doorbell: waits for its end
             if not at_once:
                 dl.dl_trigger()
             dl.dl_wait()
-            if it % 40 == 0:
-                got = d_out[B][it // 40 % W]
-                assert np.array_equal(got.host(), np.concatenate(ins[B])) and got.guards_intact(), f"request {it}, {B} bytes"
+            assert np.array_equal(h_out[B].numpy(), want[B][v]), f"request {it}, {B} bytes, at once {at_once}"
+            for r, got in enumerate(d_out[B]):
+                assert torch.equal(got.view(), d_want[B][v]), f"request {it}, {B} bytes, at once {at_once}, rank {r}"
+            reused[B, at_once] += it >= 64
     finally:
         dl.dl_set_mode(dl.DL_MODE_PRELAUNCH)
+    assert min(reused.values()) >= 10
     for B in sizes:
-        for r, w in zip(d_out[B], ref.allgather(ins[B])):
-            assert np.array_equal(r.host(), w) and r.guards_intact()
+        assert all(r.guards_intact() for r in d_out[B])
 
 
 # at once: one kernel, or (from 12 MiB moved) an ordinary one and a second that reports; lists in the kernel arguments of
