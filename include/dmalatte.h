@@ -390,8 +390,13 @@ int dl_trace_clock(double *ticks_per_us, double *host_ns_at_tick0);
  * "moved bytes" are the algorithmic bytes read plus written (an all-gather of
  * B bytes per rank over W ranks: (W + W*W) * B); a tile count is what
  * dl_plan_tiles() gives for 8192-byte tiles.  The large requests go one-shot
- * because the kernels of the other modes load and store at system scope and
- * wait on a capped grid, which costs bandwidth once the copy dominates.
+ * because an armed kernel loads at system scope, which costs bandwidth once
+ * the copy dominates, and so does a signalled one whose list needs a table:
+ * 100 copies of one source each to seven destinations, 100 / 288 / 600 MiB
+ * moved, 29 / 56 / 101 us one-shot, 28 / 69 / 150 signalled.  A signalled
+ * request of fewer items stays 4 us ahead at every size that was measured (to
+ * 1152 MiB); the table does not look at that, since 4 us are 4 % of a request
+ * of 600 MiB.
  *
  * dl_plan_mode() is that table as a host-only function (no GPU needed).
  * op: a dl_op; items and max_fanout: length of the lowered list and the most

@@ -12,8 +12,8 @@
 //
 // Before, a kernel built a table of 88-byte items from the mask (and another counted for it) and the row kernel for
 // long lists read the table back, one workgroup of two wavefronts per 1 KiB row.  Rows of 14 336 bytes, call to call:
-// 128 tokens per rank (93 MB moved) with the mask on the host 25.1 us in two launches, now 15.2 in one, with the mask
-// on the device 28.4 (three launches) and 16.4; 512 per rank (370 MB) 72.6 : 57.9 and 75.7 : 58.9.
+// 128 tokens per rank (93 MB moved) with the mask on the host 25.1 us in two launches, now 13.8 in one, with the mask
+// on the device 28.4 (three launches) and 14.3; 512 per rank (370 MB) 72.6 : 55.4 and 75.7 : 57.0 (6.5 TB/s).
 #include "dl_device.h"
 #include "dl_internal.h"
 

@@ -1383,11 +1383,13 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
         // 9.94 : 4.64 / 6.94 / 9.85; by how the last tile of a copy falls 16 of 90 001 5.70 / 8.30 / 11.1 : 5.82 / 8.29 / 10.7, 20 of
         // 60 003 6.02 / 8.69 / 11.9 : 6.73 / 8.60 / 11.4.  Beyond, where workgroups are one wavefront, an eighth of the copy to every
         // XCD, so that they meet in one L2; 512 threads have the better figures while all is in the caches, and lose to what was there
-        // before where nothing is.  Rows in turn : 512 threads : eighths, 8 of 420 001 7.95 / 9.55 / 11.58 : 6.10 / 8.91 / 12.2 : 7.47 /
-        // 9.03 / 11.4, 8 of 524 291 10.2 / 11.2 / 13.5 : 9.0 / 10.6 / 14.0 : 9.3 / 10.8 / 13.3, 15 of 164 228 12.1 / 13.3 / 15.4 : 10.7 /
-        // 11.7 / 15.6 : 11.1 / 12.0 / 14.5, 2 of 9 000 001 11.5 / 11.6 / 14.3 : 11.3 / 11.7 / 14.9 : 10.7 / 11.1 / 14.1.  (Cold sets do not
-        // want more loads in flight: two rows per wavefront 7.0 / 9.4 / 13.4 for the first of these; nor 512 threads with rows in turn,
-        // 7.3 / 9.5 / 12.9, or in eighths, 6.9 / 9.4 / 12.2.  Larger ones in turn, as any list: 8 of 2 MiB and 3 bytes.)
+        // before where nothing is.  Rows in turn : 512 threads : eighths, 8 of 420 001 7.82 / 9.52 / 11.5 : 6.20 / 8.95 / 12.3 : 7.58 /
+        // 9.09 / 11.4, 8 of 524 291 10.7 / 11.2 / 13.5 : 9.1 / 10.7 / 14.1 : 10.7 / 10.9 / 13.4, 15 of 164 228 12.8 / 13.4 / 15.4 : 10.8 /
+        // 11.8 / 15.7 : 10.8 / 12.1 / 14.6, 10 of 400 009 13.0 / 13.4 / 15.7 : 12.5 / 13.1 / 16.1 : 11.5 / 12.7 / 15.4, 2 of 9 000 001 11.5 / 11.7 /
+        // 14.2 : 11.2 / 11.7 / 14.9 : 10.9 / 11.2 / 14.1.  (Cold sets do not want more loads in flight: two rows per wavefront 7.0 / 9.4 / 13.4
+        // for the first of these; nor 512 threads with rows in turn, 7.3 / 9.5 / 12.9, or in eighths, 6.9 / 9.4 / 12.2; nor 128 or 256 in
+        // eighths, 6.8 / 9.0 / 12.0 and 6.7 / 9.0 / 12.2, 15 of 164 228 12.3 / 12.7 / 14.7 and 12.2 / 12.3 / 15.4.  Larger ones in turn, as any
+        // list: 8 of 2 MiB and 3 bytes.)
         if (free_shape && sh.policy == DL_POL_WT && 2u * total >= OFF_GRID_MIN_BYTES && biggest >= 8192u && !all_on_grid(items, n)) {
             if (sh.block_threads == 64u) {
                 sh.eighths = true;
