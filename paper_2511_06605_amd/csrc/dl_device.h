@@ -751,6 +751,46 @@ __device__ __forceinline__ void dl_run_rows(const dl_klist<Item, NMAX> &p, uint3
     dl_rows_body<POL, ON_GRID>(p.item[d], b - first_tile, p.wpg_log2, p.split_log2);
 }
 
+// The bytes of a row in front of and behind its item's whole vectors, to all of the item's destinations.
+template <class Item>
+__device__ __forceinline__ void dl_coherent_edges(const Item &it, uint32_t shift, uint64_t row, uint32_t lane)
+{
+    dl_row_edges(shift, it.bytes, row, lane, [&](uint64_t i) {
+        const uint8_t x = dl_ld<DL_POL_COHERENT>(dl_global<uint8_t>(it.src) + i);
+        if constexpr (std::is_same<Item, dl_plain_item>::value) {
+            dl_st<DL_POL_COHERENT>(dl_global<uint8_t>(it.dst) + i, x);
+        } else {
+            for (uint32_t q = 0; q < (uint32_t)DL_FAN; ++q) {
+                char *dq = it.dst[q];  // filled from the front, the rest null
+                if (!dq) break;
+                dl_st<DL_POL_COHERENT>(dl_global<uint8_t>(dq) + i, x);
+            }
+        }
+    });
+}
+
+// ... and a wavefront's whole vectors of R rows, loaded already: row r of item d[r], from byte[r] on in lanes that have one.
+template <int R, class Item, int NMAX>
+__device__ __forceinline__ void dl_coherent_store(const dl_klist<Item, NMAX> &p, const uint32_t (&d)[R], const uint64_t (&byte)[R],
+                                                  const bool (&whole)[R], const dl_u32x4 (&v)[R])
+{
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (!whole[r]) continue;
+        const Item &it = p.item[d[r]];
+        if constexpr (std::is_same<Item, dl_plain_item>::value) {
+            dl_st16<DL_POL_COHERENT>(it.dst + byte[r], v[r]);
+        } else {
+#pragma unroll
+            for (uint32_t q = 0; q < (uint32_t)DL_FAN; ++q) {
+                char *dq = it.dst[q];  // filled from the front, the rest null
+                if (!dq) break;
+                dl_st16<DL_POL_COHERENT>(dq + byte[r], v[r]);
+            }
+        }
+    }
+}
+
 // Row path of the armed kernels, whose loads go to memory at system scope and take long to come back: a
 // wavefront takes up to R global tiles per pass (b0, b0 + stride, ...; those below `total`), issues the loads
 // of all of them, waits once and stores.  Rows and lanes as in dl_rows_body, with one sub-group per workgroup
@@ -800,51 +840,64 @@ struct dl_coherent_rows {
 
     __device__ __forceinline__ void run(const dl_klist<Item, NMAX> &p) const
     {
-        const uint32_t lane = threadIdx.x & 63u;
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (kind[r] != DL_ROW_EDGE) continue;  // the bytes in front of and behind the item's whole vectors
-            const Item &it = p.item[d[r]];
-            dl_row_edges(dl_item_shift(it), it.bytes, row[r], lane, [&](uint64_t i) {
-                const uint8_t x = dl_ld<DL_POL_COHERENT>(dl_global<uint8_t>(it.src) + i);
-                if constexpr (std::is_same<Item, dl_plain_item>::value) {
-                    dl_st<DL_POL_COHERENT>(dl_global<uint8_t>(it.dst) + i, x);
-                } else {
-                    for (uint32_t q = 0; q < (uint32_t)DL_FAN; ++q) {
-                        char *dq = it.dst[q];  // filled from the front, the rest null
-                        if (!dq) break;
-                        dl_st<DL_POL_COHERENT>(dl_global<uint8_t>(dq) + i, x);
-                    }
-                }
-            });
-        }
+        for (int r = 0; r < R; ++r)
+            if (kind[r] == DL_ROW_EDGE) dl_coherent_edges(p.item[d[r]], dl_item_shift(p.item[d[r]]), row[r], threadIdx.x & 63u);
         dl_u32x4 v[R];
         dl_ld_many<DL_POL_COHERENT, R>(v, from);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (!whole[r]) continue;
-            const Item &it = p.item[d[r]];
-            if constexpr (std::is_same<Item, dl_plain_item>::value) {
-                dl_st16<DL_POL_COHERENT>(it.dst + byte[r], v[r]);
-            } else {
-#pragma unroll
-                for (uint32_t q = 0; q < (uint32_t)DL_FAN; ++q) {
-                    char *dq = it.dst[q];  // filled from the front, the rest null
-                    if (!dq) break;
-                    dl_st16<DL_POL_COHERENT>(dq + byte[r], v[r]);
-                }
-            }
-        }
+        dl_coherent_store<R>(p, d, byte, whole, v);
     }
 };
 
+// The same where the sources may be read already.  Finding a row of a long list is a chain of loads, and the chains of R rows
+// run side by side only with nothing in between; in a short list the edges go out as their row is found, and nothing of them is
+// kept.  Eight copies, armed, trigger to done and the call, all found first : this, off the grid 20 / 50 / 130 / 200 MiB moved 17.3 / 26.3 /
+// 50.8 / 71.7 : 16.7 / 25.7 / 49.7 / 70.4 us, on it 14.9 / 21.6 / 39.7 / 54.0 : 14.3 / 20.8 / 37.7 / 50.9.  Sixty-four, off the grid, this : all
+// found first 130 / 200 MiB 61.7 / 88.4 : 51.6 / 69.0.
 template <int R, class Item, int NMAX>
 __device__ __forceinline__ void dl_run_rows_coherent(const dl_klist<Item, NMAX> &p, uint32_t b0, uint32_t stride,
                                                      uint32_t total, const void *spare)
 {
-    dl_coherent_rows<R, Item, NMAX> rows;
-    rows.prepare(p, b0, stride, total, spare);
-    rows.run(p);
+    if constexpr (NMAX > 8) {
+        dl_coherent_rows<R, Item, NMAX> rows;
+        rows.prepare(p, b0, stride, total, spare);
+        rows.run(p);
+    } else {
+        const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const uint32_t lane = threadIdx.x & 63u;
+        const uint32_t wl = p.wpg_log2;
+        uint32_t first;
+        const uint32_t d0 = dl_find_item(p, b0, &first);
+        const char *const safe = p.item[d0].bytes >= 16u ? p.item[d0].src : (const char *)spare;  // (as in prepare())
+        uint32_t d[R];
+        uint64_t byte[R];
+        bool whole[R];
+        const char *from[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t b = b0 + (uint32_t)r * stride;
+            d[r] = p.n;
+            byte[r] = 0;
+            whole[r] = false;
+            from[r] = safe;
+            if (b < total && b >= b0) {  // (b >= b0: no wrap-around)
+                d[r] = dl_find_item(p, b, &first);
+                if (d[r] < p.n) {
+                    const Item &it = p.item[d[r]];
+                    const uint64_t row = ((uint64_t)(b - first) << wl) + (wave & ((1u << wl) - 1u));
+                    const uint32_t shift = dl_item_shift(it);
+                    byte[r] = ((row << 10) - shift) + (lane << 4);
+                    const uint32_t kind = dl_row_kind(dl_item_ragged(it), shift, it.bytes, row);
+                    whole[r] = dl_lane_whole(byte[r], it.bytes, kind);
+                    if (whole[r]) from[r] = it.src + byte[r];
+                    if (kind == DL_ROW_EDGE) dl_coherent_edges(it, shift, row, lane);
+                }
+            }
+        }
+        dl_u32x4 v[R];
+        dl_ld_many<DL_POL_COHERENT, R>(v, from);
+        dl_coherent_store<R>(p, d, byte, whole, v);
+    }
 }
 
 // Global tile b of a list, any alignment and tile size: find its item, then

@@ -303,6 +303,7 @@ def test_slots_reused_by_requests_that_count_and_that_do_not(ref, armed):
 @pytest.mark.parametrize("mode", [dl.DL_MODE_SIGNAL, dl.DL_MODE_PRELAUNCH])
 @pytest.mark.parametrize("n,size,off", [
     (1, 6 * MiB - 16, 0), (1, 6 * MiB, 0), (1, 6 * MiB + 1, 3), (8, 768 * KiB, 0), (8, 128 * KiB, 0), (8, 129 * KiB + 16, 0), (8, 1 * MiB, 5), (8, 4 * MiB, 0),
+    (3, 9 * MiB + 5, 7), (8, 2 * MiB + 13, 3), (9, 1 * MiB + 9, 3),
     (30, 40 * KiB + 7, 1), (30, 140 * KiB + 7, 1), (64, 96 * KiB, 0), (64, 96 * KiB - 128, 0), (100, 61440, 0), (100, 63 * KiB, 9), (300, 40000, 0)])
 def test_copies_around_the_armed_shapes(ref, armed, n, size, off, mode, own_stream):
     rng = np.random.default_rng(n + size)
