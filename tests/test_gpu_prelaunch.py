@@ -326,6 +326,19 @@ def test_copies_around_the_armed_shapes(ref, armed, n, size, off, mode, own_stre
     assert np.array_equal(d.host(), want) and d.guards_intact()
 
 
+# four tiles of 16 KiB a workgroup of a waiting grid and one more, with four destinations, with five and more, in lists of eight items and longer
+@pytest.mark.parametrize("W,B", [(4, 2 * MiB), (4, 2 * MiB + 1024), (5, 102 * 16 * KiB), (5, 103 * 16 * KiB), (8, 1 * MiB), (8, 1 * MiB + 16), (9, 1 * MiB + 128)])
+def test_allgathers_around_the_passes_of_a_waiting_grid(ref, armed, W, B):
+    ins = inputs.allgather_inputs(W, B, seed=W + B)
+    d_in = [DevBuf(B, fill=a) for a in ins]
+    d_out = [DevBuf(W * B) for _ in range(W)]
+    sync()
+    dl.dl_allgather([b.ptr() for b in d_in], [b.ptr() for b in d_out], B)
+    fire()
+    for r, w in zip(d_out, ref.allgather(ins)):
+        assert np.array_equal(r.host(), w) and r.guards_intact()
+
+
 def test_sources_written_after_arming_are_seen(ref, armed):
     """The point of prelaunch: the request is armed first, its inputs are
     produced afterwards, and only then is the doorbell rung.  The same device
