@@ -1366,8 +1366,10 @@ int exec_list(const Item *items, size_t n, hipStream_t stream, const dl_arm *arm
             // ranks, 132 919 bytes per rank: 3 tiles of 16 KiB at most instead of 4 of 8, 20.7 us with eight, 21.6 with sixteen),
             // nor many passes of unaligned loads (over eight, 1 500 003 bytes 40.2 : 44.7; over twelve, 1 MiB 61.5 : 53.1), nor in a
             // short list with five destinations and more, where the stores set the pace (from four tiles of 16 KiB a workgroup,
-            // eight ranks, 80 / 130 / 200 MiB moved 22.2 / 28.1 / 36.8 : 23.6 / 29.8 / 39.5, five ranks 64 MiB 3 to 5 % slower, seven 130 MiB 7;
-            // two to four ranks 2 to 17 % faster, and so are longer lists, whose rows take more finding: nine ranks 6 to 12)
+            // eight ranks, 80 / 130 / 200 MiB moved 22.2 / 28.1 / 36.8 : 23.6 / 29.8 / 39.5; five to eight ranks of 1.1 to 3.5 MiB, one or three
+            // buffer sets, 1 to 6 % slower on average, the call counted; with the kernel resident before the doorbell rings
+            // five ranks 3 to 5 % faster with sixteen, six to eight from 9 % faster to 7 slower by size, within 2.5 on average.  Two to four
+            // ranks gain 2 to 17 %, and so do longer lists, whose rows take more finding: nine ranks 6 to 12)
             uint64_t t16 = 0;
             for (size_t i = 0; i < n; ++i) t16 += dl_item_tiles(items[i], 16384);
             const uint64_t g = armed_grid(t8, 512u, true), most8 = (t8 + g - 1) / g, most16 = (t16 + g - 1) / g;
